@@ -1,4 +1,4 @@
-// bf16 GEMM on the matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// bf16 GEMM on the matrix cores, fp32 accumulation.
 //   C[M,N] (+)= opA(A) * opB(B)
 // Operand layouts (all row-major):
 //   TA = false: A is [M,K] (K contiguous)      TA = true: A is [K,M] (M contiguous)
@@ -6,7 +6,10 @@
 // The forward projections use (TA=0,TB=0) with weights [in,out]; data gradients (dY * W^T) use
 // (TA=0,TB=1); weight gradients (X^T * dY) use (TA=1,TB=0) and add into a float32 buffer.
 //
-// Tiling.  A block of WM x WN waves owns a BM x BN tile of C; a wave owns (BM/WM) x (BN/WN) as 32x32
+// Two kernels: gemm_bf16_wide_kernel (256x256 tiles; described there) takes the products that fill the chip with such
+// tiles, gemm_bf16_kernel (256x128 and 128x128 tiles, v_mfma_f32_32x32x16_bf16) the smaller ones.
+//
+// Tiling of gemm_bf16_kernel.  A block of WM x WN waves owns a BM x BN tile of C; a wave owns (BM/WM) x (BN/WN) as 32x32
 // MFMA tiles.  K is consumed BK = 32 at a time through a ring of 4 LDS stages.  Tiles travel global
 // -> LDS directly (global_load_lds_dwordx4: each lane moves 16 bytes, a wave fills 1 KiB of consecutive
 // LDS), so no registers or LDS-write instructions are spent on staging; the loads of stage s+3 are
@@ -30,6 +33,7 @@
 // split order, so results never depend on scheduling (no atomics anywhere).
 // Requirements: N % 8 == 0 and every contiguous operand dimension % 8 == 0 (16-byte chunks).
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
 
 #define GB_BK 32
@@ -64,7 +68,7 @@ struct GemmArgs {
   // SwiGLU fused into the epilogue (whole tiles only, bf16 result).  GLU_FWD: the GEMM is the gate/up projection with
   // N = 2*glu_f columns [gate | up]; a tile takes 128 gate columns and the 128 up columns of the same outputs (its B
   // panel is fetched from two places), stores both to C and gate*sigmoid(gate)*up to glu_out [M, glu_f].
-  // GLU_BWD: the GEMM yields dA [M, N = glu_f]; instead of storing it the epilogue reads gate/up from glu_in
+  // (256x256 tiles only.)  GLU_BWD: the GEMM yields dA [M, N = glu_f]; instead of storing it the epilogue reads gate/up from glu_in
   // [M, 2*glu_f] and stores d(gate), d(up) to C [M, 2*glu_f].  Element arithmetic: swiglu_*_elem, as the row-wise kernels.
   int glu_mode, glu_f;
   const bf16_t* glu_in;
@@ -112,6 +116,44 @@ __device__ __forceinline__ bool grouped_split_remainders(const GemmArgs& g) {
   return tail != 0 && tail * 4 < g.cus && bulk <= full / g.cus * g.cus;
 }
 
+// Grouped launches: the groups' rows lie behind one another; this block's group is blockIdx.z.  The row counts are data
+// (expert routing), so the extents are fixed up here from device memory and the grid is sized for the largest possible
+// group; surplus blocks leave at the tile check.  False: this block has nothing to do.
+template <int BM, int BK>
+__device__ __forceinline__ bool group_setup(GemmArgs& g) {
+  int row0 = 0;
+  for (int i = 0; i < (int)blockIdx.z; i++) row0 += g.group_rows[i];
+  int rows = g.group_rows[blockIdx.z];
+  if (g.group_part != 0) {
+    const bool split = grouped_split_remainders(g);
+    if (g.group_part == 1) {
+      if (split) rows -= rows % g.part1_bm;
+    } else {
+      if (!split) return false;
+      row0 += rows - rows % g.part1_bm;
+      rows %= g.part1_bm;
+    }
+  }
+  row0 = __builtin_amdgcn_readfirstlane(row0);  // the same in every lane, as the compiler may not know of loaded values
+  rows = __builtin_amdgcn_readfirstlane(rows);
+  if (rows == 0) return false;
+  if (g.group_mode == 2) {
+    g.A += (size_t)row0 * g.M;
+    g.B += (size_t)row0 * g.N;
+    g.C = reinterpret_cast<float*>(g.C) + (size_t)blockIdx.z * g.M * g.N;
+    g.K = rows;
+    g.kt_per_split = (rows + BK - 1) / BK;
+  } else {
+    g.A += (size_t)row0 * g.K;
+    g.B += (size_t)blockIdx.z * g.K * g.N;
+    g.C = reinterpret_cast<bf16_t*>(g.C) + (size_t)row0 * g.N;
+    g.M = rows;
+    g.tiles_m = (rows + BM - 1) / BM;
+    g.tiles_per_xcd = (g.tiles_m * g.tiles_n + 7) / 8;
+  }
+  return true;
+}
+
 // One 16-byte chunk per lane, global -> LDS.  lds_wave_base must be wave-uniform.  Written as inline
 // assembly so that the compiler does not order later LDS reads behind the transfer with a full
 // vmcnt(0) wait (it cannot tell the stages apart); the kernel waits for the transfers itself, once per
@@ -121,6 +163,9 @@ __device__ __forceinline__ void dma16(const void* gptr, bf16_t* lds_wave_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory", "m0");
 }
 
+__device__ __forceinline__ void dma16_lds(const void* gptr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory", "m0");
+}
 // Same with a wave-uniform 64-bit base (SGPR pair) and a per-lane 32-bit byte offset: the offsets of a
 // tile do not change from one K step to the next, only the base advances.
 __device__ __forceinline__ void dma16_base(const void* sbase, uint32_t voff, uint32_t lds_addr) {
@@ -130,10 +175,9 @@ __device__ __forceinline__ void dma16_base(const void* sbase, uint32_t voff, uin
 // Per-lane byte offsets of this wave's chunks relative to the tile origin (row r0, k = tile start).
 // Rows/columns beyond the matrix are clamped to the last valid one: they only feed rows/columns of C
 // that are never stored.  (K must not be clamped; ragged K tiles take issue_tile below.)
-// half_jump != 0 (K-major only, whole tiles): the tile's second half of columns lies half_jump columns further on.
 template <int ROWS, int NWAVES, bool KMAJOR>
 __device__ __forceinline__ void tile_offsets(uint32_t (&voff)[ROWS * GB_BK / 8 / 64 / NWAVES], int r0, int R, int K, int wave,
-                                             int lane, int half_jump = 0) {
+                                             int lane) {
   constexpr int IPW = ROWS * GB_BK / 8 / 64 / NWAVES;
 #pragma unroll
   for (int j = 0; j < IPW; j++) {
@@ -141,8 +185,7 @@ __device__ __forceinline__ void tile_offsets(uint32_t (&voff)[ROWS * GB_BK / 8 /
     if (KMAJOR) {
       constexpr int CPR = ROWS / 8;
       const int kr = p / CPR, c = (p % CPR) ^ ((kr & 3) << 2);
-      int col = min(r0 + c * 8, R - 8) - r0;
-      if (half_jump != 0) col = c * 8 + (c * 8 >= ROWS / 2 ? half_jump : 0);
+      const int col = min(r0 + c * 8, R - 8) - r0;
       voff[j] = (uint32_t)(((size_t)kr * R + col) * sizeof(bf16_t));
     } else {
       const int row = p >> 2, c = (p & 3) ^ ((row >> 2) & 3);
@@ -205,39 +248,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs g, con
                              (size_t)g.ar_blocks * blockDim.x);
     return;
   }
-  if (g.group_rows != nullptr) {
-    // Grouped: the groups' rows lie behind one another; this block's group is blockIdx.z.  The row
-    // counts are data (expert routing), so the extents are fixed up here from device memory and the
-    // grid is sized for the largest possible group; surplus blocks leave at the tile check below.
-    int row0 = 0;
-    for (int i = 0; i < (int)blockIdx.z; i++) row0 += g.group_rows[i];
-    int rows = g.group_rows[blockIdx.z];
-    if (g.group_part != 0) {
-      const bool split = grouped_split_remainders(g);
-      if (g.group_part == 1) {
-        if (split) rows -= rows % g.part1_bm;
-      } else {
-        if (!split) return;
-        row0 += rows - rows % g.part1_bm;
-        rows %= g.part1_bm;
-      }
-    }
-    if (rows == 0) return;
-    if (g.group_mode == 2) {
-      g.A += (size_t)row0 * g.M;
-      g.B += (size_t)row0 * g.N;
-      g.C = reinterpret_cast<float*>(g.C) + (size_t)blockIdx.z * g.M * g.N;
-      g.K = rows;
-      g.kt_per_split = (rows + GB_BK - 1) / GB_BK;
-    } else {
-      g.A += (size_t)row0 * g.K;
-      g.B += (size_t)blockIdx.z * g.K * g.N;
-      g.C = reinterpret_cast<bf16_t*>(g.C) + (size_t)row0 * g.N;
-      g.M = rows;
-      g.tiles_m = (rows + BM - 1) / BM;
-      g.tiles_per_xcd = (g.tiles_m * g.tiles_n + 7) / 8;
-    }
-  }
+  if (g.group_rows != nullptr && !group_setup<BM, GB_BK>(g)) return;
   constexpr int WTM = BM / WM, WTN = BN / WN, MT = WTM / 32, NT = WTN / 32;
   constexpr int A_ELEMS = BM * GB_BK, B_ELEMS = BN * GB_BK, STAGE = A_ELEMS + B_ELEMS;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -250,8 +261,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs g, con
   int tm, tn;
   if (!tile_of_launch((int)blockIdx.x - g.ar_blocks + g.tile_first, g.tiles_m, g.tiles_n, g.tiles_per_xcd, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
-  const bool glu_fwd = !TA && !TB && BN == 256 && g.glu_mode == GLU_FWD;
-  const int nb0 = glu_fwd ? tn * (BN / 2) : n0;  // first column of the tile's B panel (its first half, if fused)
   const int nkt_total = (g.K + GB_BK - 1) / GB_BK;
   const int kt_begin = blockIdx.y * g.kt_per_split;
   const int kt_end = min(nkt_total, kt_begin + g.kt_per_split);
@@ -267,10 +276,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs g, con
   constexpr int IPA = BM * GB_BK / 8 / 64 / NW, IPB = BN * GB_BK / 8 / 64 / NW, IPS = IPA + IPB;
   uint32_t voa[IPA], vob[IPB];
   tile_offsets<BM, NW, TA>(voa, m0, g.M, g.K, wave, lane);
-  tile_offsets<BN, NW, !TB>(vob, n0, g.N, g.K, wave, lane, glu_fwd ? g.glu_f - BN / 2 : 0);
+  tile_offsets<BN, NW, !TB>(vob, n0, g.N, g.K, wave, lane);
   // tile origins at k = 0 and the byte stride of one K step
   const char* a0 = reinterpret_cast<const char*>(g.A + (TA ? (size_t)m0 : (size_t)m0 * g.K));
-  const char* b0 = reinterpret_cast<const char*>(g.B + (TB ? (size_t)n0 * g.K : (size_t)nb0));
+  const char* b0 = reinterpret_cast<const char*>(g.B + (TB ? (size_t)n0 * g.K : (size_t)n0));
   const size_t sa = (TA ? (size_t)GB_BK * g.M : (size_t)GB_BK) * sizeof(bf16_t);
   const size_t sb = (TB ? (size_t)GB_BK : (size_t)GB_BK * g.N) * sizeof(bf16_t);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
@@ -412,33 +421,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs g, con
           *reinterpret_cast<bf16x4*>(reg + row * WTN + ((((c0 >> 3) ^ (row & 7)) << 3) | (c0 & 4))) = o;
         }
     __builtin_amdgcn_wave_barrier();
-    if (glu_fwd) {
-      // the wave's 64 columns are gate columns (first two wave columns) or up columns (last two) of outputs nb0 + ...
-      const int cb = nb0 + (wn0 < BN / 2 ? wn0 : g.glu_f - BN / 2 + wn0);
-#pragma unroll
-      for (int it = 0; it < WTM / 8; it++) {
-        const int row = it * 8 + (lane >> 3), ch = lane & 7;
-        const bf16x8 o = *reinterpret_cast<const bf16x8*>(reg + row * WTN + ((ch ^ (row & 7)) << 3));
-        *reinterpret_cast<bf16x8*>(Cb + (size_t)(m0 + wm0 + row) * g.N + cb + ch * 8) = o;
-      }
-      // gate and up of one output sit in the regions of waves two wave columns apart: once every wave has written,
-      // each wave combines half of the rows of its pair (the values as stored, i.e. rounded to bf16)
-      __syncthreads();
-      const int pw = (wave % WN) & 1, hi = (wave % WN) >> 1;
-      const bf16_t* rg = smem + ((wave / WN) * WN + pw) * (WTM * WTN);
-      const bf16_t* ru = rg + 2 * (WTM * WTN);
-#pragma unroll
-      for (int it = 0; it < WTM / 16; it++) {
-        const int row = hi * (WTM / 2) + it * 8 + (lane >> 3), ch = lane & 7;
-        const bf16x8 gv = *reinterpret_cast<const bf16x8*>(rg + row * WTN + ((ch ^ (row & 7)) << 3));
-        const bf16x8 uv = *reinterpret_cast<const bf16x8*>(ru + row * WTN + ((ch ^ (row & 7)) << 3));
-        bf16x8 o;
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = (bf16_t)swiglu_fwd_elem((float)gv[e], (float)uv[e]);
-        *reinterpret_cast<bf16x8*>(g.glu_out + (size_t)(m0 + wm0 + row) * g.glu_f + nb0 + pw * WTN + ch * 8) = o;
-      }
-      return;
-    }
     if (g.glu_mode == GLU_BWD) {
       // gate/up of 8 row groups are fetched together (the accumulators' registers are free by now), so that the
       // epilogue waits for memory twice, not once per row group
@@ -539,6 +521,386 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmArgs g, con
   }
 }
 
+// ------------------------------------------------------------------------------------ 256x256 tiles
+// Bound: the matrix cores under the chip's power limit.  At 8192^3 the clock settles where power allows (1.6-2.0 GHz), so
+// energy per product counts as much as idle cycles: the 16x16x32 instruction (half the accumulator traffic of
+// 32x32x16 per product), 128x128 wave tiles (a third fewer LDS reads than 128x64) and whole-line transfers
+// each raised the clock at the same utilisation.  Measured against an 8-wave kernel with 128x64 wave tiles, 32x32x16
+// instructions and K tiles of 32 (same box): 8192^3 832 -> 723 us (1520 TFLOP/s), B transposed 880 -> 727, A transposed
+// with float32 accumulation 889 -> 785; 4096x3584x4096 100 -> 86 us; 4096x4096x1792 53 -> 46 us.  With 32x32x16
+// instructions in the same schedule: 766 us at 8192^3.
+// The large-tile kernel: four waves, one per SIMD, each owning a 128x128 part of C (256 accumulator registers in AGPRs).
+// K is consumed 64 at a time from two LDS stages (A and B, 32 KiB each).  A K tile is worked off in four quadrants
+// (a0 b0, a0 b1, a1 b1, a1 b0: halves of 64 rows / columns); the fragments of the half that comes next are read while
+// the current quadrant's products are issued, so a stage has been read completely after the second quadrant.  One barrier
+// there (it also publishes the next stage), and the transfers of tile t+2 follow into the stage just emptied.  Matrix
+// instructions, LDS reads and transfers are interleaved two products at a time and pinned in that order.
+//   K-contiguous operand: LDS [256 rows][64 k], 128-byte rows; 16-byte chunk c of row r sits at c ^ ((r>>1)&7).
+//   K-major operand: LDS [4 panels of 64 columns][64 k][64 columns]; 32-byte slot s of k-row r sits at
+//   s ^ (((r>>1)&1) | ((r>>3)&1)<<1).
+// Either way a transfer moves whole 128-byte lines and fragment reads touch every bank once.
+#define GW_BK 64
+#define GW_STAGE 65536u
+#define GW_PIN() __builtin_amdgcn_sched_barrier(0)
+#define GW_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
+
+// Row of the operand's non-K dimension (relative to the tile) and k of the 16-byte chunk lane `lane` fetches in
+// transfer j of wave `wave`.
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_chunk(int wave, int j, int lane, int& r, int& k) {
+  if (KMAJOR) {
+    k = j * 8 + (lane >> 3);
+    const int slot = ((lane & 7) >> 1) ^ (((k >> 1) & 1) | (((k >> 3) & 1) << 1));
+    r = wave * 64 + slot * 16 + (lane & 1) * 8;
+  } else {
+    r = (wave * 8 + j) * 8 + (lane >> 3);
+    k = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+  }
+}
+// Byte offsets relative to the tile's origin (clamped to the last valid row or column: those only feed results that are
+// never stored).  half_jump: the tile's second half of columns lies that many columns further on.
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_offsets(uint32_t (&voff)[8], int r0, int R, int K, int wave, int lane, int half_jump = 0) {
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    int r, k;
+    gw_chunk<KMAJOR>(wave, j, lane, r, k);
+    if (KMAJOR) {
+      const int col = half_jump != 0 ? r + (wave >= 2 ? half_jump : 0) : min(r0 + r, R - 8) - r0;
+      voff[j] = (uint32_t)(((size_t)k * R + col) * sizeof(bf16_t));
+    } else {
+      voff[j] = (uint32_t)(((size_t)(min(r0 + r, R - 1) - r0) * K + k) * sizeof(bf16_t));
+    }
+  }
+}
+// A K tile that reaches beyond K: chunks outside the matrix come from the zero constant.
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_issue_ragged(uint32_t lds_wave, const bf16_t* __restrict__ base, int r0, int k0, int R, int K,
+                                                int wave, int lane, int half_jump = 0) {
+  asm volatile("" : "+v"(lane));  // computed here: shared with the steady path's offsets it would hold registers through the main loop
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    int r, k;
+    gw_chunk<KMAJOR>(wave, j, lane, r, k);
+    r += r0 + (wave >= 2 ? half_jump : 0);
+    k += k0;
+    const bf16_t* src = (r < R && k < K) ? base + (KMAJOR ? (size_t)k * R + r : (size_t)r * K + k) : reinterpret_cast<const bf16_t*>(dh_zero_chunk);
+    dma16_lds(src, lds_wave + j * 1024);
+  }
+}
+
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+// Fragment of 16 rows (tile index i of the wave's 128) and 32 k (step ks of the stage).
+template <bool KMAJOR>
+__device__ __forceinline__ bf16x8 gw_frag(const lds_char* const (&p)[4], int ks, int i) {
+  if (!KMAJOR) return *reinterpret_cast<const lds_bf16x8*>(p[ks] + i * 2048);
+  const lds_char* q = p[i & 3] + (i >> 2) * 8192 + ks * 4096;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)q);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + 512));
+  return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_pointers(const lds_char* (&p)[4], const lds_char* base, int lane) {
+  const int l16 = lane & 15, kg = lane >> 4;
+#pragma unroll
+  for (int x = 0; x < 4; x++) {
+    if (KMAJOR) {  // lane l16 of a group fetches k-row kg*8 + l16/4 (and the one 4 further), 4 columns
+      const int kr = kg * 8 + (l16 >> 2);
+      p[x] = base + kr * 128 + (x ^ (((kr >> 1) & 1) | (((kr >> 3) & 1) << 1))) * 32 + (l16 & 3) * 8;
+    } else {       // row l16, chunk ks*4 + kg
+      p[x] = base + l16 * 128 + ((((x & 1) * 4 + kg) ^ ((l16 >> 1) & 7)) << 4);
+    }
+  }
+}
+
+// acc += A * B with the accumulator tied to one AGPR quad: the accumulators fill that half of the register file exactly,
+// and through the intrinsic (whose result may land elsewhere) the compiler moves them around inside the loop.  The
+// operands come straight from LDS reads, so no vector-ALU write precedes the instruction closely; gw_settle() covers
+// the result's latency before anything else reads an accumulator.
+__device__ __forceinline__ void gw_mfma(f32x4& acc, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void gw_settle(f32x4 (&acc)[8][8]) {
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+    asm volatile("s_nop 15" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
+}
+
+__device__ __forceinline__ const char* gw_uniform(const char* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (const char*)(((uint64_t)hi << 32) | lo);
+}
+
+template <bool TA, bool TB, bool F32OUT>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmArgs g, const GemmAr ar) {
+  constexpr int BM = 256, BN = 256;
+  if (g.ar_blocks > 0 && blockIdx.x < (unsigned)g.ar_blocks) {  // this block is a share of the stand-in, not a tile
+    if (blockIdx.y == 0 && blockIdx.z == 0)
+      allreduce_span<bf16_t>(ar.parts, ar.ranks, ar.out, ar.n8, (size_t)blockIdx.x * blockDim.x + threadIdx.x,
+                             (size_t)g.ar_blocks * blockDim.x);
+    return;
+  }
+  if (g.group_rows != nullptr && !group_setup<BM, GW_BK>(g)) return;
+  int tm, tn;
+  if (!tile_of_launch((int)blockIdx.x - g.ar_blocks + g.tile_first, g.tiles_m, g.tiles_n, g.tiles_per_xcd, tm, tn)) return;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm0 = (wave >> 1) * 128, wn0 = (wave & 1) * 128;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const bool glu_fwd = !TA && !TB && !F32OUT && g.glu_mode == GLU_FWD;
+  const int jump = glu_fwd ? g.glu_f - BN / 2 : 0;  // B panel: 128 gate columns, then the 128 up columns of the same outputs
+  const int nb0 = glu_fwd ? tn * (BN / 2) : n0;
+  const int kt_begin = blockIdx.y * g.kt_per_split;
+  const int n = min((g.K + GW_BK - 1) / GW_BK, kt_begin + g.kt_per_split) - kt_begin;
+  const int n_full = min(kt_begin + n, g.K / GW_BK) - kt_begin;
+
+  uint32_t voa[8], vob[8];
+  gw_offsets<TA>(voa, m0, g.M, g.K, wave, lane);
+  gw_offsets<!TB>(vob, nb0, g.N, g.K, wave, lane, jump);
+  const size_t sa = (TA ? (size_t)GW_BK * g.M : (size_t)GW_BK) * sizeof(bf16_t);
+  const size_t sb = (TB ? (size_t)GW_BK : (size_t)GW_BK * g.N) * sizeof(bf16_t);
+  // next tile to transfer (wave-uniform, told to the compiler so that the addresses stay in scalar registers)
+  const char* ap = gw_uniform(reinterpret_cast<const char*>(g.A + (TA ? (size_t)m0 : (size_t)m0 * g.K)) + kt_begin * sa);
+  const char* bp = gw_uniform(reinterpret_cast<const char*>(g.B + (TB ? (size_t)nb0 * g.K : (size_t)nb0)) + kt_begin * sb);
+  const uint32_t ldsA = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem_raw + wave * 8192u, ldsB = ldsA + 32768u;
+  auto issue = [&](int t) {
+    const uint32_t so = (t & 1) * GW_STAGE;
+    if (t < n_full) {
+#pragma unroll
+      for (int j = 0; j < 8; j++) dma16_base(ap, voa[j], ldsA + so + j * 1024);
+#pragma unroll
+      for (int j = 0; j < 8; j++) dma16_base(bp, vob[j], ldsB + so + j * 1024);
+    } else {
+      gw_issue_ragged<TA>(ldsA + so, g.A, m0, (kt_begin + t) * GW_BK, g.M, g.K, wave, lane);
+      gw_issue_ragged<!TB>(ldsB + so, g.B, nb0, (kt_begin + t) * GW_BK, g.N, g.K, wave, lane, jump);
+    }
+  };
+  if (n > 0) issue(0);
+  ap += sa;
+  bp += sb;
+  if (n > 1) issue(1);
+  ap += sa;
+  bp += sb;
+
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  gw_settle(acc);
+  const lds_char* pa[4];
+  const lds_char* pb[4];
+  gw_pointers<TA>(pa, (const lds_char*)smem_raw + wm0 * 128, lane);  // 128 rows or two 64-column panels: 16 KiB
+  gw_pointers<!TB>(pb, (const lds_char*)smem_raw + 32768 + wn0 * 128, lane);
+
+  bf16x8 fa0[8], fa1[8], fbx[8], fby[8];  // halves of 64 rows / columns: [k-step of 32][16-row tile]
+  auto rd_a = [&](int half, int e) { return gw_frag<TA>(pa, e >> 2, half * 4 + (e & 3)); };
+  auto rd_b = [&](int half, int e) { return gw_frag<!TB>(pb, e >> 2, half * 4 + (e & 3)); };
+  auto shift = [&](const lds_char* (&p)[4], int d) {
+#pragma unroll
+    for (int x = 0; x < 4; x++) p[x] += d;
+  };
+  // operands swapped: the result tile is C^T, so a lane holds 4 consecutive columns of one row
+  auto quad = [&](const bf16x8 (&a)[8], const bf16x8 (&b)[8], int ah, int bh, auto aux) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+#pragma unroll
+      for (int u = 0; u < 2; u++) {
+        const int m = i * 2 + u, ks = m >> 4, x = (m >> 2) & 3, y = m & 3;
+        gw_mfma(acc[ah * 4 + x][bh * 4 + y], b[ks * 4 + y], a[ks * 4 + x]);
+      }
+      aux(i);
+      GW_PIN();
+    }
+  };
+  if (n > 0) {
+    if (n > 1) GW_VMCNT(16); else GW_VMCNT(0);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; e++) { fa0[e] = rd_a(0, e); fbx[e] = rd_b(0, e); }
+  }
+  int t = 0;
+  // Works off tile t in stage S.  b0 holds the fragments of its first B half, b1 receives those of the second and then
+  // the next tile's first half.  STEADY: tile t+2 is a full tile, its transfers go out between the products.
+  auto step = [&](auto stage, auto steady, bf16x8 (&f0)[8], bf16x8 (&f1)[8]) {
+    constexpr int S = decltype(stage)::value;
+    constexpr bool STEADY = decltype(steady)::value;
+    constexpr int to_next = S == 0 ? (int)GW_STAGE : -(int)GW_STAGE;
+    quad(fa0, f0, 0, 0, [&](int i) { if ((i & 1) == 0) f1[i >> 1] = rd_b(1, i >> 1); });
+    quad(fa0, f1, 0, 1, [&](int i) {
+      if (i < 8) fa1[i] = rd_a(1, i);
+      if (i == 13) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    });
+    shift(pa, to_next);
+    shift(pb, to_next);
+    if (!STEADY && t + 2 < n) issue(t + 2);
+    quad(fa1, f1, 1, 1, [&](int i) {
+      if ((i & 1) == 0) fa0[i >> 1] = rd_a(0, i >> 1);
+      else if (STEADY) dma16_base(ap, voa[i >> 1], ldsA + S * GW_STAGE + (i >> 1) * 1024);
+    });
+    quad(fa1, f0, 1, 0, [&](int i) {
+      if ((i & 1) == 0) f1[i >> 1] = rd_b(0, i >> 1);
+      else if (STEADY) dma16_base(bp, vob[i >> 1], ldsB + S * GW_STAGE + (i >> 1) * 1024);
+    });
+    ap += sa;
+    bp += sb;
+  };
+  const std::integral_constant<int, 0> s0{};
+  const std::integral_constant<int, 1> s1{};
+  for (; t + 4 <= n_full; t += 2) {
+    step(s0, std::true_type{}, fbx, fby);
+    step(s1, std::true_type{}, fby, fbx);
+  }
+  while (t < n) {
+    step(s0, std::false_type{}, fbx, fby);
+    if (++t >= n) break;
+    step(s1, std::false_type{}, fby, fbx);
+    ++t;
+  }
+
+  // Epilogue: acc[i][j][e] = C[row i*16 + lane%16][column j*16 + 4*(lane/16) + e] of the wave's part.  It is turned around
+  // in LDS (wave-private regions) so that a lane stores 16 bytes of a contiguous 128-byte row segment.
+  const int l16 = lane & 15, kg = lane >> 4, r8 = lane >> 3, ch = lane & 7;
+  gw_settle(acc);
+  __syncthreads();  // the stages are free
+  if (F32OUT) {
+    float* Cf = reinterpret_cast<float*>(g.C);
+    size_t ld = g.N;
+    int row0 = m0 + wm0, col0 = n0 + wn0, rows = g.M, cols = g.N;
+    if (g.epi == EPI_PARTIAL_F32) Cf += (size_t)blockIdx.y * g.M * g.N;
+    if (g.epi == EPI_TAIL_F32) {  // whole tile, tile-local layout
+      Cf += ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (BM * BN);
+      ld = BN; row0 = wm0; col0 = wn0; rows = BM; cols = BN;
+    }
+    const bool add = g.epi == EPI_ACC_F32;
+    float* reg = reinterpret_cast<float*>(smem_raw) + wave * (128 * 32);
+    f32x4 old[2][8];  // C of half a slab (64 rows x 32 columns), fetched one half ahead
+    auto at = [&](int j, int it) { return Cf + (size_t)(row0 + it * 8 + r8) * ld + col0 + j * 32 + ch * 4; };
+    auto in = [&](int j, int it) { return row0 + it * 8 + r8 < rows && col0 + j * 32 + ch * 4 < cols; };
+    auto fetch = [&](int x) {
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const int j = x >> 1, it = (x & 1) * 8 + u;
+        old[x & 1][u] = add && in(j, it) ? *reinterpret_cast<const f32x4*>(at(j, it)) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    };
+    fetch(0);
+#pragma unroll
+    for (int x = 0; x < 8; x++) {
+      const int j = x >> 1;
+      if (x < 7) fetch(x + 1);
+      if ((x & 1) == 0) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+#pragma unroll
+          for (int q = 0; q < 2; q++) {
+            const int row = i * 16 + l16, c = 4 * q + kg;
+            *reinterpret_cast<f32x4*>(reg + row * 32 + ((c ^ (row & 7)) << 2)) = acc[i][j * 2 + q];
+            GW_PIN();
+          }
+        __builtin_amdgcn_wave_barrier();
+      }
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const int it = (x & 1) * 8 + u, row = it * 8 + r8;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(reg + row * 32 + ((ch ^ (row & 7)) << 2));
+        if (in(j, it)) *reinterpret_cast<f32x4*>(at(j, it)) = add ? old[x & 1][u] + v : v;
+      }
+      GW_PIN();
+    }
+  } else {
+    bf16_t* Cb = reinterpret_cast<bf16_t*>(g.C);
+    bf16_t* reg = reinterpret_cast<bf16_t*>(smem_raw) + wave * (128 * 128);  // two halves of [128 rows][64 columns]
+#pragma unroll
+    for (int hh = 0; hh < 2; hh++) {
+      bf16_t* rh = reg + hh * (128 * 64);
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int c0 = j * 16 + 4 * kg;
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if (g.bias != nullptr && n0 + wn0 + hh * 64 + c0 < g.N) {
+          const bf16x4 bb = *reinterpret_cast<const bf16x4*>(g.bias + n0 + wn0 + hh * 64 + c0);
+          bias = f32x4{(float)bb[0], (float)bb[1], (float)bb[2], (float)bb[3]};
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+          const int row = i * 16 + l16;
+          const f32x4 v = acc[i][hh * 4 + j] + bias;
+          const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+          *reinterpret_cast<bf16x4*>(rh + row * 64 + ((((c0 >> 3) ^ (row & 7)) << 3) | (c0 & 4))) = o;
+        }
+        GW_PIN();
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (g.glu_mode != GLU_BWD) {
+        // gate/up projection: wave column 0 holds gate columns, wave column 1 the up columns of outputs nb0 + ...
+        const int cb = (glu_fwd ? nb0 + (wave & 1) * g.glu_f : n0 + wn0) + hh * 64 + ch * 8;
+#pragma unroll
+        for (int it = 0; it < 16; it++) {
+          const int row = it * 8 + r8;
+          const bf16x8 o = *reinterpret_cast<const bf16x8*>(rh + row * 64 + ((ch ^ (row & 7)) << 3));
+          if (m0 + wm0 + row < g.M && cb < g.N) *reinterpret_cast<bf16x8*>(Cb + (size_t)(m0 + wm0 + row) * g.N + cb) = o;
+          if ((it & 3) == 3) GW_PIN();
+        }
+      }
+    }
+    if (glu_fwd) {
+      // once both waves of a row have written, each combines half of the rows (the values as stored, i.e. rounded to bf16)
+      __syncthreads();
+      const bf16_t* rg = reinterpret_cast<const bf16_t*>(smem_raw) + (wave & 2) * (128 * 128);
+      const bf16_t* ru = rg + 128 * 128;
+#pragma unroll 1
+      for (int hh = 0; hh < 2; hh++)
+#pragma unroll 2
+        for (int it = 0; it < 8; it++) {
+          const int row = (wave & 1) * 64 + it * 8 + r8, off = hh * (128 * 64) + row * 64 + ((ch ^ (row & 7)) << 3);
+          const bf16x8 gv = *reinterpret_cast<const bf16x8*>(rg + off), uv = *reinterpret_cast<const bf16x8*>(ru + off);
+          bf16x8 o;
+#pragma unroll
+          for (int e = 0; e < 8; e++) o[e] = (bf16_t)swiglu_fwd_elem((float)gv[e], (float)uv[e]);
+          *reinterpret_cast<bf16x8*>(g.glu_out + (size_t)(m0 + wm0 + row) * g.glu_f + nb0 + hh * 64 + ch * 8) = o;
+          GW_PIN();
+        }
+    }
+    if (g.glu_mode == GLU_BWD) {
+      // gate/up of 8 row groups are fetched together, so that the epilogue waits for memory once per batch
+#pragma unroll 1
+      for (int hh = 0; hh < 2; hh++)
+#pragma unroll 1
+        for (int it0 = 0; it0 < 16; it0 += 8) {
+          bf16x8 gv[8], uv[8];
+#pragma unroll
+          for (int u = 0; u < 8; u++) {
+            const size_t r2 = (size_t)(m0 + wm0 + (it0 + u) * 8 + r8) * (2 * (size_t)g.glu_f) + n0 + wn0 + hh * 64 + ch * 8;
+            gv[u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(g.glu_in + r2));
+            uv[u] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(g.glu_in + r2 + g.glu_f));
+          }
+#pragma unroll
+          for (int u = 0; u < 8; u++) {
+            const int row = (it0 + u) * 8 + r8;
+            const size_t r2 = (size_t)(m0 + wm0 + row) * (2 * (size_t)g.glu_f) + n0 + wn0 + hh * 64 + ch * 8;
+            const bf16x8 o = *reinterpret_cast<const bf16x8*>(reg + hh * (128 * 64) + row * 64 + ((ch ^ (row & 7)) << 3));
+            bf16x8 dg, du;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+              float a, b;
+              swiglu_bwd_elem((float)gv[u][e], (float)uv[u][e], (float)o[e], a, b);
+              dg[e] = (bf16_t)a;
+              du[e] = (bf16_t)b;
+            }
+            *reinterpret_cast<bf16x8*>(Cb + r2) = dg;
+            *reinterpret_cast<bf16x8*>(Cb + r2 + g.glu_f) = du;
+            GW_PIN();
+          }
+        }
+    }
+  }
+}
+
 // Adds the split-K partials in split order; writes bf16 or accumulates into float32.
 __global__ void splitk_reduce_kernel(const float* __restrict__ part, int splits, size_t mn, void* __restrict__ C, int epi,
                                      const bf16_t* __restrict__ bias, int N) {
@@ -615,12 +977,13 @@ static GemmPlan choose_plan(bool ta, int M, int N, int K, size_t ws_bytes) {
   if (tiles(256, 256) * 2 >= cus) { p.cfg = 0; p.bm = 256; p.bn = 256; }
   else if (!ta && tiles(256, 128) <= cus && tiles(256, 128) * 4 >= (long long)cus * 3) { p.cfg = 2; p.bm = 256; p.bn = 128; }
   else { p.cfg = 1; p.bm = 128; p.bn = 128; }
-  const int nkt = (K + GB_BK - 1) / GB_BK;
+  const int bk = p.cfg == 0 ? GW_BK : GB_BK;  // K tile of the kernel
+  const int nkt = (K + bk - 1) / bk, min_kt = 512 / bk;  // a split keeps at least 512 of K
   const long long t = tiles(p.bm, p.bn);
   int splits = 1;
-  if (t * 4 <= cus * 3 && nkt >= 32) {
+  if (t * 4 <= cus * 3 && nkt >= 2 * min_kt) {
     splits = (int)(cus / t);
-    if (splits > nkt / 16) splits = nkt / 16;
+    if (splits > nkt / min_kt) splits = nkt / min_kt;
     const size_t per = (size_t)M * N * sizeof(float);
     if (per == 0 || ws_bytes / per < (size_t)splits) splits = per ? (int)(ws_bytes / per) : 1;
     if (splits < 2) splits = 1;
@@ -631,10 +994,10 @@ static GemmPlan choose_plan(bool ta, int M, int N, int K, size_t ws_bytes) {
   // the last round takes 1/splits of a round (plus a small ordered reduction) instead of a whole one.
   p.tail_tiles = p.tail_splits = p.tail_kt = 0;
   const int tail = (int)(t % cus);
-  if (p.cfg == 0 && p.splits == 1 && t > cus && tail > 0 && tail * 2 <= cus && nkt >= 64) {
+  if (p.cfg == 0 && p.splits == 1 && t > cus && tail > 0 && tail * 2 <= cus && nkt >= 4 * min_kt) {
     int ts = cus / tail;
     if (ts > 8) ts = 8;
-    if (ts > nkt / 16) ts = nkt / 16;
+    if (ts > nkt / min_kt) ts = nkt / min_kt;
     const size_t per = (size_t)(tail + 7) * p.bm * p.bn * sizeof(float);  // the launch index range is padded to a multiple of 8
     if (ws_bytes / per < (size_t)ts) ts = (int)(ws_bytes / per);
     if (ts >= 2) {
@@ -688,11 +1051,35 @@ static int launch_cfg(GemmArgs g, int splits, hipStream_t stream, int n_groups =
   return DH_OK;
 }
 
+template <bool TA, bool TB, bool F32OUT>
+static int launch_wide(GemmArgs g, int splits, hipStream_t stream, int n_groups, int tile_first, int n_tiles, const GemmAr* ar) {
+  constexpr int LDS_BYTES = 2 * GW_STAGE;
+  static bool attr_set[DH_MAX_DEVICES] = {};
+  const int dev = dh_device_index();
+  if (!attr_set[dev]) {
+    DH_HIP(hipFuncSetAttribute((const void*)gemm_bf16_wide_kernel<TA, TB, F32OUT>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES));
+    attr_set[dev] = true;
+  }
+  g.tiles_m = (g.M + 255) / 256;
+  g.tiles_n = (g.N + 255) / 256;
+  g.tiles_per_xcd = (g.tiles_m * g.tiles_n + 7) / 8;
+  g.tile_first = tile_first;
+  dim3 grid((n_tiles >= 0 ? n_tiles : g.tiles_per_xcd * 8) + g.ar_blocks, splits, n_groups);
+  GemmAr none;
+  none.ranks = 0; none.n8 = 0; none.out = nullptr;
+  for (int r = 0; r < DH_MAX_RANKS; r++) none.parts.p[r] = nullptr;
+  gemm_bf16_wide_kernel<TA, TB, F32OUT><<<grid, 256, LDS_BYTES, stream>>>(g, ar ? *ar : none);
+  DH_LAUNCH_CHECK();
+  return DH_OK;
+}
+
 template <bool TA, bool TB>
 static int launch_layout(const GemmArgs& g, const GemmPlan& p, hipStream_t stream, int n_groups = 1, int tile_first = 0,
                          int n_tiles = -1, int splits = 0, const GemmAr* ar = nullptr) {
   if (splits == 0) splits = p.splits;
-  if (p.cfg == 0) return launch_cfg<256, 256, 2, 4, TA, TB>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
+  if (p.cfg == 0)
+    return g.epi == EPI_STORE_BF16 ? launch_wide<TA, TB, false>(g, splits, stream, n_groups, tile_first, n_tiles, ar)
+                                   : launch_wide<TA, TB, true>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
   if (p.cfg == 2) return launch_cfg<256, 128, 2, 2, TA, TB>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
   return launch_cfg<128, 128, 2, 2, TA, TB>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
 }
@@ -770,9 +1157,8 @@ int dh_launch_gemm_bf16_ar(bool ta, bool tb, int M, int N, int K, const bf16_t* 
   g.bias = nullptr; g.group_rows = nullptr; g.group_mode = 0;
   g.group_part = 0; g.n_groups = 1; g.part1_bm = g.part1_bn = 256; g.cus = 0; g.tile_first = 0;
   g.glu_mode = GLU_NONE; g.glu_f = 0; g.glu_in = nullptr; g.glu_out = nullptr;
-  const int threads = p.cfg == 0 ? 512 : 256;
-  const size_t n8 = ar_elems / 8, want = (n8 + threads - 1) / threads;
-  size_t nb = ((size_t)ar_blocks * 256 + threads - 1) / threads;
+  const size_t n8 = ar_elems / 8, want = (n8 + 255) / 256;
+  size_t nb = ar_blocks;
   if (nb > want) nb = want;
   g.ar_blocks = (int)nb;
   GemmAr ar;
@@ -794,12 +1180,12 @@ int dh_launch_gemm_swiglu_fwd_bf16(int T, int F, int H, const bf16_t* x, const b
   if (!dh_glu_fwd_fits(T, F, H)) DH_FAIL(DH_ERR_SHAPE, "gemm+swiglu forward: T=%d F=%d H=%d does not fit the fused kernel", T, F, H);
   GemmArgs g;
   g.M = T; g.N = 2 * F; g.K = H; g.A = x; g.B = Wgu; g.C = gu; g.epi = EPI_STORE_BF16;
-  g.kt_per_split = H / GB_BK;
+  g.kt_per_split = (H + GW_BK - 1) / GW_BK;
   g.tiles_m = g.tiles_n = g.tiles_per_xcd = 0;
   g.bias = nullptr; g.group_rows = nullptr; g.group_mode = 0;
   g.group_part = 0; g.n_groups = 1; g.part1_bm = g.part1_bn = 256; g.cus = 0; g.tile_first = 0;
   g.glu_mode = GLU_FWD; g.glu_f = F; g.glu_in = nullptr; g.glu_out = a; g.ar_blocks = 0;
-  return launch_cfg<256, 256, 2, 4, false, false>(g, 1, stream);
+  return launch_wide<false, false, false>(g, 1, stream, 1, 0, -1, nullptr);
 }
 
 // Data gradient of the down projection with SwiGLU's backward in its epilogue: dA = dY[T, H] * Wd[F, H]^T is not
@@ -842,7 +1228,7 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
   if (mode == 2) { g.M = dim_a; g.N = dim_b; g.K = max_rows; p = choose_plan(true, dim_a, dim_b, avg, 0); }
   else { g.M = max_rows; g.N = dim_b; g.K = dim_a; p = choose_plan(false, avg, dim_b, dim_a, 0); }
   p.splits = 1;
-  g.kt_per_split = (g.K + GB_BK - 1) / GB_BK;
+  g.kt_per_split = g.K;  // no K split
   g.epi = mode == 2 ? EPI_ACC_F32 : EPI_STORE_BF16;
   if (mode == 2) return launch_layout<true, false>(g, p, stream, n_groups);
   if (p.cfg != 0 || n_groups > 64)  // small tiles already, or too many groups for the in-kernel row scan: one launch
