@@ -1,20 +1,78 @@
-// float32 GEMM for the fp32 configuration: C[M,N] (+)= opA(A) * opB(B) with plain FMA arithmetic.
-// 64x64 output tile per 256-thread block, 4x4 outputs per thread, K consumed 16 at a time through
-// LDS.  The sum over K runs in index order in one accumulator per output, so results do not depend
-// on scheduling.  Any M, N, K >= 0 is accepted (edges are predicated).
+// float32 GEMM for the fp32 configuration: C[M,N] (+)= opA(A) * opB(B), on the float32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: float32 operands, products and sums).
+// Bound: at the sizes this configuration is used for (a few hundred rows and columns) a product is a chain of
+// memory latencies, not a rate.  So the tiles are small (32x32, or 16x16 where
+// those would leave compute units idle), their K range is cut over the waves of a block (each at
+// least 32 of K, up to 16 waves) and operands go from memory straight into the fragments, two K steps ahead of their
+// products; the waves' partial tiles meet in LDS and are added in wave order, so results do not depend on scheduling.
+// 128x768x256: 38 -> 4.6 us, 128x256x1376: 123 -> 7.8 us against a 64x64 tile per 256 threads with the whole of K walked by each.
+// Any M, N, K >= 0 is accepted; VEC: rows of both operands can be read 16 bytes (K-contiguous) or 8 bytes (K-major)
+// at a time, otherwise every element is fetched and checked on its own.
+#include <algorithm>
 #include "common.h"
 
-#define F32_BM 64
-#define F32_BN 64
-#define F32_BK 16
+#define F32_KS 16          // K of one step: four matrix instructions deep
+#define F32_AHEAD 2
+#define F32_MAX_WAVES 16
 
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
-                                                       const float* __restrict__ B, float* __restrict__ C, int accumulate,
-                                                       const float* __restrict__ bias, const int32_t* __restrict__ group_rows,
-                                                       int group_mode) {
-  __shared__ float As[F32_BK][F32_BM + 4];
-  __shared__ float Bs[F32_BK][F32_BN + 4];
+// Fragments of one K step of an operand: v[t][e] = element (row, k0 + 4*(lane/16) + e) for the NT 16-row tiles t, where
+// row = 16 t + lane%16 for a K-contiguous operand and NT*(lane%16) + t for a K-major one (two tiles interleave, so
+// that a lane's pair is contiguous in memory).
+template <int NT>
+struct F32Frag {
+  float v[NT][4];
+};
+template <int NT, bool KMAJOR, bool VEC>
+__device__ __forceinline__ void f32_fetch(F32Frag<NT>& f, const float* __restrict__ p, int r0, int k0, int R, int K, int kend, int lane) {
+  const int l16 = lane & 15, k = k0 + 4 * (lane >> 4);
+  if (KMAJOR) {
+    const int r = r0 + NT * l16;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+#pragma unroll
+      for (int t = 0; t < NT; t++) f.v[t][e] = 0.f;
+      if (k + e >= kend) continue;
+      const float* row = p + (size_t)(k + e) * R + r;
+      if (NT == 2 && VEC) {
+        if (r < R) {
+          const float2 x = *reinterpret_cast<const float2*>(row);
+          f.v[0][e] = x.x;
+          f.v[NT - 1][e] = x.y;
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+          if (r + t < R) f.v[t][e] = row[t];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      const int r = r0 + 16 * t + l16;
+#pragma unroll
+      for (int e = 0; e < 4; e++) f.v[t][e] = 0.f;
+      if (r >= R) continue;
+      if (VEC) {
+        if (k < kend) {
+          const float4 x = *reinterpret_cast<const float4*>(p + (size_t)r * K + k);
+          f.v[t][0] = x.x; f.v[t][1] = x.y; f.v[t][2] = x.z; f.v[t][3] = x.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (k + e < kend) f.v[t][e] = p[(size_t)r * K + k + e];
+      }
+    }
+  }
+}
+
+template <int NT, bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
+                                                                      const float* __restrict__ B, float* __restrict__ C, int accumulate,
+                                                                      const float* __restrict__ bias, const int32_t* __restrict__ group_rows,
+                                                                      int group_mode) {
+  constexpr int TILE = 16 * NT, LD = TILE + 4;  // square tiles; row pitch of a partial tile
+  extern __shared__ float part[];               // [waves][TILE][LD]
   if (group_rows != nullptr) {  // grouped: blockIdx.z = group, its rows follow those of the groups before it
     int row0 = 0;
     for (int i = 0; i < (int)blockIdx.z; i++) row0 += group_rows[i];
@@ -24,84 +82,114 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, cons
     } else {
       A += (size_t)row0 * K; B += (size_t)blockIdx.z * K * N; C += (size_t)row0 * N; M = rows;
     }
-    if (rows == 0 || (int)blockIdx.y * F32_BM >= M) return;
+    if (rows == 0 || (int)blockIdx.y * TILE >= M) return;
   }
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * F32_BM, n0 = blockIdx.x * F32_BN;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += F32_BK) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
+  const int steps = (K + F32_KS - 1) / F32_KS, per = (steps + waves - 1) / waves;
+  const int k_begin = wave * per * F32_KS, k_end = min(K, k_begin + per * F32_KS);
+  f32x4 acc[NT][NT];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      int idx = tid + i * 256;
-      int m, k;
-      if (TA) { k = idx / F32_BM; m = idx % F32_BM; } else { m = idx / F32_BK; k = idx % F32_BK; }
-      int gm = m0 + m, gk = k0 + k;
-      float v = 0.f;
-      if (gm < M && gk < K) v = TA ? A[(size_t)gk * M + gm] : A[(size_t)gm * K + gk];
-      As[k][m] = v;
-      int n;
-      if (TB) { n = idx / F32_BK; k = idx % F32_BK; } else { k = idx / F32_BN; n = idx % F32_BN; }
-      int gn = n0 + n;
-      gk = k0 + k;
-      v = 0.f;
-      if (gn < N && gk < K) v = TB ? B[(size_t)gn * K + gk] : B[(size_t)gk * N + gn];
-      Bs[k][n] = v;
+  for (int i = 0; i < NT; i++)
+#pragma unroll
+    for (int j = 0; j < NT; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  F32Frag<NT> a[F32_AHEAD], b[F32_AHEAD];
+  auto fetch = [&](int s, int k) {
+    f32_fetch<NT, TA, VEC>(a[s], A, m0, k, M, K, k_end, lane);
+    f32_fetch<NT, !TB, VEC>(b[s], B, n0, k, N, K, k_end, lane);
+  };
+#pragma unroll
+  for (int s = 0; s < F32_AHEAD; s++) fetch(s, k_begin + s * F32_KS);
+  for (int k = k_begin; k < k_end; k += F32_AHEAD * F32_KS) {
+#pragma unroll
+    for (int s = 0; s < F32_AHEAD; s++) {
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int i = 0; i < NT; i++)
+#pragma unroll
+          for (int j = 0; j < NT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s].v[i][e], b[s].v[j][e], acc[i][j], 0, 0, 0);
+      fetch(s, k + (s + F32_AHEAD) * F32_KS);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < F32_BK; k++) {
-      float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-      float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
   }
+  // acc[i][j][r]: row index 4*(lane/16) + r of A's tile i, column index lane%16 of B's tile j
+  float* mine = part + wave * (TILE * LD);
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    int gm = m0 + ty * 4 + i;
+  for (int i = 0; i < NT; i++)
+#pragma unroll
+    for (int j = 0; j < NT; j++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int ri = 4 * (lane >> 4) + r, cj = lane & 15;
+        const int row = TA ? NT * ri + i : 16 * i + ri, col = !TB ? NT * cj + j : 16 * j + cj;
+        mine[row * LD + col] = acc[i][j][r];
+      }
+  __syncthreads();
+  for (int x = threadIdx.x; x < TILE * TILE / 4; x += blockDim.x) {
+    const int row = x / (TILE / 4), c = (x % (TILE / 4)) * 4, gm = m0 + row, gn = n0 + c;
     if (gm >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      int gn = n0 + tx * 4 + j;
+    f32x4 s = *reinterpret_cast<const f32x4*>(part + row * LD + c);
+    for (int w = 1; w < waves; w++) s += *reinterpret_cast<const f32x4*>(part + w * (TILE * LD) + row * LD + c);
+    float* dst = C + (size_t)gm * N + gn;
+    if (N % 4 == 0) {
       if (gn >= N) continue;
-      size_t o = (size_t)gm * N + gn;
-      const float v = bias ? acc[i][j] + bias[gn] : acc[i][j];
-      C[o] = accumulate ? C[o] + v : v;
+      if (bias) s += *reinterpret_cast<const f32x4*>(bias + gn);
+      if (accumulate) s += *reinterpret_cast<const f32x4*>(dst);
+      *reinterpret_cast<f32x4*>(dst) = s;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (gn + e < N) {
+          const float v = bias ? s[e] + bias[gn + e] : s[e];
+          dst[e] = accumulate ? dst[e] + v : v;
+        }
     }
   }
+}
+
+template <bool TA, bool TB>
+static int launch_f32(int M, int N, int K, int k_typical, const float* A, const float* B, float* C, bool accumulate, const float* bias,
+                      const int32_t* group_rows, int group_mode, int n_groups, hipStream_t stream) {
+  const int waves = std::min(F32_MAX_WAVES, std::max(1, (k_typical + 31) / 32));
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  const bool vec = aligned(A) && aligned(B) && aligned(C) && aligned(bias) && (TA ? M : K) % 4 == 0 && (TB ? K : N) % 4 == 0;
+  // 16x16 tiles load twice as much per product: they pay only while 32x32 tiles come to fewer blocks than compute units.
+  const bool small = (long long)((M + 31) / 32) * ((N + 31) / 32) * n_groups < 256;
+#define GO(NT, V)                                                                                                               \
+  do {                                                                                                                          \
+    constexpr int TILE = 16 * NT, PART = TILE * (TILE + 4) * (int)sizeof(float);                                                \
+    static bool attr_set[DH_MAX_DEVICES] = {};                                                                                  \
+    const int dev = dh_device_index();                                                                                          \
+    if (!attr_set[dev]) {                                                                                                       \
+      DH_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<NT, TA, TB, V>, hipFuncAttributeMaxDynamicSharedMemorySize,       \
+                                 F32_MAX_WAVES * PART));                                                                        \
+      attr_set[dev] = true;                                                                                                     \
+    }                                                                                                                           \
+    dim3 grid((N + TILE - 1) / TILE, (M + TILE - 1) / TILE, n_groups);                                                          \
+    gemm_f32_kernel<NT, TA, TB, V><<<grid, 64 * waves, waves * PART, stream>>>(M, N, K, A, B, C, accumulate ? 1 : 0, bias,      \
+                                                                               group_rows, group_mode);                         \
+  } while (0)
+  if (small) { if (vec) GO(1, true); else GO(1, false); }
+  else { if (vec) GO(2, true); else GO(2, false); }
+#undef GO
+  DH_LAUNCH_CHECK();
+  return DH_OK;
 }
 
 int dh_launch_gemm_f32(bool ta, bool tb, int M, int N, int K, const float* A, const float* B, float* C,
                        bool accumulate, const float* bias, hipStream_t stream) {
   if (M == 0 || N == 0) return DH_OK;
-  dim3 grid((N + F32_BN - 1) / F32_BN, (M + F32_BM - 1) / F32_BM), block(256);
-  if (!ta && !tb) gemm_f32_kernel<false, false><<<grid, block, 0, stream>>>(M, N, K, A, B, C, accumulate, bias, nullptr, 0);
-  else if (!ta && tb) gemm_f32_kernel<false, true><<<grid, block, 0, stream>>>(M, N, K, A, B, C, accumulate, bias, nullptr, 0);
-  else if (ta && !tb) gemm_f32_kernel<true, false><<<grid, block, 0, stream>>>(M, N, K, A, B, C, accumulate, bias, nullptr, 0);
-  else gemm_f32_kernel<true, true><<<grid, block, 0, stream>>>(M, N, K, A, B, C, accumulate, bias, nullptr, 0);
-  DH_LAUNCH_CHECK();
-  return DH_OK;
+  if (!ta && !tb) return launch_f32<false, false>(M, N, K, K, A, B, C, accumulate, bias, nullptr, 0, 1, stream);
+  if (!ta && tb) return launch_f32<false, true>(M, N, K, K, A, B, C, accumulate, bias, nullptr, 0, 1, stream);
+  if (ta && !tb) return launch_f32<true, false>(M, N, K, K, A, B, C, accumulate, bias, nullptr, 0, 1, stream);
+  return launch_f32<true, true>(M, N, K, K, A, B, C, accumulate, bias, nullptr, 0, 1, stream);
 }
 
 // Grouped form: see dh_launch_gemm_grouped_bf16.  max_rows bounds every group's row count (grid size).
 int dh_launch_gemm_grouped_f32(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                const float* A, const float* B, float* C, hipStream_t stream) {
   if (max_rows == 0) return DH_OK;
-  if (mode == 0) {
-    dim3 grid((dim_b + F32_BN - 1) / F32_BN, (max_rows + F32_BM - 1) / F32_BM, n_groups);
-    gemm_f32_kernel<false, false><<<grid, 256, 0, stream>>>(max_rows, dim_b, dim_a, A, B, C, 0, nullptr, group_rows, 0);
-  } else if (mode == 1) {
-    dim3 grid((dim_b + F32_BN - 1) / F32_BN, (max_rows + F32_BM - 1) / F32_BM, n_groups);
-    gemm_f32_kernel<false, true><<<grid, 256, 0, stream>>>(max_rows, dim_b, dim_a, A, B, C, 0, nullptr, group_rows, 1);
-  } else {
-    dim3 grid((dim_b + F32_BN - 1) / F32_BN, (dim_a + F32_BM - 1) / F32_BM, n_groups);
-    gemm_f32_kernel<true, false><<<grid, 256, 0, stream>>>(dim_a, dim_b, max_rows, A, B, C, 1, nullptr, group_rows, 2);
-  }
-  DH_LAUNCH_CHECK();
-  return DH_OK;
+  if (mode == 0) return launch_f32<false, false>(max_rows, dim_b, dim_a, dim_a, A, B, C, false, nullptr, group_rows, 0, n_groups, stream);
+  if (mode == 1) return launch_f32<false, true>(max_rows, dim_b, dim_a, dim_a, A, B, C, false, nullptr, group_rows, 1, n_groups, stream);
+  return launch_f32<true, false>(dim_a, dim_b, max_rows, max_rows / n_groups, A, B, C, true, nullptr, group_rows, 2, n_groups, stream);
 }

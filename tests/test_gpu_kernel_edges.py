@@ -1,0 +1,90 @@
+"""GPU parity of single operators at the edges of their kernels' tiles, steps and dispatch rules, against plain float64
+products on the host or float32 ones on the device."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer_ref as R
+from paper_2411_15871_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dh():
+    from paper_2411_15871_amd import dhelix
+    assert torch.cuda.is_available()
+    return dhelix
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-30))
+
+
+# float32 GEMM: 16x16 tiles (few blocks) and 32x32 tiles, K ranges that leave waves without work, rows that allow 16-byte
+# loads and rows that do not
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(16, 16, 16), (17, 33, 31), (128, 256, 1376), (520, 516, 36), (513, 1031, 70), (1024, 512, 33)])
+def test_gemm_f32_tiles(dh, ta, tb, M, N, K):
+    A, B = gen.normal(80, (K, M) if ta else (M, K)), gen.normal(81, (N, K) if tb else (K, N))
+    bias = gen.normal(82, (N,))
+    Ad, Bd, bd = (torch.from_numpy(v).cuda() for v in (A, B, bias))
+    ref = (A.T if ta else A).astype(np.float64) @ (B.T if tb else B).astype(np.float64)
+    C = torch.full((M * N + 64,), 3.0, device="cuda")
+    dh.dh_gemm_bias(dh.DH_F32, ta, tb, M, N, K, Ad, Bd, bd, C, False)
+    assert rel(C[: M * N].cpu().numpy().reshape(M, N), ref + bias) <= 1e-6
+    C.fill_(3.0)
+    dh.dh_gemm(dh.DH_F32, ta, tb, M, N, K, Ad, Bd, C, True)
+    assert rel(C[: M * N].cpu().numpy().reshape(M, N), ref + 3.0) <= 1e-6
+    assert torch.all(C[M * N:] == 3.0)
+
+
+# float32 attention: every instantiation of the head width, ragged last tiles, grouped heads, a query offset that is no
+# multiple of a tile
+@pytest.mark.parametrize("batch,seq,q_off,nq,nkv,d", [(1, 1, 0, 1, 1, 16), (2, 17, 0, 4, 2, 32), (1, 130, 0, 3, 1, 64), (1, 200, 0, 4, 4, 128),
+                                                      (1, 70, 0, 2, 1, 256), (2, 37, 21, 4, 2, 40), (1, 48, 160, 8, 1, 128)])
+def test_attention_f32_tiles(dh, batch, seq, q_off, nq, nkv, d):
+    T, S = batch * seq, q_off + seq
+    full = [gen.normal(83 + i, (batch * S, n * d)) for i, n in enumerate((nq, nkv, nkv))]
+    dof = gen.normal(86, (batch * S, nq * d))
+    own = np.concatenate([np.arange(b * S + q_off, (b + 1) * S) for b in range(batch)])
+    dof[np.setdiff1d(np.arange(batch * S), own)] = 0.0   # only the last seq positions are queries
+    q64, k64, v64 = (a.astype(np.float64).reshape(batch * S, n, d) for a, n in zip(full, (nq, nkv, nkv)))
+    o_ref, lse_ref = R.attention_fwd(q64, k64, v64, batch, S)
+    dq, dk, dv = R.attention_bwd(dof.astype(np.float64).reshape(batch * S, nq, d), q64, k64, v64, batch, S)
+    qkv = torch.from_numpy(np.concatenate(full, axis=1)[own].copy()).cuda()
+    kv = torch.from_numpy(np.concatenate(full[1:], axis=1).copy()).cuda()
+    do = torch.from_numpy(dof[own].copy()).cuda()
+    o, lse, delta = torch.empty(T, nq * d, device="cuda"), torch.empty(nq, T, device="cuda"), torch.empty(nq, T, device="cuda")
+    dqkv, dkv = torch.zeros_like(qkv), torch.zeros_like(kv)
+    dh.dh_attn_ctx_fwd(dh.DH_F32, batch, seq, q_off, nq, nkv, d, qkv, kv, o, lse)
+    dh.dh_attn_ctx_bwd(dh.DH_F32, batch, seq, q_off, nq, nkv, d, qkv, kv, o, do, lse, dqkv, dkv, delta)
+    assert rel(o.cpu().numpy(), o_ref.reshape(batch * S, -1)[own]) <= 2e-6
+    assert np.max(np.abs(lse.cpu().numpy() - lse_ref[:, own])) <= 1e-5
+    floor = np.linalg.norm(dv) if S == 1 else 0.0        # dq = dk = 0 exactly when a row sees one key
+    for got, ref in ((dqkv.cpu().numpy()[:, : nq * d], dq.reshape(batch * S, -1)[own]), (dkv.cpu().numpy()[:, : nkv * d], dk.reshape(batch * S, -1)),
+                     (dkv.cpu().numpy()[:, nkv * d:], dv.reshape(batch * S, -1))):
+        assert np.linalg.norm(got - ref) <= 5e-6 * max(np.linalg.norm(ref), floor)
+
+
+# bf16 GEMM with 256x256 tiles: K below, at and beyond its two-stage pipeline and off the K step, ragged rows and columns
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(2824, 3080, 8), (2817, 3080, 64), (2560, 3336, 72), (2560, 3328, 128), (3080, 2568, 200), (2832, 2824, 264),
+                                   (2568, 3088, 328)])
+def test_gemm_bf16_wide_tiles(dh, ta, tb, M, N, K):
+    if ta:
+        M = (M + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda", dtype=torch.bfloat16)
+    B = torch.randn((N, K) if tb else (K, N), generator=g, device="cuda", dtype=torch.bfloat16)
+    bias = torch.randn(N, generator=g, device="cuda", dtype=torch.bfloat16)
+    ref = (A.float().t().contiguous() if ta else A.float()) @ (B.float().t().contiguous() if tb else B.float())
+    C = torch.full((M * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    dh.dh_gemm_bias(dh.DH_BF16, ta, tb, M, N, K, A, B, bias, C, False)
+    want = ref + bias.float()
+    assert float((C[: M * N].view(M, N).float() - want).norm() / want.norm()) <= 4e-3
+    assert torch.all(C[M * N:] == 7.0)
+    Cf = torch.full((M * N + 64,), 1.0, device="cuda")
+    dh.dh_gemm(dh.DH_BF16, ta, tb, M, N, K, A, B, Cf, True)
+    assert float((Cf[: M * N].view(M, N) - 1.0 - ref).norm() / ref.norm()) <= 2e-5
+    assert torch.all(Cf[M * N:] == 1.0)
