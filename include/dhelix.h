@@ -704,10 +704,10 @@ int dh_gemm_allreduce(int trans_a, int trans_b, int M, int N, int K, const void*
  * launch and no second pass over the gate/up tensor.  Results are bit-identical to dh_gemm followed by
  * dh_swiglu_fwd / dh_swiglu_bwd.  All pointers device, row-major, 16-byte aligned; nothing is allocated.
  *   forward : gu[T,2F] = x[T,H] * w_gate_up[H,2F] (columns [gate | up]), a[T,F] = gate * sigmoid(gate) * up.
- *             Fits (dh_gemm_swiglu_fwd_fits = 1) when T % 256 == 0, F % 128 == 0, H % 32 == 0 and the plain GEMM
- *             would be a single launch of 256x256 tiles.
+ *             Fits (dh_gemm_swiglu_fwd_fits = 1) when F % 128 == 0, H % 8 == 0 and the plain GEMM would be a single
+ *             launch without workspace.
  *   backward: dgu[T,2F] = (d gate | d up) from dA = dy[T,H] * w_down[F,H]^T (never stored) and gu[T,2F].
- *             Fits when the plain GEMM would be a single launch of whole tiles without a K split.
+ *             Fits when F % 8 == 0, H % 8 == 0 and the plain GEMM would be a single launch without workspace.
  * A shape that does not fit returns DH_ERR_UNSUPPORTED (the caller then uses the two separate operators, as the
  * layer does); null pointers DH_ERR_INVALID_ARG. */
 int dh_gemm_swiglu_fwd_fits(int T, int F, int H);

@@ -88,3 +88,48 @@ def test_gemm_bf16_wide_tiles(dh, ta, tb, M, N, K):
     dh.dh_gemm(dh.DH_BF16, ta, tb, M, N, K, A, B, Cf, True)
     assert float((Cf[: M * N].view(M, N) - 1.0 - ref).norm() / ref.norm()) <= 2e-5
     assert torch.all(Cf[M * N:] == 1.0)
+
+
+# bf16 GEMM over its tile shapes: 64x64 alone and with K ranges summed in the block (also ranges that end inside a stage), 128x128
+# one and two blocks to a unit, 256x128, K split through the workspace, 256x256; K below the ring's depth and off its step
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (64, 64, 64), (130, 200, 520), (65, 72, 1000), (72, 136, 1576), (1000, 520, 1064), (2056, 264, 328),
+                                   (656, 384, 7680), (1030, 2304, 1000), (264, 4096, 3560), (3081, 3080, 136), (4096, 2072, 1032), (2050, 3080, 1992),
+                                   (4090, 4088, 200), (4096, 3848, 456)])
+def test_gemm_bf16_tile_shapes(dh, ta, tb, M, N, K):
+    test_gemm_bf16_wide_tiles(dh, ta, tb, M, N, K)
+    if ta:
+        M = (M + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda", dtype=torch.bfloat16)
+    B = torch.randn((N, K) if tb else (K, N), generator=g, device="cuda", dtype=torch.bfloat16)
+    ref = (A.float().t().contiguous() if ta else A.float()) @ (B.float().t().contiguous() if tb else B.float())
+    C = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+    wsb = dh.dh_gemm_workspace_bytes(dh.DH_BF16, ta, tb, M, N, K)
+    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device="cuda")
+    dh.dh_gemm(dh.DH_BF16, ta, tb, M, N, K, A, B, C, False, ws, wsb)
+    assert float((C.float() - ref).norm() / ref.norm()) <= 4e-3
+
+
+# SwiGLU in the epilogues of every tile shape, token counts and feature widths that fill no tile
+@pytest.mark.parametrize("T,F,H", [(1, 128, 64), (200, 384, 1096), (700, 1152, 1000), (2049, 1792, 1024), (4000, 3584, 1536), (130, 136, 200), (2047, 1800, 1024)])
+def test_gemm_swiglu_ragged(dh, T, F, H):
+    g = torch.Generator(device="cuda").manual_seed(T + F)
+    bf = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    x, w1, dy, wd = bf(T, H), bf(H, 2 * F) * 0.05, bf(T, H), bf(F, H) * 0.05
+    wsb = max(dh.dh_gemm_workspace_bytes(dh.DH_BF16, 0, 0, T, 2 * F, H), dh.dh_gemm_workspace_bytes(dh.DH_BF16, 0, 1, T, F, H))
+    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device="cuda")
+    gu, a, da, dgu = (torch.zeros(T, n, dtype=torch.bfloat16, device="cuda") for n in (2 * F, F, F, 2 * F))
+    dh.dh_gemm(dh.DH_BF16, 0, 0, T, 2 * F, H, x, w1, gu, False, ws, wsb)
+    dh.dh_swiglu_fwd(dh.DH_BF16, T, F, gu, a)
+    dh.dh_gemm(dh.DH_BF16, 0, 1, T, F, H, dy, wd, da, False, ws, wsb)
+    dh.dh_swiglu_bwd(dh.DH_BF16, T, F, gu, da, dgu)
+    if dh.dh_gemm_swiglu_fwd_fits(T, F, H):
+        gu1, a1 = (torch.full((T * n + 64,), 7.0, dtype=torch.bfloat16, device="cuda") for n in (2 * F, F))
+        dh.dh_gemm_swiglu_fwd(T, F, H, x, w1, gu1, a1)
+        assert torch.equal(gu1[:-64].view_as(gu), gu) and torch.equal(a1[:-64].view_as(a), a)
+        assert torch.all(gu1[-64:] == 7.0) and torch.all(a1[-64:] == 7.0)
+    if dh.dh_gemm_swiglu_bwd_fits(T, F, H):
+        dgu1 = torch.full((T * 2 * F + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+        dh.dh_gemm_swiglu_bwd(T, F, H, dy, wd, gu, dgu1)
+        assert torch.equal(dgu1[:-64].view_as(dgu), dgu) and torch.all(dgu1[-64:] == 7.0)
