@@ -191,6 +191,17 @@ int dh_launch_gemm_grouped_f32(int mode, int n_groups, const int32_t* group_rows
                                const float* A, const float* B, float* C, hipStream_t stream);
 int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                 const bf16_t* A, const bf16_t* B, void* C, hipStream_t stream);
+// Norm, residual add and their gradients behind a reduction over n_parts partial buffers (rowops.hip).
+int dh_launch_sum_rmsnorm_fwd(int dtype, int T, int H, const void* x, int n_parts, const void* const* parts, const void* gamma, float eps,
+                              void* x_out, void* h, float* rstd, hipStream_t s);
+int dh_launch_sum_rmsnorm_bwd(int dtype, int T, int H, int n_parts, const void* const* parts, const void* x, const void* gamma, const float* rstd,
+                              const void* dres, void* dx, float* dgamma, float* ws, hipStream_t s);
+int dh_launch_sum_layernorm_fwd(int dtype, int T, int H, const void* x, int n_parts, const void* const* parts, const void* res_bias,
+                                const void* gamma, const void* beta, float eps, void* x_out, void* h, float* mu, float* rstd, hipStream_t s);
+int dh_launch_sum_layernorm_bwd(int dtype, int T, int H, int n_parts, const void* const* parts, const void* x, const void* gamma,
+                                const float* mu, const float* rstd, const void* dres, void* dx, float* dgamma, float* dbeta, float* ws,
+                                hipStream_t s);
+int dh_launch_sum_add(int dtype, int T, int H, const void* a, int n_parts, const void* const* parts, const void* bias, void* out, hipStream_t s);
 size_t dh_gemm_bf16_ws_bytes(bool ta, bool tb, int M, int N, int K);
 // A bf16 GEMM launch that carries an all-reduce stand-in along: the first ar_blocks*256/(block size) thread blocks of the
 // launch stream the payload (elems bf16 elements, n_ranks partials), the others compute the GEMM's tiles.  *_fits: the

@@ -443,12 +443,22 @@ static int gemm(const dh_layer* L, bool ta, bool tb, int M, int N, int K, const 
 }
 
 // Collective stand-in over parts = {own, peers[0], ..., peers[R-2]}, each `elems` elements.
-static int collective(const dh_layer* L, int kind, const void* own, const void* peers, size_t elems, void* out, hipStream_t s) {
-  const void* parts[16];
-  parts[0] = own;
-  for (int r = 1; r < L->c.n_ranks; r++) parts[r] = (const char*)peers + (size_t)(r - 1) * elems * L->es;
-  return dh_comm_standin(kind, L->c.n_ranks, parts, out, elems, L->c.dtype, L->c.comm_blocks, (void*)s);
+struct Parts {
+  const void* p[DH_MAX_RANKS];
+};
+static Parts parts_of(const dh_layer* L, const void* own, const void* peers, size_t elems) {
+  Parts parts;
+  parts.p[0] = own;
+  for (int r = 1; r < L->c.n_ranks; r++) parts.p[r] = (const char*)peers + (size_t)(r - 1) * elems * L->es;
+  return parts;
 }
+static int collective(const dh_layer* L, int kind, const void* own, const void* peers, size_t elems, void* out, hipStream_t s) {
+  const Parts parts = parts_of(L, own, peers, elems);
+  return dh_comm_standin(kind, L->c.n_ranks, parts.p, out, elems, L->c.dtype, L->c.comm_blocks, (void*)s);
+}
+// Whether a reduction and the norm or residual add behind it are one launch (made by the reduction; the other operator then
+// launches nothing): wherever the stand-in may use the whole chip.  On a block budget it is a transfer of its own.
+static bool reduction_with_consumer(const dh_layer* L) { return L->c.comm_blocks == 0; }
 
 // Whether backward all-reduce `which` (1: AR3, 2: AR4) is carried by its weight-gradient GEMM right now.
 static bool fused_collective(const dh_layer* L, int which) { return (L->fuse_comm & which) != 0 && L->c.comm_blocks > 0; }
@@ -456,10 +466,8 @@ static bool fused_collective(const dh_layer* L, int which) { return (L->fuse_com
 // The all-reduce stand-in over {own, peers...} and an unrelated bf16 GEMM in one launch.
 static int collective_with_gemm(const dh_layer* L, const void* own, const void* peers, size_t elems, void* out, bool ta, bool tb, int M,
                                 int N, int K, const void* A, const void* B, void* C, bool acc, hipStream_t s) {
-  const void* parts[16];
-  parts[0] = own;
-  for (int r = 1; r < L->c.n_ranks; r++) parts[r] = (const char*)peers + (size_t)(r - 1) * elems * L->es;
-  return dh_launch_gemm_bf16_ar(ta, tb, M, N, K, (const bf16_t*)A, (const bf16_t*)B, C, acc, L->c.n_ranks, parts, (bf16_t*)out, elems,
+  const Parts parts = parts_of(L, own, peers, elems);
+  return dh_launch_gemm_bf16_ar(ta, tb, M, N, K, (const bf16_t*)A, (const bf16_t*)B, C, acc, L->c.n_ranks, parts.p, (bf16_t*)out, elems,
                                 L->c.comm_blocks, s);
 }
 
@@ -512,8 +520,12 @@ static int llama_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hip
     case DH_F_PROJ:
       return gemm(L, false, false, T, H, L->n_o, sv + L->s_o, L->w.Wo, ws + L->f_part, false, gws, L->f_gemm_bytes, s);
     case DH_F_AR1:
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_rmsnorm_fwd(dt, T, H, a.x, c.n_ranks, parts_of(L, ws + L->f_part, a.peers_ar1, n).p, L->w.g2, c.eps,
+                                         sv + L->s_x2, sv + L->s_h2, (float*)(sv + L->s_rstd2), s);
       return collective(L, DH_COMM_ALLREDUCE, ws + L->f_part, a.peers_ar1, n, ws + L->f_red, s);
     case DH_F_NORM2:  // x2 = x + y (residual of the bias-dropout-add operator), h2 = norm(x2)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by F_AR1's launch
       return dh_rmsnorm_fwd(dt, T, H, a.x, ws + L->f_red, L->w.g2, c.eps, sv + L->s_x2, sv + L->s_h2, (float*)(sv + L->s_rstd2), s);
     case DH_F_FC1:
       if (L->fuse_act_fwd)
@@ -526,8 +538,11 @@ static int llama_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hip
     case DH_F_FC2:
       return gemm(L, false, false, T, H, F, sv + L->s_a, L->w.Wd, ws + L->f_part, false, gws, L->f_gemm_bytes, s);
     case DH_F_AR2:
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_add(dt, T, H, sv + L->s_x2, c.n_ranks, parts_of(L, ws + L->f_part, a.peers_ar2, n).p, nullptr, a.out, s);
       return collective(L, DH_COMM_ALLREDUCE, ws + L->f_part, a.peers_ar2, n, ws + L->f_red, s);
     case DH_F_BDA2:
+      if (reduction_with_consumer(L)) return DH_OK;  // done by F_AR2's launch
       return dh_add(dt, n, sv + L->s_x2, ws + L->f_red, a.out, s);
   }
   DH_FAIL(DH_ERR_INVALID_ARG, "unknown forward operator %d", op);
@@ -561,8 +576,12 @@ static int llama_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hip
       if (fused_collective(L, 1))
         return collective_with_gemm(L, ws + L->b_part, b.peers_ar3, n, ws + L->b_red, true, false, H, 2 * F, T, sv + L->s_h2,
                                     ws + L->b_dgu, L->g.dWgu, true, s);
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_rmsnorm_bwd(dt, T, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar3, n).p, sv + L->s_x2, L->w.g2,
+                                         (const float*)(sv + L->s_rstd2), b.dout, ws + L->b_dx2, L->g.dg2, (float*)(ws + L->b_norm), s);
       return collective(L, DH_COMM_ALLREDUCE, ws + L->b_part, b.peers_ar3, n, ws + L->b_red, s);
     case DH_B_NORM2:  // dx2 = dout + norm2_bwd(dh2)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by B_AR3's launch
       return dh_rmsnorm_bwd(dt, T, H, ws + L->b_red, sv + L->s_x2, L->w.g2, (const float*)(sv + L->s_rstd2), b.dout,
                             ws + L->b_dx2, L->g.dg2, ws + L->b_norm, L->b_norm_bytes, s);
     case DH_B_PROJ_DGRAD:
@@ -582,8 +601,12 @@ static int llama_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hip
       if (fused_collective(L, 2))
         return collective_with_gemm(L, ws + L->b_part, b.peers_ar4, n, ws + L->b_red, true, false, H, L->n_qkv, T, sv + L->s_h1,
                                     ws + L->b_dqkv, L->g.dWqkv, true, s);
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_rmsnorm_bwd(dt, T, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar4, n).p, b.x, L->w.g1,
+                                         (const float*)(sv + L->s_rstd1), ws + L->b_dx2, b.dx, L->g.dg1, (float*)(ws + L->b_norm), s);
       return collective(L, DH_COMM_ALLREDUCE, ws + L->b_part, b.peers_ar4, n, ws + L->b_red, s);
     case DH_B_NORM1:  // dx = dx2 + norm1_bwd(dh1)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by B_AR4's launch
       return dh_rmsnorm_bwd(dt, T, H, ws + L->b_red, b.x, L->w.g1, (const float*)(sv + L->s_rstd1), ws + L->b_dx2, b.dx,
                             L->g.dg1, ws + L->b_norm, L->b_norm_bytes, s);
   }
@@ -687,8 +710,12 @@ static int gpt_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hipSt
     case DH_GF_PROJ:
       return gemm(L, false, false, T, H, L->n_o, sv + L->s_o, L->w.Wo, ws + L->f_part, false, gws, L->f_gemm_bytes, s);
     case DH_GF_RS1:
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_layernorm_fwd(dt, Ts, H, a.x, c.n_ranks, parts_of(L, ws + L->f_part, a.peers_ar1, ns).p, L->w.bo, L->w.g2, L->w.b2,
+                                           c.eps, sv + L->s_x2, ws + L->f_hs, (float*)(sv + L->s_mu2), (float*)(sv + L->s_rstd2), s);
       return collective(L, DH_COMM_REDUCESCATTER, ws + L->f_part, a.peers_ar1, ns, ws + L->f_red, s);
     case DH_GF_NORM2:  // x2 = x + y + bo, h2 = norm(x2)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by GF_RS1's launch
       return dh_layernorm_fwd(dt, Ts, H, a.x, ws + L->f_red, L->w.bo, L->w.g2, L->w.b2, c.eps, sv + L->s_x2, ws + L->f_hs,
                               (float*)(sv + L->s_mu2), (float*)(sv + L->s_rstd2), s);
     case DH_GF_AG2:
@@ -700,8 +727,11 @@ static int gpt_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hipSt
     case DH_GF_FC2:
       return gemm(L, false, false, T, H, F, sv + L->s_a, L->w.Wd, ws + L->f_part, false, gws, L->f_gemm_bytes, s);
     case DH_GF_RS2:
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_add(dt, Ts, H, sv + L->s_x2, c.n_ranks, parts_of(L, ws + L->f_part, a.peers_ar2, ns).p, L->w.bfc2, a.out, s);
       return collective(L, DH_COMM_REDUCESCATTER, ws + L->f_part, a.peers_ar2, ns, ws + L->f_red, s);
     case DH_GF_BDA2:
+      if (reduction_with_consumer(L)) return DH_OK;  // done by GF_RS2's launch
       return dh_bias_residual_add(dt, Ts, H, sv + L->s_x2, ws + L->f_red, L->w.bfc2, a.out, s);
   }
   DH_FAIL(DH_ERR_INVALID_ARG, "unknown forward operator %d", op);
@@ -730,8 +760,13 @@ static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
       if ((rc = gemm(L, true, false, H, F, T, sv + L->s_h2, ws + L->b_dgu, L->g.dWgu, true, gws, gwb, s))) return rc;
       return dh_colsum(dt, T, F, ws + L->b_dgu, L->g.dbfc1, ws + L->b_colsum, L->b_colsum_bytes, s);
     case DH_GB_RS3:  // the backward of an all-gather reduce-scatters
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_layernorm_bwd(dt, Ts, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar3, ns).p, sv + L->s_x2, L->w.g2,
+                                           (const float*)(sv + L->s_mu2), (const float*)(sv + L->s_rstd2), b.dout, ws + L->b_dx2, L->g.dg2,
+                                           L->g.db2, (float*)(ws + L->b_norm), s);
       return collective(L, DH_COMM_REDUCESCATTER, ws + L->b_part, b.peers_ar3, ns, ws + L->b_red, s);
     case DH_GB_NORM2:  // dx2 = dout + norm2_bwd(dh2)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by GB_RS3's launch
       return dh_layernorm_bwd(dt, Ts, H, ws + L->b_red, sv + L->s_x2, L->w.g2, (const float*)(sv + L->s_mu2),
                               (const float*)(sv + L->s_rstd2), b.dout, ws + L->b_dx2, L->g.dg2, L->g.db2, ws + L->b_norm,
                               L->b_norm_bytes, s);
@@ -750,8 +785,13 @@ static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
       if ((rc = gemm(L, true, false, H, L->n_qkv, T, sv + L->s_h1, ws + L->b_dqkv, L->g.dWqkv, true, gws, gwb, s))) return rc;
       return dh_colsum(dt, T, L->n_qkv, ws + L->b_dqkv, L->g.dbqkv, ws + L->b_colsum, L->b_colsum_bytes, s);
     case DH_GB_RS4:
+      if (reduction_with_consumer(L))
+        return dh_launch_sum_layernorm_bwd(dt, Ts, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar4, ns).p, b.x, L->w.g1,
+                                           (const float*)(sv + L->s_mu1), (const float*)(sv + L->s_rstd1), ws + L->b_dx2, b.dx, L->g.dg1,
+                                           L->g.db1, (float*)(ws + L->b_norm), s);
       return collective(L, DH_COMM_REDUCESCATTER, ws + L->b_part, b.peers_ar4, ns, ws + L->b_red, s);
     case DH_GB_NORM1:  // dx = dx2 + norm1_bwd(dh1)
+      if (reduction_with_consumer(L)) return DH_OK;  // done by GB_RS4's launch
       return dh_layernorm_bwd(dt, Ts, H, ws + L->b_red, b.x, L->w.g1, (const float*)(sv + L->s_mu1),
                               (const float*)(sv + L->s_rstd1), ws + L->b_dx2, b.dx, L->g.dg1, L->g.db1, ws + L->b_norm,
                               L->b_norm_bytes, s);
@@ -1026,8 +1066,16 @@ static int wait_for_all(const dh_op_graph& g, PendingComm& pd, hipStream_t stran
 
 // Whether a collective stand-in is worth a stream of its own in an SI step.  Sending it there and back takes four event
 // calls (about 17 us of host time, and two waits on the device); a stand-in shorter than that goes into its strand's
-// stream.  Its time: bytes moved at what it reaches, the whole chip 5.5 TB/s, a block of a budget 6 GB/s.
-static bool crosses_streams(const dh_layer* L, int kind) {
+// stream.  Its time: bytes moved at what it reaches, the whole chip 5.5 TB/s, a block of a budget 6 GB/s.  So does one
+// that may use the whole chip and whose strand could only wait for it (`next`, the operator the strand issues next in the segment
+// pair, needs it).
+static bool crosses_streams(const dh_layer* L, const dh_op_graph& g, int op, const int* next) {
+  const int kind = g.is_comm[op];
+  if (kind == 1 && L->c.comm_blocks == 0) {
+    if (next == nullptr) return false;
+    for (int e = 0; e < g.n_deps; e++)
+      if (g.dep_src[e] == op && g.dep_dst[e] == *next) return false;
+  }
   const double rows = L->c.arch == DH_ARCH_MOE ? L->Tf : L->Ts, R = L->c.n_ranks;
   const double bytes = (L->c.arch == DH_ARCH_MOE ? 2.0 : R + 1.0) * rows * L->c.hidden * L->es;
   const double rate = L->c.comm_blocks > 0 ? std::min(5.5e12, 6.0e9 * L->c.comm_blocks) : 5.5e12;
@@ -1075,7 +1123,7 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
       if (fi < p.f_end) {
         const int op = plan->fwd_order[fi++];
         if ((rc = wait_for_inputs(L->gf, pf, op, sa))) return rc;
-        if (L->gf.is_comm[op] && crosses_streams(L, L->gf.is_comm[op])) rc = on_comm_stream(L, sa, comm_stream_of(L, L->gf.is_comm[op], sc), &pf.ev[op], [&](hipStream_t s) { return run_fwd_op(L, op, *alpha, ws_f, s); });
+        if (L->gf.is_comm[op] && crosses_streams(L, L->gf, op, fi < p.f_end ? &plan->fwd_order[fi] : nullptr)) rc = on_comm_stream(L, sa, comm_stream_of(L, L->gf.is_comm[op], sc), &pf.ev[op], [&](hipStream_t s) { return run_fwd_op(L, op, *alpha, ws_f, s); });
         else rc = run_fwd_op(L, op, *alpha, ws_f, sa);
         if (rc) return rc;
       }
@@ -1089,7 +1137,7 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
           if ((rc = run_bwd_op(LB, op, *beta, ws_b, sa, ws_f + L->f_gemm))) return rc;
           continue;
         }
-        if (L->gb.is_comm[op] && crosses_streams(L, L->gb.is_comm[op])) rc = on_comm_stream(L, sb, comm_stream_of(L, L->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
+        if (L->gb.is_comm[op] && crosses_streams(L, L->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, L->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
         else rc = run_bwd_op(LB, op, *beta, ws_b, sb);
         if (rc) return rc;
       }

@@ -133,3 +133,28 @@ def test_gemm_swiglu_ragged(dh, T, F, H):
         dgu1 = torch.full((T * 2 * F + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
         dh.dh_gemm_swiglu_bwd(T, F, H, dy, wd, gu, dgu1)
         assert torch.equal(dgu1[:-64].view_as(dgu), dgu) and torch.all(dgu1[-64:] == 7.0)
+
+
+# Norms and residual adds that take in the reduction in front of them (stand-ins that may use the whole chip) against the
+# separate operators (stand-ins on a block budget): one to sixteen partials, one to eight vectors a thread, row remainders
+@pytest.mark.parametrize("arch,ranks,seq,hidden", [("llama", 1, 33, 72), ("llama", 3, 513, 2056), ("llama", 8, 1030, 4104), ("llama", 16, 70, 8200),
+                                                   ("gpt", 1, 33, 72), ("gpt", 2, 1026, 2056), ("gpt", 9, 63, 4104), ("gpt", 8, 64, 8200)])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_reduction_with_its_consumer(dh, arch, ranks, seq, hidden, bf16):
+    from paper_2411_15871_amd import harness as H
+    run = H.LayerRun(dict(arch=arch, batch=1, seq=seq, hidden=hidden, nq=2, nkv=1, d=64, ffn=72, n_ranks=ranks, bf16=bf16))
+    try:
+        got = []
+        for blocks in (0, 5):
+            dh.dh_layer_set_comm_blocks(run.layer, blocks)
+            s = run.strand(0)
+            s.saved.zero_()
+            run.zero_grads()
+            run.fwd(s)
+            run.bwd(s)
+            torch.cuda.synchronize()
+            got.append([s.out.clone(), s.saved.clone(), s.dx.clone()] + [v.clone() for v in run.g.values()])
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+    finally:
+        run.close()
