@@ -37,6 +37,10 @@
 #define AB_THREADS 256
 #define AB_KT 64   // tokens per LDS tile
 #define AB_RING 3  // tile slots
+// Tile slots of the dQ kernel in a launch of its own: two at D = 128, so that two of its blocks fit a compute unit (64 KiB each,
+// 256 registers a lane).  The arithmetic of one block's waves then runs beside the products of the other's: 32 heads x 4096
+// tokens 250 -> 205 us, 4 heads x 4096 queries over 12288 keys 167 -> 136 us.  (Two blocks fit anyway at D = 64.)
+__host__ __device__ constexpr int dq_ring(int d) { return d == 128 ? 2 : AB_RING; }
 #define AB_CH 16   // backward: a block walks at most g.ch 64-token tiles, this many by default (longer causal rows are split
                    // into chunks whose float32 partial results a second kernel adds in chunk order)
 
@@ -119,22 +123,23 @@ __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[2]) {
 __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[4]) {
   asm volatile("s_nop 15\n\ts_nop 15" : "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3]));
 }
-// The AGPR placement pays where ordinary registers are short (D = 128: 64 or 128 accumulator registers next to
-// the operand fragments and two score tiles).  With D = 64 everything fits the ordinary registers, where the
-// compiler would only shuttle an AGPR-constrained value back and forth, so those kernels use the intrinsic.
-template <int D> __device__ __forceinline__ void acc_zero(f32x16& acc) {
-  if constexpr (D == 128) mfma_acc_zero(acc);
+// The AGPR placement (AGPR = true) pays where one wave has a SIMD's register file to itself and ordinary registers are short
+// (D = 128, one block per compute unit).  With D = 64 everything fits the ordinary registers, and where two waves share the
+// file (the dQ kernel at D = 128) they are one budget of 256: there the compiler would only shuttle an AGPR-constrained value
+// back and forth (64 moves per tile, dQ 205 -> 250 us at 32 heads x 4096 tokens), so those kernels use the intrinsic.
+template <bool AGPR> __device__ __forceinline__ void acc_zero(f32x16& acc) {
+  if constexpr (AGPR) mfma_acc_zero(acc);
   else {
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[r] = 0.f;
   }
 }
-template <int D> __device__ __forceinline__ void acc_mfma(f32x16& acc, bf16x8 a, bf16x8 b) {
-  if constexpr (D == 128) mfma_acc(acc, a, b);
+template <bool AGPR> __device__ __forceinline__ void acc_mfma(f32x16& acc, bf16x8 a, bf16x8 b) {
+  if constexpr (AGPR) mfma_acc(acc, a, b);
   else acc = MFMA(a, b, acc);
 }
-template <int D, int N> __device__ __forceinline__ void acc_settle(f32x16 (&a)[N]) {
-  if constexpr (D == 128) mfma_acc_settle(a);
+template <bool AGPR, int N> __device__ __forceinline__ void acc_settle(f32x16 (&a)[N]) {
+  if constexpr (AGPR) mfma_acc_settle(a);
 }
 
 
@@ -225,12 +230,11 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // Score tiles of a 64-token LDS tile: acc[mt] = sum over k of T[rows 32 mt .. 32 mt + 31][k] * b[k] (direct fragments
 // of the tile behind P against the D-long register fragments b).  A matrix instruction that accumulates into the
-// result of the one just before it has to wait for that result, so the products of the independent tiles are
-// issued round robin: score_tiles interleaves its two tiles, score_tiles2 the four tiles of two operand pairs
-// (the backward kernels' S and dP).  The LDS fragments of step k+1 are requested before the products of step k
-// are issued, and the matrix and LDS instructions are pinned in that order (vector-ALU work of the caller may
-// still move across), so no product waits for an LDS read issued just before it.
-#define SCHED_PIN_MFMA_DS() __builtin_amdgcn_sched_barrier(0x1 | 0x2 | 0x4 | 0x400)  // ALU, VALU, SALU, TRANS may cross
+// result of the one just before it has to wait for that result, so the products of the two independent tiles are
+// issued round robin.  The LDS fragments of the next two k-steps are requested before the products of the current two are
+// issued, and the matrix and LDS instructions are pinned in that order (vector arithmetic of the caller may still move
+// across), so no product waits for an LDS read issued just before it.
+#define SCHED_PIN_MFMA_DS() __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x400)  // vector (not matrix), scalar and transcendental arithmetic may cross
 template <int D>
 __device__ __forceinline__ void score_tiles(f32x16 (&acc)[2], const TilePtrs<D>& P, const bf16x8 (&b)[D / 16]) {
   using TL = ATile<D>;
@@ -254,53 +258,66 @@ __device__ __forceinline__ void score_tiles(f32x16 (&acc)[2], const TilePtrs<D>&
     SCHED_PIN_MFMA_DS();
   }
 }
-template <int D>
+// The backward kernels' two operand pairs, one after the other: S from the tile behind P0 in the first D/16 steps, dP from the
+// tile OFF1 bytes further in the next; arith(j) follows the products of dP's step j and turns a part of S into P beside
+// them (32 exponentials take about as long as the 16 products of dP).  Fragments are requested AHEAD steps of 64 matrix
+// cycles ahead: three where registers allow it, one where a second wave on the SIMD covers the wait.  Every step is pinned
+// as written.  dK/dV at 32 heads x 4096 tokens, one wave a SIMD: 335 -> 315 us.
+template <int D, int OFF1, int AHEAD, class F>
 __device__ __forceinline__ void score_tiles2(f32x16 (&acc0)[2], const TilePtrs<D>& P0, const bf16x8 (&b0)[D / 16],
-                                             f32x16 (&acc1)[2], const TilePtrs<D>& P1, const bf16x8 (&b1)[D / 16]) {
+                                             f32x16 (&acc1)[2], const bf16x8 (&b1)[D / 16], F arith) {
   using TL = ATile<D>;
   constexpr int KS = D / 16;
   const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 fr[2][4];  // one k-step of both operand pairs per chunk
-  auto fetch = [&](int ks) {
-    fr[ks & 1][0] = lds_frag(P0.dir[ks], 0);
-    fr[ks & 1][1] = lds_frag(P0.dir[ks], 32 * TL::LD * 2);
-    fr[ks & 1][2] = lds_frag(P1.dir[ks], 0);
-    fr[ks & 1][3] = lds_frag(P1.dir[ks], 32 * TL::LD * 2);
-  };
-  fetch(0);
+  bf16x8 fr[AHEAD + 1][2];
+  auto fetch = [&](int i) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-    if (ks + 1 < KS) fetch(ks + 1);
-    SCHED_PIN_MFMA_DS();
-    acc0[0] = MFMA(fr[ks & 1][0], b0[ks], ks == 0 ? z : acc0[0]);
-    acc0[1] = MFMA(fr[ks & 1][1], b0[ks], ks == 0 ? z : acc0[1]);
-    acc1[0] = MFMA(fr[ks & 1][2], b1[ks], ks == 0 ? z : acc1[0]);
-    acc1[1] = MFMA(fr[ks & 1][3], b1[ks], ks == 0 ? z : acc1[1]);
-    SCHED_PIN_MFMA_DS();
+    for (int mt = 0; mt < 2; mt++) fr[i % (AHEAD + 1)][mt] = lds_frag(P0.dir[i % KS], (i < KS ? 0 : OFF1) + mt * 32 * TL::LD * 2);
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; i++) fetch(i);
+#pragma unroll
+  for (int i = 0; i < 2 * KS; i++) {
+    if (i + AHEAD < 2 * KS) fetch(i + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i < KS) {
+      acc0[0] = MFMA(fr[i % (AHEAD + 1)][0], b0[i], i == 0 ? z : acc0[0]);
+      acc0[1] = MFMA(fr[i % (AHEAD + 1)][1], b0[i], i == 0 ? z : acc0[1]);
+    } else {
+      acc1[0] = MFMA(fr[i % (AHEAD + 1)][0], b1[i - KS], i == KS ? z : acc1[0]);
+      acc1[1] = MFMA(fr[i % (AHEAD + 1)][1], b1[i - KS], i == KS ? z : acc1[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      arith(i - KS);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
 // acc[dt] += T[64 x D]^T (transposed fragments of the LDS tile behind P) * src, src = a 64 x 32 score tile held as
 // two 32x32 register tiles.  The 64 "k" rows go in four groups of 16 (g = 2*mt + c); the transposed fragments
 // of group g+1 are fetched before the products of group g are issued, so no product waits for its own LDS
-// read, and between(g) runs after group g's products are issued (independent vector work to overlap them).
-template <int D, class F>
-__device__ __forceinline__ void acc_tile_tr(f32x16 (&acc)[D / 32], const TilePtrs<D>& P, const f32x16 (&src)[2], F between) {
-  using TL = ATile<D>;
-  bf16x8 fr[2][D / 32];
+// read, and between(g) runs after group g's products are issued (independent vector work to overlap them).  The caller has
+// fetched group 0 (tr_fetch); NEXT: group 0 of the tile behind P2 is fetched beside the last products.
+template <int D> using TrFrags = bf16x8[2][D / 32];
+template <int D>
+__device__ __forceinline__ void tr_fetch(TrFrags<D>& fr, const TilePtrs<D>& P, int g) {
 #pragma unroll
-  for (int dt = 0; dt < D / 32; dt++) fr[0][dt] = lds_frag_tr(P.t0[dt], P.t1[dt], 0);
+  for (int dt = 0; dt < D / 32; dt++) fr[g & 1][dt] = lds_frag_tr(P.t0[dt], P.t1[dt], g * 16 * ATile<D>::LD * 2);
+}
+template <int D, bool NEXT, bool AGPR, class F>
+__device__ __forceinline__ void acc_tile_tr(f32x16 (&acc)[D / 32], TrFrags<D>& fr, const TilePtrs<D>& P, const f32x16 (&src)[2],
+                                            const TilePtrs<D>& P2, F between) {
 #pragma unroll
   for (int g = 0; g < 4; g++) {
-    if (g + 1 < 4) {
-      const int ro = (g + 1) * 16 * TL::LD * 2;
-#pragma unroll
-      for (int dt = 0; dt < D / 32; dt++) fr[(g + 1) & 1][dt] = lds_frag_tr(P.t0[dt], P.t1[dt], ro);
-    }
+    if (g + 1 < 4) tr_fetch<D>(fr, P, g + 1);
+    else if (NEXT) tr_fetch<D>(fr, P2, 0);
     const bf16x8 pf = pack_rows(src[g >> 1], g & 1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int dt = 0; dt < D / 32; dt++) acc_mfma<D>(acc[dt], fr[g & 1][dt], pf);
+    for (int dt = 0; dt < D / 32; dt++) acc_mfma<AGPR>(acc[dt], fr[g & 1][dt], pf);
+    __builtin_amdgcn_sched_barrier(0);
     between(g);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -592,13 +609,14 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(int seq, int q_of
 // own rows itself (a row's two lanes each hold half of dO).  The dK/dV blocks read them from memory: when the dQ blocks
 // are launched ahead of them, the block of a query block's first chunk stores them (delta_out != nullptr); when both
 // kinds share one launch, attn_bwd_prep_kernel has filled the arrays.
-template <int D>
+template <int D, int RING>
 __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom& g, const bf16_t* __restrict__ qkv,
                                                   const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
                                                   const float* __restrict__ lse, float* __restrict__ lse2_out,
                                                   float* __restrict__ delta_out, bf16_t* __restrict__ dqkv,
                                                   float* __restrict__ part, int pairs, int T, float scale, float scale_log2) {
   using TL = ATile<D>;
+  constexpr bool AGPR = D == 128 && RING > 2;
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // K ring, then V ring
   const lds_char* sm = (const lds_char*)smem;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -636,13 +654,13 @@ __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom&
   }
   f32x16 dqt[D / 32];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; dt++) acc_zero<D>(dqt[dt]);
+  for (int dt = 0; dt < D / 32; dt++) acc_zero<AGPR>(dqt[dt]);
 
   FragAddr<D> fa;
   fa.init(lane);
   uint32_t voff[TL::IPW];
   tile_voff<D>(voff, ldkv, wave, lane, AB_KT);
-  const uint32_t ldsK = lds_address(smem), ldsV = ldsK + AB_RING * TL::BYTES;
+  const uint32_t ldsK = lds_address(smem), ldsV = ldsK + RING * TL::BYTES;
   const int t0 = cm.chunk * g.ch, ntiles = min(dq_tiles(cm.blk, seq), t0 + g.ch);  // this block walks key tiles [t0, ntiles)
   auto issue = [&](int t, int slot) {
     const int valid = seq - t * AB_KT;
@@ -661,24 +679,28 @@ __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom&
   pin_scalar(l2);
   pin_scalar(dl);
   issue(t0, 0);
-  if (t0 + 1 < ntiles) issue(t0 + 1, 1);
+  if (RING > 2 && t0 + 1 < ntiles) issue(t0 + 1, 1);
   int slot = 0;
-  for (int t = t0; t < ntiles; t++, slot = slot == AB_RING - 1 ? 0 : slot + 1) {
-    if (t + 1 < ntiles) dma_wait<2 * TL::IPW>(); else dma_wait<0>();
-    __syncthreads();
-    if (t + 2 < ntiles) issue(t + 2, slot == 0 ? AB_RING - 1 : slot - 1);
+  for (int t = t0; t < ntiles; t++, slot = slot == RING - 1 ? 0 : slot + 1) {
+    if (RING > 2 && t + 1 < ntiles) dma_wait<2 * TL::IPW>(); else dma_wait<0>();
+    __syncthreads();  // tile t is visible; every wave is done with tile t-1, whose slot is filled next
+    if (t + RING - 1 < ntiles) issue(t + RING - 1, slot == 0 ? RING - 1 : slot - 1);
     const int kb = t * AB_KT;
     if (kb > iw + 31) continue;
-    TilePtrs<D> Kp, Vp;
+    TilePtrs<D> Kp;
     Kp.set(sm + slot * TL::BYTES, fa);
-    Vp.set(sm + (AB_RING + slot) * TL::BYTES, fa);
     f32x16 st[2], dp[2];
-    score_tiles2<D>(st, Kp, qf, dp, Vp, dof);
-    // P^T from S^T while the dP^T products are still in the matrix pipeline
+    // P^T from S^T beside the dP^T products
+    score_tiles2<D, RING * TL::BYTES, (RING == 2 ? 1 : 3)>(st, Kp, qf, dp, dof, [&](int j) {
+      constexpr int N = 32 / (D / 16);
 #pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) st[mt][r] = fast_exp2(fmaf(st[mt][r], scale_log2, -l2));
+      for (int i = 0; i < N; i++) {
+        const int x = j * N + i;
+        st[x >> 4][x & 15] = fast_exp2(fmaf(st[x >> 4][x & 15], scale_log2, -l2));
+      }
+    });
+    TrFrags<D> fr;
+    tr_fetch<D>(fr, Kp, 0);
     if (kb + AB_KT - 1 > iw) {
 #pragma unroll
       for (int mt = 0; mt < 2; mt++)
@@ -692,9 +714,9 @@ __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom&
       for (int r = 0; r < 8; r++) st[g >> 1][8 * (g & 1) + r] *= dp[g >> 1][8 * (g & 1) + r] - dl;
     };
     ds_quarter(0);
-    acc_tile_tr<D>(dqt, Kp, st, [&](int g) { if (g + 1 < 4) ds_quarter(g + 1); });
+    acc_tile_tr<D, false, AGPR>(dqt, fr, Kp, st, Kp, [&](int g) { if (g + 1 < 4) ds_quarter(g + 1); });
   }
-  acc_settle<D>(dqt);
+  acc_settle<AGPR>(dqt);
   __syncthreads();  // every wave is done with the K/V rings: their LDS serves the output turn
   if (part != nullptr) {  // float32 partial of this chunk: part[batch][head][pair][128 rows][D], unscaled
     float* rows = part + ((((size_t)b * nq + h) * pairs + cm.pair) * 128 + wave * 32) * D;
@@ -746,6 +768,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
                                                    const float* __restrict__ delta, float* __restrict__ part, int pairs, int T,
                                                    float scale, float scale_log2) {
   using TL = ATile<D>;
+  constexpr bool AGPR = D == 128;
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // Q ring, dO ring, lse2 ring, delta ring
   const lds_char* sm = (const lds_char*)smem;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -772,7 +795,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   load_row_frags<D>(vf, g.kv + (ktok0 + jkc) * g.ldkv + (size_t)(nkv + hk) * D, jk < seq, kg);
   f32x16 dkt[D / 32], dvt[D / 32];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; dt++) { acc_zero<D>(dkt[dt]); acc_zero<D>(dvt[dt]); }
+  for (int dt = 0; dt < D / 32; dt++) { acc_zero<AGPR>(dkt[dt]); acc_zero<AGPR>(dvt[dt]); }
 
   FragAddr<D> fa;
   fa.init(lane);
@@ -823,17 +846,24 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     Op.set(sm + (AB_RING + slot) * TL::BYTES, fa);
     const float* ls = lse_s + slot * AB_KT;
     const float* ds = del_s + slot * AB_KT;
+    f32x4 lv[8];  // rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
+#pragma unroll
+    for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ls + 8 * x + 4 * kg);
     f32x16 st[2], dp[2];
-    score_tiles2<D>(st, Qp, kf, dp, Op, vf);
-    // P from S (rows 8*q4 + 4*kg + e of each 32-row half) while dP is in the matrix pipeline
+    // P from S beside the dP products
+    score_tiles2<D, AB_RING * TL::BYTES, 3>(st, Qp, kf, dp, vf, [&](int j) {
+      constexpr int N = 8 / (D / 16);
 #pragma unroll
-    for (int mt = 0; mt < 2; mt++)
+      for (int i = 0; i < N; i++) {
+        const int x = j * N + i, mt = x >> 2, q4 = x & 3;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; q4++) {
-        const f32x4 lv = *reinterpret_cast<const f32x4*>(ls + mt * 32 + 8 * q4 + 4 * kg);
-#pragma unroll
-        for (int e = 0; e < 4; e++) st[mt][4 * q4 + e] = fast_exp2(fmaf(st[mt][4 * q4 + e], scale_log2, -lv[e]));
+        for (int e = 0; e < 4; e++) st[mt][4 * q4 + e] = fast_exp2(fmaf(st[mt][4 * q4 + e], scale_log2, -lv[x][e]));
       }
+    });
+    TrFrags<D> fr;
+    tr_fetch<D>(fr, Op, 0);
+#pragma unroll
+    for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ds + 8 * x + 4 * kg);
     if (qb < jw + 32 || qb + AB_KT > seq) {  // diagonal tile, or rows past the end of the sequence
 #pragma unroll
       for (int mt = 0; mt < 2; mt++)
@@ -845,19 +875,14 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     }
     // dV^T += dO^T P; once a quarter of P (8 registers of a tile) is packed for its products, it is turned
     // into dS = P (dP - delta) in place while those products run; then dK^T += Q^T dS.
-    acc_tile_tr<D>(dvt, Op, st, [&](int g) {
-      const int mt = g >> 1, c = g & 1;
+    acc_tile_tr<D, true, AGPR>(dvt, fr, Op, st, Qp, [&](int g) {
 #pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const f32x4 dv4 = *reinterpret_cast<const f32x4*>(ds + mt * 32 + 8 * (2 * c + q) + 4 * kg);
-#pragma unroll
-        for (int e = 0; e < 4; e++) st[mt][8 * c + 4 * q + e] *= dp[mt][8 * c + 4 * q + e] - dv4[e];
-      }
+      for (int r = 8 * (g & 1); r < 8 * (g & 1) + 8; r++) st[g >> 1][r] *= dp[g >> 1][r] - lv[4 * (g >> 1) + (r >> 2)][r & 3];
     });
-    acc_tile_tr<D>(dkt, Qp, st, [](int) {});
+    acc_tile_tr<D, false, AGPR>(dkt, fr, Qp, st, Qp, [](int) {});
   }
-  acc_settle<D>(dkt);
-  acc_settle<D>(dvt);
+  acc_settle<AGPR>(dkt);
+  acc_settle<AGPR>(dvt);
   __syncthreads();  // every wave is done with the Q/dO rings: their LDS serves the output turn (dK, then dV)
   auto dk_quad = [&](int dt, int q4) {
     return f32x4{dkt[dt][4 * q4] * scale, dkt[dt][4 * q4 + 1] * scale, dkt[dt][4 * q4 + 2] * scale, dkt[dt][4 * q4 + 3] * scale};
@@ -899,16 +924,16 @@ __global__ __launch_bounds__(AB_THREADS) void attn_bwd_bf16_kernel(const AttnGeo
   if (u < both) { dkv = (u & 1) == 0; idx = u >> 1; }
   else { dkv = pairs_k > pairs_q; idx = u - both / 2; }
   if (dkv) attn_bwd_dkv_block<D>(idx * gk.nq_all + hb, gk, qkv, dout, lse2, delta, part_kv, pairs_k, T, scale, scale_log2);
-  else attn_bwd_dq_block<D>(idx * gq.nq_all + hb, gq, qkv, o, dout, lse, nullptr, nullptr, dqkv, part_q, pairs_q, T, scale, scale_log2);
+  else attn_bwd_dq_block<D, AB_RING>(idx * gq.nq_all + hb, gq, qkv, o, dout, lse, nullptr, nullptr, dqkv, part_q, pairs_q, T, scale, scale_log2);
 }
 // The two halves as launches of their own (dQ first: it stores the row statistics the dK/dV blocks read).
 template <int D>
-__global__ __launch_bounds__(AB_THREADS) void attn_bwd_dq_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
+__global__ __launch_bounds__(AB_THREADS, 2) void attn_bwd_dq_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
                                                                       const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
                                                                       const float* __restrict__ lse, float* __restrict__ lse2,
                                                                       float* __restrict__ delta, bf16_t* __restrict__ dqkv,
                                                                       float* __restrict__ part, int pairs, int T, float scale, float scale_log2) {
-  attn_bwd_dq_block<D>((int)blockIdx.x, g, qkv, o, dout, lse, lse2, delta, dqkv, part, pairs, T, scale, scale_log2);
+  attn_bwd_dq_block<D, dq_ring(D)>((int)blockIdx.x, g, qkv, o, dout, lse, lse2, delta, dqkv, part, pairs, T, scale, scale_log2);
 }
 template <int D>
 __global__ __launch_bounds__(AB_THREADS) void attn_bwd_dkv_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
@@ -1013,7 +1038,7 @@ static int attn_num_cus() {  // of the current device
 // simulated for each candidate length: a unit costs its tiles plus a fixed overhead, every chunk of a split launch
 // costs the traffic of its float32 partial result (written, then read by the merging kernel), and a split launch
 // pays for the merging kernels.  The constants are measured on MI355X (microseconds): a compute unit finishes a
-// forward tile in 1.45 whether one or two blocks share it, a dQ tile in 1.8, a dK/dV tile in 2.5; HBM moves 4 MB per
+// forward tile in 1.45, a dQ tile in 1.55 with two blocks on it or 1.8 beside dK/dV units, a dK/dV tile in 2.4; HBM moves 4 MB per
 // microsecond under this load.
 enum { PICK_FWD = 0, PICK_DQ = 1, PICK_DKV = 2 };
 struct PickKey {
@@ -1051,7 +1076,7 @@ static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, bool grou
   if (it != cache.end()) return it->second;
   const int nblk = (seq + 127) / 128, qb0 = q_off / 128;
   const int max_tiles = kind == PICK_DKV ? dkv_tiles(0, seq, q_off) : dq_tiles(nblk - 1, seq);
-  const double t_tile = (kind == PICK_FWD ? 1.45 : kind == PICK_DQ ? 1.8 : 2.5) * d / 128.0, t_ovh = 3.0;
+  const double t_tile = (kind == PICK_FWD ? 1.45 : kind == PICK_DQ ? (grouped ? 1.55 : 1.8) : 2.4) * d / 128.0, t_ovh = 3.0;
   const double us_per_byte = 2.0 / 4.0e6, t_merge = 12.0;
   static const int cand_fwd[] = {4, 8, 16, 32, 64, 1 << 20}, cand_bwd[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 1 << 20};
   const int* cand = kind == PICK_FWD ? cand_fwd : cand_bwd;
@@ -1076,9 +1101,10 @@ static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, bool grou
   // When splitting pays at all it is because the launch would leave compute units idle, and then the finest split
   // whose units are still all resident at once balances them best (measured: 4 heads x 4096 tokens, forward 16 -> 10
   // tiles per chunk 48 -> 42 us, backward 24 -> 22 tiles 116 -> 113 us; one more unit than fits costs a second round).
-  // Resident blocks per compute unit: forward 2 (4 at D = 64, counted as 2), backward 1 (2 at D = 64).
+  // Resident blocks per compute unit: forward, and dQ in a launch of its own, 2 (forward at D = 64: 4, counted as 2);
+  // dK/dV, and dQ beside it, 1 (2 at D = 64).
   if (best < (1 << 20)) {
-    const long long resident = (long long)attn_num_cus() * (kind == PICK_FWD || d == 64 ? 2 : 1);
+    const long long resident = (long long)attn_num_cus() * (kind == PICK_FWD || (kind == PICK_DQ && grouped) || d == 64 ? 2 : 1);
     for (int ch = 8; ch < best; ch += 2) {
       long long units = 0;
       if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) units += chunks_of(dkv_tiles(i, seq, q_off), ch);
@@ -1097,7 +1123,7 @@ static int fwd_chunk_tiles(int batch, int seq, int q_off, int nq, int d) {
 }
 // Tiles per chunk of the dQ and of the dK/dV kernel.
 static void bwd_chunk_tiles(int batch, int seq, int q_off, int nq, int nkv, int d, int& ch_q, int& ch_k) {
-  ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, false);
+  ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, nq > nkv);
   ch_k = pick_chunk(PICK_DKV, seq, q_off, nq * batch, d, nq > nkv);
 }
 
@@ -1210,7 +1236,7 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   dim3 gw((unsigned)(pq + pk) * nq * batch), gwq((unsigned)pq * nq * batch), gwk((unsigned)pk * nq * batch), gq(nblk_q * 16, nq, batch),
       gk(nblk * 32, nkv, batch);
   const unsigned nb_q = part_q ? gq.x * gq.y * gq.z : 0, nb_k = part_kv ? gk.x * gk.y * gk.z : 0;
-  const size_t lds_dq = 2 * AB_RING * (size_t)AB_KT * d * 2, lds_dkv = lds_dq + 2 * AB_RING * AB_KT * sizeof(float);
+  const size_t lds_dq = 2 * dq_ring(d) * (size_t)AB_KT * d * 2, lds_dkv = 2 * AB_RING * ((size_t)AB_KT * d * 2 + AB_KT * sizeof(float));
   static bool ready_dev[DH_MAX_DEVICES][2] = {};
   bool* ready = ready_dev[dh_device_index()];
 #define DH_ATTN_BWD(DD, IDX)                                                                                                   \
