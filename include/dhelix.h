@@ -390,7 +390,7 @@ int dh_plan_sequential(const dh_layer* layer, dh_plan* out);
  * A collective stand-in too short to pay for the way to another stream and back (under about 10 us) stays in its
  * strand's stream, and so does one that may use the whole chip (comm_blocks 0) when the strand's next operator needs it.
  * With comm_blocks 0 a reduction also does the norm or residual add behind it, whose operator then launches nothing
- * (the same bits).
+ * (the same bits), and the MoE layer's forward dispatch and backward combine do the token permute beside them.
  * A stand-in issued on another stream than its strand's starts after what the strand has issued so far; the strand
  * waits for it only when an operator that depends on it (operator graph) comes up, or at the end of the segment
  * pair, so operators of the same strand that do not need the result overlap the transfer (Sec. 4.2, the

@@ -189,6 +189,11 @@ int dh_launch_gemm_bf16(bool ta, bool tb, int M, int N, int K, const bf16_t* A, 
                         bool out_f32_accumulate, const bf16_t* bias, void* ws, size_t ws_bytes, hipStream_t stream);
 int dh_launch_gemm_grouped_f32(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                const float* A, const float* B, float* C, hipStream_t stream);
+// dh_moe_gather_rows / dh_moe_combine with a second row map in between (nullptr: none)
+int dh_launch_moe_gather_rows(int dtype, int n_rows, int H, const void* in, const int32_t* map, const int32_t* via, void* out, int n_blocks,
+                              hipStream_t stream);
+int dh_launch_moe_combine(int dtype, int T, int H, const void* yp, const int32_t* dest, const int32_t* via, const float* prob,
+                          const void* residual, void* y, hipStream_t stream);
 int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                 const bf16_t* A, const bf16_t* B, void* C, hipStream_t stream);
 // Norm, residual add and their gradients behind a reduction over n_parts partial buffers (rowops.hip).

@@ -459,6 +459,9 @@ static int collective(const dh_layer* L, int kind, const void* own, const void* 
 // Whether a reduction and the norm or residual add behind it are one launch (made by the reduction; the other operator then
 // launches nothing): wherever the stand-in may use the whole chip.  On a block budget it is a transfer of its own.
 static bool reduction_with_consumer(const dh_layer* L) { return L->c.comm_blocks == 0; }
+// Likewise an all-to-all and the token permute beside it (forward dispatch, backward combine): the exchange moves the rows
+// between the tokens' order and the experts' in one pass, and the permute launches nothing.
+static bool exchange_with_permute(const dh_layer* L) { return L->c.comm_blocks == 0; }
 
 // Whether backward all-reduce `which` (1: AR3, 2: AR4) is carried by its weight-gradient GEMM right now.
 static bool fused_collective(const dh_layer* L, int which) { return (L->fuse_comm & which) != 0 && L->c.comm_blocks > 0; }
@@ -827,8 +830,11 @@ static int moe_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hipSt
       if ((rc = dh_moe_route(T, E, a.logits, idx, prob, s))) return rc;
       return dh_moe_plan(T, E, nl, idx, &tb, s);
     case DH_MF_PERMUTE:
+      if (exchange_with_permute(L)) return DH_OK;  // done by MF_A2A_DISPATCH
       return dh_moe_gather_rows(dt, Tf, H, sv + L->s_h2, tb.src_tok, ws + L->f_xp, 0, s);
     case DH_MF_A2A_DISPATCH:
+      if (exchange_with_permute(L))
+        return dh_launch_moe_gather_rows(dt, Tf, H, sv + L->s_h2, tb.src_tok, tb.send_of_recv, sv + L->s_xg, 0, s);
       return dh_moe_gather_rows(dt, Tf, H, ws + L->f_xp, tb.send_of_recv, sv + L->s_xg, c.comm_blocks, s);
     case DH_MF_FC1:
       return dh_gemm_grouped(dt, 0, nl, tb.group_rows, Tf, H, 2 * F, sv + L->s_xg, L->w.Wgu, sv + L->s_gu, s);
@@ -871,8 +877,12 @@ static int moe_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
     case DH_MB_FC1_WGRAD:
       return dh_gemm_grouped(dt, 2, nl, tb.group_rows, Tf, H, 2 * F, sv + L->s_xg, ws + L->b_dgu, L->g.dWgu, s);
     case DH_MB_A2A_COMBINE:  // the un-dispatched rows reuse the buffer of the dispatched upstream gradient
+      if (exchange_with_permute(L))
+        return dh_launch_moe_combine(dt, T, H, ws + L->b_dxg, tb.dest, tb.recv_of_send, nullptr, nullptr, ws + L->b_red, s);
       return dh_moe_gather_rows(dt, Tf, H, ws + L->b_dxg, tb.recv_of_send, ws + L->b_dyp, c.comm_blocks, s);
-    case DH_MB_PERMUTE:  // dh2[t] = sum of the gradients of token t's two permuted copies
+    case DH_MB_PERMUTE:
+      if (exchange_with_permute(L)) return DH_OK;  // done by MB_A2A_COMBINE
+      // dh2[t] = sum of the gradients of token t's two permuted copies
       return dh_moe_combine(dt, T, H, ws + L->b_dyp, tb.dest, nullptr, nullptr, ws + L->b_red, s);
     case DH_MB_NORM2:
       return dh_rmsnorm_bwd(dt, T, H, ws + L->b_red, sv + L->s_x2, L->w.g2, (const float*)(sv + L->s_rstd2), b.dout,

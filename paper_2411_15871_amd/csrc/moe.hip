@@ -103,23 +103,26 @@ __global__ void moe_tables_kernel(int n_assign, const int32_t* __restrict__ idx,
 
 // ------------------------------------------------------------------------------------ row movement
 // out[r,:] = in[map[r],:]  (token permute, all-to-all stand-in in both directions).  One wave per row chunk.
+// Bound by memory (8192 rows of 8 KiB: 21 us, 6.4 TB/s), so two movements one behind the other are one where they may be:
+// via != nullptr takes row map[via[r]].
 template <typename T>
 __global__ __launch_bounds__(256) void gather_rows_kernel(int n_rows, int H, const T* __restrict__ in, const int32_t* __restrict__ map,
-                                                          T* __restrict__ out) {
+                                                          const int32_t* __restrict__ via, T* __restrict__ out) {
   const int chunks = H / 8;
   const size_t total = (size_t)n_rows * chunks, stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
     const size_t r = i / chunks;
     const int c = (int)(i % chunks) * 8;
     Vec8<T> v;
-    v.load(in + (size_t)map[r] * H + c);
+    v.load(in + (size_t)map[via ? via[r] : r] * H + c);
     v.store(out + r * H + c);
   }
 }
 
 // y[t,:] = w0*yp[dest[t,0],:] + w1*yp[dest[t,1],:] (+ res[t,:]); weights = prob[t,:] or 1 when prob == nullptr.
+// via != nullptr: yp's rows lie in another order, row d at via[d].
 template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(int Ttok, int H, const T* __restrict__ yp, const int32_t* __restrict__ dest,
+__global__ __launch_bounds__(256) void combine_kernel(int Ttok, int H, const T* __restrict__ yp, const int32_t* __restrict__ dest, const int32_t* __restrict__ via,
                                                       const float* __restrict__ prob, const T* __restrict__ res, T* __restrict__ y) {
   const int chunks = H / 8;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -128,8 +131,10 @@ __global__ __launch_bounds__(256) void combine_kernel(int Ttok, int H, const T* 
   const int c = (int)(i % chunks) * 8;
   const float w0 = prob ? prob[2 * t] : 1.f, w1 = prob ? prob[2 * t + 1] : 1.f;
   Vec8<T> a, b;
-  a.load(yp + (size_t)dest[2 * t] * H + c);
-  b.load(yp + (size_t)dest[2 * t + 1] * H + c);
+  int r0 = dest[2 * t], r1 = dest[2 * t + 1];
+  if (via != nullptr) { r0 = via[r0]; r1 = via[r1]; }
+  a.load(yp + (size_t)r0 * H + c);
+  b.load(yp + (size_t)r1 * H + c);
 #pragma unroll
   for (int k = 0; k < 8; k++) a.v[k] = w0 * a.v[k] + w1 * b.v[k];
   if (res != nullptr) {
@@ -212,26 +217,34 @@ extern "C" int dh_moe_plan(int T, int E, int n_local, const int32_t* idx, const 
 
 extern "C" int dh_moe_gather_rows(int dtype, int n_rows, int H, const void* in, const int32_t* map, void* out, int n_blocks,
                                   void* stream) {
+  return dh_launch_moe_gather_rows(dtype, n_rows, H, in, map, nullptr, out, n_blocks, (hipStream_t)stream);
+}
+int dh_launch_moe_gather_rows(int dtype, int n_rows, int H, const void* in, const int32_t* map, const int32_t* via, void* out, int n_blocks,
+                              hipStream_t stream) {
   if (n_rows < 0 || H <= 0 || H % 8) DH_FAIL(DH_ERR_SHAPE, "moe_gather_rows: rows=%d H=%d (H must be a positive multiple of 8)", n_rows, H);
   if (n_blocks < 0 || n_blocks > 65536) DH_FAIL(DH_ERR_INVALID_ARG, "moe_gather_rows: n_blocks %d outside 0..65536", n_blocks);
   if (n_rows == 0) return DH_OK;
   if (!in || !map || !out) DH_FAIL(DH_ERR_INVALID_ARG, "moe_gather_rows: null pointer");
   size_t want = ((size_t)n_rows * (H / 8) + 255) / 256, cap = n_blocks > 0 ? (size_t)n_blocks : 4096;
   unsigned grid = (unsigned)(want < cap ? want : cap);
-  if (dtype == DH_BF16) gather_rows_kernel<bf16_t><<<grid, 256, 0, (hipStream_t)stream>>>(n_rows, H, (const bf16_t*)in, map, (bf16_t*)out);
-  else gather_rows_kernel<float><<<grid, 256, 0, (hipStream_t)stream>>>(n_rows, H, (const float*)in, map, (float*)out);
+  if (dtype == DH_BF16) gather_rows_kernel<bf16_t><<<grid, 256, 0, stream>>>(n_rows, H, (const bf16_t*)in, map, via, (bf16_t*)out);
+  else gather_rows_kernel<float><<<grid, 256, 0, stream>>>(n_rows, H, (const float*)in, map, via, (float*)out);
   DH_LAUNCH_CHECK();
   return DH_OK;
 }
 
 extern "C" int dh_moe_combine(int dtype, int T, int H, const void* yp, const int32_t* dest, const float* prob,
                               const void* residual, void* y, void* stream) {
+  return dh_launch_moe_combine(dtype, T, H, yp, dest, nullptr, prob, residual, y, (hipStream_t)stream);
+}
+int dh_launch_moe_combine(int dtype, int T, int H, const void* yp, const int32_t* dest, const int32_t* via, const float* prob,
+                          const void* residual, void* y, hipStream_t stream) {
   if (T < 0 || H <= 0 || H % 8) DH_FAIL(DH_ERR_SHAPE, "moe_combine: T=%d H=%d (H must be a positive multiple of 8)", T, H);
   if (T == 0) return DH_OK;
   if (!yp || !dest || !y) DH_FAIL(DH_ERR_INVALID_ARG, "moe_combine: null pointer");
   unsigned grid = (unsigned)(((size_t)T * (H / 8) + 255) / 256);
-  if (dtype == DH_BF16) combine_kernel<bf16_t><<<grid, 256, 0, (hipStream_t)stream>>>(T, H, (const bf16_t*)yp, dest, prob, (const bf16_t*)residual, (bf16_t*)y);
-  else combine_kernel<float><<<grid, 256, 0, (hipStream_t)stream>>>(T, H, (const float*)yp, dest, prob, (const float*)residual, (float*)y);
+  if (dtype == DH_BF16) combine_kernel<bf16_t><<<grid, 256, 0, stream>>>(T, H, (const bf16_t*)yp, dest, via, prob, (const bf16_t*)residual, (bf16_t*)y);
+  else combine_kernel<float><<<grid, 256, 0, stream>>>(T, H, (const float*)yp, dest, via, prob, (const float*)residual, (float*)y);
   DH_LAUNCH_CHECK();
   return DH_OK;
 }

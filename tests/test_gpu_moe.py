@@ -261,3 +261,28 @@ def test_moe_errors(dh):
     tb, tbs = make_tables(dh, 4, 6, 2)
     with pytest.raises(dh.DhelixError):
         dh.dh_moe_plan(4, 6, 4, i32(8), tbs)
+
+
+# the exchange that also permutes (stand-ins on the whole chip) against exchange and permute apart (on a block budget): the same
+# bits, with experts of few or no rows and row counts that fill no block
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("seq,hidden,experts,local", [(1, 64, 4, 2), (37, 136, 16, 8), (515, 256, 8, 1)])
+def test_moe_layer_exchange_with_permute_same_bits(dh, bf16, seq, hidden, experts, local):
+    from paper_2411_15871_amd import harness as H
+    run = H.LayerRun(dict(arch="moe", batch=1, seq=seq, hidden=hidden, nq=2, nkv=1, d=64, ffn=72, n_ranks=1, bf16=bf16,
+                          n_experts=experts, n_local=local))
+    try:
+        st = run.strand(0)
+        got = []
+        for blocks in (0, 16):
+            dh.dh_layer_set_comm_blocks(run.layer, blocks)
+            st.saved.zero_(); st.dx.zero_(); run.zero_grads()
+            torch.cuda.synchronize()
+            run.fwd(st)
+            run.bwd(st)
+            torch.cuda.synchronize()
+            got.append([st.out.clone(), st.dx.clone(), st.dlogits.clone(), st.saved.clone()] + [g.clone() for g in run.g.values()])
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+    finally:
+        run.close()
