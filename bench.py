@@ -29,8 +29,8 @@ if int(os.environ.get("GPU_MAX_HW_QUEUES", "0") or 0) < 8:
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E
 # kernels behind an operator name (for the roofline's description)
-OP_KERNELS = {"ATTN": "attention kernels and their merge launches", "FC1": "gemm_bf16_kernel", "FC2": "gemm_bf16_kernel",
-              "QKV": "gemm_bf16_kernel", "PROJ": "gemm_bf16_kernel"}
+OP_KERNELS = {"ATTN": "attention kernels and their merge launches", "FC1": "bf16 GEMM kernels", "FC2": "bf16 GEMM kernels",
+              "QKV": "bf16 GEMM kernels", "PROJ": "bf16 GEMM kernels"}
 
 
 def read_traffic(workload, op):
