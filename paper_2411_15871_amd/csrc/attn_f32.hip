@@ -51,29 +51,61 @@ __device__ __forceinline__ f32x4 dot_tile(const RowFrag<DT>& a, const RowFrag<DT
 template <int DT>
 struct ColFrag {
   static constexpr bool EARLY = DT <= 8;
-  const float* r[4];
+  const float* base;
+  size_t ld;
   float x[EARLY ? DT : 1][4];
-  int l16, d;
-  __device__ __forceinline__ void start(const float* __restrict__ base, size_t ld, int row0, int row_last, int l16_, int g, int d_) {
-    l16 = l16_; d = d_;
-#pragma unroll
-    for (int e = 0; e < 4; e++) r[e] = base + (size_t)min(row0 + 4 * g + e, row_last) * ld;  // p is zero where the row was clamped
+  int row0, row_last, l16, g, d;
+  __device__ __forceinline__ const float* row(int j) const { return base + (size_t)min(row0 + j, row_last) * ld; }  // p is zero where clamped
+  __device__ __forceinline__ void start(const float* __restrict__ base_, size_t ld_, int row0_, int row_last_, int l16_, int g_, int d_) {
+    base = base_; ld = ld_; row0 = row0_; row_last = row_last_; l16 = l16_; g = g_; d = d_;
     if constexpr (EARLY) {
 #pragma unroll
       for (int e = 0; e < 4; e++)
 #pragma unroll
-        for (int c = 0; c < DT; c++) x[c][e] = 16 * c + l16 < d ? r[e][16 * c + l16] : 0.f;
+        for (int c = 0; c < DT; c++) x[c][e] = 16 * c + l16 < d ? row(4 * g + e)[16 * c + l16] : 0.f;
     }
+  }
+  __device__ __forceinline__ float elem(int c, int e) const {
+    if constexpr (EARLY) return x[c][e];
+    else return 16 * c + l16 < d ? row(4 * g + e)[16 * c + l16] : 0.f;
   }
   __device__ __forceinline__ void accumulate(f32x4 (&acc)[DT], const f32x4 p) const {
 #pragma unroll
     for (int e = 0; e < 4; e++)
 #pragma unroll
-      for (int c = 0; c < DT; c++) {
-        float v;
-        if constexpr (EARLY) v = x[c][e];
-        else v = 16 * c + l16 < d ? r[e][16 * c + l16] : 0.f;
-        acc[c] = A32_MFMA(v, p[e], acc[c]);
+      for (int c = 0; c < DT; c++) acc[c] = A32_MFMA(elem(c, e), p[e], acc[c]);
+  }
+  // The same for a tile in which some rows may not count for some columns (partial; bit e of seen: row 4g+e counts for column
+  // l16; p is zero where it does not).  The instruction multiplies those rows too, and zero times an infinity or a NaN
+  // is a NaN: a partial tile whose elements are not all finite is summed over the rows that count alone.
+  __device__ __forceinline__ void accumulate_seen(f32x4 (&acc)[DT], const f32x4 p, bool partial, int seen) const {
+    unsigned top = 0;
+    if (partial) {
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int c = 0; c < DT; c++) top = max(top, __float_as_uint(elem(c, e)) & 0x7fffffffu);
+    }
+    if (__all(top < 0x7f800000u)) {
+      accumulate(acc, p);
+      return;
+    }
+#pragma unroll 1
+    for (int q = 0; q < 4; q++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float pj = __shfl(p[e], 16 * q + l16, 64);
+        const bool counts = (__shfl(seen, 16 * q + l16, 64) >> e) & 1;
+        const float* r = row(4 * q + e) + 4 * g;
+        if (counts) {
+#pragma unroll
+          for (int c = 0; c < DT; c++)
+            if (16 * c + 4 * g < d) {
+              const f32x4 x4 = *reinterpret_cast<const f32x4*>(r + 16 * c);
+#pragma unroll
+              for (int i = 0; i < 4; i++) acc[c][i] = fmaf(x4[i], pj, acc[c][i]);
+            }
+        }
       }
   }
 };
@@ -108,7 +140,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
     for (int e = 0; e < 4; e++) q.v[c][e] *= scale;
   const float* kbase = kv + (size_t)b * (q_off + seq) * ldkv + (size_t)hk * d;
   const float* vbase = kbase + (size_t)nkv * d;
-  const int pos = q_off + iq, key_last = q_off + seq - 1, tiles = (q_off + min(i0 + 16, seq) + 15) / 16;
+  const int key_last = q_off + seq - 1, last = min(q_off + iq, key_last), tiles = (q_off + min(i0 + 16, seq) + 15) / 16;
   float m = -INFINITY, l = 0.f;
   f32x4 acc[DT];
 #pragma unroll
@@ -120,9 +152,12 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
     ColFrag<DT> vc;
     vc.start(vbase, ldkv, j0, key_last, l16, g, d);
     f32x4 s = dot_tile<DT>(k, q);  // rows = keys, column = query
+    int seen = 0;
 #pragma unroll
-    for (int e = 0; e < 4; e++)
-      if (j0 + 4 * g + e > pos) s[e] = -INFINITY;
+    for (int e = 0; e < 4; e++) {
+      if (j0 + 4 * g + e > last) s[e] = -INFINITY;
+      else seen |= 1 << e;
+    }
     const float mn = fmaxf(m, group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
     if (__any(mn > m)) {
       const float alpha = mn == -INFINITY ? 1.f : expf(m - mn);  // a row past the sequence end of a masked tile sees no key
@@ -135,7 +170,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
 #pragma unroll
     for (int e = 0; e < 4; e++) p[e] = s[e] == -INFINITY ? 0.f : expf(s[e] - m);
     l += group_sum(p[0] + p[1] + p[2] + p[3]);
-    vc.accumulate(acc, p);
+    vc.accumulate_seen(acc, p, j0 + 15 > q_off + i0, seen);
   }
   if (g == 0) { ms[wave][l16] = m; ls[wave][l16] = l; }
   __syncthreads();
@@ -200,7 +235,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
   const float Lq = lse[(size_t)h * T + tok];
   const float* kbase = kv + (size_t)b * (q_off + seq) * ldkv + (size_t)hk * d;
   const float* vbase = kbase + (size_t)nkv * d;
-  const int pos = q_off + iq, key_last = q_off + seq - 1, tiles = (q_off + min(i0 + 16, seq) + 15) / 16;
+  const int key_last = q_off + seq - 1, last = min(q_off + iq, key_last), tiles = (q_off + min(i0 + 16, seq) + 15) / 16;
   f32x4 acc[DT];
 #pragma unroll
   for (int c = 0; c < DT; c++) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -215,9 +250,13 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
     const f32x4 s = dot_tile<DT>(k, q);
     const f32x4 dp = dot_tile<DT>(v, dof);
     f32x4 ds;
+    int seen = 0;
 #pragma unroll
-    for (int e = 0; e < 4; e++) ds[e] = j0 + 4 * g + e > pos ? 0.f : expf(s[e] - Lq) * (dp[e] - dl);
-    kc.accumulate(acc, ds);
+    for (int e = 0; e < 4; e++) {
+      ds[e] = j0 + 4 * g + e > last ? 0.f : expf(s[e] - Lq) * (dp[e] - dl);
+      seen |= j0 + 4 * g + e > last ? 0 : 1 << e;
+    }
+    kc.accumulate_seen(acc, ds, j0 + 15 > q_off + i0, seen);
   }
   for (int w = 0; w < A32_WAVES; w++) {
     if (wave == w) {
@@ -277,15 +316,19 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
     const f32x4 s = dot_tile<DT>(q, k);  // rows = queries, column = key
     const f32x4 dp = dot_tile<DT>(dof, v);
     f32x4 p, ds;
+    int seen = 0;
 #pragma unroll
     for (int e = 0; e < 4; e++) {
       const int i = i0 + 4 * g + e;
       const size_t st = (size_t)h * T + tok0 + min(i, seq - 1);
-      p[e] = i < seq && q_off + i >= jk ? expf(s[e] - lse[st]) : 0.f;
-      ds[e] = p[e] * (dp[e] - delta[st]);
+      const bool counts = i < seq && q_off + i >= jk;
+      p[e] = counts ? expf(s[e] - lse[st]) : 0.f;
+      ds[e] = counts ? p[e] * (dp[e] - delta[st]) : 0.f;
+      seen |= counts ? 1 << e : 0;
     }
-    oc.accumulate(dv, p);
-    qc.accumulate(dk, ds);
+    const bool partial = i0 + 16 > seq || q_off + i0 < j0 + 15;
+    oc.accumulate_seen(dv, p, partial, seen);
+    qc.accumulate_seen(dk, ds, partial, seen);
   }
   for (int w = 0; w < A32_WAVES; w++) {
     if (wave == w) {

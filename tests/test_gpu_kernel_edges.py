@@ -67,6 +67,51 @@ def test_attention_f32_tiles(dh, batch, seq, q_off, nq, nkv, d):
         assert np.linalg.norm(got - ref) <= 5e-6 * max(np.linalg.norm(ref), floor)
 
 
+# float32 attention with an infinity or a NaN in one row of one operand: what may not see that row keeps its values (sums of
+# at most q_off + seq terms in another order), what sees it does not stay finite
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("what", ["q", "k", "v", "do"])
+@pytest.mark.parametrize("batch,seq,q_off,nq,nkv,d,row", [(2, 37, 0, 4, 2, 24, 15), (1, 64, 0, 2, 2, 64, 0), (1, 150, 0, 2, 1, 128, 149), (1, 40, 0, 2, 1, 256, 20),
+                                                          (1, 37, 21, 4, 2, 64, 30), (1, 40, 160, 2, 1, 128, 5)])
+def test_attention_f32_nonfinite_rows(dh, batch, seq, q_off, nq, nkv, d, row, what, bad):
+    print("case", batch, seq, q_off, nq, nkv, d, row, what, bad, flush=True)
+    T, S, b = batch * seq, q_off + seq, batch - 1
+
+    def run(dirty):
+        qkv, kv, do = gen.normal(90, (T, (nq + 2 * nkv) * d)), gen.normal(91, (batch * S, 2 * nkv * d)), gen.normal(92, (T, nq * d))
+        if dirty:  # element 1 of head 0 of the row (k, v) or of the query at position q_off + row (q, do)
+            a, r, c = {"q": (qkv, b * seq + row, 1), "k": (kv, b * S + q_off + row, 1), "v": (kv, b * S + q_off + row, nkv * d + 1),
+                       "do": (do, b * seq + row, 1)}[what]
+            a[r, c] = bad
+        qkv, kv, do = (torch.from_numpy(x).cuda() for x in (qkv, kv, do))
+        o, lse, delta = torch.empty(T, nq * d, device="cuda"), torch.empty(nq, T, device="cuda"), torch.empty(nq, T, device="cuda")
+        dqkv, dkv = torch.zeros_like(qkv), torch.zeros_like(kv)
+        dh.dh_attn_ctx_fwd(dh.DH_F32, batch, seq, q_off, nq, nkv, d, qkv, kv, o, lse)
+        dh.dh_attn_ctx_bwd(dh.DH_F32, batch, seq, q_off, nq, nkv, d, qkv, kv, o, do, lse, dqkv, dkv, delta)
+        heads = lambda t, n, m: t.cpu().numpy().reshape(batch, m, n, d)
+        return {"o": heads(o, nq, seq), "dq": heads(dqkv[:, : nq * d].contiguous(), nq, seq),
+                "dk": heads(dkv[:, : nkv * d].contiguous(), nkv, S), "dv": heads(dkv[:, nkv * d:].contiguous(), nkv, S)}
+
+    clean, got = run(False), run(True)
+    i = np.arange(seq)
+    spoilt = {"o": {"q": i == row, "k": i >= row, "v": i >= row, "do": i < 0}[what],    # queries of head 0 that see it
+              "dq": {"q": i == row, "k": i >= row, "v": i >= row, "do": i == row}[what]}
+    j = np.arange(S)                                                                     # keys of the group of head 0
+    spoilt["dk"] = {"q": j <= q_off + row, "k": j >= 0, "v": j >= 0, "do": j <= q_off + row}[what]
+    spoilt["dv"] = {"q": j <= q_off + row, "k": j >= 0, "v": j < 0, "do": j <= q_off + row}[what]
+    n_h = {"o": 1 if what in ("q", "do") else nq // nkv, "dq": 1 if what in ("q", "do") else nq // nkv, "dk": 1, "dv": 1}
+    for name, ref in clean.items():
+        keep = np.ones(ref.shape, bool)
+        hs = np.arange(n_h[name])
+        keep[b, np.flatnonzero(spoilt[name])[:, None], hs[None, :]] = False
+        scale = np.abs(ref).max()
+        assert np.all(np.isfinite(got[name][keep])), name
+        # a query's or key's terms in another order: S (and nq / nkv times as many for dk, dv) roundings of 2^-24 of the partial sums
+        assert np.max(np.abs(got[name] - ref)[keep], initial=0.0) <= 2.0 ** -24 * S * (nq // nkv) * scale, name
+        for r in np.flatnonzero(spoilt[name]) if np.isnan(bad) or what in ("v", "do") else ():  # an infinite score may be minus infinity
+            assert not np.all(np.isfinite(got[name][b, r, 0])), (name, r)
+
+
 # bf16 GEMM with 256x256 tiles: K below, at and beyond its two-stage pipeline and off the K step, ragged rows and columns
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(2824, 3080, 8), (2817, 3080, 64), (2560, 3336, 72), (2560, 3328, 128), (3080, 2568, 200), (2832, 2824, 264),
