@@ -179,7 +179,8 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
   for (int w = 1; w < A32_WAVES; w++) M = fmaxf(M, ms[w][l16]);
 #pragma unroll
   for (int w = 0; w < A32_WAVES; w++) L += ls[w][l16] == 0.f ? 0.f : ls[w][l16] * expf(ms[w][l16] - M);
-  const float f = l == 0.f ? 0.f : expf(m - M) / L;
+  if (M == -INFINITY) L = NAN;  // every score the row sees is minus infinity (or a NaN): no softmax
+  const float f = l == 0.f && L == L ? 0.f : expf(m - M) / L;
   for (int w = 0; w < A32_WAVES; w++) {  // the waves' shares, added in wave order
     if (wave == w) {
 #pragma unroll

@@ -112,6 +112,21 @@ def test_attention_f32_nonfinite_rows(dh, batch, seq, q_off, nq, nkv, d, row, wh
             assert not np.all(np.isfinite(got[name][b, r, 0])), (name, r)
 
 
+# float32 attention where every score a query sees is minus infinity: the softmax of such a row has no value, and says so; a row
+# that also sees a finite score has the softmax of those, wherever the tiles lie
+@pytest.mark.parametrize("seq,first,d", [(20, 1, 32), (150, 64, 64), (300, 150, 128), (40, 17, 256)])
+def test_attention_f32_no_finite_score(dh, seq, first, d):
+    qkv = np.abs(gen.normal(93, (seq, 3 * d))) + 0.1
+    qkv[:first, d: 2 * d] = -np.inf                    # the first keys: scores of minus infinity
+    qkv = torch.from_numpy(qkv.astype(np.float32)).cuda()
+    o, lse = torch.empty(seq, d, device="cuda"), torch.empty(1, seq, device="cuda")
+    dh.dh_attn_fwd(dh.DH_F32, 1, seq, 1, 1, d, qkv, o, lse)
+    assert torch.all(torch.isnan(o[:first])) and torch.all(torch.isnan(lse[0, :first]))
+    ref, ref_lse = R.attention_fwd(*(qkv[first:, i * d: (i + 1) * d].cpu().double().numpy()[:, None] for i in range(3)), 1, seq - first)
+    assert rel(o[first:].cpu().numpy(), ref[:, 0]) <= 2e-6
+    assert np.max(np.abs(lse[0, first:].cpu().numpy() - ref_lse[0])) <= 1e-5
+
+
 # bf16 GEMM with 256x256 tiles: K below, at and beyond its two-stage pipeline and off the K step, ragged rows and columns
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(2824, 3080, 8), (2817, 3080, 64), (2560, 3336, 72), (2560, 3328, 128), (3080, 2568, 200), (2832, 2824, 264),
