@@ -808,7 +808,14 @@ extern "C" int dh_layernorm_bwd(int dtype, int T, int H, const void* dy, const v
 // The operators above with the reduction in front of them taken in: the operand comes as n_parts partial buffers.  A
 // row of eight partials is 10 to 12 reads and one or two writes of memory against the two kernels' 12 to 14 and two to three; at
 // 4096 x 4096 in bf16 on eight ranks, separate against one: norm forward 47 + 20 -> 60 us, norm backward 48 + 28 -> 67, add
-// 47 + 16 -> 56 (5.5 to 6 TB/s all of them).  Callers have checked shapes and pointers.
+// 47 + 16 -> 56 (5.5 to 6 TB/s all of them).  Callers have checked shapes and the operators' own pointers; the partial
+// buffers are checked here, as dh_comm_standin checks them.
+static int check_parts(int n_parts, const void* const* parts) {
+  if (n_parts < 1 || n_parts > DH_MAX_RANKS) DH_FAIL(DH_ERR_INVALID_ARG, "reduction: %d partial buffers outside 1..%d", n_parts, DH_MAX_RANKS);
+  for (int r = 0; r < n_parts; r++)
+    if (!parts[r] || ((uintptr_t)parts[r] & 15)) DH_FAIL(DH_ERR_INVALID_ARG, "reduction: partial %d is null or not 16-byte aligned", r);
+  return DH_OK;
+}
 template <typename T>
 static RowSrc<T, true> sum_of(int n_parts, const void* const* parts) {
   RowSrc<T, true> src;
@@ -818,26 +825,36 @@ static RowSrc<T, true> sum_of(int n_parts, const void* const* parts) {
 }
 int dh_launch_sum_rmsnorm_fwd(int dtype, int T, int H, const void* x, int n_parts, const void* const* parts, const void* gamma, float eps,
                               void* x_out, void* h, float* rstd, hipStream_t s) {
+  const int rc = check_parts(n_parts, parts);
+  if (rc) return rc;
   return dtype == DH_BF16 ? rmsnorm_fwd_t(T, H, x, sum_of<bf16_t>(n_parts, parts), gamma, eps, x_out, h, rstd, s)
                           : rmsnorm_fwd_t(T, H, x, sum_of<float>(n_parts, parts), gamma, eps, x_out, h, rstd, s);
 }
 int dh_launch_sum_rmsnorm_bwd(int dtype, int T, int H, int n_parts, const void* const* parts, const void* x, const void* gamma, const float* rstd,
                               const void* dres, void* dx, float* dgamma, float* ws, hipStream_t s) {
+  const int rc = check_parts(n_parts, parts);
+  if (rc) return rc;
   return dtype == DH_BF16 ? rmsnorm_bwd_t(T, H, sum_of<bf16_t>(n_parts, parts), x, gamma, rstd, dres, dx, dgamma, ws, s)
                           : rmsnorm_bwd_t(T, H, sum_of<float>(n_parts, parts), x, gamma, rstd, dres, dx, dgamma, ws, s);
 }
 int dh_launch_sum_layernorm_fwd(int dtype, int T, int H, const void* x, int n_parts, const void* const* parts, const void* res_bias,
                                 const void* gamma, const void* beta, float eps, void* x_out, void* h, float* mu, float* rstd, hipStream_t s) {
+  const int rc = check_parts(n_parts, parts);
+  if (rc) return rc;
   return dtype == DH_BF16 ? layernorm_fwd_t(T, H, x, sum_of<bf16_t>(n_parts, parts), res_bias, gamma, beta, eps, x_out, h, mu, rstd, s)
                           : layernorm_fwd_t(T, H, x, sum_of<float>(n_parts, parts), res_bias, gamma, beta, eps, x_out, h, mu, rstd, s);
 }
 int dh_launch_sum_layernorm_bwd(int dtype, int T, int H, int n_parts, const void* const* parts, const void* x, const void* gamma,
                                 const float* mu, const float* rstd, const void* dres, void* dx, float* dgamma, float* dbeta, float* ws,
                                 hipStream_t s) {
+  const int rc = check_parts(n_parts, parts);
+  if (rc) return rc;
   return dtype == DH_BF16 ? layernorm_bwd_t(T, H, sum_of<bf16_t>(n_parts, parts), x, gamma, mu, rstd, dres, dx, dgamma, dbeta, ws, s)
                           : layernorm_bwd_t(T, H, sum_of<float>(n_parts, parts), x, gamma, mu, rstd, dres, dx, dgamma, dbeta, ws, s);
 }
 int dh_launch_sum_add(int dtype, int T, int H, const void* a, int n_parts, const void* const* parts, const void* bias, void* out, hipStream_t s) {
+  const int rc = check_parts(n_parts, parts);
+  if (rc) return rc;
   const size_t n8 = (size_t)T * (H / 8);
   const unsigned g = (unsigned)((n8 + 255) / 256);
 #define GO(TT)                                                                                                              \

@@ -384,6 +384,34 @@ def test_si_step_bitwise_equals_sequential_at_full_size(name):
         run.close()
 
 
+@pytest.mark.parametrize("comm_blocks", [0, 64])
+@pytest.mark.parametrize("arch,bf16", [("llama", True), ("llama", False), ("gpt", True), ("gpt", False)])
+def test_misaligned_partial_buffers_are_refused(arch, bf16, comm_blocks):
+    """The reductions read 16 bytes at a time: a buffer of the other ranks' partials that is not 16-byte aligned is an error
+    whether the stand-in is a kernel of its own (on a block budget) or one with the norm or residual add behind it."""
+    from paper_2411_15871_amd import dhelix as dh
+    run = H.LayerRun(dict(arch=arch, batch=1, seq=64, hidden=64, nq=2, nkv=1, d=64, ffn=64, n_ranks=2, bf16=bf16, comm_blocks=comm_blocks))
+    try:
+        s = run.strand(0)
+        run.fwd(s)
+        run.bwd(s)
+        for k, args, call in (("ar1", s.fwd_args, run.fwd), ("ar2", s.fwd_args, run.fwd), ("ar3", s.bwd_args, run.bwd), ("ar4", s.bwd_args, run.bwd)):
+            t = s.peers[k]
+            big = torch.zeros(t.numel() + 16, dtype=t.dtype, device="cuda")  # room for the shifted buffer
+            for shift, ok in ((0, True), (4 // t.element_size(), False), (8 // t.element_size(), False), (16 // t.element_size(), True)):
+                setattr(args, "peers_" + k, big[shift:].data_ptr())
+                if ok:
+                    call(s)
+                else:
+                    with pytest.raises(dh.DhelixError) as e:
+                        call(s)
+                    assert e.value.code == dh.DH_ERR_INVALID_ARG
+            setattr(args, "peers_" + k, t.data_ptr())
+        torch.cuda.synchronize()
+    finally:
+        run.close()
+
+
 def test_empty_micro_batch_is_a_no_op():
     run = H.LayerRun(dict(batch=0, seq=16, hidden=64, nq=2, nkv=1, d=32, ffn=64, n_ranks=2, bf16=False))
     try:
