@@ -13,6 +13,7 @@
 // probabilities feeds the next product from the registers it was formed in: the instruction's k index of lane group g and
 // step e may be any row as long as both operands agree, and row 4g + e is the one the lane already holds.
 // 128 tokens, 4 heads of 64: forward 26 -> 7 us, backward 62 -> 19 us against one wave per row with dot products.
+#include <algorithm>
 #include "common.h"
 
 // Waves of a block: eight where the fragments of a 64-wide head leave room for two waves per SIMD, else four.
@@ -118,7 +119,7 @@ __device__ __forceinline__ float group_max(float v) {
   return fmaxf(v, __shfl_xor(v, 32, 64));
 }
 
-// grid (16-query tiles per sequence, nq, batch)
+// grid (16-query tiles per sequence, nq, sequences)
 template <int DT>
 __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int seq, int nq, int nkv, int d, const float* __restrict__ qkv,
                                                                       const float* __restrict__ kv, int ldkv, int q_off,
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
   }
 }
 
-// dK, dV.  grid (16-key tiles per sequence, nkv, batch); a tile's work is every (query head of the group, query tile) pair.
+// dK, dV.  grid (16-key tiles per sequence, nkv, sequences); a tile's work is every (query head of the group, query tile) pair.
 template <int DT>
 __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(int seq, int nq, int nkv, int d, const float* __restrict__ qkv,
                                                                           const float* __restrict__ kv, int ldkv, int q_off,
@@ -357,11 +358,20 @@ static int check_f32(int d) {
   return DH_OK;
 }
 
+// Sequences of one launch: the third dimension of a grid holds 65535 blocks.
+#define A32_MAX_BATCH 65535
+
 template <int DT>
-static void fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv, int q_off, float* o, float* lse,
-                    hipStream_t stream) {
-  attn_fwd_f32_kernel<DT><<<dim3((seq + 15) / 16, nq, batch), 64 * a32_waves<DT>(), 16 * (DT * 16 + 4) * sizeof(float), stream>>>(
-      seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, batch * seq);
+static int fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv, int q_off, float* o, float* lse,
+                   hipStream_t stream) {
+  const size_t ld = (size_t)(nq + 2 * nkv) * d;
+  for (int b0 = 0; b0 < batch; b0 += A32_MAX_BATCH) {
+    const size_t t0 = (size_t)b0 * seq, k0 = (size_t)b0 * (q_off + seq);
+    attn_fwd_f32_kernel<DT><<<dim3((seq + 15) / 16, nq, std::min(batch - b0, A32_MAX_BATCH)), 64 * a32_waves<DT>(), 16 * (DT * 16 + 4) * sizeof(float), stream>>>(
+        seq, nq, nkv, d, qkv + t0 * ld, kv + k0 * ldkv, ldkv, q_off, o + t0 * nq * d, lse + t0, batch * seq);
+    DH_LAUNCH_CHECK();
+  }
+  return DH_OK;
 }
 
 int dh_launch_attn_fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv,
@@ -370,24 +380,27 @@ int dh_launch_attn_fwd_f32(int batch, int seq, int nq, int nkv, int d, const flo
   if (rc) return rc;
   if (batch * seq == 0) return DH_OK;
   if (!kv) { kv = qkv + (size_t)nq * d; ldkv = (nq + 2 * nkv) * d; q_off = 0; }
-  if (d <= 32) fwd_f32<2>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
-  else if (d <= 64) fwd_f32<4>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
-  else if (d <= 128) fwd_f32<8>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
-  else fwd_f32<16>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
-  DH_LAUNCH_CHECK();
-  return DH_OK;
+  if (d <= 32) return fwd_f32<2>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
+  if (d <= 64) return fwd_f32<4>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
+  if (d <= 128) return fwd_f32<8>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
+  return fwd_f32<16>(batch, seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, lse, stream);
 }
 
 template <int DT>
 static int bwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv, int q_off, const float* o,
                    const float* dout, const float* lse, float* dqkv, float* dkv, int lddkv, float* delta, hipStream_t stream) {
   const int T = batch * seq;
-  attn_bwd_dq_f32_kernel<DT><<<dim3((seq + 15) / 16, nq, batch), 64 * a32_waves<DT>(), 16 * (DT * 16 + 4) * sizeof(float), stream>>>(
-      seq, nq, nkv, d, qkv, kv, ldkv, q_off, o, dout, lse, delta, dqkv, T);
-  DH_LAUNCH_CHECK();
-  attn_bwd_dkv_f32_kernel<DT><<<dim3((q_off + seq + 15) / 16, nkv, batch), 64 * a32_waves<DT>(), 16 * (2 * DT * 16 + 4) * sizeof(float), stream>>>(
-      seq, nq, nkv, d, qkv, kv, ldkv, q_off, dout, lse, delta, dkv, lddkv, T);
-  DH_LAUNCH_CHECK();
+  const size_t ld = (size_t)(nq + 2 * nkv) * d;
+  for (int b0 = 0; b0 < batch; b0 += A32_MAX_BATCH) {
+    const size_t t0 = (size_t)b0 * seq, k0 = (size_t)b0 * (q_off + seq);
+    const int nb = std::min(batch - b0, A32_MAX_BATCH);
+    attn_bwd_dq_f32_kernel<DT><<<dim3((seq + 15) / 16, nq, nb), 64 * a32_waves<DT>(), 16 * (DT * 16 + 4) * sizeof(float), stream>>>(
+        seq, nq, nkv, d, qkv + t0 * ld, kv + k0 * ldkv, ldkv, q_off, o + t0 * nq * d, dout + t0 * nq * d, lse + t0, delta + t0, dqkv + t0 * ld, T);
+    DH_LAUNCH_CHECK();
+    attn_bwd_dkv_f32_kernel<DT><<<dim3((q_off + seq + 15) / 16, nkv, nb), 64 * a32_waves<DT>(), 16 * (2 * DT * 16 + 4) * sizeof(float), stream>>>(
+        seq, nq, nkv, d, qkv + t0 * ld, kv + k0 * ldkv, ldkv, q_off, dout + t0 * nq * d, lse + t0, delta + t0, dkv + k0 * lddkv, lddkv, T);
+    DH_LAUNCH_CHECK();
+  }
   return DH_OK;
 }
 

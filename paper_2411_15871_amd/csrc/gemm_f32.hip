@@ -70,9 +70,10 @@ template <int NT, bool TA, bool TB, bool VEC>
 __global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
                                                                       const float* __restrict__ B, float* __restrict__ C, int accumulate,
                                                                       const float* __restrict__ bias, const int32_t* __restrict__ group_rows,
-                                                                      int group_mode) {
+                                                                      int group_mode, int rows_in_x) {
   constexpr int TILE = 16 * NT, LD = TILE + 4;  // square tiles; row pitch of a partial tile
   extern __shared__ float part[];               // [waves][TILE][LD]
+  const int tile_m = rows_in_x ? blockIdx.x : blockIdx.y, tile_n = rows_in_x ? blockIdx.y : blockIdx.x;
   if (group_rows != nullptr) {  // grouped: blockIdx.z = group, its rows follow those of the groups before it
     int row0 = 0;
     for (int i = 0; i < (int)blockIdx.z; i++) row0 += group_rows[i];
@@ -82,10 +83,10 @@ __global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int
     } else {
       A += (size_t)row0 * K; B += (size_t)blockIdx.z * K * N; C += (size_t)row0 * N; M = rows;
     }
-    if (rows == 0 || (int)blockIdx.y * TILE >= M) return;
+    if (rows == 0 || tile_m * TILE >= M) return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
+  const int m0 = tile_m * TILE, n0 = tile_n * TILE;
   const int steps = (K + F32_KS - 1) / F32_KS, per = (steps + waves - 1) / waves;
   const int k_begin = wave * per * F32_KS, k_end = min(K, k_begin + per * F32_KS);
   f32x4 acc[NT][NT];
@@ -165,9 +166,10 @@ static int launch_f32(int M, int N, int K, int k_typical, const float* A, const 
                                  F32_MAX_WAVES * PART));                                                                        \
       attr_set[dev] = true;                                                                                                     \
     }                                                                                                                           \
-    dim3 grid((N + TILE - 1) / TILE, (M + TILE - 1) / TILE, n_groups);                                                          \
+    const int tm = (M + TILE - 1) / TILE, tn = (N + TILE - 1) / TILE, rows_in_x = tm > 65535; /* y holds no more blocks */       \
+    dim3 grid(rows_in_x ? tm : tn, rows_in_x ? tn : tm, n_groups);                                                              \
     gemm_f32_kernel<NT, TA, TB, V><<<grid, 64 * waves, waves * PART, stream>>>(M, N, K, A, B, C, accumulate ? 1 : 0, bias,      \
-                                                                               group_rows, group_mode);                         \
+                                                                               group_rows, group_mode, rows_in_x);              \
   } while (0)
   if (small) { if (vec) GO(1, true); else GO(1, false); }
   else { if (vec) GO(2, true); else GO(2, false); }

@@ -127,6 +127,41 @@ def test_attention_f32_no_finite_score(dh, seq, first, d):
     assert np.max(np.abs(lse[0, first:].cpu().numpy() - ref_lse[0])) <= 1e-5
 
 
+# float32 attention with more sequences than a grid's third dimension holds: every sequence is one token that sees itself
+@pytest.mark.parametrize("batch", [65535, 65537, 140001])
+def test_attention_f32_many_sequences(dh, batch):
+    nq, nkv, d = 2, 1, 16
+    g = torch.Generator(device="cuda").manual_seed(5)
+    qkv = torch.randn(batch, (nq + 2 * nkv) * d, generator=g, device="cuda")
+    do = torch.randn(batch, nq * d, generator=g, device="cuda")
+    o, lse, delta = torch.zeros(batch, nq * d, device="cuda"), torch.zeros(nq, batch, device="cuda"), torch.zeros(nq, batch, device="cuda")
+    dqkv = torch.full_like(qkv, 7.0)
+    dh.dh_attn_fwd(dh.DH_F32, batch, 1, nq, nkv, d, qkv, o, lse)
+    dh.dh_attn_bwd(dh.DH_F32, batch, 1, nq, nkv, d, qkv, o, do, lse, dqkv, delta)
+    q, k, v = qkv[:, : nq * d].view(batch, nq, d), qkv[:, nq * d: (nq + 1) * d], qkv[:, (nq + 1) * d:]
+    # one key: o = v, dv = the sum of the group's dO; dq and dk are zero up to the rounding of dP - delta
+    assert torch.equal(o.view(batch, nq, d), v[:, None].expand(batch, nq, d))
+    s = (q.double() * k.double()[:, None]).sum(-1) / d ** 0.5
+    assert float((lse.t().double() - s).abs().max()) <= 1e-5
+    assert float((dqkv[:, (nq + 1) * d:] - do.view(batch, nq, d).sum(1)).abs().max()) <= 1e-5
+    assert float(dqkv[:, : (nq + 1) * d].abs().max()) <= 1e-3
+
+
+# float32 GEMM with more tiles of rows, and of columns, than a grid's second dimension holds
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(65535 * 32 + 5, 8, 8), (8, 65535 * 32 + 4, 8), (65535 * 16 + 40, 7, 5)])
+def test_gemm_f32_long_sides(dh, ta, tb, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(6)
+    A, B = torch.randn((K, M) if ta else (M, K), generator=g, device="cuda"), torch.randn((N, K) if tb else (K, N), generator=g, device="cuda")
+    C = torch.full((M, N), 3.0, device="cuda")
+    dh.dh_gemm(dh.DH_F32, ta, tb, M, N, K, A, B, C, False)
+    a, b = (A.t() if ta else A).double(), (B.t() if tb else B).double()
+    err = torch.zeros(M, N, dtype=torch.float64, device="cuda") - C
+    for k in range(K):
+        err += a[:, k: k + 1] * b[k: k + 1]
+    assert float(err.abs().max()) <= 1e-4   # 8 products of normal numbers in 32 bits
+
+
 # bf16 GEMM with 256x256 tiles: K below, at and beyond its two-stage pipeline and off the K step, ragged rows and columns
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(2824, 3080, 8), (2817, 3080, 64), (2560, 3336, 72), (2560, 3328, 128), (3080, 2568, 200), (2832, 2824, 264),
