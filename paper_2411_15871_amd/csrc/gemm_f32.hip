@@ -7,7 +7,7 @@
 // products; the waves' partial tiles meet in LDS and are added in wave order, so results do not depend on scheduling.
 // 128x768x256: 38 -> 4.6 us, 128x256x1376: 123 -> 7.8 us against a 64x64 tile per 256 threads with the whole of K walked by each.
 // Any M, N, K >= 0 is accepted; VEC: rows of both operands can be read 16 bytes (K-contiguous) or 8 bytes (K-major)
-// at a time, otherwise every element is fetched and checked on its own.
+// at a time, otherwise every element is fetched and checked on its own.  Results (and a bias) likewise, 16 bytes or one element.
 #include <algorithm>
 #include "common.h"
 
@@ -70,7 +70,7 @@ template <int NT, bool TA, bool TB, bool VEC>
 __global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
                                                                       const float* __restrict__ B, float* __restrict__ C, int accumulate,
                                                                       const float* __restrict__ bias, const int32_t* __restrict__ group_rows,
-                                                                      int group_mode, int rows_in_x) {
+                                                                      int group_mode, int rows_in_x, int vec_out) {
   constexpr int TILE = 16 * NT, LD = TILE + 4;  // square tiles; row pitch of a partial tile
   extern __shared__ float part[];               // [waves][TILE][LD]
   const int tile_m = rows_in_x ? blockIdx.x : blockIdx.y, tile_n = rows_in_x ? blockIdx.y : blockIdx.x;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int
     f32x4 s = *reinterpret_cast<const f32x4*>(part + row * LD + c);
     for (int w = 1; w < waves; w++) s += *reinterpret_cast<const f32x4*>(part + w * (TILE * LD) + row * LD + c);
     float* dst = C + (size_t)gm * N + gn;
-    if (N % 4 == 0) {
+    if (vec_out) {  // N a multiple of 4, C and bias 16-byte aligned
       if (gn >= N) continue;
       if (bias) s += *reinterpret_cast<const f32x4*>(bias + gn);
       if (accumulate) s += *reinterpret_cast<const f32x4*>(dst);
@@ -153,7 +153,8 @@ static int launch_f32(int M, int N, int K, int k_typical, const float* A, const 
                       const int32_t* group_rows, int group_mode, int n_groups, hipStream_t stream) {
   const int waves = std::min(F32_MAX_WAVES, std::max(1, (k_typical + 31) / 32));
   auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  const bool vec = aligned(A) && aligned(B) && aligned(C) && aligned(bias) && (TA ? M : K) % 4 == 0 && (TB ? K : N) % 4 == 0;
+  const bool vec = aligned(A) && aligned(B) && (TA ? M : K) % 4 == 0 && (TB ? K : N) % 4 == 0;
+  const int vec_out = N % 4 == 0 && aligned(C) && aligned(bias);
   // 16x16 tiles load twice as much per product: they pay only while 32x32 tiles come to fewer blocks than compute units.
   const bool small = (long long)((M + 31) / 32) * ((N + 31) / 32) * n_groups < 256;
 #define GO(NT, V)                                                                                                               \
@@ -169,7 +170,7 @@ static int launch_f32(int M, int N, int K, int k_typical, const float* A, const 
     const int tm = (M + TILE - 1) / TILE, tn = (N + TILE - 1) / TILE, rows_in_x = tm > 65535; /* y holds no more blocks */       \
     dim3 grid(rows_in_x ? tm : tn, rows_in_x ? tn : tm, n_groups);                                                              \
     gemm_f32_kernel<NT, TA, TB, V><<<grid, 64 * waves, waves * PART, stream>>>(M, N, K, A, B, C, accumulate ? 1 : 0, bias,      \
-                                                                               group_rows, group_mode, rows_in_x);              \
+                                                                               group_rows, group_mode, rows_in_x, vec_out);     \
   } while (0)
   if (small) { if (vec) GO(1, true); else GO(1, false); }
   else { if (vec) GO(2, true); else GO(2, false); }

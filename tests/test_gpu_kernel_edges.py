@@ -162,6 +162,19 @@ def test_gemm_f32_long_sides(dh, ta, tb, M, N, K):
     assert float(err.abs().max()) <= 1e-4   # 8 products of normal numbers in 32 bits
 
 
+# float32 GEMM with a result or a bias that is 4-byte aligned only: stored (and read) one element at a time
+@pytest.mark.parametrize("M,N,K", [(40, 36, 20), (520, 516, 36)])
+def test_gemm_f32_misaligned_result(dh, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    A, B = torch.randn(M, K, generator=g, device="cuda"), torch.randn(K, N, generator=g, device="cuda")
+    buf, bias = torch.full((M * N + 8,), 3.0, device="cuda"), torch.randn(N + 1, generator=g, device="cuda")[1:]
+    ref = torch.empty(M, N, device="cuda")
+    dh.dh_gemm_bias(dh.DH_F32, 0, 0, M, N, K, A, B, bias.clone(), ref, False)
+    dh.dh_gemm_bias(dh.DH_F32, 0, 0, M, N, K, A, B, bias, buf[1:], False)
+    assert torch.equal(buf[1: M * N + 1].view(M, N), ref)
+    assert float(buf[0]) == 3.0 and torch.all(buf[M * N + 1:] == 3.0)
+
+
 # bf16 GEMM with 256x256 tiles: K below, at and beyond its two-stage pipeline and off the K step, ragged rows and columns
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(2824, 3080, 8), (2817, 3080, 64), (2560, 3336, 72), (2560, 3328, 128), (3080, 2568, 200), (2832, 2824, 264),
