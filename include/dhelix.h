@@ -685,6 +685,9 @@ int dh_moe_combine_bwd(int dtype, int T, int H, const void* dy, const void* yp, 
  * dim_a, dim_b multiples of 8 for DH_BF16; at most 64 groups. */
 int dh_gemm_grouped(int dtype, int mode, int n_groups, const int32_t* group_rows, int max_rows,
                     int dim_a, int dim_b, const void* A, const void* B, void* C, void* stream);
+/* The tile of C (rows x cols) that a block of the bf16 launch for these arguments computes; it follows from the sizes alone
+ * (groups of about max_rows / n_groups rows are assumed).  Host only. */
+int dh_gemm_grouped_tile(int mode, int n_groups, int max_rows, int dim_a, int dim_b, int* rows, int* cols);
 
 /* A bf16 GEMM and an all-reduce stand-in in ONE launch (the direction the closing paragraph of the cross-node analysis
  * of Sec. 6.3 / Table 7 names: computation and communication inside one kernel, so that their shares of the machine

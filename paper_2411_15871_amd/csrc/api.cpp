@@ -50,6 +50,13 @@ extern "C" int dh_gemm_grouped(int dtype, int mode, int n_groups, const int32_t*
   DH_FAIL(DH_ERR_INVALID_ARG, "gemm_grouped: unknown dtype %d", dtype);
 }
 
+extern "C" int dh_gemm_grouped_tile(int mode, int n_groups, int max_rows, int dim_a, int dim_b, int* rows, int* cols) {
+  if (mode < 0 || mode > 2 || n_groups < 1 || n_groups > 64 || max_rows < 0 || dim_a <= 0 || dim_b <= 0 || !rows || !cols)
+    DH_FAIL(DH_ERR_INVALID_ARG, "gemm_grouped_tile: mode=%d groups=%d max_rows=%d dims=%d,%d", mode, n_groups, max_rows, dim_a, dim_b);
+  dh_gemm_grouped_bf16_tile(mode, n_groups, max_rows, dim_a, dim_b, rows, cols);
+  return DH_OK;
+}
+
 extern "C" int dh_gemm_allreduce_fits(int trans_a, int trans_b, int M, int N, int K) {
   return dh_gemm_ar_fits(trans_a != 0, trans_b != 0, M, N, K) ? 1 : 0;
 }

@@ -196,6 +196,7 @@ int dh_launch_moe_combine(int dtype, int T, int H, const void* yp, const int32_t
                           const void* residual, void* y, hipStream_t stream);
 int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                 const bf16_t* A, const bf16_t* B, void* C, hipStream_t stream);
+void dh_gemm_grouped_bf16_tile(int mode, int n_groups, int max_rows, int dim_a, int dim_b, int* rows, int* cols);
 // Norm, residual add and their gradients behind a reduction over n_parts partial buffers (rowops.hip).
 int dh_launch_sum_rmsnorm_fwd(int dtype, int T, int H, const void* x, int n_parts, const void* const* parts, const void* gamma, float eps,
                               void* x_out, void* h, float* rstd, hipStream_t s);

@@ -824,7 +824,10 @@ static const TileCost kTiles[] = {{0, 256, 256, 1250, 1500}, {2, 256, 128, 780, 
 // The tile shape is the one with the least rounds * (stages * stage + fill + store): large tiles cost least per product, small ones
 // leave fewer units idle.  The store goes at a unit's share of the memory's rate, 20 bytes a ns.  Ranges go to blocks of their own and through the workspace (splitk_reduce_kernel), or, with 64x64
 // tiles, are summed one after the other in the block (no workspace, no second launch), whichever is expected sooner.
-static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int groups = 1) {
+//
+// groups > 0: a grouped launch, `groups` products of this (average) size.  Its K is never cut (a group's extents are known on
+// the device alone), so there are no ranges, and every tile shape is considered over the tiles of all groups.
+static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int groups = 0) {
   const int cus = num_cus();
   auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const int nkt = std::max(1, (K + 31) / 32);  // ranges are made in units of 32
@@ -833,12 +836,12 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
   const bool wide = t256 * 2 >= cus;
   const long long t = wide ? t256 : (t2 <= cus && t2 * 4 >= (long long)cus * 3) ? t2 : tiles(128, 128);
   int ranges = 1;
-  if (t * 4 <= cus * 3 && nkt >= 32) ranges = std::max(1, std::min((int)(cus / t), nkt / 16));
+  if (groups == 0 && t * 4 <= cus * 3 && nkt >= 32) ranges = std::max(1, std::min((int)(cus / t), nkt / 16));
   const int per = (nkt + ranges - 1) / ranges;
   ranges = (nkt + per - 1) / per;
   p.ranges = ranges;
   const int tail = (int)(t % cus);
-  if (wide && t > cus && tail > 0 && tail * 2 <= cus && nkt >= 64 && groups == 1) {
+  if (wide && t > cus && tail > 0 && tail * 2 <= cus && nkt >= 64 && groups == 0) {
     int ts = std::min(std::min(cus / tail, 8), nkt / 16);
     const size_t bytes = (size_t)(tail + 7) * 256 * 256 * sizeof(float);  // the launch index range is padded to a multiple of 8
     if (ws_bytes / bytes < (size_t)ts) ts = (int)(ws_bytes / bytes);
@@ -853,7 +856,7 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
   const size_t mn = (size_t)M * N;
   double best = 0;
   auto consider = [&](const TileCost& c, int splits, bool chained) {
-    const long long blocks = tiles(c.bm, c.bn) * splits * groups;
+    const long long blocks = tiles(c.bm, c.bn) * splits * std::max(1, groups);
     const int stages = ((splits > 1 ? per : nkt) + 1) / 2;
     double stage = c.stage, store = (double)c.bm * c.bn * (splits > 1 ? 4 : acc ? 8 : 2) / 20;
     if (c.cfg == 3) stage += chained ? 25 : 0;
@@ -1078,6 +1081,15 @@ int dh_launch_gemm_swiglu_bwd_bf16(int T, int F, int H, const bf16_t* dy, const 
 // rows, max_rows bounds any group (the grid is sized for it).  mode 0: C[rows,dim_b] = A[rows,dim_a] B_z[dim_a,dim_b];
 // mode 1: C[rows,dim_b] = A[rows,dim_a] B_z[dim_b,dim_a]^T; mode 2: C_z[dim_a,dim_b] += A[rows,dim_a]^T B[rows,dim_b]
 // (float32).  No split-K: every group is one launch slice of the same grid.
+static GemmPlan grouped_plan(int mode, int n_groups, int max_rows, int dim_a, int dim_b) {  // for groups of about equal size
+  const int avg = std::max(1, max_rows / n_groups);
+  return mode == 2 ? choose_plan(dim_a, dim_b, avg, true, 0, n_groups) : choose_plan(avg, dim_b, dim_a, false, 0, n_groups);
+}
+void dh_gemm_grouped_bf16_tile(int mode, int n_groups, int max_rows, int dim_a, int dim_b, int* rows, int* cols) {
+  const GemmPlan p = grouped_plan(mode, n_groups, max_rows, dim_a, dim_b);
+  *rows = p.bm;
+  *cols = p.bn;
+}
 int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_rows, int max_rows, int dim_a, int dim_b,
                                 const bf16_t* A, const bf16_t* B, void* C, hipStream_t stream) {
   if (dim_a % 8 || dim_b % 8) DH_FAIL(DH_ERR_SHAPE, "gemm_grouped (bf16): feature dimensions must be multiples of 8 (%d, %d)", dim_a, dim_b);
@@ -1088,10 +1100,9 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
   g.tiles_m = g.tiles_n = g.tiles_per_xcd = 0;
   g.group_part = 0; g.n_groups = n_groups; g.part1_bm = g.part1_bn = 256; g.cus = num_cus(); g.tile_first = 0;
   g.glu_mode = GLU_NONE; g.glu_f = 0; g.glu_in = nullptr; g.glu_out = nullptr; g.ar_blocks = 0;
-  const int avg = std::max(1, max_rows / n_groups);
-  GemmPlan p;
-  if (mode == 2) { g.M = dim_a; g.N = dim_b; g.K = max_rows; p = choose_plan(dim_a, dim_b, avg, true, 0, n_groups); }
-  else { g.M = max_rows; g.N = dim_b; g.K = dim_a; p = choose_plan(avg, dim_b, dim_a, false, 0, n_groups); }
+  GemmPlan p = grouped_plan(mode, n_groups, max_rows, dim_a, dim_b);
+  if (mode == 2) { g.M = dim_a; g.N = dim_b; g.K = max_rows; }
+  else { g.M = max_rows; g.N = dim_b; g.K = dim_a; }
   g.k_per_split = g.K; g.k_chain = g.n_split = 0;  // no K split
   g.epi = mode == 2 ? EPI_ACC_F32 : EPI_STORE_BF16;
   if (mode == 2) return launch_layout<true, false>(g, p, stream, n_groups);

@@ -210,6 +210,7 @@ SIGNATURES = {
     "dh_moe_combine": (_I, [_I, _I, _I, _P, _P, _P, _P, _P, _P]),
     "dh_moe_combine_bwd": (_I, [_I, _I, _I, _P, _P, _P, _P, _P, _P, _P]),
     "dh_gemm_grouped": (_I, [_I, _I, _I, _P, _I, _I, _I, _P, _P, _P, _P]),
+    "dh_gemm_grouped_tile": (_I, [_I, _I, _I, _I, _I, C.POINTER(C.c_int), C.POINTER(C.c_int)]),
     "dh_gemm_bias": (_I, [_I, _I, _I, _I, _I, _I, _P, _P, _P, _P, _I, _P, _Z, _P]),
     "dh_layernorm_fwd": (_I, [_I, _I, _I, _P, _P, _P, _P, _P, _F, _P, _P, _P, _P, _P]),
     "dh_layernorm_bwd": (_I, [_I, _I, _I, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _Z, _P]),
@@ -726,6 +727,12 @@ def dh_moe_combine_bwd(dtype, T, H, dy, yp, dest, prob, dyp, dprob, stream=None)
 def dh_gemm_grouped(dtype, mode, n_groups, group_rows, max_rows, dim_a, dim_b, A, B, Cout, stream=None):
     _check(lib.dh_gemm_grouped(dtype, mode, n_groups, _ptr(group_rows), max_rows, dim_a, dim_b, _ptr(A), _ptr(B), _ptr(Cout),
                                _stream(stream)))
+
+
+def dh_gemm_grouped_tile(mode, n_groups, max_rows, dim_a, dim_b):
+    rows, cols = C.c_int(), C.c_int()
+    _check(lib.dh_gemm_grouped_tile(mode, n_groups, max_rows, dim_a, dim_b, C.byref(rows), C.byref(cols)))
+    return rows.value, cols.value
 
 
 def dh_gemm_bias(dtype, trans_a, trans_b, M, N, K, A, B, bias, Cout, out_f32_accumulate=False, ws=None, ws_bytes=0, stream=None):

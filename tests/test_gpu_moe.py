@@ -196,6 +196,35 @@ def test_gemm_grouped_large_tiles_and_remainders(dh, rows):
         r0 = r1
 
 
+# every tile shape a grouped bf16 product takes, with groups of unequal size, empty ones and sizes that fill no tile or K step
+@pytest.mark.parametrize("rows,a,b", [([512] * 4, 2048, 1408), ([700, 0, 1037, 311], 2048, 1408), ([1024] * 4, 1024, 2048), ([1, 2047, 1030, 1018], 1024, 2048),
+                                      ([512] * 8, 2048, 2048), ([3, 900, 0, 131, 1500, 513, 257, 792], 2048, 2048), ([2048] * 4, 4096, 1600),
+                                      ([8000], 1024, 3000), ([4999, 1], 768, 776), ([1000] * 4, 6000, 512), ([60, 70], 200, 136)])
+def test_gemm_grouped_tile_shapes(dh, rows, a, b):
+    print("case", rows, a, b, flush=True)
+    G, tot = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(a + b)
+    bf = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    x, y, W = bf(tot, a), bf(tot, b), bf(G, a, b)
+    rd = torch.tensor(rows, dtype=torch.int32, device="cuda")
+    c, d = torch.full((tot + 1, b), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((tot + 1, a), 7.0, dtype=torch.bfloat16, device="cuda")
+    dW = torch.full((G, a, b), 0.5, device="cuda")
+    dh.dh_gemm_grouped(dh.DH_BF16, 0, G, rd, tot, a, b, x, W, c)
+    dh.dh_gemm_grouped(dh.DH_BF16, 1, G, rd, tot, b, a, y, W, d)
+    dh.dh_gemm_grouped(dh.DH_BF16, 2, G, rd, tot, a, b, x, y, dW)
+    assert torch.all(c[tot] == 7.0) and torch.all(d[tot] == 7.0)
+    r0 = 0
+    for i, r in enumerate(rows):
+        xs, ys, w = x[r0: r0 + r].float(), y[r0: r0 + r].float(), W[i].float()
+        if r:
+            for got, ref in ((c[r0: r0 + r], xs @ w), (d[r0: r0 + r], ys @ w.t().contiguous())):  # a rounding of 2^-9 each
+                assert float((got.float() - ref).norm() / ref.norm()) <= 4e-3
+                assert float((got.float() - ref).norm(dim=1).max() / ref.norm(dim=1).mean()) <= 8e-3
+        ref = xs.t().contiguous() @ ys
+        assert float((dW[i] - 0.5 - ref).norm()) <= 2e-5 * max(float(ref.norm()), (a * b) ** 0.5)
+        r0 += r
+
+
 @pytest.mark.parametrize("bf16,T,H,F,E,n_local", [(False, 300, 64, 96, 8, 2), (True, 1000, 256, 384, 16, 2),
                                                   (True, 257, 128, 64, 4, 4)])
 def test_moe_block_fwd_bwd(dh, bf16, T, H, F, E, n_local):

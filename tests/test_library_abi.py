@@ -76,3 +76,20 @@ def test_context_parallel_layer_configuration_is_checked():
     plain = dh.dh_layer_create(**{**base, "arch": dh.DH_ARCH_LLAMA, "cp_ranks": 0})
     assert dh.dh_layer_saved_bytes(plain) < sizes[0][0]
     dh.dh_layer_destroy(plain)
+
+
+@pytest.mark.parametrize("groups,rows,a,b", [(4, 512, 2048, 1408), (4, 1024, 1024, 2048), (8, 512, 2048, 2048), (4, 2048, 4096, 1600), (1, 8000, 1024, 3000),
+                                             (4, 1000, 6000, 512), (2, 2500, 768, 768), (2, 1500, 2048, 3200)])
+def test_grouped_gemm_tiles_fill_the_chip_once(groups, rows, a, b):
+    """A grouped product whose groups make enough blocks together takes tiles larger than 64x64, however few blocks one group
+    makes: its K is never cut, so a group's own tile count is no reason for small tiles."""
+    for mode in (0, 1):
+        for ka, kb in ((a, b), (b, a)):
+            tm, tn = dh.dh_gemm_grouped_tile(mode, groups, groups * rows, ka, kb)
+            blocks_128 = groups * -(-rows // 128) * -(-kb // 128)
+            assert (tm, tn) in ((64, 64), (128, 128), (256, 128), (256, 256))
+            if blocks_128 >= 96:
+                assert tm * tn > 64 * 64, (mode, ka, kb)
+    assert dh.dh_gemm_grouped_tile(0, 1, 64, 64, 64) == (64, 64)  # one small product: small tiles
+    with pytest.raises(dh.DhelixError):
+        dh.dh_gemm_grouped_tile(3, 1, 64, 64, 64)
