@@ -354,6 +354,7 @@ def main():
     def regime(label, comm_blocks, steps, warmup, table_path=None):
         """Offline part of the method (Sec. 3.2, 4.2) and the timed step, with the stand-ins at one cost."""
         dh.dh_layer_set_comm_blocks(run.layer, comm_blocks)
+        gf, gb = dh.dh_layer_op_graph(run.layer, 0), dh.dh_layer_op_graph(run.layer, 1)   # where the stand-ins go depends on their cost
         dh.dh_layer_set_beta_comm_stream(run.layer, scb)   # the profile co-runs the two strands' collectives on two streams
         t0 = time.perf_counter()
         table = dh.dh_profile_pairs(run.layer, alpha.fwd_args, beta.bwd_args, run.ws, run.ws_bytes, sa, sb, sc, args.profile_reps)

@@ -235,21 +235,26 @@ typedef enum {
 #define DH_MAX_DEPS 96
 typedef struct {
   int n_ops;
-  int is_comm[DH_MAX_OPS];   /* 1 = collective stand-in (issued on the communication stream); 2 = cross-node
-                                Send/Recv stand-in (issued on the layer's cross-node stream if one is set) */
+  int is_comm[DH_MAX_OPS];   /* 1 = collective stand-in (issued on the communication stream, but see in_strand); 2 =
+                                cross-node Send/Recv stand-in (issued on the layer's cross-node stream if one is set) */
   int n_deps;
   int dep_src[DH_MAX_DEPS];
   int dep_dst[DH_MAX_DEPS];
   int side_ok[DH_MAX_OPS];   /* backward graph: 1 = the operator has no dependents and touches no buffer a later operator
                                 of its strand writes, so a plan may run it beside the strand (dh_plan.bwd_side) */
-  int like_other[DH_MAX_OPS]; /* 1 + id of the operator of the OTHER direction's graph that runs the same kernel on the
-                                same amount of data (a backward all-reduce and a forward one; a weight-gradient GEMM and
-                                the forward GEMM of its shape), 0 = none.  The pair profiler co-runs forward with backward
-                                operators only; the lane model (dh_plan_cost) looks up two operators of one direction
-                                through this. */
+  int like_other[DH_MAX_OPS]; /* 1 + id of the operator of the OTHER direction's graph that is most like it: the same kind of
+                                work on the same amount of data (a backward all-reduce and a forward one; a weight-gradient
+                                GEMM and the forward GEMM of its shape), 0 = none.  The pair profiler co-runs forward with
+                                backward operators only; the lane model (dh_plan_cost) looks up two operators of one
+                                direction through this.  Reductions are like each other by the partial buffers they read: with
+                                comm_blocks 0 each also does the norm, its gradient or the add behind it, which differ. */
+  int in_strand[DH_MAX_OPS]; /* collective stand-ins: 0 = goes to the communication stream (if there is one); 1 = stays in its
+                                strand's stream where the strand's next operator of the segment pair needs its result, or
+                                none follows in the pair; 2 = always stays.  dh_si_step and the lane model both follow it. */
 } dh_op_graph;
 
-/* Fills the forward (direction 0) or backward (direction 1) operator graph of the layer. */
+/* Fills the forward (direction 0) or backward (direction 1) operator graph of the layer.  in_strand follows from the
+ * layer's shape and its present comm_blocks (dh_layer_set_comm_blocks): take the graphs anew after changing those. */
 int dh_layer_op_graph(const dh_layer* layer, int direction, dh_op_graph* out);
 /* Static name of an operator of an architecture ("F_QKV", "B_ATTN", ...), NULL if out of range. */
 const char* dh_op_name(int arch, int direction, int op);
@@ -292,8 +297,8 @@ int dh_profile_pairs(dh_layer* layer, const dh_fwd_args* alpha, const dh_bwd_arg
                      int reps, dh_overlap_table* out);
 
 /* The solo times alone (Sec. 3.2, the T_i of Eq. 1): every operator launched reps times back to back (after one
- * warm-up launch; two such groups, the shorter counts) on the stream dh_si_step would issue it to, timed with events on
- * that stream.  t_fwd / t_bwd: host
+ * warm-up launch; two such groups, the shorter counts) on its strand's stream, a stand-in on the stream given for it,
+ * timed with events on that stream.  t_fwd / t_bwd: host
  * arrays of DH_MAX_OPS doubles, seconds.  Same requirements and side effects as dh_profile_pairs.  Blocks until done. */
 int dh_profile_solo(dh_layer* layer, const dh_fwd_args* alpha, const dh_bwd_args* beta, void* ws, size_t ws_bytes,
                     void* stream_alpha, void* stream_beta, void* comm_stream, int reps, double* t_fwd, double* t_bwd);
@@ -347,7 +352,8 @@ typedef struct {
 /* Predicted time of a plan under the lane model: the segment pairs are replayed the way dh_si_step issues them -- the
  * two strands, the communication stream(s) and the cross-node stream are lanes that run their operators in issue
  * order; a stand-in on a lane of its own starts behind what its strand has issued and holds up only the operators
- * that consume its result; bwd_side operators run in alpha's lane -- and integrated as a fluid: every active operator
+ * that consume its result (dh_op_graph.in_strand says which stand-ins stay in their strand's lane instead); bwd_side
+ * operators run in alpha's lane -- and integrated as a fluid: every active operator
  * advances at the product of its profiled pairwise rates against the other active operators (operators of one
  * direction through like_other, rate 1 where that is 0).  barrier_cost is added per segment pair.  This is P of Eq. 2
  * for three and more participants (a stand-in beside two compute kernels), which the two-queue dh_segment_cost cannot

@@ -158,15 +158,18 @@ def rates_from_corun(t_a, t_b, end_a, end_b):
 
 
 def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm_f=None, comm_b=None, lanes=(0, 0, 0),
-              side=(), like_f=None, like_b=None):
+              side=(), like_f=None, like_b=None, stay_f=None, stay_b=None):
     """Fluid co-run time of one segment pair on the executor's streams.
     comm_x[op]: 0 compute, 1 collective stand-in, 2 cross-node transfer.  lanes = (comm_alpha, comm_beta, cross):
     comm_alpha 0/1 = alpha's collectives in alpha's stream / on the communication stream; comm_beta 0/1/2 = in beta's
     stream / on the shared communication stream / on beta's own communication stream; cross 1 = cross-node transfers on
     the cross-node stream.  side: backward operators that run beside their strand (in alpha's stream).
-    like_x[op]: id of the like operator in the other direction (or absent)."""
+    like_x[op]: id of the like operator in the other direction (or absent).
+    stay_x[op]: collectives kept in their strand's stream: 2 always, 1 where the strand's next operator of the pair needs
+    the result or none follows (absent or 0: never)."""
     comm_f, comm_b = comm_f or {}, comm_b or {}
     like_f, like_b = like_f or {}, like_b or {}
+    stay_f, stay_b = stay_f or {}, stay_b or {}
     A, B, COMM, COMM_B, CROSS = "alpha", "beta", "comm", "comm_beta", "cross"
 
     def stream_of(direction, kind):
@@ -177,6 +180,9 @@ def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm
         if direction == "f":
             return COMM if lanes[0] else A
         return {0: B, 1: COMM, 2: COMM_B}[lanes[1]]
+
+    def stays(stay, deps, op, rest):
+        return stay.get(op, 0) == 2 or (stay.get(op, 0) == 1 and (not rest or (op, rest[0]) in set(map(tuple, deps))))
 
     # ---- issue: operators alternate between the strands, every stream keeps its issue order
     jobs = []                       # dicts: dir, op, stream, work, after (set of job indices)
@@ -205,7 +211,7 @@ def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm
         if fi < len(seg_f):
             op = seg_f[fi]; fi += 1
             strand_waits_for_inputs("f", op, deps_f, A)
-            st = stream_of("f", comm_f.get(op, 0))
+            st = A if stays(stay_f, deps_f, op, seg_f[fi:]) else stream_of("f", comm_f.get(op, 0))
             if st != A:
                 pending["f"][op] = submit("f", op, st, queue[A][-1:] )
             else:
@@ -216,7 +222,7 @@ def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm
             if op in side:
                 submit("b", op, A, set(queue[B][-1:]) | waits[B])   # behind beta's issued work and what beta waits for
                 continue
-            st = stream_of("b", comm_b.get(op, 0))
+            st = B if stays(stay_b, deps_b, op, seg_b[bi:]) else stream_of("b", comm_b.get(op, 0))
             if st != B:
                 pending["b"][op] = submit("b", op, st, queue[B][-1:])
             else:

@@ -40,6 +40,18 @@ static inline int dh_device_index() {
 static inline size_t dh_elem_size(int dtype) { return dtype == DH_BF16 ? 2 : 4; }
 static inline size_t dh_align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Whether an operator of a strand is issued on another stream than its strand's (given that there is one): a stand-in that
+// dh_op_graph.in_strand does not keep there.  next: the operator the strand issues next in the segment pair, or nullptr.  The
+// executor and the lane model of the plan search both ask here.
+static inline bool dh_leaves_strand(const dh_op_graph& g, int op, const int* next) {
+  if (!g.is_comm[op] || g.in_strand[op] == 2) return false;
+  if (g.in_strand[op] != 1) return true;
+  if (next == nullptr) return false;
+  for (int e = 0; e < g.n_deps; e++)
+    if (g.dep_src[e] == op && g.dep_dst[e] == *next) return false;
+  return true;
+}
+
 // ---- device helpers ----------------------------------------------------------------------------
 // bf16 <-> fp32.  Conversion to bf16 rounds to nearest even.
 __device__ __forceinline__ float to_f32(float v) { return v; }

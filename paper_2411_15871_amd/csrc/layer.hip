@@ -165,7 +165,22 @@ static void build_graphs(dh_layer* L) {
   }
 }
 
-// like_other: pairs (forward op, backward op) that run the same kernel on the same amount of data.
+// Which collective stand-ins of an SI step stay in their strand's stream (dh_op_graph.in_strand).  Sending one to a stream of
+// its own and back takes four event calls (about 17 us of host time, and two waits on the device): a stand-in shorter than
+// that stays.  Its time: bytes moved at what it reaches, the whole chip 5.5 TB/s, a block of a budget 6 GB/s.  One that may
+// use the whole chip also stays where its strand could only wait for it.
+static void place_standins(dh_layer* L) {
+  const double rows = L->c.arch == DH_ARCH_MOE ? L->Tf : L->Ts, R = L->c.n_ranks;
+  const double bytes = (L->c.arch == DH_ARCH_MOE ? 2.0 : R + 1.0) * rows * L->c.hidden * L->es;
+  const double rate = L->c.comm_blocks > 0 ? std::min(5.5e12, 6.0e9 * L->c.comm_blocks) : 5.5e12;
+  for (dh_op_graph* g : {&L->gf, &L->gb})
+    for (int op = 0; op < g->n_ops; op++) {
+      if (g->is_comm[op] != 1 || L->c.comm_blocks < 0) g->in_strand[op] = 0;  // -1: timing the schedule, events and all
+      else g->in_strand[op] = bytes / rate <= 10e-6 ? 2 : L->c.comm_blocks == 0 ? 1 : 0;
+    }
+}
+
+// like_other: pairs (forward op, backward op) that do the same kind of work on the same amount of data.
 static void link_like(dh_op_graph& f, dh_op_graph& b, int fop, int bop) {
   if (f.like_other[fop] == 0) f.like_other[fop] = bop + 1;
   if (b.like_other[bop] == 0) b.like_other[bop] = fop + 1;
@@ -349,6 +364,7 @@ extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   L->bwd_bytes = cur;
   build_graphs(L);
   build_likes(L);
+  place_standins(L);
   for (int i = 0; i < DH_EVENT_POOL; i++) L->ev[i] = nullptr;
   L->have_events = false;
   L->ev_next = 0;
@@ -423,6 +439,7 @@ extern "C" int dh_layer_set_comm_blocks(dh_layer* L, int comm_blocks) {
   if (!L) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_comm_blocks: null layer");
   if (comm_blocks < -1 || comm_blocks > 65536) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_comm_blocks: %d outside -1..65536", comm_blocks);
   L->c.comm_blocks = comm_blocks;
+  place_standins(L);
   return DH_OK;
 }
 
@@ -1074,24 +1091,6 @@ static int wait_for_all(const dh_op_graph& g, PendingComm& pd, hipStream_t stran
   return DH_OK;
 }
 
-// Whether a collective stand-in is worth a stream of its own in an SI step.  Sending it there and back takes four event
-// calls (about 17 us of host time, and two waits on the device); a stand-in shorter than that goes into its strand's
-// stream.  Its time: bytes moved at what it reaches, the whole chip 5.5 TB/s, a block of a budget 6 GB/s.  So does one
-// that may use the whole chip and whose strand could only wait for it (`next`, the operator the strand issues next in the segment
-// pair, needs it).
-static bool crosses_streams(const dh_layer* L, const dh_op_graph& g, int op, const int* next) {
-  const int kind = g.is_comm[op];
-  if (kind == 1 && L->c.comm_blocks == 0) {
-    if (next == nullptr) return false;
-    for (int e = 0; e < g.n_deps; e++)
-      if (g.dep_src[e] == op && g.dep_dst[e] == *next) return false;
-  }
-  const double rows = L->c.arch == DH_ARCH_MOE ? L->Tf : L->Ts, R = L->c.n_ranks;
-  const double bytes = (L->c.arch == DH_ARCH_MOE ? 2.0 : R + 1.0) * rows * L->c.hidden * L->es;
-  const double rate = L->c.comm_blocks > 0 ? std::min(5.5e12, 6.0e9 * L->c.comm_blocks) : 5.5e12;
-  return kind == 2 || L->c.comm_blocks < 0 || bytes / rate > 10e-6;
-}
-
 // Stream of a communication operator: cross-node transfers (kind 2) use the layer's cross-node stream if one is set.
 static hipStream_t comm_stream_of(const dh_layer* L, int kind, hipStream_t comm) {
   return kind == 2 && L->cross_stream ? L->cross_stream : comm;
@@ -1133,7 +1132,7 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
       if (fi < p.f_end) {
         const int op = plan->fwd_order[fi++];
         if ((rc = wait_for_inputs(L->gf, pf, op, sa))) return rc;
-        if (L->gf.is_comm[op] && crosses_streams(L, L->gf, op, fi < p.f_end ? &plan->fwd_order[fi] : nullptr)) rc = on_comm_stream(L, sa, comm_stream_of(L, L->gf.is_comm[op], sc), &pf.ev[op], [&](hipStream_t s) { return run_fwd_op(L, op, *alpha, ws_f, s); });
+        if (dh_leaves_strand(L->gf, op, fi < p.f_end ? &plan->fwd_order[fi] : nullptr)) rc = on_comm_stream(L, sa, comm_stream_of(L, L->gf.is_comm[op], sc), &pf.ev[op], [&](hipStream_t s) { return run_fwd_op(L, op, *alpha, ws_f, s); });
         else rc = run_fwd_op(L, op, *alpha, ws_f, sa);
         if (rc) return rc;
       }
@@ -1147,7 +1146,7 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
           if ((rc = run_bwd_op(LB, op, *beta, ws_b, sa, ws_f + L->f_gemm))) return rc;
           continue;
         }
-        if (L->gb.is_comm[op] && crosses_streams(L, L->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, L->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
+        if (dh_leaves_strand(L->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, L->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
         else rc = run_bwd_op(LB, op, *beta, ws_b, sb);
         if (rc) return rc;
       }
@@ -1277,7 +1276,7 @@ static int launch_op(dh_layer* L, const TimedOp& o, const dh_fwd_args& a, const 
   return o.dir == 0 ? run_fwd_op(L, o.op, a, ws_f, s) : run_bwd_op(L, o.op, b, ws_b, s);
 }
 
-// Solo time of every operator (the first half of the pair profiler), each on the stream dh_si_step would issue it to.
+// Solo time of every operator (the first half of the pair profiler), each on its strand's stream or the stand-ins' stream.
 extern "C" int dh_profile_solo(dh_layer* L, const dh_fwd_args* alpha, const dh_bwd_args* beta, void* ws, size_t ws_bytes,
                                void* stream_alpha, void* stream_beta, void* comm_stream, int reps, double* t_fwd, double* t_bwd) {
   int rc = check_fwd_args(L, alpha);

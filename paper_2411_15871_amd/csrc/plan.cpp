@@ -236,11 +236,11 @@ extern "C" int dh_plan_search(const dh_op_graph* fwd, const dh_op_graph* bwd, co
 // stream.  A stand-in issued on another lane than its strand's starts when everything its strand has issued so far
 // is done, and the strand waits for it only before an operator that consumes its result (operator graph) -- so weight
 // gradients overlap their own strand's collective (Sec. 4.2: the movable, "self-overlapping" operators), and an
-// operator flagged bwd_side runs on alpha's lane once beta's operators before it are done.  The model replays exactly
-// that issue logic as a dependency graph over lanes (a lane runs its operators in issue order) and integrates it as a
+// operator flagged bwd_side runs on alpha's lane once beta's operators before it are done; which stand-ins stay in their
+// strand's lane is the executor's own rule (dh_leaves_strand).  The model replays exactly that issue logic as a dependency graph over lanes (a lane runs its operators in issue order) and integrates it as a
 // fluid: an active operator advances at the product of the pairwise rates of the table against every other active
 // operator.  Pairs of one direction are not in the table (the profiler co-runs forward with backward operators); they
-// are looked up through the operator of the other direction that runs the same kernel on the same data size
+// are looked up through the operator of the other direction that does the same kind of work on the same data size
 // (dh_op_graph.like_other), and count as undisturbed (rate 1) when there is none.
 namespace {
 enum { LANE_A = 0, LANE_B = 1, LANE_COMM = 2, LANE_COMM_B = 3, LANE_CROSS = 4, N_LANES = 5 };
@@ -303,7 +303,7 @@ struct LaneSim {
       if (fi < nf) {
         const int op = fo[fi++];
         wait_inputs(gf, pend_f, op, LANE_A);
-        const int lane = gf.is_comm[op] ? comm_lane(0, gf.is_comm[op]) : LANE_A;
+        const int lane = dh_leaves_strand(gf, op, fi < nf ? &fo[fi] : nullptr) ? comm_lane(0, gf.is_comm[op]) : LANE_A;
         if (lane != LANE_A) pend_f[op] = add(0, op, lane, last_of(LANE_A));
         else add(0, op, LANE_A, -1);
       }
@@ -317,7 +317,7 @@ struct LaneSim {
           for (int d : deps) nodes[n].dep[nodes[n].ndep++] = d;
           continue;
         }
-        const int lane = gb.is_comm[op] ? comm_lane(1, gb.is_comm[op]) : LANE_B;
+        const int lane = dh_leaves_strand(gb, op, bj < nb ? &bo[bj] : nullptr) ? comm_lane(1, gb.is_comm[op]) : LANE_B;
         if (lane != LANE_B) pend_b[op] = add(1, op, lane, last_of(LANE_B));
         else add(1, op, LANE_B, -1);
       }

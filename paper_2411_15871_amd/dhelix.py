@@ -74,7 +74,7 @@ class dh_bwd_args(C.Structure):
 class dh_op_graph(C.Structure):
     _fields_ = [("n_ops", C.c_int), ("is_comm", C.c_int * DH_MAX_OPS), ("n_deps", C.c_int),
                 ("dep_src", C.c_int * DH_MAX_DEPS), ("dep_dst", C.c_int * DH_MAX_DEPS), ("side_ok", C.c_int * DH_MAX_OPS),
-                ("like_other", C.c_int * DH_MAX_OPS)]
+                ("like_other", C.c_int * DH_MAX_OPS), ("in_strand", C.c_int * DH_MAX_OPS)]
 
 
 class dh_lanes(C.Structure):
@@ -331,8 +331,8 @@ def make_table(t_fwd, t_bwd, rate_fwd, rate_bwd):
     return t
 
 
-def make_graph(n_ops, deps, comm=(), side_ok=(), like=None):
-    """like: {op: id of the like operator of the other direction's graph}."""
+def make_graph(n_ops, deps, comm=(), side_ok=(), like=None, in_strand=None):
+    """like: {op: id of the like operator of the other direction's graph}; in_strand: {op: 1 or 2} (see dh_op_graph)."""
     g = dh_op_graph()
     g.n_ops = n_ops
     g.n_deps = len(deps)
@@ -344,6 +344,8 @@ def make_graph(n_ops, deps, comm=(), side_ok=(), like=None):
         g.side_ok[c] = 1
     for op, other in (like or {}).items():
         g.like_other[op] = other + 1
+    for op, v in (in_strand or {}).items():
+        g.in_strand[op] = v
     return g
 
 

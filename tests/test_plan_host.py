@@ -179,6 +179,55 @@ def test_plan_cost_matches_oracle_lane_model():
         dh.dh_plan_cost(gf, gb, tab, plan, dh.lanes(3, 0, 0), 0.0)
 
 
+def test_plan_cost_keeps_standins_in_their_strand_as_the_executor_does():
+    """dh_op_graph.in_strand: a collective that stays in its strand's stream always, or only where the strand's next operator of
+    the pair waits for it anyway (or the pair ends), against the oracle's lane model."""
+    rng = random.Random(3)
+    for trial in range(40):
+        nf, nb, deps_f, deps_b, t_f, t_b, rf, rb, _, _, okw = rand_case()
+        stay_f, stay_b = {1: rng.randrange(3)}, {1: rng.randrange(3)}
+        gf = dh.make_graph(nf, deps_f, comm={1: 1}, like=okw["like_f"], in_strand=stay_f)
+        gb = dh.make_graph(nb, deps_b, comm={1: 1}, side_ok=(4, 5), like=okw["like_b"], in_strand=stay_b)
+        tab = dh.make_table(t_f, t_b, rf, rb)
+        fo, bo = rand_order(nf, deps_f), rand_order(nb, deps_b)
+        cut_f, cut_b = rng.randrange(nf + 1), rng.randrange(nb + 1)
+        pairs = [q for q in [(0, cut_f, 0, cut_b), (cut_f, nf, cut_b, nb)] if q[0] != q[1] or q[2] != q[3]]
+        side = tuple(op for op in (4, 5) if rng.random() < 0.3)
+        plan = dh.make_plan(fo, bo, pairs, side)
+        for lanes in [(0, 0, 0), (1, 1, 0), (1, 2, 0), (0, 2, 0)]:
+            got = dh.dh_plan_cost(gf, gb, tab, plan, dh.lanes(*lanes), 0.01)
+            ref = P.plan_cost_lanes(pairs, fo, bo, t_f, t_b, rf, rb, 0.01, lanes=lanes, side=side, stay_f=stay_f, stay_b=stay_b, **okw)
+            assert abs(got - ref) <= 1e-11 * max(1.0, ref), (lanes, fo, bo, pairs, side, stay_f, stay_b)
+    # kept in the strand, a collective holds up the movable operator issued behind it; on its own stream it does not
+    deps_b, ones = [(0, 1), (1, 2)], [[1.0] * 4]
+    plan = dh.make_plan([0], [0, 1, 3, 2], [(0, 1, 0, 4)])
+    tab = dh.make_table([0.1], [1.0] * 4, ones, ones)
+    cost = lambda v: dh.dh_plan_cost(dh.make_graph(1, []), dh.make_graph(4, deps_b, comm=(1,), in_strand={1: v}), tab, plan, dh.lanes(0, 2, 0), 0.0)
+    assert abs(cost(0) - 3.0) <= 1e-12 and abs(cost(1) - 3.0) <= 1e-12 and abs(cost(2) - 4.0) <= 1e-12
+
+
+@pytest.mark.parametrize("name", ["llama", "gpt", "moe", "llama_cp"])
+def test_in_strand_follows_the_size_and_the_block_budget(name):
+    """A stand-in of the whole chip stays where its strand can only wait for it (1), a short one always (2), one on a block
+    budget leaves unless it is short; cross-node transfers never stay; the timing mode without communication keeps nothing."""
+    cfg = dict(dtype=1, batch=1, hidden=4096, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=64, eps=1e-5, rope_base=1e4)
+    cfg.update(ARCH_CFGS[name])
+    if name == "llama_cp":
+        cfg["cp_rank"] = 0  # any chunk length
+    for seq, blocks, want in ((8192, 0, 1), (128, 0, 2), (8192, 64, 0), (8, 64, 2), (8192, -1, 0)):
+        L = dh.dh_layer_create(seq=seq, **cfg)
+        try:
+            dh.dh_layer_set_comm_blocks(L, blocks)
+            for g in (dh.dh_layer_op_graph(L, 0), dh.dh_layer_op_graph(L, 1)):
+                for op in range(g.n_ops):
+                    if g.is_comm[op] != 1:
+                        assert g.in_strand[op] == 0
+                    else:
+                        assert g.in_strand[op] == want, (seq, blocks, op)
+        finally:
+            dh.dh_layer_destroy(L)
+
+
 def test_plan_search_lanes_matches_brute_force_and_moves_the_weight_gradient():
     # brute force over all orders, side subsets and barrier placements with the oracle's lane model
     for trial in range(2):
