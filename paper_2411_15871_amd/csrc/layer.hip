@@ -165,19 +165,41 @@ static void build_graphs(dh_layer* L) {
   }
 }
 
+// Rows of H elements that collective stand-in `op` reads and writes: the payload's buffers (an all-gather reads and writes all
+// n_ranks shards, a reduction reads n_ranks partial buffers and writes one, an exchange reads and writes every row), and where it
+// does its neighbour's work too, that operator's rows instead of the ones it saves.
+static double standin_rows(const dh_layer* L, int dir, int op) {
+  const double R = L->c.n_ranks;
+  const bool whole_chip = L->c.comm_blocks == 0;
+  switch (L->c.arch) {
+    case DH_ARCH_GPT: {
+      if (dir == 0 ? (op == DH_GF_AG1 || op == DH_GF_AG2) : (op == DH_GB_AG3 || op == DH_GB_AG4)) return 2.0 * R * L->Ts;
+      if (!whole_chip) return (R + 1.0) * L->Ts;
+      return (R + (dir == 0 && op == DH_GF_RS2 ? 2.0 : 3.0)) * L->Ts;  // add: one row in, one out; norms: one or two in, two or one out
+    }
+    case DH_ARCH_MOE:
+      return dir == 1 && op == DH_MB_A2A_COMBINE && whole_chip ? 1.5 * L->Tf : 2.0 * L->Tf;  // sums a token's two rows
+    default: {
+      const bool add = dir == 0 && op == (L->c.arch == DH_ARCH_LLAMA_CP ? (int)DH_CF_AR2 : (int)DH_F_AR2);
+      return (R + (!whole_chip ? 1.0 : add ? 2.0 : 3.0)) * L->Ts;
+    }
+  }
+}
+
 // Which collective stand-ins of an SI step stay in their strand's stream (dh_op_graph.in_strand).  Sending one to a stream of
 // its own and back takes four event calls (about 17 us of host time, and two waits on the device): a stand-in shorter than
 // that stays.  Its time: bytes moved at what it reaches, the whole chip 5.5 TB/s, a block of a budget 6 GB/s.  One that may
 // use the whole chip also stays where its strand could only wait for it.
 static void place_standins(dh_layer* L) {
-  const double rows = L->c.arch == DH_ARCH_MOE ? L->Tf : L->Ts, R = L->c.n_ranks;
-  const double bytes = (L->c.arch == DH_ARCH_MOE ? 2.0 : R + 1.0) * rows * L->c.hidden * L->es;
   const double rate = L->c.comm_blocks > 0 ? std::min(5.5e12, 6.0e9 * L->c.comm_blocks) : 5.5e12;
-  for (dh_op_graph* g : {&L->gf, &L->gb})
-    for (int op = 0; op < g->n_ops; op++) {
-      if (g->is_comm[op] != 1 || L->c.comm_blocks < 0) g->in_strand[op] = 0;  // -1: timing the schedule, events and all
-      else g->in_strand[op] = bytes / rate <= 10e-6 ? 2 : L->c.comm_blocks == 0 ? 1 : 0;
+  for (int dir = 0; dir < 2; dir++) {
+    dh_op_graph& g = dir == 0 ? L->gf : L->gb;
+    for (int op = 0; op < g.n_ops; op++) {
+      if (g.is_comm[op] != 1 || L->c.comm_blocks < 0) g.in_strand[op] = 0;  // -1: timing the schedule, events and all
+      else if (standin_rows(L, dir, op) * L->c.hidden * L->es / rate <= 10e-6) g.in_strand[op] = 2;
+      else g.in_strand[op] = L->c.comm_blocks == 0 ? 1 : 0;
     }
+  }
 }
 
 // like_other: pairs (forward op, backward op) that do the same kind of work on the same amount of data.

@@ -228,6 +228,37 @@ def test_in_strand_follows_the_size_and_the_block_budget(name):
             dh.dh_layer_destroy(L)
 
 
+def test_in_strand_counts_what_a_standin_moves():
+    """The bytes a stand-in is judged by: an all-gather moves 2 R shards, a reduction R + 1 row buffers on a block budget and two
+    rows more together with a norm, one more with an add; an exchange all its rows twice, summing a token's rows three quarters of that."""
+    R, H, limit = 4, 4096, 10e-6
+    def first_leaving(arch, direction, name, blocks, rate):
+        """Rows of the layer's input at which the stand-in first takes longer than the limit."""
+        lo, hi = 8, 1 << 16   # multiples of 8
+        while hi - lo > 8:
+            mid = (lo + hi) // 16 * 8
+            cfg = dict(arch=arch, dtype=dh.DH_BF16, batch=1, seq=mid, hidden=H, n_q_heads=2, n_kv_heads=2, head_dim=64, ffn=64, eps=1e-5,
+                       rope_base=1e4, n_ranks=R if arch != dh.DH_ARCH_MOE else 1)
+            if arch == dh.DH_ARCH_MOE:
+                cfg.update(n_experts=4, n_local_experts=2)
+            L = dh.dh_layer_create(**cfg)
+            dh.dh_layer_set_comm_blocks(L, blocks)
+            op = dh.op_names(arch, direction).index(name)
+            lo, hi = (mid, hi) if dh.dh_layer_op_graph(L, direction).in_strand[op] == 2 else (lo, mid)
+            dh.dh_layer_destroy(L)
+        return lo
+    for blocks, rate in ((0, 5.5e12), (256, 256 * 6e9)):
+        fused = blocks == 0
+        cases = [(dh.DH_ARCH_GPT, 0, "F_AG1", 2 * R / R), (dh.DH_ARCH_GPT, 1, "B_AG4", 2 * R / R),          # per token: Ts = T / R rows
+                 (dh.DH_ARCH_GPT, 0, "F_RS1", (R + (3 if fused else 1)) / R), (dh.DH_ARCH_GPT, 0, "F_RS2", (R + (2 if fused else 1)) / R),
+                 (dh.DH_ARCH_GPT, 1, "B_RS4", (R + (3 if fused else 1)) / R), (dh.DH_ARCH_LLAMA, 0, "F_AR2", R + (2 if fused else 1)),
+                 (dh.DH_ARCH_LLAMA, 1, "B_AR3", R + (3 if fused else 1)), (dh.DH_ARCH_MOE, 0, "F_A2A_COMBINE", 4.0),
+                 (dh.DH_ARCH_MOE, 1, "B_A2A_COMBINE", 3.0 if fused else 4.0)]
+        for arch, direction, name, rows_per_token in cases:
+            expect = limit * rate / (rows_per_token * H * 2)
+            assert abs(first_leaving(arch, direction, name, blocks, rate) - expect) <= 16, (blocks, name)
+
+
 def test_plan_search_lanes_matches_brute_force_and_moves_the_weight_gradient():
     # brute force over all orders, side subsets and barrier placements with the oracle's lane model
     for trial in range(2):
