@@ -439,8 +439,9 @@ int dh_layer_set_comm_blocks(dh_layer* layer, int comm_blocks);
 int dh_layer_set_cross_stream(dh_layer* layer, void* stream_cross);
 
 /* One SI step across two layers of identical shape: forward of strand alpha through layer_alpha while
- * strand beta runs backward through layer_beta (each layer has its own weights and gradient buffers).
- * dh_si_step is the case layer_alpha == layer_beta. */
+ * strand beta runs backward through layer_beta (each layer has its own weights and gradient buffers, and its own
+ * comm_blocks: a strand's collectives run, and are placed, by the layer they belong to).  Streams set on a layer are
+ * taken from layer_alpha.  dh_si_step is the case layer_alpha == layer_beta. */
 int dh_si_step_layers(dh_layer* layer_alpha, dh_layer* layer_beta, const dh_fwd_args* alpha,
                       const dh_bwd_args* beta, const dh_plan* plan, void* ws, size_t ws_bytes,
                       void* stream_alpha, void* stream_beta, void* stream_comm);

@@ -1130,7 +1130,8 @@ static int check_si_args(dh_layer* L, const dh_fwd_args* alpha, const dh_bwd_arg
 
 // Enqueues one SI step.  Stream beta (and the communication stream, through the events around each stand-in)
 // forks from stream alpha at the start and is joined back into it at the end, so the whole step is one
-// fork/join region of stream alpha -- which is also what stream capture requires.
+// fork/join region of stream alpha -- which is also what stream capture requires.  The two layers have the same operators and
+// dependencies; where a backward collective goes follows from beta's layer, which runs it and may have another block budget.
 static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const dh_bwd_args* beta, const dh_plan* plan, void* ws,
                       hipStream_t sa, hipStream_t sb, hipStream_t sc) {  // L: alpha's layer (also the event pool), LB: beta's
   int rc;
@@ -1160,7 +1161,7 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
       }
       if (bj < p.b_end) {
         const int op = plan->bwd_order[bj++];
-        if ((rc = wait_for_inputs(L->gb, pb, op, sb))) return rc;
+        if ((rc = wait_for_inputs(LB->gb, pb, op, sb))) return rc;
         if (two && plan->bwd_side[op]) {  // beside the strand: after what the strand has issued so far, on the other stream
           hipEvent_t e = next_event(L);
           DH_HIP(hipEventRecord(e, sb));
@@ -1168,13 +1169,13 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
           if ((rc = run_bwd_op(LB, op, *beta, ws_b, sa, ws_f + L->f_gemm))) return rc;
           continue;
         }
-        if (dh_leaves_strand(L->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, L->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
+        if (dh_leaves_strand(LB->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, LB->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
         else rc = run_bwd_op(LB, op, *beta, ws_b, sb);
         if (rc) return rc;
       }
     }
     // a segment pair ends with all of its transfers done
-    if ((rc = wait_for_all(L->gf, pf, sa)) || (rc = wait_for_all(L->gb, pb, sb))) return rc;
+    if ((rc = wait_for_all(L->gf, pf, sa)) || (rc = wait_for_all(LB->gb, pb, sb))) return rc;
     if (two) {  // cross-strand barrier on the device; after the last pair beta only joins alpha
       hipEvent_t ea = next_event(L), eb = next_event(L);
       const bool last = k + 1 == plan->n_pairs;

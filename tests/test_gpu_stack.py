@@ -82,3 +82,38 @@ def test_stack_phases_match_oracle(bf16, n_layers, n_mb):
                 assert rel(H.to_np(g[l][k]), v) <= tol, (l, k)
     finally:
         dh.dh_stack_destroy(stack)
+
+
+@pytest.mark.parametrize("blocks_alpha,blocks_beta", [(0, 0), (0, 64), (64, 0), (64, 64)])
+def test_two_layers_place_their_own_collectives(blocks_alpha, blocks_beta):
+    """dh_si_step_layers with unlike block budgets: results as from the two layers apart, bit for bit, and each strand's
+    collectives on its communication stream exactly if its own layer's budget sends them there (a whole-chip reduction that
+    its strand waits for stays).  Alpha's stream is kept busy first, so that a stream that got work still has it."""
+    from paper_2411_15871_amd import dhelix as dh
+    cfg = dict(batch=1, seq=1024, hidden=1024, nq=2, nkv=1, d=128, ffn=256, n_ranks=4, bf16=True)
+    ra, rb = H.LayerRun(dict(cfg, comm_blocks=blocks_alpha)), H.LayerRun(dict(cfg, comm_blocks=blocks_beta))
+    try:
+        alpha, beta = ra.strand(0), rb.strand(1)
+        sa, sb, sc, scb = (torch.cuda.Stream() for _ in range(4))
+        dh.dh_layer_set_beta_comm_stream(ra.layer, scb)
+        rb.fwd(beta)
+        ra.fwd(alpha)
+        rb.bwd(beta)
+        torch.cuda.synchronize()
+        ref = [alpha.out.clone(), beta.dx.clone()] + [v.clone() for v in rb.g.values()]
+        alpha.out.zero_(); beta.dx.zero_(); rb.zero_grads()
+        gf, gb = dh.dh_layer_op_graph(ra.layer, 0), dh.dh_layer_op_graph(rb.layer, 1)
+        plan = dh.make_plan(list(range(gf.n_ops)), list(range(gb.n_ops)), [(0, gf.n_ops, 0, gb.n_ops)])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(sa):
+            torch.cuda._sleep(50_000_000)
+        dh.dh_si_step_layers(ra.layer, rb.layer, alpha.fwd_args, beta.bwd_args, plan, ra.ws, ra.ws_bytes, sa, sb, sc)
+        busy = (not sc.query(), not scb.query())
+        assert not sa.query()
+        torch.cuda.synchronize()
+        assert busy == (blocks_alpha > 0, blocks_beta > 0)
+        for got, want in zip([alpha.out, beta.dx] + list(rb.g.values()), ref):
+            assert torch.equal(got, want)
+    finally:
+        ra.close()
+        rb.close()
