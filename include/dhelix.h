@@ -429,7 +429,8 @@ int dh_layer_set_beta_comm_stream(dh_layer* layer, void* stream_comm_beta);
 
 /* Thread blocks of the layer's collective stand-ins from now on (the layer configuration's comm_blocks): 0 = cover the
  * payload, n > 0 = n blocks (a link-like rate), -1 = the stand-ins launch nothing (their events and stream
- * dependencies stay): the step then computes nothing meaningful and serves only to time the schedule without its
+ * dependencies stay as the value before had them, dh_op_graph.in_strand included; the operators beside them do their own
+ * work): the step then computes nothing meaningful and serves only to time the schedule without its
  * communication, T_SI,no-comm of the hidden-communication measure.  Host only. */
 int dh_layer_set_comm_blocks(dh_layer* layer, int comm_blocks);
 

@@ -195,7 +195,7 @@ static void place_standins(dh_layer* L) {
   for (int dir = 0; dir < 2; dir++) {
     dh_op_graph& g = dir == 0 ? L->gf : L->gb;
     for (int op = 0; op < g.n_ops; op++) {
-      if (g.is_comm[op] != 1 || L->c.comm_blocks < 0) g.in_strand[op] = 0;  // -1: timing the schedule, events and all
+      if (g.is_comm[op] != 1) g.in_strand[op] = 0;
       else if (standin_rows(L, dir, op) * L->c.hidden * L->es / rate <= 10e-6) g.in_strand[op] = 2;
       else g.in_strand[op] = L->c.comm_blocks == 0 ? 1 : 0;
     }
@@ -461,7 +461,7 @@ extern "C" int dh_layer_set_comm_blocks(dh_layer* L, int comm_blocks) {
   if (!L) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_comm_blocks: null layer");
   if (comm_blocks < -1 || comm_blocks > 65536) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_comm_blocks: %d outside -1..65536", comm_blocks);
   L->c.comm_blocks = comm_blocks;
-  place_standins(L);
+  if (comm_blocks >= 0) place_standins(L);  // stand-ins that launch nothing keep the place they had, events and all
   return DH_OK;
 }
 

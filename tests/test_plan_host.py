@@ -209,21 +209,19 @@ def test_plan_cost_keeps_standins_in_their_strand_as_the_executor_does():
 @pytest.mark.parametrize("name", ["llama", "gpt", "moe", "llama_cp"])
 def test_in_strand_follows_the_size_and_the_block_budget(name):
     """A stand-in of the whole chip stays where its strand can only wait for it (1), a short one always (2), one on a block
-    budget leaves unless it is short; cross-node transfers never stay; the timing mode without communication keeps nothing."""
+    budget leaves unless it is short; cross-node transfers never stay; stand-ins that launch nothing keep the place they had."""
     cfg = dict(dtype=1, batch=1, hidden=4096, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=64, eps=1e-5, rope_base=1e4)
     cfg.update(ARCH_CFGS[name])
     if name == "llama_cp":
         cfg["cp_rank"] = 0  # any chunk length
-    for seq, blocks, want in ((8192, 0, 1), (128, 0, 2), (8192, 64, 0), (8, 64, 2), (8192, -1, 0)):
+    for seq, blocks, want in ((8192, 0, 1), (128, 0, 2), (8192, 64, 0), (8, 64, 2)):
         L = dh.dh_layer_create(seq=seq, **cfg)
         try:
-            dh.dh_layer_set_comm_blocks(L, blocks)
-            for g in (dh.dh_layer_op_graph(L, 0), dh.dh_layer_op_graph(L, 1)):
-                for op in range(g.n_ops):
-                    if g.is_comm[op] != 1:
-                        assert g.in_strand[op] == 0
-                    else:
-                        assert g.in_strand[op] == want, (seq, blocks, op)
+            for b in (blocks, -1):
+                dh.dh_layer_set_comm_blocks(L, b)
+                for g in (dh.dh_layer_op_graph(L, 0), dh.dh_layer_op_graph(L, 1)):
+                    for op in range(g.n_ops):
+                        assert g.in_strand[op] == (want if g.is_comm[op] == 1 else 0), (seq, blocks, b, op)
         finally:
             dh.dh_layer_destroy(L)
 
