@@ -7,7 +7,7 @@ A step = one dh_si_step over one micro-batch per strand with all inputs resident
 JSON line: model TFLOP/s of the step (2MNK per GEMM, causal attention at half dense, backward =
 2x forward; the step time is the median of per-step event times), SI speedup over sequential
 alpha-then-beta through the same executor, the share of the collective stand-ins' time that is hidden
-(1 - (T_SI - T_SI without communication) / sum of the stand-ins' solo times), the same again with the
+(1 - (T_SI - T_SI without communication) / what the stand-ins take alone), the same again with the
 stand-ins at a link-like rate (`link_rate`), predicted against measured step time, the roofline of
 every operator and of the one with the largest share of the solo time, and the CPU oracle baseline.
 """
@@ -28,6 +28,8 @@ if int(os.environ.get("GPU_MAX_HW_QUEUES", "0") or 0) < 8:
 
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E
+APART_BLOCKS = 2048             # a block budget that covers the payload as "no budget" does, with the stand-ins as operators of
+                                # their own (with no budget they also do the norm, add or permute beside them)
 # kernels behind an operator name (for the roofline's description)
 OP_KERNELS = {"ATTN": "attention kernels and their merge launches", "FC1": "bf16 GEMM kernels", "FC2": "bf16 GEMM kernels",
               "QKV": "bf16 GEMM kernels", "PROJ": "bf16 GEMM kernels"}
@@ -69,12 +71,13 @@ def op_work(cfg, name):
     if op == "ATTN":
         return "mfma", attn * (2.0 if direction == "B" else 1.0)
     row = Ts * Hd * es
-    if op in ("AR1", "AR2", "AR3", "AR4"):
-        return "hbm", (R + 1.0) * T * Hd * es
-    if op in ("RS1", "RS2", "RS3", "RS4"):
-        return "hbm", (R + 1.0) * row
+    if op in ("AR1", "AR2", "AR3", "AR4", "RS1", "RS2", "RS3", "RS4"):
+        # a whole-chip reduction also does the add (one row in, one out) or the norm (three in and out) behind it
+        return "hbm", (R + (1.0 if cfg["comm_blocks"] else 2.0 if op[2] == "2" else 3.0)) * row
     if op in ("AG1", "AG2", "AG3", "AG4"):
         return "hbm", 2.0 * T * Hd * es
+    if direction == "B" and op == "A2A_COMBINE" and not cfg["comm_blocks"]:
+        return "hbm", 1.5 * Tf * Hd * es               # sums each token's two rows, as the permute behind it would
     if op in ("A2A_DISPATCH", "A2A_COMBINE", "PERMUTE") and arch == "moe":
         return "hbm", 2.0 * Tf * Hd * es
     if op == "NORM1":
@@ -361,8 +364,19 @@ def main():
         t_prof = time.perf_counter() - t0
         t_f = [table.t_fwd[i] for i in range(nf)]
         t_b = [table.t_bwd[j] for j in range(nb)]
+        # what communication takes alone: the collective operators, less the work they do for neighbours that then launch
+        # nothing (those do it themselves in the run without communication)
         t_comm = sum(t_f[i] for i in range(nf) if gf.is_comm[i]) + sum(t_b[j] for j in range(nb) if gb.is_comm[j])
-        log("[%s] profile %.2fs; sum of solo times %.1f us, of which stand-ins %.1f us" % (label, t_prof, (sum(t_f) + sum(t_b)) * 1e6, t_comm * 1e6))
+        t_for_others = 0.0
+        if comm_blocks == 0:
+            dh.dh_layer_set_comm_blocks(run.layer, APART_BLOCKS)
+            apart = dh.dh_profile_solo(run.layer, alpha.fwd_args, beta.bwd_args, run.ws, run.ws_bytes, sa, sb, sc, args.profile_reps)
+            dh.dh_layer_set_comm_blocks(run.layer, comm_blocks)
+            for n, g, merged, own in ((nf, gf, t_f, apart[0]), (nb, gb, t_b, apart[1])):
+                t_for_others += sum(own[k] for k in range(n) if not g.is_comm[k] and merged[k] < 1e-6 <= own[k])
+        t_comm -= t_for_others
+        log("[%s] profile %.2fs; sum of solo times %.1f us; the stand-ins take %.1f us of it, and %.1f us for operators beside them" %
+            (label, t_prof, (sum(t_f) + sum(t_b)) * 1e6, t_comm * 1e6, t_for_others * 1e6))
         log("[%s] fwd solo us:" % label, {fnames[i]: round(t_f[i] * 1e6, 1) for i in range(nf)})
         log("[%s] bwd solo us:" % label, {bnames[j]: round(t_b[j] * 1e6, 1) for j in range(nb)})
         if args.pair_table:
@@ -512,7 +526,7 @@ def main():
             if w is None:
                 continue
             kind, amount = w
-            if ts[k] < 1e-6:   # launches nothing: SwiGLU merged into the neighbouring GEMM's epilogue
+            if ts[k] < 1e-6:   # launches nothing: done by a neighbour's launch (GEMM epilogue, reduction, exchange)
                 fused.append(name)
                 continue
             peak = BF16_MFMA_PEAK_TFLOPS if kind == "mfma" else HBM_PEAK_GBS
