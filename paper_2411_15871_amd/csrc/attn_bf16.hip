@@ -40,6 +40,10 @@
 // Tile slots of the dQ kernel in a launch of its own: two at D = 128, so that two of its blocks fit a compute unit (64 KiB each,
 // 256 registers a lane).  The arithmetic of one block's waves then runs beside the products of the other's: 32 heads x 4096
 // tokens 250 -> 205 us, 4 heads x 4096 queries over 12288 keys 167 -> 136 us.  (Two blocks fit anyway at D = 64.)
+// The 256 registers are eight too few: they go to scratch (36 bytes a lane), five of them around the whole tile loop, the others read
+// again on diagonal tiles and for the transfers of a ragged tile only.
+// Where rows are cut into chunks, two resident blocks also mean finer chunks (pick_chunk): the float32 partial rows
+// then add up over other ranges of keys than with one block a unit, and some results round to the other bf16 neighbour.
 __host__ __device__ constexpr int dq_ring(int d) { return d == 128 ? 2 : AB_RING; }
 #define AB_CH 16   // backward: a block walks at most g.ch 64-token tiles, this many by default (longer causal rows are split
                    // into chunks whose float32 partial results a second kernel adds in chunk order)

@@ -443,11 +443,13 @@ __device__ __forceinline__ bool g_begin(GemmArgs& g, const GemmAr& ar, GemmTile&
 #define G_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
 
 // ------------------------------------------------------------------------------------ 256x256 tiles
-// Bound: the matrix cores under the chip's power limit.  At 8192^3 the clock settles where power allows (1.6-2.0 GHz), so
+// Bound: the matrix cores under the chip's power limit.  At 8192^3 they are 81 % busy (A transposed with float32 accumulation:
+// 71 %) at the clock that power allows, 1.4 to 1.9 GHz, so
 // energy per product counts as much as idle cycles: the 16x16x32 instruction (half the accumulator traffic of
 // 32x32x16 per product), 128x128 wave tiles (a third fewer LDS reads than 128x64) and whole-line transfers
 // each raised the clock at the same utilisation.  Measured against an 8-wave kernel with 128x64 wave tiles, 32x32x16
-// instructions and K tiles of 32 (same box): 8192^3 832 -> 723 us (1520 TFLOP/s), B transposed 880 -> 727, A transposed
+// instructions and K tiles of 32 (same box, N(0,1) operands, a steady sequence; the first tens of launches after idling take
+// 10-15 % longer, operands of zeros 12 % less): 8192^3 832 -> 723 us (1520 TFLOP/s), B transposed 880 -> 727, A transposed
 // with float32 accumulation 889 -> 785; 4096x3584x4096 100 -> 86 us; 4096x4096x1792 53 -> 46 us.  With 32x32x16
 // instructions in the same schedule: 766 us at 8192^3.
 // The large-tile kernel: four waves, one per SIMD, each owning a 128x128 part of C (256 accumulator registers in AGPRs).
@@ -815,15 +817,16 @@ static const TileCost kTiles[] = {{0, 256, 256, 1250, 1500}, {2, 256, 128, 780, 
 
 // K ranges, tile shape, split-K.
 //
-// The ranges of K that are summed apart (and then added in order) depend on the shape alone, so that a product has the
-// same bits whatever tile it is computed with: a product whose tiles (256x256 from 128 of them on, else 256x128 if these
+// The ranges of K that are summed apart (and then added in order) depend on the shape alone (but for the tail's, below), so
+// that a product has the same bits whatever tile it is computed with: a product whose tiles (256x256 from 128 of them on, else 256x128 if these
 // make one nearly full round, else 128x128) leave a quarter of the units idle has its K cut into as many ranges as
 // fill them, of at least 512; with more than one round of 256x256 tiles and a last round at most half full, the tiles of
-// that round have theirs cut (the tail, issued apart: it takes 1/splits of a round and a small ordered sum).
+// that round have theirs cut (the tail, issued apart: it takes 1/splits of a round and a small ordered sum; into fewer ranges,
+// or none, where the caller's workspace does not hold them all, so that its bits depend on the workspace too).
 //
 // The tile shape is the one with the least rounds * (stages * stage + fill + store): large tiles cost least per product, small ones
-// leave fewer units idle.  The store goes at a unit's share of the memory's rate, 20 bytes a ns.  Ranges go to blocks of their own and through the workspace (splitk_reduce_kernel), or, with 64x64
-// tiles, are summed one after the other in the block (no workspace, no second launch), whichever is expected sooner.
+// leave fewer units idle.  The store goes at a unit's share of the memory's rate, 20 bytes a ns.  Ranges go to blocks of their
+// own and through the workspace (splitk_reduce_kernel), or, with 64x64 tiles, are summed one after the other in the block (no workspace, no second launch), whichever is expected sooner.
 //
 // groups > 0: a grouped launch, `groups` products of this (average) size.  Its K is never cut (a group's extents are known on
 // the device alone), so there are no ranges, and every tile shape is considered over the tiles of all groups.
