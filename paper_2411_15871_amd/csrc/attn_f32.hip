@@ -12,8 +12,11 @@
 // into fragments.  Score tiles are formed transposed where that keeps a row's statistics in its lane, and a tile of
 // probabilities feeds the next product from the registers it was formed in: the instruction's k index of lane group g and
 // step e may be any row as long as both operands agree, and row 4g + e is the one the lane already holds.
-// 128 tokens, 4 heads of 64: forward 26 -> 7 us, backward 62 -> 19 us against one wave per row with dot products.
+// 128 tokens, 4 heads of 64: forward 26 -> 7 us, backward 62 -> 19 us against one wave per row with dot products.  Looking for
+// infinities and NaNs in the tiles that have masked entries costs nothing there (1024 tokens, 4 heads of 64: backward 172.8 ->
+// 173.6 us), 2-4 % with heads of 128 and, at 300 tokens, 11 % with heads of 256, whose elements are fetched twice for it.
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
 
 // Waves of a block: eight where the fragments of a 64-wide head leave room for two waves per SIMD, else four.
@@ -76,18 +79,21 @@ struct ColFrag {
 #pragma unroll
       for (int c = 0; c < DT; c++) acc[c] = A32_MFMA(elem(c, e), p[e], acc[c]);
   }
-  // The same for a tile in which some rows may not count for some columns (partial; bit e of seen: row 4g+e counts for column
-  // l16; p is zero where it does not).  The instruction multiplies those rows too, and zero times an infinity or a NaN
-  // is a NaN: a partial tile whose elements are not all finite is summed over the rows that count alone.
-  __device__ __forceinline__ void accumulate_seen(f32x4 (&acc)[DT], const f32x4 p, bool partial, int seen) const {
-    unsigned top = 0;
-    if (partial) {
+  // Largest magnitude among the elements this lane holds, as an integer that orders infinities and NaNs last.
+  __device__ __forceinline__ unsigned largest() const {
+    unsigned t = 0;
 #pragma unroll
-      for (int e = 0; e < 4; e++)
+    for (int e = 0; e < 4; e++)
 #pragma unroll
-        for (int c = 0; c < DT; c++) top = max(top, __float_as_uint(elem(c, e)) & 0x7fffffffu);
-    }
-    if (__all(top < 0x7f800000u)) {
+      for (int c = 0; c < DT; c++) t = max(t, __float_as_uint(elem(c, e)) & 0x7fffffffu);
+    return t;
+  }
+  // The same sum for a tile in which some rows do not count for some columns (partial; bit e of seen: row 4g+e counts for
+  // column l16; p is zero where it does not).  The instruction multiplies those rows too, and zero times an infinity or a
+  // NaN is a NaN: such a tile is summed over the rows that count alone if its elements are not all finite.
+  template <typename Partial>
+  __device__ __forceinline__ void accumulate_seen(f32x4 (&acc)[DT], const f32x4 p, Partial partial, int seen) const {
+    if (!partial || __all(largest() < 0x7f800000u)) {
       accumulate(acc, p);
       return;
     }
@@ -119,6 +125,16 @@ __device__ __forceinline__ float group_max(float v) {
   return fmaxf(v, __shfl_xor(v, 32, 64));
 }
 
+// Runs a tile's body for a partial tile (true) or a whole one.  Two copies of the body, so that whole tiles carry nothing of the
+// masks; one with a run-time switch where the fragments leave no registers for two (heads above 128).
+template <int DT, typename Fn>
+__device__ __forceinline__ void with_partial(bool partial, Fn body) {
+  partial = __builtin_amdgcn_readfirstlane(partial);
+  if constexpr (DT > 8) body(partial);
+  else if (partial) body(std::true_type{});
+  else body(std::false_type{});
+}
+
 // grid (16-query tiles per sequence, nq, sequences)
 template <int DT>
 __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int seq, int nq, int nkv, int d, const float* __restrict__ qkv,
@@ -146,18 +162,19 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
   f32x4 acc[DT];
 #pragma unroll
   for (int c = 0; c < DT; c++) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int t = wave; t < tiles; t += A32_WAVES) {
-    const int j0 = t * 16;
+  auto tile = [&](auto partial, int j0) {  // partial: some keys of the tile lie behind some of the queries
     RowFrag<DT> k;
     k.load(kbase + (size_t)min(j0 + l16, key_last) * ldkv, true, g, d);
     ColFrag<DT> vc;
     vc.start(vbase, ldkv, j0, key_last, l16, g, d);
     f32x4 s = dot_tile<DT>(k, q);  // rows = keys, column = query
     int seen = 0;
+    if (partial) {
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      if (j0 + 4 * g + e > last) s[e] = -INFINITY;
-      else seen |= 1 << e;
+      for (int e = 0; e < 4; e++) {
+        if (j0 + 4 * g + e > last) s[e] = -INFINITY;
+        else seen |= 1 << e;
+      }
     }
     const float mn = fmaxf(m, group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
     if (__any(mn > m)) {
@@ -171,7 +188,10 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
 #pragma unroll
     for (int e = 0; e < 4; e++) p[e] = s[e] == -INFINITY ? 0.f : expf(s[e] - m);
     l += group_sum(p[0] + p[1] + p[2] + p[3]);
-    vc.accumulate_seen(acc, p, j0 + 15 > q_off + i0, seen);
+    vc.accumulate_seen(acc, p, partial, seen);
+  };
+  for (int t = wave; t < tiles; t += A32_WAVES) {
+    with_partial<DT>(t * 16 + 15 > q_off + i0, [&](auto partial) { tile(partial, t * 16); });
   }
   if (g == 0) { ms[wave][l16] = m; ls[wave][l16] = l; }
   __syncthreads();
@@ -241,8 +261,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
   f32x4 acc[DT];
 #pragma unroll
   for (int c = 0; c < DT; c++) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int t = wave; t < tiles; t += A32_WAVES) {
-    const int j0 = t * 16;
+  auto tile = [&](auto partial, int j0) {
     const size_t row = (size_t)min(j0 + l16, key_last) * ldkv;
     RowFrag<DT> k, v;
     k.load(kbase + row, true, g, d);
@@ -255,10 +274,14 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
     int seen = 0;
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      ds[e] = j0 + 4 * g + e > last ? 0.f : expf(s[e] - Lq) * (dp[e] - dl);
-      seen |= j0 + 4 * g + e > last ? 0 : 1 << e;
+      const bool counts = !partial || j0 + 4 * g + e <= last;
+      ds[e] = counts ? expf(s[e] - Lq) * (dp[e] - dl) : 0.f;
+      seen |= counts ? 1 << e : 0;
     }
-    kc.accumulate_seen(acc, ds, j0 + 15 > q_off + i0, seen);
+    kc.accumulate_seen(acc, ds, partial, seen);
+  };
+  for (int t = wave; t < tiles; t += A32_WAVES) {
+    with_partial<DT>(t * 16 + 15 > q_off + i0, [&](auto partial) { tile(partial, t * 16); });
   }
   for (int w = 0; w < A32_WAVES; w++) {
     if (wave == w) {
@@ -304,8 +327,7 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
 #pragma unroll
   for (int c = 0; c < DT; c++) dk[c] = dv[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int t_first = max(j0 - q_off, 0) / 16, tiles = (seq + 15) / 16 - t_first;  // query tiles that see any key of this one
-  for (int x = wave; x < grp * tiles; x += A32_WAVES) {
-    const int h = hk * grp + x / tiles, i0 = (t_first + x % tiles) * 16;
+  auto tile = [&](auto partial, int h, int i0) {  // partial: some queries of the tile lie before some of the keys, or past the end
     const size_t tok0 = (size_t)b * seq, row = tok0 + min(i0 + l16, seq - 1);
     const float* qb = qkv + tok0 * ld + (size_t)h * d;
     const float* ob = dout + tok0 * nq * d + (size_t)h * d;
@@ -323,14 +345,17 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
     for (int e = 0; e < 4; e++) {
       const int i = i0 + 4 * g + e;
       const size_t st = (size_t)h * T + tok0 + min(i, seq - 1);
-      const bool counts = i < seq && q_off + i >= jk;
+      const bool counts = !partial || (i < seq && q_off + i >= jk);
       p[e] = counts ? expf(s[e] - lse[st]) : 0.f;
       ds[e] = counts ? p[e] * (dp[e] - delta[st]) : 0.f;
       seen |= counts ? 1 << e : 0;
     }
-    const bool partial = i0 + 16 > seq || q_off + i0 < j0 + 15;
     oc.accumulate_seen(dv, p, partial, seen);
     qc.accumulate_seen(dk, ds, partial, seen);
+  };
+  for (int x = wave; x < grp * tiles; x += A32_WAVES) {
+    const int h = hk * grp + x / tiles, i0 = (t_first + x % tiles) * 16;
+    with_partial<DT>(i0 + 16 > seq || q_off + i0 < j0 + 15, [&](auto partial) { tile(partial, h, i0); });
   }
   for (int w = 0; w < A32_WAVES; w++) {
     if (wave == w) {
