@@ -19,6 +19,10 @@ __global__ void moe_route_kernel(int T, int E, const float* __restrict__ logits,
     if (v > v0) { i1 = i0; v1 = v0; i0 = e; v0 = v; }
     else if (v > v1) { i1 = e; v1 = v; }
   }
+  if (i1 < 0) {  // every other logit is minus infinity or a NaN: the lowest other expert, so that the tables stay in range
+    i1 = i0 == 0 ? 1 : 0;
+    v1 = l[i1];
+  }
   float d = expf(v1 - v0);
   idx[2 * t] = i0;
   idx[2 * t + 1] = i1;

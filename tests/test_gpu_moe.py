@@ -75,6 +75,25 @@ def test_route_exact_indices(dh, T, E, ties):
     assert rel(host(dl), dl_ref) <= 1e-5
 
 
+@pytest.mark.parametrize("E", [2, 8, 64])
+def test_route_without_a_second_finite_logit(dh, E):
+    """Experts masked with minus infinity (and NaN) down to one, or none: two different experts all the same, the lowest other
+    one second, with probability 0 where the first is finite."""
+    T = 4 * E
+    l = np.full((T, E), -np.inf, dtype=np.float32)
+    l[np.arange(E), np.arange(E)] = 1.5                       # rows 0 .. E-1: one expert is left
+    l[E: 2 * E] = np.nan
+    l[E + np.arange(E), np.arange(E)] = 1.5                   # rows E .. 2E-1: the others are NaN
+    l[3 * E:] = np.nan                                        # rows 2E .. 3E-1: all masked; from 3E: all NaN
+    idx, prob = i32(2 * T), torch.zeros(2 * T, dtype=torch.float32, device="cuda")
+    dh.dh_moe_route(T, E, torch.from_numpy(l).cuda(), idx, prob)
+    i, p = idx.cpu().numpy()[: 2 * T].reshape(T, 2), host(prob).reshape(T, 2)
+    assert i.min() >= 0 and i.max() < E and np.all(i[:, 0] != i[:, 1])
+    assert np.array_equal(i[:E, 0], np.arange(E)) and np.array_equal(i[:E, 1], np.where(np.arange(E) == 0, 1, 0))
+    assert np.array_equal(p[:E], np.tile([1.0, 0.0], (E, 1))) and np.all(np.isnan(p[2 * E:]))
+    assert np.array_equal(i[2 * E:], np.tile([0, 1], (2 * E, 1)))
+
+
 @pytest.mark.parametrize("ties", [False, True])
 @pytest.mark.parametrize("T,E,n_local", [(0, 8, 2), (1, 2, 1), (777, 8, 2), (4096, 16, 2), (513, 64, 8), (300, 16, 16)])
 def test_plan_tables_exact(dh, T, E, n_local, ties):
