@@ -11,8 +11,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdhelix.so")
-SOURCES = ["api.cpp", "plan.cpp", "rowops.hip", "standin.hip", "gemm_f32.hip", "gemm_bf16.hip", "attn_f32.hip",
-           "attn_bf16.hip", "moe.hip", "layer.hip", "stack.cpp"]
+SOURCES = ["api.cpp", "plan.cpp", "rowops.hip", "standin.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_bf16_nn_bf16.hip",
+           "gemm_bf16_nn_f32.hip", "gemm_bf16_nt_bf16.hip", "gemm_bf16_nt_f32.hip", "gemm_bf16_tn_bf16.hip", "gemm_bf16_tn_f32.hip",
+           "attn_f32.hip", "attn_bf16.hip", "moe.hip", "layer.hip", "stack.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
          "-Wno-unknown-warning-option", "-Wno-inline-asm"]
@@ -22,7 +23,7 @@ EXTRA_FLAGS = {"attn_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor
 
 
 def _deps_mtime():
-    hdrs = [os.path.join(CSRC, "common.h"), os.path.join(HERE, "..", "include", "dhelix.h")]
+    hdrs = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "gemm_bf16.h"), os.path.join(HERE, "..", "include", "dhelix.h")]
     return max(os.path.getmtime(h) for h in hdrs)
 
 

@@ -15,6 +15,16 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_addr) {
 __device__ __forceinline__ void dma16_base(const void* sbase, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
 }
+// The same in two parts, for several transfers to neighbouring LDS addresses: the LDS address once (dma_lds), then each transfer with a constant byte offset, which the hardware adds to both its addresses.
+// The value is bound to M0, so the compiler keeps it there.
+__device__ __forceinline__ uint32_t dma_lds(uint32_t lds_addr) {
+  uint32_t m;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0" : "={m0}"(m) : "s"(lds_addr));
+  return m;
+}
+__device__ __forceinline__ void dma16_at(uint32_t m, const void* sbase, uint32_t voff, int offset) {
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "i"(offset), "{m0}"(m) : "memory");
+}
 // 4 bytes per lane: a wave fills 256 consecutive bytes of LDS.
 __device__ __forceinline__ void dma4_base(const void* sbase, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
