@@ -13,6 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdhelix.so")
 SOURCES = ["api.cpp", "plan.cpp", "rowops.hip", "standin.hip", "gemm_f32.hip", "gemm_bf16.hip", "gemm_bf16_nn_bf16.hip",
            "gemm_bf16_nn_f32.hip", "gemm_bf16_nt_bf16.hip", "gemm_bf16_nt_f32.hip", "gemm_bf16_tn_bf16.hip", "gemm_bf16_tn_f32.hip",
+           "gemm_bf16_pair_large.hip", "gemm_bf16_pair_mid.hip", "gemm_bf16_pair_small.hip",
            "attn_f32.hip", "attn_bf16.hip", "moe.hip", "layer.hip", "stack.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",

@@ -767,6 +767,18 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_tile_kernel(GemmArgs g, co
   g_tile<BM, BN, S, TA, TB, F32OUT>(g, (int)blockIdx.x - g.ar_blocks, smem_raw);
 }
 
+// A data gradient (A [M,K], B [N,K], bf16 result) and a weight gradient (A [K,M], B [K,N], added to float32) in one launch: the two
+// GEMMs of a linear layer's backward pass read the same dY and do not depend on each other.  The first n_first blocks are
+// the tiles of the one whose blocks take longer.
+template <int BM, int BN, int S, int OCC>
+__global__ __launch_bounds__(256, OCC) void gemm_bf16_pair_kernel(GemmArgs d, GemmArgs w, int n_first, int w_first) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const bool second = (int)blockIdx.x >= n_first;
+  const int bx = second ? (int)blockIdx.x - n_first : (int)blockIdx.x;
+  if (second != (w_first != 0)) g_tile<BM, BN, S, true, false, true>(w, bx, smem_raw);
+  else g_tile<BM, BN, S, false, true, false>(d, bx, smem_raw);
+}
+
 static int allow_lds(const void* kernel, bool* attr_set, int bytes) {
   const int dev = dh_device_index();
   if (!attr_set[dev]) {  // the attribute belongs to the kernel's code object on one device
@@ -827,4 +839,35 @@ int launch_out(const GemmArgs& g, int cfg, int splits, hipStream_t stream, int n
     case 8: return launch_tile<64, 128, 3, 2, TA, TB, F32OUT>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
     default: return launch_tile<128, 128, 2, 2, TA, TB, F32OUT>(g, splits, stream, n_groups, tile_first, n_tiles, ar);
   }
+}
+
+template <int BM, int BN, int S, int OCC>
+static int launch_pair_tile(GemmArgs d, GemmArgs w, bool w_first, hipStream_t stream, int n_groups) {
+  static bool attr_set[DH_MAX_DEVICES] = {};
+  constexpr int ld = g_lds_bytes<BM, BN, S, false, true, false>(), lw = g_lds_bytes<BM, BN, S, true, false, true>(), lds = ld > lw ? ld : lw;
+  const int rc = allow_lds((const void*)gemm_bf16_pair_kernel<BM, BN, S, OCC>, attr_set, lds);
+  if (rc) return rc;
+  int blocks[2];
+  GemmArgs* g[2] = {&d, &w};
+  for (int i = 0; i < 2; i++) {
+    g[i]->tiles_m = (g[i]->M + BM - 1) / BM;
+    g[i]->tiles_n = (g[i]->N + BN - 1) / BN;
+    g[i]->tiles_per_xcd = (g[i]->tiles_m * g[i]->tiles_n + 7) / 8;
+    blocks[i] = g[i]->tiles_per_xcd * 8;
+  }
+  gemm_bf16_pair_kernel<BM, BN, S, OCC><<<dim3(blocks[0] + blocks[1], 1, n_groups), 256, lds, stream>>>(d, w, blocks[w_first ? 1 : 0], w_first ? 1 : 0);
+  DH_LAUNCH_CHECK();
+  return DH_OK;
+}
+// Launches the pair with tile shape `cfg`.  Three sources hold the shapes, so that they compile side by side.
+template <int CFG>
+int launch_pair(const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups) {
+  if constexpr (CFG == 2) return launch_pair_tile<256, 128, 3, 1>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 3) return launch_pair_tile<64, 64, 4, 2>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 4) return launch_pair_tile<128, 128, 4, 1>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 5) return launch_pair_tile<192, 128, 4, 1>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 6) return launch_pair_tile<96, 128, 4, 1>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 7) return launch_pair_tile<96, 128, 2, 2>(d, w, w_first, stream, n_groups);
+  else if constexpr (CFG == 8) return launch_pair_tile<64, 128, 3, 2>(d, w, w_first, stream, n_groups);
+  else return launch_pair_tile<128, 128, 2, 2>(d, w, w_first, stream, n_groups);
 }

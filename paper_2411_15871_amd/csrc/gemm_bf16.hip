@@ -5,6 +5,14 @@ extern template int launch_out<false, true, false>(const GemmArgs&, int, int, hi
 extern template int launch_out<false, true, true>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
 extern template int launch_out<true, false, false>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
 extern template int launch_out<true, false, true>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
+extern template int launch_pair<1>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<2>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<3>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<4>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<5>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<6>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<7>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<8>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
 
 // Adds the split-K partials in split order; writes bf16 or accumulates into float32.
 __global__ void splitk_reduce_kernel(const float* __restrict__ part, int splits, size_t mn, void* __restrict__ C, int epi,
@@ -77,20 +85,22 @@ static int num_cus() {  // of the current device
 // the time is then a unit's per tile).  Fitted to 37 shapes in three layouts (M 200-8192, N 512-8192, K 512-8192) with
 // weights and float32 gradients that come from memory, as they do in a layer (a ring of few stages looks better with operands that stay
 // in the caches: 2056x768x4096 with 64x128 tiles 22 us then, 29 in fact): the shape taken is 1.1 % slower than the best one on
-// average, 13 % at worst (a shape's own time is met within 5-13 % rms).
-struct TileCost { int cfg_one, cfg_many, bm, bn, one, fill_one, many, fill_many; };
-static const TileCost kTiles[] = {{0, 0, 256, 256, 1270, 800, 1337, 3000}, {2, 2, 256, 128, 710, 1900, 760, 2000},
-                                  {5, 5, 192, 128, 500, 2800, 620, 1600}, {4, 1, 128, 128, 464, 1000, 500, 100},
-                                  {6, 7, 96, 128, 410, 1000, 370, 300}, {8, 8, 64, 128, 400, 400, 295, 300},
-                                  {3, 3, 64, 64, 235, 1100, 225, 150}};
+// average, 13 % at worst (a shape's own time is met within 5-13 % rms).  alone: how much longer a block takes by itself
+// than `many` says where that is for two resident ones, with operands just written (a weight gradient's) and with weights from memory.
+struct TileCost { int cfg_one, cfg_many, bm, bn, one, fill_one, many, fill_many; double alone, alone_cold; };
+static const TileCost kTiles[] = {{0, 0, 256, 256, 1270, 800, 1337, 3000, 0, 0}, {2, 2, 256, 128, 710, 1900, 760, 2000, 0, 0},
+                                  {5, 5, 192, 128, 500, 2800, 620, 1600, 0, 0}, {4, 1, 128, 128, 464, 1000, 500, 100, 1.2, 1.7},
+                                  {6, 7, 96, 128, 410, 1000, 370, 300, 1.5, 1.9}, {8, 8, 64, 128, 400, 400, 295, 300, 1.15, 1.4},
+                                  {3, 3, 64, 64, 235, 1100, 225, 150, 0.9, 1.1}};
 static const double kLaunch = 2000, kSecondLaunch = 4000, kLong = 100e3;  // ns: a launch's ramp; a dependent second launch, ramp and gap
-struct TileTime { int cfg; double block; };  // ns a block takes of its unit
+struct TileTime { int cfg; double block; bool two; };  // ns a block takes of its unit; whether two share one
 // blocks: of the whole launch; stages, store bytes an element, ranges: of one product's tiles.
 static TileTime tile_time(const TileCost& c, long long blocks, int stages, double store_bytes, int chained_ranges) {
   const bool many = blocks > num_cus();
   double store = (double)c.bm * c.bn * store_bytes / 20;  // a unit's share of the memory's rate, 20 bytes a ns
   if (c.cfg_many == 1 && many) store *= 0.6;               // one block stores while the other multiplies
-  return {many ? c.cfg_many : c.cfg_one, stages * (double)(many ? c.many : c.one) + (many ? c.fill_many : c.fill_one) + store + chained_ranges * 200.0};
+  return {many ? c.cfg_many : c.cfg_one, stages * (double)(many ? c.many : c.one) + (many ? c.fill_many : c.fill_one) + store + chained_ranges * 200.0,
+          many && c.alone > 0};
 }
 
 // K ranges, tile shape, split-K.
@@ -165,6 +175,63 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
     if (ranges > 1 && c.bm * c.bn < 256 * 256) consider(c, 1, true);
   }
   return p;
+}
+
+// The tile shape of a data and a weight gradient that go out as one launch, each with the K ranges it has by itself (the same bits),
+// summed in the block.  False where two launches are expected to be as fast: large products, which fill the chip by themselves.
+// The estimate hands the blocks of the product whose blocks take longer to the units first, then the other's to whichever is free.
+struct GemmShape { int M, N, K; };
+static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, GemmPlan& pd, GemmPlan& pw, bool& w_first) {
+  const int cus = num_cus(), ng = std::max(1, groups);
+  pd = choose_plan(d.M, d.N, d.K, false, (size_t)-1, groups);
+  pw = choose_plan(w.M, w.N, w.K, true, (size_t)-1, groups);
+  if (pd.tail_tiles > 0 || pw.tail_tiles > 0) return false;  // more than a round of the largest tiles, and K ranges of its own
+  // A data gradient cut into many ranges would walk them one after the other, with weights that come from memory: 1344x512x4608
+  // 35 us apart, 40 as one launch.  (A weight gradient's operands have just been written: 512x1024x4000 in seven ranges 26 -> 20.)
+  if (pd.ranges > 4) return false;
+  const double apart = pd.ns + pw.ns;
+  double best = 0;
+  for (const TileCost& c : kTiles) {
+    if (c.bm * c.bn == 256 * 256) continue;
+    auto blocks_of = [&](const GemmShape& g) { return (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * ng; };
+    const long long nd = blocks_of(d), nw = blocks_of(w);
+    const TileTime td = tile_time(c, nd + nw, (d.K + 63) / 64, 2, pd.ranges > 1 ? pd.ranges : 0);
+    const TileTime tw = tile_time(c, nd + nw, (w.K + 63) / 64, 8, pw.ranges > 1 ? pw.ranges : 0);
+    const bool wf = tw.block > td.block;
+    const long long n1 = wf ? nw : nd, n2 = wf ? nd : nw, q = n1 / cus, r = n1 % cus;
+    const double t1 = wf ? tw.block : td.block, t2 = wf ? td.block : tw.block;
+    const double a = q * t1, b = r > 0 ? a + t1 : a;  // the other units, and r of them, are free for the second product
+    auto fits = [&](double end) {  // the second product's blocks that are through by then
+      return (cus - r) * (long long)std::max(0.0, (end - a) / t2 + 1e-6) + r * (long long)std::max(0.0, (end - b) / t2 + 1e-6) >= n2;
+    };
+    const double even = (n1 * t1 + n2 * t2) / cus;
+    double end = -1;
+    for (double from : {a, b}) {
+      double e = from + std::floor(std::max(0.0, even - from) / t2) * t2;
+      while (!fits(e)) e += t2;
+      if (end < 0 || e < end) end = e;
+    }
+    end = std::max(end, b);
+    if (td.two) {  // two blocks share a unit: a long one goes on at half the unit's rate, and by itself once the others are through
+      const double beside = std::min(t1, std::max(0.0, even - t1));
+      end = std::max(end, 2 * beside + (t1 - beside) * (wf ? c.alone : c.alone_cold));
+    }
+    const double ns = kLaunch + end;
+    if (best != 0 && ns >= best) continue;
+    best = ns;
+    w_first = wf;
+    auto take = [&](GemmPlan& p, const GemmShape& g) {
+      p.cfg = td.cfg; p.bm = c.bm; p.bn = c.bn; p.splits = 1;
+      p.k_per_split = std::max(1, (g.K + 63) / 64) * 64;
+      p.k_chain = p.ranges > 1 ? p.range_k : 0;
+    };
+    take(pd, d);
+    take(pw, w);
+  }
+  // (Nor where the weight gradient's float32 result is most of the work: a data gradient of few long blocks beside blocks that keep
+  // the memory busy takes longer than by itself, T = 384, 3680 x 8496: 121 us apart, 158 as one launch.)
+  // The second launch's gap is not in the estimate; of long products the forward strand's blocks use the units left idle.
+  return best < apart * (apart > kLong * 1.5 ? 0.95 : 1.03) && 8.0 * w.M * w.N * ng / 5000 < 0.5 * best;
 }
 
 // Launch indices of the tail launch: from the first index of the last round to the end of the (padded) index range.
@@ -339,4 +406,54 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
   g.M = std::min(max_rows, g.part1_bm - 1);  // a remainder is shorter than a large tile
   p.cfg = 1;
   return mode == 0 ? launch_layout<false, false>(g, p, stream, n_groups) : launch_layout<false, true>(g, p, stream, n_groups);
+}
+
+// The two gradient products of a linear layer whose dY is [T, n], weight [k, n] and input [T, k]: dX[T, k] = dY * W^T and
+// dW[k, n] += X^T * dY, as one launch with the bits of the two apart.  gu != nullptr: dX goes through SwiGLU's backward as in
+// dh_launch_gemm_swiglu_bwd_bf16 (dX is then d(gate | up)[T, 2k]).
+static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups) {
+  switch (cfg) {
+    case 1: return launch_pair<1>(d, w, w_first, stream, n_groups);
+    case 2: return launch_pair<2>(d, w, w_first, stream, n_groups);
+    case 3: return launch_pair<3>(d, w, w_first, stream, n_groups);
+    case 4: return launch_pair<4>(d, w, w_first, stream, n_groups);
+    case 5: return launch_pair<5>(d, w, w_first, stream, n_groups);
+    case 6: return launch_pair<6>(d, w, w_first, stream, n_groups);
+    case 7: return launch_pair<7>(d, w, w_first, stream, n_groups);
+    default: return launch_pair<8>(d, w, w_first, stream, n_groups);
+  }
+}
+bool dh_gemm_pair_pays(int T, int k, int n) {
+  if (T <= 0 || k % 8 || n % 8) return false;
+  GemmPlan pd, pw;
+  bool w_first;
+  return choose_pair({T, k, n}, {k, n, T}, 0, pd, pw, w_first);
+}
+int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
+                             hipStream_t stream) {
+  if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
+  GemmPlan pd, pw;
+  bool w_first;
+  (void)choose_pair({T, k, n}, {k, n, T}, 0, pd, pw, w_first);
+  GemmArgs d = gemm_args(T, k, n, dY, W, dX, EPI_STORE_BF16, pd), w = gemm_args(k, n, T, X, dY, dW, EPI_ACC_F32, pw);
+  if (gu != nullptr) { d.glu_mode = GLU_BWD; d.glu_f = k; d.glu_in = gu; }
+  return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1);
+}
+// The same for the experts' linears (group_rows as in dh_launch_gemm_grouped_bf16; T bounds the rows of all groups).
+bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n) {
+  if (T <= 0 || n_groups > 64 || k % 8 || n % 8) return false;
+  GemmPlan pd, pw;
+  bool w_first;
+  const int avg = std::max(1, T / n_groups);
+  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, pd, pw, w_first);
+}
+int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
+                                     bf16_t* dX, float* dW, hipStream_t stream) {
+  if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "grouped gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
+  GemmPlan pd, pw;
+  bool w_first;
+  const int avg = std::max(1, T / n_groups);
+  (void)choose_pair({avg, k, n}, {k, n, avg}, n_groups, pd, pw, w_first);
+  return launch_pair_cfg(pd.cfg, grouped_args(1, n_groups, group_rows, T, n, k, dY, W, dX, pd),
+                         grouped_args(2, n_groups, group_rows, T, k, n, X, dY, dW, pw), w_first, stream, n_groups);
 }

@@ -28,6 +28,8 @@ struct dh_layer {
   // SwiGLU runs in the epilogue of the gate/up projection (forward) / of the down projection's data gradient (backward)
   // where the shapes allow; the activation operator of that direction then launches nothing
   bool fuse_act_fwd, fuse_act_bwd;
+  // the linears (PairedLinear) whose data and weight gradient go out as one launch when the plan has them next to each other
+  bool pair_launch[4];
   // backward all-reduces carried by a weight-gradient GEMM's launch: bit 1 = B_AR3 with B_FC1_WGRAD, bit 2 = B_AR4 with
   // B_QKV_WGRAD; in force only while the stand-ins run on a block budget (comm_blocks > 0)
   int fuse_comm;
@@ -248,6 +250,18 @@ static size_t take(size_t& cur, size_t bytes) {
   return o;
 }
 
+// The linears of the layer whose two gradient operators may share a launch.
+enum PairedLinear { PAIR_FC2, PAIR_FC1, PAIR_PROJ, PAIR_QKV };
+static void choose_pairs(dh_layer* L) {
+  const dh_layer_config& c = L->c;
+  const bool bf = c.dtype == DH_BF16, moe = c.arch == DH_ARCH_MOE;
+  const int Fin = c.arch == DH_ARCH_GPT ? c.ffn : 2 * c.ffn;
+  L->pair_launch[PAIR_FC2] = bf && (moe ? dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, c.ffn, c.hidden) : dh_gemm_pair_pays(L->T, c.ffn, c.hidden));
+  L->pair_launch[PAIR_FC1] = bf && (moe ? dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, c.hidden, Fin) : dh_gemm_pair_pays(L->T, c.hidden, Fin));
+  L->pair_launch[PAIR_PROJ] = bf && dh_gemm_pair_pays(L->T, L->n_o, c.hidden);
+  L->pair_launch[PAIR_QKV] = bf && dh_gemm_pair_pays(L->T, c.hidden, L->n_qkv);
+}
+
 extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   if (!cfg || !out) DH_FAIL(DH_ERR_INVALID_ARG, "layer_create: null pointer");
   const dh_layer_config& c = *cfg;
@@ -298,6 +312,7 @@ extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   L->fuse_act_bwd = glu_layer && dh_glu_bwd_fits(L->T, c.ffn, c.hidden);
   L->n_qkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   L->n_o = c.n_q_heads * c.head_dim;
+  choose_pairs(L);
   L->es = dh_elem_size(c.dtype);
   L->have_w = L->have_g = false;
   const size_t T = L->T, Ts = L->Ts, Tf = L->Tf, H = c.hidden, F = c.ffn, es = L->es;
@@ -779,6 +794,18 @@ static int gpt_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hipSt
   DH_FAIL(DH_ERR_INVALID_ARG, "unknown forward operator %d", op);
 }
 
+// Bias gradients of the GPT layer's linears: part of their weight-gradient operators.
+static int gpt_bias_grad(dh_layer* L, int which, const dh_bwd_args& b, char* ws, hipStream_t s) {
+  const dh_layer_config& c = L->c;
+  const int T = L->T, Ts = L->Ts, H = c.hidden, F = c.ffn, dt = c.dtype;
+  void* cws = ws + L->b_colsum;
+  switch (which) {
+    case PAIR_FC2: return dh_colsum(dt, Ts, H, b.dout, L->g.dbfc2, cws, L->b_colsum_bytes, s);
+    case PAIR_FC1: return dh_colsum(dt, T, F, ws + L->b_dgu, L->g.dbfc1, cws, L->b_colsum_bytes, s);
+    case PAIR_PROJ: return dh_colsum(dt, Ts, H, ws + L->b_dx2, L->g.dbo, cws, L->b_colsum_bytes, s);
+    default: return dh_colsum(dt, T, L->n_qkv, ws + L->b_dqkv, L->g.dbqkv, cws, L->b_colsum_bytes, s);
+  }
+}
 static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipStream_t s) {
   const dh_layer_config& c = L->c;
   const int T = L->T, Ts = L->Ts, H = c.hidden, F = c.ffn, dt = c.dtype;
@@ -793,14 +820,14 @@ static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
       return gemm(L, false, true, T, F, H, ws + L->b_dz, L->w.Wd, ws + L->b_da, false, gws, gwb, s);
     case DH_GB_FC2_WGRAD:
       if ((rc = gemm(L, true, false, F, H, T, sv + L->s_a, ws + L->b_dz, L->g.dWd, true, gws, gwb, s))) return rc;
-      return dh_colsum(dt, Ts, H, b.dout, L->g.dbfc2, ws + L->b_colsum, L->b_colsum_bytes, s);
+      return gpt_bias_grad(L, PAIR_FC2, b, ws, s);
     case DH_GB_ACT:
       return dh_gelu_bwd_form(dt, c.gelu_form, (size_t)T * F, sv + L->s_gu, ws + L->b_da, ws + L->b_dgu, s);
     case DH_GB_FC1_DGRAD:
       return gemm(L, false, true, T, H, F, ws + L->b_dgu, L->w.Wgu, ws + L->b_part, false, gws, gwb, s);
     case DH_GB_FC1_WGRAD:
       if ((rc = gemm(L, true, false, H, F, T, sv + L->s_h2, ws + L->b_dgu, L->g.dWgu, true, gws, gwb, s))) return rc;
-      return dh_colsum(dt, T, F, ws + L->b_dgu, L->g.dbfc1, ws + L->b_colsum, L->b_colsum_bytes, s);
+      return gpt_bias_grad(L, PAIR_FC1, b, ws, s);
     case DH_GB_RS3:  // the backward of an all-gather reduce-scatters
       if (reduction_with_consumer(L))
         return dh_launch_sum_layernorm_bwd(dt, Ts, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar3, ns).p, sv + L->s_x2, L->w.g2,
@@ -818,14 +845,14 @@ static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
       return gemm(L, false, true, T, L->n_o, H, ws + L->b_dy, L->w.Wo, ws + L->b_do, false, gws, gwb, s);
     case DH_GB_PROJ_WGRAD:
       if ((rc = gemm(L, true, false, L->n_o, H, T, sv + L->s_o, ws + L->b_dy, L->g.dWo, true, gws, gwb, s))) return rc;
-      return dh_colsum(dt, Ts, H, ws + L->b_dx2, L->g.dbo, ws + L->b_colsum, L->b_colsum_bytes, s);
+      return gpt_bias_grad(L, PAIR_PROJ, b, ws, s);
     case DH_GB_ATTN:
       return op_attn_bwd(L, sv, ws, s);
     case DH_GB_QKV_DGRAD:
       return gemm(L, false, true, T, H, L->n_qkv, ws + L->b_dqkv, L->w.Wqkv, ws + L->b_part, false, gws, gwb, s);
     case DH_GB_QKV_WGRAD:
       if ((rc = gemm(L, true, false, H, L->n_qkv, T, sv + L->s_h1, ws + L->b_dqkv, L->g.dWqkv, true, gws, gwb, s))) return rc;
-      return dh_colsum(dt, T, L->n_qkv, ws + L->b_dqkv, L->g.dbqkv, ws + L->b_colsum, L->b_colsum_bytes, s);
+      return gpt_bias_grad(L, PAIR_QKV, b, ws, s);
     case DH_GB_RS4:
       if (reduction_with_consumer(L))
         return dh_launch_sum_layernorm_bwd(dt, Ts, H, c.n_ranks, parts_of(L, ws + L->b_part, b.peers_ar4, ns).p, b.x, L->w.g1,
@@ -964,6 +991,48 @@ static int run_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
   }
 }
 
+// The linear whose data gradient is `op` and whose weight gradient is `next`, if the two are to share a launch; -1 otherwise.
+static int paired_linear(const dh_layer* L, int op, int next) {
+  static const int llama[4][2] = {{DH_B_FC2_DGRAD, DH_B_FC2_WGRAD}, {DH_B_FC1_DGRAD, DH_B_FC1_WGRAD}, {DH_B_PROJ_DGRAD, DH_B_PROJ_WGRAD}, {DH_B_QKV_DGRAD, DH_B_QKV_WGRAD}};
+  static const int cp[4][2] = {{DH_CB_FC2_DGRAD, DH_CB_FC2_WGRAD}, {DH_CB_FC1_DGRAD, DH_CB_FC1_WGRAD}, {DH_CB_PROJ_DGRAD, DH_CB_PROJ_WGRAD}, {DH_CB_QKV_DGRAD, DH_CB_QKV_WGRAD}};
+  static const int gpt[4][2] = {{DH_GB_FC2_DGRAD, DH_GB_FC2_WGRAD}, {DH_GB_FC1_DGRAD, DH_GB_FC1_WGRAD}, {DH_GB_PROJ_DGRAD, DH_GB_PROJ_WGRAD}, {DH_GB_QKV_DGRAD, DH_GB_QKV_WGRAD}};
+  static const int moe[4][2] = {{DH_MB_FC2_DGRAD, DH_MB_FC2_WGRAD}, {DH_MB_FC1_DGRAD, DH_MB_FC1_WGRAD}, {DH_MB_PROJ_DGRAD, DH_MB_PROJ_WGRAD}, {DH_MB_QKV_DGRAD, DH_MB_QKV_WGRAD}};
+  const int(*ops)[2] = L->c.arch == DH_ARCH_GPT ? gpt : L->c.arch == DH_ARCH_MOE ? moe : L->c.arch == DH_ARCH_LLAMA_CP ? cp : llama;
+  for (int i = 0; i < 4; i++) {
+    if (ops[i][0] != op || ops[i][1] != next) continue;
+    if ((i == PAIR_FC1 && fused_collective(L, 1)) || (i == PAIR_QKV && fused_collective(L, 2))) return -1;  // the weight gradient rides in an all-reduce's launch
+    return L->pair_launch[i] ? i : -1;
+  }
+  return -1;
+}
+static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, hipStream_t s) {
+  const dh_layer_config& c = L->c;
+  const int T = L->T, Tf = L->Tf, H = c.hidden, F = c.ffn;
+  const bool gpt = c.arch == DH_ARCH_GPT, moe = c.arch == DH_ARCH_MOE;
+  const char* sv = (const char*)b.saved;
+  auto dense = [&](int k, int n, const void* dY, const void* W, const void* X, size_t dX, float* dW, const void* gu = nullptr) {
+    const int rc = dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, s);
+    return rc || !gpt ? rc : gpt_bias_grad(L, which, b, ws, s);
+  };
+  auto experts = [&](int k, int n, size_t dY, const void* W, size_t X, size_t dX, float* dW) {
+    return dh_launch_gemm_grouped_pair_bf16(c.n_local_experts, moe_tables_of(L, b.saved).group_rows, Tf, k, n, (const bf16_t*)(ws + dY), (const bf16_t*)W,
+                                            (const bf16_t*)(sv + X), (bf16_t*)(ws + dX), dW, s);
+  };
+  switch (which) {
+    case PAIR_FC2:
+      if (moe) return experts(F, H, L->b_dyg, L->w.Wd, L->s_a, L->b_da, (float*)L->g.dWd);
+      if (L->fuse_act_bwd) return dense(F, H, b.dout, L->w.Wd, sv + L->s_a, L->b_dgu, (float*)L->g.dWd, sv + L->s_gu);
+      return dense(F, H, gpt ? ws + L->b_dz : b.dout, L->w.Wd, sv + L->s_a, L->b_da, (float*)L->g.dWd);
+    case PAIR_FC1:
+      if (moe) return experts(H, 2 * F, L->b_dgu, L->w.Wgu, L->s_xg, L->b_dxg, (float*)L->g.dWgu);
+      return dense(H, gpt ? F : 2 * F, ws + L->b_dgu, L->w.Wgu, sv + L->s_h2, L->b_part, (float*)L->g.dWgu);
+    case PAIR_PROJ:
+      return dense(L->n_o, H, ws + (gpt ? L->b_dy : L->b_dx2), L->w.Wo, sv + L->s_o, L->b_do, (float*)L->g.dWo);
+    default:
+      return dense(H, L->n_qkv, ws + L->b_dqkv, L->w.Wqkv, sv + L->s_h1, L->b_part, (float*)L->g.dWqkv);
+  }
+}
+
 static int check_fwd_args(const dh_layer* L, const dh_fwd_args* a) {
   if (!L || !a) DH_FAIL(DH_ERR_INVALID_ARG, "forward: null pointer");
   if (!L->have_w) DH_FAIL(DH_ERR_INVALID_ARG, "forward: weights not bound");
@@ -1033,8 +1102,12 @@ extern "C" int dh_layer_bwd(dh_layer* L, const dh_bwd_args* b, void* ws, size_t 
   if (L->T == 0) return DH_OK;
   int order[DH_MAX_OPS];
   default_order(L->gb, order);
-  for (int k = 0; k < L->gb.n_ops; k++)
-    if ((rc = run_bwd_op(L, order[k], *b, (char*)ws, (hipStream_t)stream))) return rc;
+  for (int k = 0; k < L->gb.n_ops; k++) {
+    const int pair = k + 1 < L->gb.n_ops ? paired_linear(L, order[k], order[k + 1]) : -1;
+    if (pair >= 0) k++;
+    rc = pair >= 0 ? run_bwd_pair(L, pair, *b, (char*)ws, (hipStream_t)stream) : run_bwd_op(L, order[k], *b, (char*)ws, (hipStream_t)stream);
+    if (rc) return rc;
+  }
   return DH_OK;
 }
 
@@ -1167,6 +1240,13 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
           DH_HIP(hipEventRecord(e, sb));
           DH_HIP(hipStreamWaitEvent(sa, e, 0));
           if ((rc = run_bwd_op(LB, op, *beta, ws_b, sa, ws_f + L->f_gemm))) return rc;
+          continue;
+        }
+        const int next = bj < p.b_end ? plan->bwd_order[bj] : -1;
+        const int pair = next >= 0 && !(two && plan->bwd_side[next]) ? paired_linear(LB, op, next) : -1;
+        if (pair >= 0) {  // a linear's two gradients, next to each other on this strand
+          bj++;
+          if ((rc = wait_for_inputs(LB->gb, pb, next, sb)) || (rc = run_bwd_pair(LB, pair, *beta, ws_b, sb))) return rc;
           continue;
         }
         if (dh_leaves_strand(LB->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, LB->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
