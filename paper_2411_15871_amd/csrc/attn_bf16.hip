@@ -26,6 +26,7 @@
 // order; the chunk length is chosen per launch from a simulation of the launch (pick_chunk below).
 // No atomics: dQ is produced per query block, dK/dV per (key block, query head), then the heads of
 // a group are added in index order.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <queue>
@@ -62,8 +63,9 @@ struct AttnGeom {
   const bf16_t* kv; int ldkv;
   bf16_t* dkv; int lddkv;
   int ch;      // backward kernels: 64-token tiles per chunk
-  int nq_all;  // nq * batch: a launch index is (pair index) * nq_all + (batch * nq + head), so that the heaviest
-               // chunks of every head start first
+  int nq_all;  // heads * batch (query heads; key/value heads for dK/dV): a launch index is (pair index) * nq_all + (batch * heads + head),
+               // so that the heaviest chunks of every head start first
+  int grp;     // query heads of a key/value head (dK/dV: a key block walks the tiles of all of them, head after head)
 };
 struct ChunkMap { int blk, chunk, pair, chunks; };
 __host__ __device__ static inline int dq_tiles(int i, int seq) { int e = (i + 1) * 128; return ((e < seq ? e : seq) + AB_KT - 1) / AB_KT; }
@@ -75,25 +77,75 @@ static int total_pairs_dq(int seq, int q_off, int c) {
   for (int i = q_off / 128; i < (seq + 127) / 128; i++) n += chunks_of(dq_tiles(i, seq), c);
   return n;
 }
-static int total_pairs_dkv(int seq, int q_off, int c) {
+static int total_pairs_dkv(int seq, int q_off, int c, int grp) {
   int n = 0;
-  for (int i = 0; i < (seq + 127) / 128; i++) n += chunks_of(dkv_tiles(i, seq, q_off), c);
+  for (int i = 0; i < (seq + 127) / 128; i++) n += chunks_of(grp * dkv_tiles(i, seq, q_off), c);
   return n;
 }
-template <bool DKV>
-__device__ __forceinline__ ChunkMap map_chunk(int id, int seq, int q_off, int total, int c) {
-  const int nblk = (seq + 127) / 128;
+// Which of n blocks, of count(v) units each, holds unit id, and how many units lie before that block.  The wave looks at all blocks
+// side by side (a count takes an integer division: one after the other they took microseconds).  found == false: id is not among them.
+struct UnitOf { int v, rem, before, total; bool found; };
+template <class Count>
+__device__ __forceinline__ UnitOf find_unit(int id, int n, Count count) {
+  const int lane = threadIdx.x & 63, per = (n + 63) >> 6, v0 = lane * per;
+  int mine = 0;
+  for (int k = 0; k < per; k++) mine += v0 + k < n ? count(v0 + k) : 0;
+  int upto = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int t = __shfl_up(upto, d, 64);
+    if (lane >= d) upto += t;
+  }
+  UnitOf u;
+  int v = v0, before = upto - mine;
+  const bool own = id >= before && id < upto;
+  if (own)
+    for (int c; id - before >= (c = count(v)); v++) before += c;
+  const unsigned long long who = __ballot(own);
+  u.found = who != 0;
+  u.total = __builtin_amdgcn_readlane(upto, 63);
+  const int src = who != 0 ? __builtin_ctzll(who) : 0;
+  u.v = __builtin_amdgcn_readlane(v, src);
+  u.before = __builtin_amdgcn_readlane(before, src);
+  u.rem = id - u.before;
+  return u;
+}
+// Sum of count(k) over first <= k < end, by the whole wave.
+template <class Count>
+__device__ __forceinline__ int wave_sum(int first, int end, Count count) {
+  int s = 0;
+  for (int k = first + (int)(threadIdx.x & 63); k < end; k += 64) s += count(k);
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  return __builtin_amdgcn_readfirstlane(s);
+}
+// dQ: heaviest = last block; the first block with queries is q_off/128.  (One block after the other: this kernel has no register
+// left for find_unit, 36 -> 68 bytes a lane in scratch.)
+__device__ __forceinline__ ChunkMap map_dq(int id, int seq, int q_off, int total, int c) {
   ChunkMap m;
   int rem = id, after = 0;  // `after` = pairs of the blocks visited before this one
-  if (DKV) {  // heaviest = block 0; natural pair order = visiting order
-    int i = 0;
-    for (;; i++) { int ch = chunks_of(dkv_tiles(i, seq, q_off), c); if (rem < ch || i == nblk - 1) { m.chunks = ch; break; } rem -= ch; after += ch; }
-    m.blk = i; m.chunk = rem; m.pair = after + rem;
-  } else {    // heaviest = last block; the first block with queries is q_off/128
-    int i = nblk - 1;
-    for (;; i--) { int ch = chunks_of(dq_tiles(i, seq), c); if (rem < ch || i == q_off / 128) { m.chunks = ch; break; } rem -= ch; after += ch; }
-    m.blk = i; m.chunk = rem; m.pair = total - after - m.chunks + rem;
-  }
+  int i = (seq + 127) / 128 - 1;
+  for (;; i--) { int ch = chunks_of(dq_tiles(i, seq), c); if (rem < ch || i == q_off / 128) { m.chunks = ch; break; } rem -= ch; after += ch; }
+  m.blk = i; m.chunk = rem; m.pair = total - after - m.chunks + rem;
+  return m;
+}
+// dK/dV: first every chunk of c tiles (all alike), then what is left of the blocks, longest first (`order`, made by the host): few
+// units a compute unit leave a short last round that way only.  In the blocks' order, 8 key/value heads of 4 query heads x 4096
+// tokens in chunks of 128 took 502 us: the hardware hands blocks to the shader engines in turn, so the long chunks, each followed by a
+// block's short one, met on the same engines.  Unsplit blocks are longest first by themselves.
+#define DKV_ORDER_MAX 512
+#define AB_WHOLE (1 << 20)  // tiles per chunk of a launch that splits no block
+struct DkvOrder { uint16_t blk[DKV_ORDER_MAX]; };
+__device__ __forceinline__ ChunkMap map_dkv(int id, int seq, int q_off, int c, int grp, const DkvOrder& order) {
+  ChunkMap m;
+  if (c >= AB_WHOLE) { m.blk = m.pair = id; m.chunk = 0; m.chunks = 1; return m; }
+  const int nblk = (seq + 127) / 128;
+  const UnitOf u = find_unit(id, nblk, [&](int i) { return grp * dkv_tiles(i, seq, q_off) / c; });
+  m.blk = u.found ? u.v : __builtin_amdgcn_readfirstlane((int)order.blk[id - u.total]);
+  const int tiles = grp * dkv_tiles(m.blk, seq, q_off);
+  m.chunk = u.found ? u.rem : tiles / c;
+  m.chunks = chunks_of(tiles, c);
+  m.pair = wave_sum(0, m.blk, [&](int i) { return chunks_of(grp * dkv_tiles(i, seq, q_off), c); }) + m.chunk;
   return m;
 }
 
@@ -430,16 +482,12 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
     pair = units - 1 - launch;
     blk = qb0 + pair;
   } else {  // heaviest block first; `pair` numbers the (block, chunk) units in natural order
-    int rem = launch, after = 0;
-    blk = (seq + 127) / 128 - 1;
-    for (;; blk--) {
-      nchunks = fwd_chunks(blk, seq, ch);
-      if (rem < nchunks || blk == qb0) break;
-      rem -= nchunks;
-      after += nchunks;
-    }
-    chunk = rem;
-    pair = units - after - nchunks + rem;
+    const int last = (seq + 127) / 128 - 1;
+    const UnitOf u = find_unit(launch, last - qb0 + 1, [&](int v) { return fwd_chunks(last - v, seq, ch); });
+    blk = last - u.v;
+    nchunks = fwd_chunks(blk, seq, ch);
+    chunk = u.rem;
+    pair = units - u.before - nchunks + u.rem;
   }
   const int i0 = blk * 128, iw = i0 + wave * 32, iq = iw + l32;  // positions in the sequence
   const size_t ktok0 = (size_t)b * seq;
@@ -573,9 +621,8 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(int seq, int q_of
   const int nchunks = fwd_chunks(blk, seq, ch);
   if (nchunks == 1) return;
   const int r = (blockIdx.x & 7) * 16 + (threadIdx.x >> 4), pos = blk * 128 + r;
+  const int pair0 = wave_sum(q_off / 128, blk, [&](int i) { return fwd_chunks(i, seq, ch); });
   if (pos >= seq) return;
-  int pair0 = 0;
-  for (int i = q_off / 128; i < blk; i++) pair0 += fwd_chunks(i, seq, ch);
   const size_t unit0 = ((size_t)b * nq + h) * units + pair0;
   constexpr int CPT = D / 16;  // columns per thread
   const int c0 = (threadIdx.x & 15) * CPT;
@@ -629,7 +676,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom&
   const int hb = bid % g.nq_all;
   const int h = hb % nq, b = hb / nq, hk = h / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
-  const ChunkMap cm = map_chunk<false>(bid / g.nq_all, seq, g.q_off, pairs, g.ch);
+  const ChunkMap cm = map_dq(bid / g.nq_all, seq, g.q_off, pairs, g.ch);
   const int i0 = cm.blk * 128, iw = i0 + wave * 32, iq = iw + l32;
   const size_t ktok0 = (size_t)b * seq;
   const long long qtok0 = (long long)b * (seq - g.q_off) - g.q_off;  // local token of position p = qtok0 + p
@@ -745,8 +792,7 @@ __device__ __forceinline__ void attn_bwd_dq_reduce_block(int bx, int by, int bz,
                                                          bf16_t* __restrict__ dqkv, int seq, int q_off, int nq, int nkv, int pairs,
                                                          int cl, float scale) {
   const int i = q_off / 128 + (bx >> 4), r0 = (bx & 15) * 8, h = by, b = bz, ld = (nq + 2 * nkv) * D;
-  int base = 0;
-  for (int k = q_off / 128; k < i; k++) base += chunks_of(dq_tiles(k, seq), cl);
+  const int base = wave_sum(q_off / 128, i, [&](int k) { return chunks_of(dq_tiles(k, seq), cl); });
   const int ch = chunks_of(dq_tiles(i, seq), cl);
   const float* p0 = part + (((size_t)b * nq + h) * pairs + base) * 128 * D;
   for (int e = threadIdx.x; e < 8 * D / 4; e += 256) {
@@ -760,17 +806,19 @@ __device__ __forceinline__ void attn_bwd_dq_reduce_block(int bx, int by, int bz,
 }
 
 // ================================================================================ backward: dK, dV
-// grid (pairs * nq * batch): one block per (key block, chunk, query head); wave w owns keys
+// grid (pairs * nkv * batch): one block per (key block, chunk, key/value head); wave w owns keys
 // j0 + 32w .. +31 and keeps their K, V fragments and the dK^T, dV^T accumulators in registers while
-// 64-query tiles of that head's Q and dO stream through LDS.  With grouped heads (nq > nkv) the
-// block writes float32 partials part[batch][query head][pair][128 keys][dK | dV] and
-// attn_bwd_reduce_kernel (its dK/dV part) adds the group's heads and the key block's chunks in index order; with
-// nq == nkv and no block longer than one chunk it writes dK, dV directly.
+// 64-query tiles of Q and dO stream through LDS: those of the group's first query head, then those of the next, and so on
+// (the keys are the same), cut into chunks of g.ch tiles wherever that falls.  A key block of one chunk writes dK, dV; the
+// chunks of the others write float32 partials part[batch][kv head][pair][128 keys][dK | dV] that
+// attn_bwd_reduce_kernel (its dK/dV part) adds in chunk order.  Against a block per query head, whose partials of every head went
+// through memory, the whole backward pass (us): 4:1 heads x 4096 tokens 117 -> 106, 4096 queries over 12288 keys 391 -> 341, 32:8 heads x 4096
+// 544 -> 510, 16:4 x 1500 88 -> 81, 8:1 x 8192 535 -> 529; D = 64, 4:1 x 8192 216 -> 175, 32:4 x 2 x 1000 64 -> 66.
 template <int D>
 __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom& g, const bf16_t* __restrict__ qkv,
                                                    const bf16_t* __restrict__ dout, const float* __restrict__ lse2,
                                                    const float* __restrict__ delta, float* __restrict__ part, int pairs, int T,
-                                                   float scale, float scale_log2) {
+                                                   float scale, float scale_log2, const DkvOrder& order) {
   using TL = ATile<D>;
   constexpr bool AGPR = D == 128;
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // Q ring, dO ring, lse2 ring, delta ring
@@ -779,9 +827,9 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   const int l32 = lane & 31, kg = lane >> 5;
   const int seq = g.seq, nq = g.nq, nkv = g.nkv;
   const int hb = bid % g.nq_all;
-  const int hq = hb % nq, b = hb / nq, grp = nq / nkv, hk = hq / grp;
+  const int hk = hb % nkv, b = hb / nkv, hq = hk * g.grp;  // hq: the group's first query head
   const int ld = (nq + 2 * nkv) * D, ldo = nq * D;
-  const ChunkMap cm = map_chunk<true>(bid / g.nq_all, seq, g.q_off, pairs, g.ch);
+  const ChunkMap cm = map_dkv(bid / g.nq_all, seq, g.q_off, g.ch, g.grp, order);
   const int j0 = cm.blk * 128, jw = j0 + wave * 32, jk = jw + l32;  // key positions in the sequence (block 0 is the heaviest)
   const int q0 = dkv_first(cm.blk, g.q_off);                        // first query position this key block meets
   const size_t ktok0 = (size_t)b * seq;
@@ -807,12 +855,21 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   tile_voff<D>(vq, ld, wave, lane, AB_KT);
   tile_voff<D>(vo, ldo, wave, lane, AB_KT);
   const uint32_t ldsQ = lds_address(smem), ldsO = ldsQ + AB_RING * TL::BYTES;
-  const int t0 = cm.chunk * g.ch, ntiles = min(dkv_tiles(cm.blk, seq, g.q_off), t0 + g.ch);  // query tiles q0 + 64*[t0, ntiles)
+  // The block's tiles: nt query tiles q0 + 64*t of each head of the group, counted through; this chunk walks [f0, f1).
+  const int nt = dkv_tiles(cm.blk, seq, g.q_off), f0 = cm.chunk * g.ch, f1 = min(g.grp * nt, f0 + g.ch);
   const size_t qstride = (size_t)AB_KT * ld * sizeof(bf16_t), ostride = (size_t)AB_KT * ldo * sizeof(bf16_t);
-  auto issue = [&](int t, int slot) {
-    const int valid = seq - (q0 + t * AB_KT);
-    const char* qp = qbase + t * qstride;
-    const char* op = obase + t * ostride;
+  int gi = f0 / nt, ti = f0 - gi * nt;  // head of the group and tile to transfer next
+  int tc = ti;                          // tile to work off next
+  // per-row statistics of a tile (64 floats each): even waves transfer lse2, odd waves delta (waves 2 and 3
+  // repeat what waves 0 and 1 transfer, which keeps the transfer count of all waves equal)
+  const uint32_t ldsS = ldsQ + 2 * AB_RING * TL::BYTES + (wave & 1) * AB_RING * AB_KT * sizeof(float);
+  const float* srow = (wave & 1) ? drow : lrow;
+  pin_frags(kf);
+  pin_frags(vf);
+  auto issue = [&](int slot) {
+    const int row0 = q0 + ti * AB_KT, valid = seq - row0;
+    const char* qp = qbase + ti * qstride + gi * (D * sizeof(bf16_t));
+    const char* op = obase + ti * ostride + gi * (D * sizeof(bf16_t));
     if (valid >= AB_KT) {
       tile_dma<D>(qp, vq, ldsQ + slot * TL::BYTES, wave);
       tile_dma<D>(op, vo, ldsO + slot * TL::BYTES, wave);
@@ -823,27 +880,18 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       tile_voff<D>(vc, ldo, wave, lane, valid);
       tile_dma<D>(op, vc, ldsO + slot * TL::BYTES, wave);
     }
+    dma4_base(srow + (size_t)gi * T + ti * AB_KT, (uint32_t)(min(lane, valid - 1) * sizeof(float)), ldsS + slot * AB_KT * sizeof(float));
+    if (++ti == nt) { ti = 0; gi++; }
   };
-  // per-row statistics of a tile (64 floats each): even waves transfer lse2, odd waves delta (waves 2 and 3
-  // repeat what waves 0 and 1 transfer, which keeps the transfer count of all waves equal)
-  const uint32_t ldsS = ldsQ + 2 * AB_RING * TL::BYTES + (wave & 1) * AB_RING * AB_KT * sizeof(float);
-  const float* srow = (wave & 1) ? drow : lrow;
-  pin_frags(kf);
-  pin_frags(vf);
-  auto issue_stat = [&](int t, int slot) {
-    const int row0 = q0 + t * AB_KT;
-    dma4_base(srow + t * AB_KT, (uint32_t)((min(row0 + lane, seq - 1) - row0) * sizeof(float)),
-              ldsS + slot * AB_KT * sizeof(float));
-  };
-  issue(t0, 0);
-  issue_stat(t0, 0);
-  if (t0 + 1 < ntiles) { issue(t0 + 1, 1); issue_stat(t0 + 1, 1); }
+  issue(0);
+  if (f0 + 1 < f1) issue(1);
   int slot = 0;
-  for (int t = t0; t < ntiles; t++, slot = slot == AB_RING - 1 ? 0 : slot + 1) {
-    if (t + 1 < ntiles) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
+  for (int f = f0; f < f1; f++, slot = slot == AB_RING - 1 ? 0 : slot + 1) {
+    if (f + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
     __syncthreads();
-    if (t + 2 < ntiles) { const int ns = slot == 0 ? AB_RING - 1 : slot - 1; issue(t + 2, ns); issue_stat(t + 2, ns); }
-    const int qb = q0 + t * AB_KT;
+    if (f + 2 < f1) issue(slot == 0 ? AB_RING - 1 : slot - 1);
+    const int qb = q0 + tc * AB_KT;
+    if (++tc == nt) tc = 0;
     if (qb + AB_KT - 1 < jw) continue;  // every query of the tile precedes every key of this wave
     TilePtrs<D> Qp, Op;
     Qp.set(sm + slot * TL::BYTES, fa);
@@ -892,8 +940,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     return f32x4{dkt[dt][4 * q4] * scale, dkt[dt][4 * q4 + 1] * scale, dkt[dt][4 * q4 + 2] * scale, dkt[dt][4 * q4 + 3] * scale};
   };
   auto dv_quad = [&](int dt, int q4) { return f32x4{dvt[dt][4 * q4], dvt[dt][4 * q4 + 1], dvt[dt][4 * q4 + 2], dvt[dt][4 * q4 + 3]}; };
-  if (part != nullptr) {
-    float* rows = part + ((((size_t)b * nq + hq) * pairs + cm.pair) * 128 + wave * 32) * (2 * D);
+  if (cm.chunks > 1) {
+    float* rows = part + ((((size_t)b * nkv + hk) * pairs + cm.pair) * 128 + wave * 32) * (2 * D);
     float* reg = reinterpret_cast<float*>(smem) + wave * (32 * D);
     wave_rows_out_f32<D>(reg, lane, dk_quad, [&](int r) { return rows + (size_t)r * (2 * D); });
     __builtin_amdgcn_wave_barrier();
@@ -921,13 +969,13 @@ __global__ __launch_bounds__(AB_THREADS) void attn_bwd_bf16_kernel(const AttnGeo
                                                                    const float* __restrict__ lse, const float* __restrict__ lse2,
                                                                    const float* __restrict__ delta, bf16_t* __restrict__ dqkv,
                                                                    float* __restrict__ part_q, float* __restrict__ part_kv, int pairs_q,
-                                                                   int pairs_k, int T, float scale, float scale_log2) {
+                                                                   int pairs_k, int T, float scale, float scale_log2, const DkvOrder order) {
   const int hb = blockIdx.x % gq.nq_all, u = blockIdx.x / gq.nq_all, both = 2 * min(pairs_q, pairs_k);
   int idx;
   bool dkv;
   if (u < both) { dkv = (u & 1) == 0; idx = u >> 1; }
   else { dkv = pairs_k > pairs_q; idx = u - both / 2; }
-  if (dkv) attn_bwd_dkv_block<D>(idx * gk.nq_all + hb, gk, qkv, dout, lse2, delta, part_kv, pairs_k, T, scale, scale_log2);
+  if (dkv) attn_bwd_dkv_block<D>(idx * gk.nq_all + hb, gk, qkv, dout, lse2, delta, part_kv, pairs_k, T, scale, scale_log2, order);
   else attn_bwd_dq_block<D, AB_RING>(idx * gq.nq_all + hb, gq, qkv, o, dout, lse, nullptr, nullptr, dqkv, part_q, pairs_q, T, scale, scale_log2);
 }
 // The two halves as launches of their own (dQ first: it stores the row statistics the dK/dV blocks read).
@@ -943,8 +991,9 @@ template <int D>
 __global__ __launch_bounds__(AB_THREADS) void attn_bwd_dkv_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
                                                                        const bf16_t* __restrict__ dout, const float* __restrict__ lse2,
                                                                        const float* __restrict__ delta, float* __restrict__ part,
-                                                                       int pairs, int T, float scale, float scale_log2) {
-  attn_bwd_dkv_block<D>((int)blockIdx.x, g, qkv, dout, lse2, delta, part, pairs, T, scale, scale_log2);
+                                                                       int pairs, int T, float scale, float scale_log2,
+                                                                       const DkvOrder order) {
+  attn_bwd_dkv_block<D>((int)blockIdx.x, g, qkv, dout, lse2, delta, part, pairs, T, scale, scale_log2, order);
 }
 
 // Per-row statistics of the backward pass for the dK/dV blocks: delta[h,t] = sum_c dO[t,h,c] O[t,h,c] and
@@ -974,26 +1023,23 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __rest
   lse2[(size_t)h * T + t] = lse[(size_t)h * T + t] * LOG2E;
 }
 
-// dk,dv[token][kv head] = sum over the group's query heads (ascending) and, inside a head, over the
-// chunks of the token's key block (ascending) of the float32 partials.
+// dk,dv[token][kv head] = sum over the chunks of the token's key block (ascending) of the float32 partials, where it has several.
 // grid (32*ceil(seq/128), nkv, batch), 256 threads: a block owns 4 rows of a key block, thread = (key row, 4
 // columns of [dK | dV]).
 template <int D>
 __device__ __forceinline__ void attn_bwd_group_reduce_block(int bx, int by, int bz, const float* __restrict__ part, const AttnGeom& g,
                                                             int pairs) {
-  const int seq = g.seq, nq = g.nq, nkv = g.nkv;
-  const int i = bx >> 5, r0 = (bx & 31) * 4, hk = by, b = bz, grp = nq / nkv;
-  int base = 0;
-  for (int k = 0; k < i; k++) base += chunks_of(dkv_tiles(k, seq, g.q_off), g.ch);
-  const int ch = chunks_of(dkv_tiles(i, seq, g.q_off), g.ch);
+  const int seq = g.seq, nkv = g.nkv;
+  const int i = bx >> 5, r0 = (bx & 31) * 4, hk = by, b = bz;
+  const int ch = chunks_of(g.grp * dkv_tiles(i, seq, g.q_off), g.ch);
+  if (ch == 1) return;  // written by its only chunk
+  const int base = wave_sum(0, i, [&](int k) { return chunks_of(g.grp * dkv_tiles(k, seq, g.q_off), g.ch); });
+  const float* p0 = part + (((size_t)b * nkv + hk) * pairs + base) * 128 * (2 * D);
   for (int e = threadIdx.x; e < 4 * 2 * D / 4; e += 256) {
     const int row = r0 + e / (2 * D / 4), c4 = (e % (2 * D / 4)) * 4;
     if (i * 128 + row >= seq) continue;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    for (int gh = 0; gh < grp; gh++) {
-      const float* p0 = part + (((size_t)b * nq + hk * grp + gh) * pairs + base) * 128 * (2 * D);
-      for (int c = 0; c < ch; c++) s += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p0 + ((size_t)c * 128 + row) * (2 * D) + c4));
-    }
+    for (int c = 0; c < ch; c++) s += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p0 + ((size_t)c * 128 + row) * (2 * D) + c4));
     bf16x4 o = {(bf16_t)s[0], (bf16_t)s[1], (bf16_t)s[2], (bf16_t)s[3]};
     bf16_t* dst = g.dkv + ((size_t)b * seq + i * 128 + row) * g.lddkv + (c4 < D ? (size_t)hk * D + c4 : (size_t)(nkv + hk) * D + (c4 - D));
     *reinterpret_cast<bf16x4*>(dst) = o;
@@ -1042,20 +1088,60 @@ static int attn_num_cus() {  // of the current device
 // simulated for each candidate length: a unit costs its tiles plus a fixed overhead, every chunk of a split launch
 // costs the traffic of its float32 partial result (written, then read by the merging kernel), and a split launch
 // pays for the merging kernels.  The constants are measured on MI355X (microseconds): a compute unit finishes a
-// forward tile in 1.45, a dQ tile in 1.55 with two blocks on it or 1.8 beside dK/dV units, a dK/dV tile in 2.4; HBM moves 4 MB per
+// forward tile in 1.45, a dQ tile in 1.55 with two blocks on it or 1.8 beside dK/dV units, a dK/dV tile in 2.4 (2.0 with chunks as
+// long as grouped heads allow); HBM moves 4 MB per
 // microsecond under this load.
 enum { PICK_FWD = 0, PICK_DQ = 1, PICK_DKV = 2 };
 struct PickKey {
-  int kind, seq, q_off, nq_all, d, grouped, cus;
+  int kind, seq, q_off, nq_all, d, grp, cus;
   bool operator<(const PickKey& o) const {
-    return std::tie(kind, seq, q_off, nq_all, d, grouped, cus) < std::tie(o.kind, o.seq, o.q_off, o.nq_all, o.d, o.grouped, o.cus);
+    return std::tie(kind, seq, q_off, nq_all, d, grp, cus) < std::tie(o.kind, o.seq, o.q_off, o.nq_all, o.d, o.grp, o.cus);
   }
 };
-static double simulate_launch(int kind, int seq, int q_off, int nq_all, int ch, int slots, double t_tile, double t_ovh) {
+// Units of a dK/dV launch in launch order (see map_dkv): tiles of each, and the blocks of those that are no whole chunk.
+static std::vector<int> dkv_units(int seq, int q_off, int grp, int ch, DkvOrder* order) {
+  const int nblk = (seq + 127) / 128;
+  std::vector<int> tiles;
+  std::vector<std::pair<int, int>> rest;
+  for (int i = 0; i < nblk; i++) {
+    const int t = grp * dkv_tiles(i, seq, q_off);
+    tiles.insert(tiles.end(), t / ch, ch);
+    if (t % ch) rest.push_back({-(t % ch), i});
+  }
+  std::sort(rest.begin(), rest.end());
+  for (size_t k = 0; k < rest.size(); k++) {
+    tiles.push_back(-rest[k].first);
+    if (order && k < DKV_ORDER_MAX) order->blk[k] = (uint16_t)rest[k].second;
+  }
+  return tiles;
+}
+static double simulate_launch(int kind, int seq, int q_off, int nq_all, int grp, int ch, int slots, double t_tile, double t_ovh) {
+  typedef std::priority_queue<double, std::vector<double>, std::greater<double>> Queue;
   const int nblk = (seq + 127) / 128, qb0 = q_off / 128;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-  for (int i = 0; i < slots; i++) free_at.push(0.0);
   double makespan = 0.0;
+  if (kind == PICK_DKV && grp > 1) {
+    // Blocks go to the 8 dies in turn and, on a die, to its 4 shader engines in turn, none before the one ahead of it: a block
+    // waits for a unit of its engine though others are free.  (Fits what chunk lengths measure: 8 heads x 8192 tokens on one key/value head,
+    // 136 / 140 / 144 tiles a chunk 535 / 504 / 509 us for the whole backward pass; with the first free unit 136 would be best.)
+    const std::vector<int> tiles = dkv_units(seq, q_off, grp, ch, nullptr);
+    Queue unit[8][4];
+    double last[8] = {};
+    for (auto& die : unit) for (auto& engine : die) for (int i = 0; i < std::max(1, slots / 32); i++) engine.push(0.0);
+    long long k = 0;
+    for (int t : tiles)
+      for (int h = 0; h < nq_all; h++, k++) {
+        Queue& q = unit[k & 7][(k >> 3) & 3];
+        double& ahead = last[k & 7];
+        ahead = std::max(ahead, q.top());
+        const double end = ahead + t * t_tile + t_ovh;
+        q.pop();
+        q.push(end);
+        makespan = std::max(makespan, end);
+      }
+    return makespan;
+  }
+  Queue free_at;
+  for (int i = 0; i < slots; i++) free_at.push(0.0);
   auto run = [&](int tiles) {
     for (int t0 = 0; t0 < tiles; t0 += ch) {
       const double cost = (tiles - t0 < ch ? tiles - t0 : ch) * t_tile + t_ovh;
@@ -1071,43 +1157,52 @@ static double simulate_launch(int kind, int seq, int q_off, int nq_all, int ch, 
   else for (int i = nblk - 1; i >= qb0; i--) run(dq_tiles(i, seq));  // forward: the tiles dQ walks
   return makespan;
 }
-static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, bool grouped) {
+// nq_all: heads * batch, grp: query heads of a key/value head (see AttnGeom).
+static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, int grp) {
+  // dK/dV of grouped heads: what matters is where the last units end, so the length is chosen finely, and storing a partial result
+  // counts as a unit's own time (beside dQ's units, with a head each, the gaps are filled anyway).
+  const bool grouped = grp > 1, fine = kind == PICK_DKV && grouped, two = fine && d == 64;
   static std::mutex mu;
   static std::map<PickKey, int> cache;
-  const PickKey key{kind, seq, q_off, nq_all, d, grouped ? 1 : 0, attn_num_cus()};
+  const PickKey key{kind, seq, q_off, nq_all, d, grp, attn_num_cus()};
   std::lock_guard<std::mutex> lock(mu);
   auto it = cache.find(key);
   if (it != cache.end()) return it->second;
   const int nblk = (seq + 127) / 128, qb0 = q_off / 128;
-  const int max_tiles = kind == PICK_DKV ? dkv_tiles(0, seq, q_off) : dq_tiles(nblk - 1, seq);
-  const double t_tile = (kind == PICK_FWD ? 1.45 : kind == PICK_DQ ? (grouped ? 1.55 : 1.8) : 2.4) * d / 128.0, t_ovh = 3.0;
-  const double us_per_byte = 2.0 / 4.0e6, t_merge = 12.0;
-  static const int cand_fwd[] = {4, 8, 16, 32, 64, 1 << 20}, cand_bwd[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 1 << 20};
-  const int* cand = kind == PICK_FWD ? cand_fwd : cand_bwd;
-  const int n_cand = kind == PICK_FWD ? 6 : 12;
+  const int max_tiles = kind == PICK_DKV ? grp * dkv_tiles(0, seq, q_off) : dq_tiles(nblk - 1, seq);
+  const double t_tile = (kind == PICK_FWD ? 1.45 : kind == PICK_DQ ? (grouped ? 1.55 : 1.8) : fine ? 2.0 : 2.4) * d / 128.0 * (two ? 1.6 : 1.0), t_ovh = (fine ? 9.0 : 3.0) * (fine ? d / 128.0 : 1.0);
+  const double us_per_byte = (fine ? 1.0 : 2.0) / 4.0e6, t_merge = 12.0;
+  static const int cand_fwd[] = {4, 8, 16, 32, 64, 1 << 20}, cand_dq[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 1 << 20};
+  std::vector<int> cand;
+  if (kind == PICK_FWD) cand.assign(cand_fwd, cand_fwd + 6);
+  else if (kind == PICK_DQ) cand.assign(cand_dq, cand_dq + 12);
+  else if (!fine) cand.assign(cand_dq, cand_dq + (nblk <= DKV_ORDER_MAX ? 12 : 0));
+  else if (nblk <= DKV_ORDER_MAX) for (int c = 4; c < max_tiles; c += std::max(1, c / 32)) cand.push_back(c);
+  if (kind == PICK_DKV) cand.push_back(AB_WHOLE);
+  const int n_cand = (int)cand.size();
   int best = cand[n_cand - 1];
   double best_t = 1e300;
   for (int k = 0; k < n_cand; k++) {
     const int ch = cand[k];
     if (ch < (1 << 20) && ch >= max_tiles) continue;  // same as not splitting
-    int units = 0;
-    if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) units += chunks_of(dkv_tiles(i, seq, q_off), ch);
+    int units = 0, apart = 0;  // apart: units that write partial results
+    if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) { const int n = chunks_of(grp * dkv_tiles(i, seq, q_off), ch); units += n; apart += n > 1 ? n : 0; }
     else for (int i = qb0; i < nblk; i++) units += chunks_of(dq_tiles(i, seq), ch);
     const bool split = units > (kind == PICK_DKV ? nblk : nblk - qb0);
-    double t = simulate_launch(kind, seq, q_off, nq_all, ch, attn_num_cus(), t_tile, t_ovh);
+    double t = simulate_launch(kind, seq, q_off, nq_all, grp, ch, attn_num_cus() * (two ? 2 : 1), t_tile, t_ovh);
     double bytes = 0.0;
     if (kind == PICK_FWD) { if (split) bytes = (double)units * (d + 2); }
     else if (kind == PICK_DQ) { if (split) bytes = (double)units * d; }
-    else if (split || grouped) bytes = (double)units * 2 * d;
-    t += bytes * nq_all * 128 * sizeof(float) * us_per_byte + (split && !(kind == PICK_DKV && grouped) ? t_merge : 0.0);
+    else if (split) bytes = (double)(fine ? apart : units) * 2 * d;
+    t += bytes * nq_all * 128 * sizeof(float) * us_per_byte + (split ? t_merge : 0.0);
     if (t < best_t) { best_t = t; best = ch; }
   }
   // When splitting pays at all it is because the launch would leave compute units idle, and then the finest split
   // whose units are still all resident at once balances them best (measured: 4 heads x 4096 tokens, forward 16 -> 10
   // tiles per chunk 48 -> 42 us, backward 24 -> 22 tiles 116 -> 113 us; one more unit than fits costs a second round).
   // Resident blocks per compute unit: forward, and dQ in a launch of its own, 2 (forward at D = 64: 4, counted as 2);
-  // dK/dV, and dQ beside it, 1 (2 at D = 64).
-  if (best < (1 << 20)) {
+  // dK/dV and dQ beside it 1 (2 at D = 64).
+  if (best < (1 << 20) && !fine) {
     const long long resident = (long long)attn_num_cus() * (kind == PICK_FWD || (kind == PICK_DQ && grouped) || d == 64 ? 2 : 1);
     for (int ch = 8; ch < best; ch += 2) {
       long long units = 0;
@@ -1122,13 +1217,13 @@ static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, bool grou
 
 // Tiles per chunk of the forward kernel; 0 = blocks are not split.
 static int fwd_chunk_tiles(int batch, int seq, int q_off, int nq, int d) {
-  const int ch = pick_chunk(PICK_FWD, seq, q_off, nq * batch, d, false);
+  const int ch = pick_chunk(PICK_FWD, seq, q_off, nq * batch, d, 1);
   return ch >= (1 << 20) ? 0 : ch;
 }
 // Tiles per chunk of the dQ and of the dK/dV kernel.
 static void bwd_chunk_tiles(int batch, int seq, int q_off, int nq, int nkv, int d, int& ch_q, int& ch_k) {
-  ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, nq > nkv);
-  ch_k = pick_chunk(PICK_DKV, seq, q_off, nq * batch, d, nq > nkv);
+  ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, nq / nkv);
+  ch_k = pick_chunk(PICK_DKV, seq, q_off, nkv * batch, d, nq / nkv);
 }
 
 // The launchers take the queries' sequence length seq_q and q_off; kv == nullptr selects plain attention (keys and
@@ -1157,7 +1252,7 @@ int dh_launch_attn_fwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   if (batch * seq_q == 0) return DH_OK;
   const int seq = q_off + seq_q, T = batch * seq_q;
   AttnGeom g;
-  g.seq = seq; g.q_off = q_off; g.nq = nq; g.nkv = nkv; g.dkv = nullptr; g.lddkv = 0; g.ch = 0; g.nq_all = nq * batch;
+  g.seq = seq; g.q_off = q_off; g.nq = nq; g.nkv = nkv; g.dkv = nullptr; g.lddkv = 0; g.ch = 0; g.nq_all = nq * batch; g.grp = nq / nkv;
   if (kv) { g.kv = kv; g.ldkv = ldkv; } else { g.kv = qkv + (size_t)nq * d; g.ldkv = (nq + 2 * nkv) * d; }
   const int nblk = (seq + 127) / 128 - q_off / 128;  // blocks that hold queries
   int ch = fwd_chunk_tiles(batch, seq, q_off, nq, d);
@@ -1185,8 +1280,8 @@ int dh_launch_attn_fwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   return DH_OK;
 }
 
-// workspace: lse2[nq*T] floats; dK/dV partials [batch][nq][pairs][128][2d] floats when heads are grouped
-// or some block needs more than one chunk; dQ partials [batch][nq][pairs][128][d] floats in the latter case
+// workspace: lse2[nq*T] floats; dK/dV partials [batch][nkv][pairs][128][2d] floats when some key block has more than one
+// chunk; dQ partials [batch][nq][pairs][128][d] floats when some query block has
 struct BwdLayout {
   size_t o_lse2, o_dkv, o_dq, total;
   int ch_q, ch_k, pq, pk;   // chunk lengths and (block, chunk) pair counts of the dQ and the dK/dV launch
@@ -1198,12 +1293,12 @@ static BwdLayout bwd_ws_layout(int batch, int seq_q, int q_off, int nq, int nkv,
   const int seq = q_off + seq_q, nblk = (seq + 127) / 128;
   bwd_chunk_tiles(batch, seq, q_off, nq, nkv, d, L.ch_q, L.ch_k);
   L.pq = total_pairs_dq(seq, q_off, L.ch_q);
-  L.pk = total_pairs_dkv(seq, q_off, L.ch_k);
+  L.pk = total_pairs_dkv(seq, q_off, L.ch_k, nq / nkv);
   L.part_q = L.pq > nblk - q_off / 128;
-  L.part_kv = nq > nkv || L.pk > nblk;
+  L.part_kv = L.pk > nblk;
   size_t cur = 0;
   L.o_lse2 = cur; cur += dh_align_up(nq * T * sizeof(float), 256);
-  L.o_dkv = cur; if (L.part_kv) cur += dh_align_up((size_t)batch * nq * L.pk * 128 * 2 * d * sizeof(float), 256);
+  L.o_dkv = cur; if (L.part_kv) cur += dh_align_up((size_t)batch * nkv * L.pk * 128 * 2 * d * sizeof(float), 256);
   L.o_dq = cur; if (L.part_q) cur += dh_align_up((size_t)batch * nq * L.pq * 128 * d * sizeof(float), 256);
   L.total = cur;
   return L;
@@ -1228,7 +1323,9 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   else { g.kv = qkv + (size_t)nq * d; g.dkv = dqkv + (size_t)nq * d; g.ldkv = g.lddkv = (nq + 2 * nkv) * d; }
   const BwdLayout lay = bwd_ws_layout(batch, seq_q, q_off, nq, nkv, d);
   g.nq_all = nq * batch;
+  g.grp = nq / nkv;
   AttnGeom gq_geom = g, gk_geom = g;
+  gk_geom.nq_all = nkv * batch;
   gq_geom.ch = lay.ch_q;
   gk_geom.ch = lay.ch_k;
   if (!ws || ws_bytes < lay.total) DH_FAIL(DH_ERR_WORKSPACE_TOO_SMALL, "attn_bwd: workspace %zu < %zu bytes", ws_bytes, lay.total);
@@ -1237,10 +1334,12 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   float* part_q = lay.part_q ? (float*)((char*)ws + lay.o_dq) : nullptr;
   const float sc = (float)(1.0 / sqrt((double)d)), sl2 = (float)(1.4426950408889634 / sqrt((double)d));
   const int nblk = (seq + 127) / 128, nblk_q = nblk - q_off / 128, pq = lay.pq, pk = lay.pk;
-  dim3 gw((unsigned)(pq + pk) * nq * batch), gwq((unsigned)pq * nq * batch), gwk((unsigned)pk * nq * batch), gq(nblk_q * 16, nq, batch),
+  dim3 gw((unsigned)(pq + pk) * nq * batch), gwq((unsigned)pq * nq * batch), gwk((unsigned)pk * nkv * batch), gq(nblk_q * 16, nq, batch),
       gk(nblk * 32, nkv, batch);
   const unsigned nb_q = part_q ? gq.x * gq.y * gq.z : 0, nb_k = part_kv ? gk.x * gk.y * gk.z : 0;
   const size_t lds_dq = 2 * dq_ring(d) * (size_t)AB_KT * d * 2, lds_dkv = 2 * AB_RING * ((size_t)AB_KT * d * 2 + AB_KT * sizeof(float));
+  DkvOrder order;
+  if (lay.ch_k < AB_WHOLE) (void)dkv_units(seq, q_off, g.grp, lay.ch_k, &order);
   static bool ready_dev[DH_MAX_DEVICES][2] = {};
   bool* ready = ready_dev[dh_device_index()];
 #define DH_ATTN_BWD(DD, IDX)                                                                                                   \
@@ -1254,11 +1353,11 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
       attn_bwd_prep_kernel<DD><<<(unsigned)(((size_t)T * nq + 255) / 256), 256, 0, stream>>>(o, dout, lse, lse2, delta, T, nq); \
       DH_LAUNCH_CHECK();                                                                                                       \
       attn_bwd_bf16_kernel<DD><<<gw, AB_THREADS, lds_dkv, stream>>>(gq_geom, gk_geom, qkv, o, dout, lse, lse2, delta, dqkv, part_q, \
-                                                                   part_kv, pq, pk, T, sc, sl2);                               \
+                                                                   part_kv, pq, pk, T, sc, sl2, order);                        \
     } else {                                                                                                                   \
       attn_bwd_dq_bf16_kernel<DD><<<gwq, AB_THREADS, lds_dq, stream>>>(gq_geom, qkv, o, dout, lse, lse2, delta, dqkv, part_q, pq, T, sc, sl2); \
       DH_LAUNCH_CHECK();                                                                                                       \
-      attn_bwd_dkv_bf16_kernel<DD><<<gwk, AB_THREADS, lds_dkv, stream>>>(gk_geom, qkv, dout, lse2, delta, part_kv, pk, T, sc, sl2); \
+      attn_bwd_dkv_bf16_kernel<DD><<<gwk, AB_THREADS, lds_dkv, stream>>>(gk_geom, qkv, dout, lse2, delta, part_kv, pk, T, sc, sl2, order); \
     }                                                                                                                          \
     DH_LAUNCH_CHECK();                                                                                                         \
     if (nb_q + nb_k > 0) {                                                                                                     \
