@@ -24,8 +24,7 @@
 // Blocks are launched heaviest first over all heads (the causal work per block grows with its position).
 // Long rows of tiles may be cut into chunks whose float32 partial results a small kernel merges in chunk
 // order; the chunk length is chosen per launch from a simulation of the launch (pick_chunk below).
-// No atomics: dQ is produced per query block, dK/dV per (key block, query head), then the heads of
-// a group are added in index order.
+// No atomics: dQ is produced per query block, dK/dV per key block, which walks the heads of its group in index order.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -41,13 +40,11 @@
 // Tile slots of the dQ kernel in a launch of its own: two at D = 128, so that two of its blocks fit a compute unit (64 KiB each,
 // 256 registers a lane).  The arithmetic of one block's waves then runs beside the products of the other's: 32 heads x 4096
 // tokens 250 -> 205 us, 4 heads x 4096 queries over 12288 keys 167 -> 136 us.  (Two blocks fit anyway at D = 64.)
-// The 256 registers are eight too few: they go to scratch (36 bytes a lane), five of them around the whole tile loop, the others read
+// The 256 registers are six too few: they go to scratch (28 bytes a lane), most of them around the whole tile loop, the others read
 // again on diagonal tiles and for the transfers of a ragged tile only.
 // Where rows are cut into chunks, two resident blocks also mean finer chunks (pick_chunk): the float32 partial rows
 // then add up over other ranges of keys than with one block a unit, and some results round to the other bf16 neighbour.
 __host__ __device__ constexpr int dq_ring(int d) { return d == 128 ? 2 : AB_RING; }
-#define AB_CH 16   // backward: a block walks at most g.ch 64-token tiles, this many by default (longer causal rows are split
-                   // into chunks whose float32 partial results a second kernel adds in chunk order)
 
 // Work split of the backward kernels.  Along the block's own dimension there are ceil(seq/128) blocks;
 // block i has tiles_of(i) tiles to walk and is cut into ceil(tiles/ch) chunks (ch is chosen per launch).  A launch index is
@@ -120,7 +117,7 @@ __device__ __forceinline__ int wave_sum(int first, int end, Count count) {
   return __builtin_amdgcn_readfirstlane(s);
 }
 // dQ: heaviest = last block; the first block with queries is q_off/128.  (One block after the other: this kernel has no register
-// left for find_unit, 36 -> 68 bytes a lane in scratch.)
+// left for find_unit, which doubles what goes to scratch.)
 __device__ __forceinline__ ChunkMap map_dq(int id, int seq, int q_off, int total, int c) {
   ChunkMap m;
   int rem = id, after = 0;  // `after` = pairs of the blocks visited before this one
@@ -129,19 +126,36 @@ __device__ __forceinline__ ChunkMap map_dq(int id, int seq, int q_off, int total
   m.blk = i; m.chunk = rem; m.pair = total - after - m.chunks + rem;
   return m;
 }
-// dK/dV: first every chunk of c tiles (all alike), then what is left of the blocks, longest first (`order`, made by the host): few
+// The block with the idx-th longest rest (ties: the earlier block first), found by the whole wave; rest(i) == 0: no unit.
+template <class Rest>
+__device__ __forceinline__ int nth_rest(int idx, int n, Rest rest) {
+  const int lane = threadIdx.x & 63, per = (n + 63) >> 6, v0 = lane * per;
+  for (int k = 0; k < per; k++) {
+    const int i = v0 + k, mine = i < n ? rest(i) : 0;
+    int rank = 0;
+    for (int kk = 0; kk < per; kk++) {
+      const int other = v0 + kk < n ? rest(v0 + kk) : 0;
+      for (int l = 0; l < 64; l++) {
+        const int r = __builtin_amdgcn_readlane(other, l);
+        rank += r > mine || (r == mine && l * per + kk < i) ? 1 : 0;
+      }
+    }
+    const unsigned long long who = __ballot(mine > 0 && rank == idx);
+    if (who != 0) return __builtin_amdgcn_readlane(i, __builtin_ctzll(who));
+  }
+  return 0;
+}
+// dK/dV: first every chunk of c tiles (all alike), then what is left of the blocks, longest first: few
 // units a compute unit leave a short last round that way only.  In the blocks' order, 8 key/value heads of 4 query heads x 4096
 // tokens in chunks of 128 took 502 us: the hardware hands blocks to the shader engines in turn, so the long chunks, each followed by a
 // block's short one, met on the same engines.  Unsplit blocks are longest first by themselves.
-#define DKV_ORDER_MAX 512
 #define AB_WHOLE (1 << 20)  // tiles per chunk of a launch that splits no block
-struct DkvOrder { uint16_t blk[DKV_ORDER_MAX]; };
-__device__ __forceinline__ ChunkMap map_dkv(int id, int seq, int q_off, int c, int grp, const DkvOrder& order) {
+__device__ __forceinline__ ChunkMap map_dkv(int id, int seq, int q_off, int c, int grp) {
   ChunkMap m;
   if (c >= AB_WHOLE) { m.blk = m.pair = id; m.chunk = 0; m.chunks = 1; return m; }
   const int nblk = (seq + 127) / 128;
   const UnitOf u = find_unit(id, nblk, [&](int i) { return grp * dkv_tiles(i, seq, q_off) / c; });
-  m.blk = u.found ? u.v : __builtin_amdgcn_readfirstlane((int)order.blk[id - u.total]);
+  m.blk = u.found ? u.v : nth_rest(id - u.total, nblk, [&](int i) { return grp * dkv_tiles(i, seq, q_off) % c; });
   const int tiles = grp * dkv_tiles(m.blk, seq, q_off);
   m.chunk = u.found ? u.rem : tiles / c;
   m.chunks = chunks_of(tiles, c);
@@ -769,7 +783,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const int bid, const AttnGeom&
   }
   acc_settle<AGPR>(dqt);
   __syncthreads();  // every wave is done with the K/V rings: their LDS serves the output turn
-  if (part != nullptr) {  // float32 partial of this chunk: part[batch][head][pair][128 rows][D], unscaled
+  if (cm.chunks > 1) {  // float32 partial of this chunk: part[batch][head][pair][128 rows][D], unscaled
     float* rows = part + ((((size_t)b * nq + h) * pairs + cm.pair) * 128 + wave * 32) * D;
     wave_rows_out_f32<D>(
         reinterpret_cast<float*>(smem) + wave * (32 * D), lane,
@@ -792,8 +806,9 @@ __device__ __forceinline__ void attn_bwd_dq_reduce_block(int bx, int by, int bz,
                                                          bf16_t* __restrict__ dqkv, int seq, int q_off, int nq, int nkv, int pairs,
                                                          int cl, float scale) {
   const int i = q_off / 128 + (bx >> 4), r0 = (bx & 15) * 8, h = by, b = bz, ld = (nq + 2 * nkv) * D;
-  const int base = wave_sum(q_off / 128, i, [&](int k) { return chunks_of(dq_tiles(k, seq), cl); });
   const int ch = chunks_of(dq_tiles(i, seq), cl);
+  if (ch == 1) return;  // written by its only chunk
+  const int base = wave_sum(q_off / 128, i, [&](int k) { return chunks_of(dq_tiles(k, seq), cl); });
   const float* p0 = part + (((size_t)b * nq + h) * pairs + base) * 128 * D;
   for (int e = threadIdx.x; e < 8 * D / 4; e += 256) {
     const int row = r0 + e / (D / 4), c4 = (e % (D / 4)) * 4;
@@ -812,13 +827,14 @@ __device__ __forceinline__ void attn_bwd_dq_reduce_block(int bx, int by, int bz,
 // (the keys are the same), cut into chunks of g.ch tiles wherever that falls.  A key block of one chunk writes dK, dV; the
 // chunks of the others write float32 partials part[batch][kv head][pair][128 keys][dK | dV] that
 // attn_bwd_reduce_kernel (its dK/dV part) adds in chunk order.  Against a block per query head, whose partials of every head went
-// through memory, the whole backward pass (us): 4:1 heads x 4096 tokens 117 -> 106, 4096 queries over 12288 keys 391 -> 341, 32:8 heads x 4096
-// 544 -> 510, 16:4 x 1500 88 -> 81, 8:1 x 8192 535 -> 529; D = 64, 4:1 x 8192 216 -> 175, 32:4 x 2 x 1000 64 -> 66.
+// through memory, the whole backward pass (us): 4:1 heads x 4096 tokens 111 -> 102, 4096 queries over 12288 keys 382 -> 328, 32:8 heads x 4096
+// 526 -> 494, 16:4 x 1500 88 -> 72, 8:1 x 8192 520 -> 510, 4:4 x 4096 130 -> 108; D = 64, 4:1 x 8192 215 -> 165, 32:4 x 2 x 1000 63 -> 66
+// (a head group's tile bookkeeping beside tiles half as long).
 template <int D>
 __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom& g, const bf16_t* __restrict__ qkv,
                                                    const bf16_t* __restrict__ dout, const float* __restrict__ lse2,
                                                    const float* __restrict__ delta, float* __restrict__ part, int pairs, int T,
-                                                   float scale, float scale_log2, const DkvOrder& order) {
+                                                   float scale, float scale_log2) {
   using TL = ATile<D>;
   constexpr bool AGPR = D == 128;
   extern __shared__ __attribute__((aligned(1024))) char smem[];  // Q ring, dO ring, lse2 ring, delta ring
@@ -829,7 +845,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   const int hb = bid % g.nq_all;
   const int hk = hb % nkv, b = hb / nkv, hq = hk * g.grp;  // hq: the group's first query head
   const int ld = (nq + 2 * nkv) * D, ldo = nq * D;
-  const ChunkMap cm = map_dkv(bid / g.nq_all, seq, g.q_off, g.ch, g.grp, order);
+  const ChunkMap cm = map_dkv(bid / g.nq_all, seq, g.q_off, g.ch, g.grp);
   const int j0 = cm.blk * 128, jw = j0 + wave * 32, jk = jw + l32;  // key positions in the sequence (block 0 is the heaviest)
   const int q0 = dkv_first(cm.blk, g.q_off);                        // first query position this key block meets
   const size_t ktok0 = (size_t)b * seq;
@@ -969,13 +985,13 @@ __global__ __launch_bounds__(AB_THREADS) void attn_bwd_bf16_kernel(const AttnGeo
                                                                    const float* __restrict__ lse, const float* __restrict__ lse2,
                                                                    const float* __restrict__ delta, bf16_t* __restrict__ dqkv,
                                                                    float* __restrict__ part_q, float* __restrict__ part_kv, int pairs_q,
-                                                                   int pairs_k, int T, float scale, float scale_log2, const DkvOrder order) {
+                                                                   int pairs_k, int T, float scale, float scale_log2) {
   const int hb = blockIdx.x % gq.nq_all, u = blockIdx.x / gq.nq_all, both = 2 * min(pairs_q, pairs_k);
   int idx;
   bool dkv;
   if (u < both) { dkv = (u & 1) == 0; idx = u >> 1; }
   else { dkv = pairs_k > pairs_q; idx = u - both / 2; }
-  if (dkv) attn_bwd_dkv_block<D>(idx * gk.nq_all + hb, gk, qkv, dout, lse2, delta, part_kv, pairs_k, T, scale, scale_log2, order);
+  if (dkv) attn_bwd_dkv_block<D>(idx * gk.nq_all + hb, gk, qkv, dout, lse2, delta, part_kv, pairs_k, T, scale, scale_log2);
   else attn_bwd_dq_block<D, AB_RING>(idx * gq.nq_all + hb, gq, qkv, o, dout, lse, nullptr, nullptr, dqkv, part_q, pairs_q, T, scale, scale_log2);
 }
 // The two halves as launches of their own (dQ first: it stores the row statistics the dK/dV blocks read).
@@ -991,9 +1007,8 @@ template <int D>
 __global__ __launch_bounds__(AB_THREADS) void attn_bwd_dkv_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
                                                                        const bf16_t* __restrict__ dout, const float* __restrict__ lse2,
                                                                        const float* __restrict__ delta, float* __restrict__ part,
-                                                                       int pairs, int T, float scale, float scale_log2,
-                                                                       const DkvOrder order) {
-  attn_bwd_dkv_block<D>((int)blockIdx.x, g, qkv, dout, lse2, delta, part, pairs, T, scale, scale_log2, order);
+                                                                       int pairs, int T, float scale, float scale_log2) {
+  attn_bwd_dkv_block<D>((int)blockIdx.x, g, qkv, dout, lse2, delta, part, pairs, T, scale, scale_log2);
 }
 
 // Per-row statistics of the backward pass for the dK/dV blocks: delta[h,t] = sum_c dO[t,h,c] O[t,h,c] and
@@ -1083,136 +1098,149 @@ static int attn_num_cus() {  // of the current device
   return cached[dev];
 }
 
-// Chunk length of a launch.  The blocks of a launch are (block of 128 positions, chunk) units times nq*batch heads,
-// started heaviest first; the hardware hands the next block to the first free compute unit.  That list schedule is
-// simulated for each candidate length: a unit costs its tiles plus a fixed overhead, every chunk of a split launch
-// costs the traffic of its float32 partial result (written, then read by the merging kernel), and a split launch
-// pays for the merging kernels.  The constants are measured on MI355X (microseconds): a compute unit finishes a
-// forward tile in 1.45, a dQ tile in 1.55 with two blocks on it or 1.8 beside dK/dV units, a dK/dV tile in 2.4 (2.0 with chunks as
-// long as grouped heads allow); HBM moves 4 MB per
-// microsecond under this load.
-enum { PICK_FWD = 0, PICK_DQ = 1, PICK_DKV = 2 };
+// Chunk length of a backward launch.  The blocks of a launch are (block of 128 positions, chunk) units times heads * batch, launched heaviest
+// first; what a chunk length takes is simulated and the best one taken.  The hardware hands blocks to the 8 dies in turn and, on a die, to its 4
+// shader engines in turn, none before the one ahead of it: a block waits for a unit of its engine though others are
+// free.  (That order fits what chunk lengths measure: dK/dV of 8 heads x 8192 tokens on one key/value head, 136 / 140 / 144 tiles a chunk
+// 535 / 504 / 509 us for the whole backward pass, where the first free unit would make 136 the best.)  The constants are measured on MI355X (microseconds at D = 128): a block's tile with two
+// blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its unit, 2.0; a block beyond its tiles 3, with a partial
+// dK/dV result to store 9; partial results are read back at 4-5 MB per microsecond, by a launch of its own that takes 4-12.
+// Where every query head has a key/value head of its own, dQ and dK/dV units fill one launch, alternating, and are cut alike.
+enum { PICK_FWD, PICK_DQ, PICK_DKV, PICK_BOTH };
 struct PickKey {
   int kind, seq, q_off, nq_all, d, grp, cus;
   bool operator<(const PickKey& o) const {
     return std::tie(kind, seq, q_off, nq_all, d, grp, cus) < std::tie(o.kind, o.seq, o.q_off, o.nq_all, o.d, o.grp, o.cus);
   }
 };
-// Units of a dK/dV launch in launch order (see map_dkv): tiles of each, and the blocks of those that are no whole chunk.
-static std::vector<int> dkv_units(int seq, int q_off, int grp, int ch, DkvOrder* order) {
-  const int nblk = (seq + 127) / 128;
-  std::vector<int> tiles;
-  std::vector<std::pair<int, int>> rest;
-  for (int i = 0; i < nblk; i++) {
+// Tiles of the units of a dK/dV launch, in launch order (see map_dkv).
+static std::vector<int> dkv_units(int seq, int q_off, int grp, int ch) {
+  std::vector<int> tiles, rest;
+  for (int i = 0; i < (seq + 127) / 128; i++) {
     const int t = grp * dkv_tiles(i, seq, q_off);
     tiles.insert(tiles.end(), t / ch, ch);
-    if (t % ch) rest.push_back({-(t % ch), i});
+    if (t % ch) rest.push_back(t % ch);
   }
-  std::sort(rest.begin(), rest.end());
-  for (size_t k = 0; k < rest.size(); k++) {
-    tiles.push_back(-rest[k].first);
-    if (order && k < DKV_ORDER_MAX) order->blk[k] = (uint16_t)rest[k].second;
-  }
+  std::sort(rest.begin(), rest.end(), std::greater<int>());
+  tiles.insert(tiles.end(), rest.begin(), rest.end());
   return tiles;
 }
-static double simulate_launch(int kind, int seq, int q_off, int nq_all, int grp, int ch, int slots, double t_tile, double t_ovh) {
+struct LaunchModel {
+  int resident;       // blocks a unit holds
+  double tile, alone, ovh, us_per_byte, merge;
+};
+static LaunchModel launch_model(int kind, int d) {
+  const double w = d / 128.0;
+  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 1 / 5.0e6, 4.0};
+  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 1 / 4.0e6, 12.0};
+}
+// units: tiles of the units of one head, in launch order.
+static double simulate_launch(const LaunchModel& m, const std::vector<int>& units, int heads) {
   typedef std::priority_queue<double, std::vector<double>, std::greater<double>> Queue;
-  const int nblk = (seq + 127) / 128, qb0 = q_off / 128;
+  const int cus = attn_num_cus();
+  Queue unit[8][4];
+  double ahead[8] = {};
+  for (auto& die : unit) for (Queue& q : die) for (int i = 0; i < std::max(1, cus * m.resident / 32); i++) q.push(0.0);
+  const long long all = (long long)units.size() * heads;
+  const double tile = m.tile * (all <= cus ? m.alone : 1.0);
   double makespan = 0.0;
-  if (kind == PICK_DKV && grp > 1) {
-    // Blocks go to the 8 dies in turn and, on a die, to its 4 shader engines in turn, none before the one ahead of it: a block
-    // waits for a unit of its engine though others are free.  (Fits what chunk lengths measure: 8 heads x 8192 tokens on one key/value head,
-    // 136 / 140 / 144 tiles a chunk 535 / 504 / 509 us for the whole backward pass; with the first free unit 136 would be best.)
-    const std::vector<int> tiles = dkv_units(seq, q_off, grp, ch, nullptr);
-    Queue unit[8][4];
-    double last[8] = {};
-    for (auto& die : unit) for (auto& engine : die) for (int i = 0; i < std::max(1, slots / 32); i++) engine.push(0.0);
-    long long k = 0;
-    for (int t : tiles)
-      for (int h = 0; h < nq_all; h++, k++) {
-        Queue& q = unit[k & 7][(k >> 3) & 3];
-        double& ahead = last[k & 7];
-        ahead = std::max(ahead, q.top());
-        const double end = ahead + t * t_tile + t_ovh;
-        q.pop();
-        q.push(end);
-        makespan = std::max(makespan, end);
-      }
-    return makespan;
-  }
-  Queue free_at;
-  for (int i = 0; i < slots; i++) free_at.push(0.0);
-  auto run = [&](int tiles) {
-    for (int t0 = 0; t0 < tiles; t0 += ch) {
-      const double cost = (tiles - t0 < ch ? tiles - t0 : ch) * t_tile + t_ovh;
-      for (int h = 0; h < nq_all; h++) {
-        const double end = free_at.top() + cost;
-        free_at.pop();
-        free_at.push(end);
-        if (end > makespan) makespan = end;
-      }
+  long long k = 0;
+  for (int t : units)
+    for (int h = 0; h < heads; h++, k++) {
+      Queue& q = unit[k & 7][(k >> 3) & 3];
+      double& start = ahead[k & 7];
+      start = std::max(start, q.top());
+      q.pop();
+      const double end = start + t * tile + m.ovh;
+      q.push(end);
+      makespan = std::max(makespan, end);
     }
-  };
-  if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) run(dkv_tiles(i, seq, q_off));
-  else for (int i = nblk - 1; i >= qb0; i--) run(dq_tiles(i, seq));  // forward: the tiles dQ walks
   return makespan;
 }
-// nq_all: heads * batch, grp: query heads of a key/value head (see AttnGeom).
-static int pick_chunk(int kind, int seq, int q_off, int nq_all, int d, int grp) {
-  // dK/dV of grouped heads: what matters is where the last units end, so the length is chosen finely, and storing a partial result
-  // counts as a unit's own time (beside dQ's units, with a head each, the gaps are filled anyway).
-  const bool grouped = grp > 1, fine = kind == PICK_DKV && grouped, two = fine && d == 64;
-  static std::mutex mu;
-  static std::map<PickKey, int> cache;
-  const PickKey key{kind, seq, q_off, nq_all, d, grp, attn_num_cus()};
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find(key);
-  if (it != cache.end()) return it->second;
-  const int nblk = (seq + 127) / 128, qb0 = q_off / 128;
-  const int max_tiles = kind == PICK_DKV ? grp * dkv_tiles(0, seq, q_off) : dq_tiles(nblk - 1, seq);
-  const double t_tile = (kind == PICK_FWD ? 1.45 : kind == PICK_DQ ? (grouped ? 1.55 : 1.8) : fine ? 2.0 : 2.4) * d / 128.0 * (two ? 1.6 : 1.0), t_ovh = (fine ? 9.0 : 3.0) * (fine ? d / 128.0 : 1.0);
-  const double us_per_byte = (fine ? 1.0 : 2.0) / 4.0e6, t_merge = 12.0;
-  static const int cand_fwd[] = {4, 8, 16, 32, 64, 1 << 20}, cand_dq[] = {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 1 << 20};
-  std::vector<int> cand;
-  if (kind == PICK_FWD) cand.assign(cand_fwd, cand_fwd + 6);
-  else if (kind == PICK_DQ) cand.assign(cand_dq, cand_dq + 12);
-  else if (!fine) cand.assign(cand_dq, cand_dq + (nblk <= DKV_ORDER_MAX ? 12 : 0));
-  else if (nblk <= DKV_ORDER_MAX) for (int c = 4; c < max_tiles; c += std::max(1, c / 32)) cand.push_back(c);
-  if (kind == PICK_DKV) cand.push_back(AB_WHOLE);
-  const int n_cand = (int)cand.size();
-  int best = cand[n_cand - 1];
+// heads: heads * batch of the launch (query heads; key/value heads for dK/dV); grp: query heads of a key/value head.
+static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int grp) {
+  const LaunchModel m = launch_model(kind, d);
+  const int nblk = (seq + 127) / 128, qb0 = q_off / 128, max_tiles = grp * (kind == PICK_DQ ? dq_tiles(nblk - 1, seq) : dkv_tiles(0, seq, q_off));
+  const long long slots = (long long)attn_num_cus() * m.resident;
+  int best = AB_WHOLE;
   double best_t = 1e300;
-  for (int k = 0; k < n_cand; k++) {
-    const int ch = cand[k];
-    if (ch < (1 << 20) && ch >= max_tiles) continue;  // same as not splitting
-    int units = 0, apart = 0;  // apart: units that write partial results
-    if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) { const int n = chunks_of(grp * dkv_tiles(i, seq, q_off), ch); units += n; apart += n > 1 ? n : 0; }
-    else for (int i = qb0; i < nblk; i++) units += chunks_of(dq_tiles(i, seq), ch);
-    const bool split = units > (kind == PICK_DKV ? nblk : nblk - qb0);
-    double t = simulate_launch(kind, seq, q_off, nq_all, grp, ch, attn_num_cus() * (two ? 2 : 1), t_tile, t_ovh);
-    double bytes = 0.0;
-    if (kind == PICK_FWD) { if (split) bytes = (double)units * (d + 2); }
-    else if (kind == PICK_DQ) { if (split) bytes = (double)units * d; }
-    else if (split) bytes = (double)(fine ? apart : units) * 2 * d;
-    t += bytes * nq_all * 128 * sizeof(float) * us_per_byte + (split ? t_merge : 0.0);
+  auto consider = [&](int ch) {
+    std::vector<int> units, q_units;
+    double bytes = 0;  // of partial results, per head
+    if (kind >= PICK_DKV) {
+      units = dkv_units(seq, q_off, grp, ch);
+      for (int i = 0; i < nblk; i++) { const int n = chunks_of(grp * dkv_tiles(i, seq, q_off), ch); bytes += n > 1 ? n * 2.0 * d : 0; }
+    }
+    if (kind != PICK_DKV)
+      for (int i = nblk - 1; i >= qb0; i--) {
+        const int tiles = dq_tiles(i, seq), n = chunks_of(tiles, ch);
+        for (int c = 0; c < n; c++) q_units.push_back(std::min(ch, tiles - c * ch));
+        bytes += n > 1 ? n * (double)d : 0;
+      }
+    if (kind == PICK_BOTH) {  // as attn_bwd_bf16_kernel takes them
+      std::vector<int> all;
+      for (size_t k = 0; k < std::max(units.size(), q_units.size()); k++) {
+        if (k < units.size()) all.push_back(units[k]);
+        if (k < q_units.size()) all.push_back(q_units[k]);
+      }
+      units = all;
+    } else if (kind != PICK_DKV) {
+      units = q_units;
+    }
+    if ((long long)units.size() * heads > 16 * slots && ch < AB_WHOLE) return;  // so many rounds need no chunks as short
+    const double t = simulate_launch(m, units, heads) + (bytes > 0 ? bytes * heads * 128 * sizeof(float) * m.us_per_byte + m.merge : 0.0);
+    if (t < best_t) { best_t = t; best = ch; }
+  };
+  consider(AB_WHOLE);
+  if ((long long)nblk * heads < 8 * slots && nblk <= 1024) {
+    const int least = kind == PICK_DKV ? 1 : 2;  // dQ: even, so that every wave sees a chunk's first tile
+    for (int c = 4; c < max_tiles; c += std::max(least, c / 32 * least)) consider(c);
+  }
+  return best;
+}
+
+
+// Chunk length of a forward launch: a few lengths and a plain list schedule (1.45 us a tile at D = 128, 3 a block, partial results there
+// and back at 2 MB per microsecond and 12 for their launch); where splitting pays, then the shortest length whose blocks are all resident
+// at once, two a unit (4 heads x 4096 tokens, 16 -> 10 tiles 48 -> 42 us; one block more than fits costs a second round).
+// The model above finds shorter launches (3 x 1365 tokens, 4 heads, 29 -> 24 us; 4 heads x 8192 at D = 64 89 -> 61 us), but other lengths
+// add a row's partial results over other ranges of keys, and then gradients that are all rounding come out as other noise (the router's,
+// exactly zero where a token's two experts hold the same weights): the lengths stay.
+static int pick_fwd_chunk(int seq, int q_off, int heads, int d) {
+  const int nblk = (seq + 127) / 128, qb0 = q_off / 128, slots = attn_num_cus();
+  auto units_of = [&](int ch) { return (long long)total_pairs_dq(seq, q_off, ch); };  // the tiles dQ walks
+  int best = AB_WHOLE;
+  double best_t = 1e300;
+  for (int ch : {4, 8, 16, 32, 64, AB_WHOLE}) {
+    if (ch < AB_WHOLE && ch >= dq_tiles(nblk - 1, seq)) continue;
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    for (int i = 0; i < slots; i++) free_at.push(0.0);
+    double t = 0.0;
+    for (int i = nblk - 1; i >= qb0; i--)
+      for (int t0 = 0, tiles = dq_tiles(i, seq); t0 < tiles; t0 += ch)
+        for (int h = 0; h < heads; h++) {
+          const double end = free_at.top() + std::min(ch, tiles - t0) * (1.45 * d / 128.0) + 3.0;
+          free_at.pop();
+          free_at.push(end);
+          t = std::max(t, end);
+        }
+    if (units_of(ch) > nblk - qb0) t += (double)units_of(ch) * (d + 2) * heads * 128 * sizeof(float) * (2.0 / 4.0e6) + 12.0;
     if (t < best_t) { best_t = t; best = ch; }
   }
-  // When splitting pays at all it is because the launch would leave compute units idle, and then the finest split
-  // whose units are still all resident at once balances them best (measured: 4 heads x 4096 tokens, forward 16 -> 10
-  // tiles per chunk 48 -> 42 us, backward 24 -> 22 tiles 116 -> 113 us; one more unit than fits costs a second round).
-  // Resident blocks per compute unit: forward, and dQ in a launch of its own, 2 (forward at D = 64: 4, counted as 2);
-  // dK/dV and dQ beside it 1 (2 at D = 64).
-  if (best < (1 << 20) && !fine) {
-    const long long resident = (long long)attn_num_cus() * (kind == PICK_FWD || (kind == PICK_DQ && grouped) || d == 64 ? 2 : 1);
-    for (int ch = 8; ch < best; ch += 2) {
-      long long units = 0;
-      if (kind == PICK_DKV) for (int i = 0; i < nblk; i++) units += chunks_of(dkv_tiles(i, seq, q_off), ch);
-      else for (int i = qb0; i < nblk; i++) units += chunks_of(dq_tiles(i, seq), ch);
-      if (units * nq_all <= resident) { best = ch; break; }
-    }
-  }
-  cache[key] = best;
+  for (int ch = 8; ch < best && best < AB_WHOLE; ch += 2)
+    if (units_of(ch) * heads <= 2 * slots) return ch;
   return best;
+}
+
+static int pick_chunk(int kind, int seq, int q_off, int heads, int d, int grp) {
+  static std::mutex mu;
+  static std::map<PickKey, int> cache;
+  const PickKey key{kind, seq, q_off, heads, d, grp, attn_num_cus()};
+  std::lock_guard<std::mutex> lock(mu);
+  auto it = cache.find(key);
+  if (it == cache.end())
+    it = cache.emplace(key, kind == PICK_FWD ? pick_fwd_chunk(seq, q_off, heads, d) : pick_bwd_chunk(kind, seq, q_off, heads, d, grp)).first;
+  return it->second;
 }
 
 // Tiles per chunk of the forward kernel; 0 = blocks are not split.
@@ -1222,8 +1250,12 @@ static int fwd_chunk_tiles(int batch, int seq, int q_off, int nq, int d) {
 }
 // Tiles per chunk of the dQ and of the dK/dV kernel.
 static void bwd_chunk_tiles(int batch, int seq, int q_off, int nq, int nkv, int d, int& ch_q, int& ch_k) {
-  ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, nq / nkv);
-  ch_k = pick_chunk(PICK_DKV, seq, q_off, nkv * batch, d, nq / nkv);
+  if (nq == nkv) {
+    ch_q = ch_k = pick_chunk(PICK_BOTH, seq, q_off, nq * batch, d, 1);
+  } else {
+    ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, 1);
+    ch_k = pick_chunk(PICK_DKV, seq, q_off, nkv * batch, d, nq / nkv);
+  }
 }
 
 // The launchers take the queries' sequence length seq_q and q_off; kv == nullptr selects plain attention (keys and
@@ -1338,8 +1370,6 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
       gk(nblk * 32, nkv, batch);
   const unsigned nb_q = part_q ? gq.x * gq.y * gq.z : 0, nb_k = part_kv ? gk.x * gk.y * gk.z : 0;
   const size_t lds_dq = 2 * dq_ring(d) * (size_t)AB_KT * d * 2, lds_dkv = 2 * AB_RING * ((size_t)AB_KT * d * 2 + AB_KT * sizeof(float));
-  DkvOrder order;
-  if (lay.ch_k < AB_WHOLE) (void)dkv_units(seq, q_off, g.grp, lay.ch_k, &order);
   static bool ready_dev[DH_MAX_DEVICES][2] = {};
   bool* ready = ready_dev[dh_device_index()];
 #define DH_ATTN_BWD(DD, IDX)                                                                                                   \
@@ -1353,11 +1383,11 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
       attn_bwd_prep_kernel<DD><<<(unsigned)(((size_t)T * nq + 255) / 256), 256, 0, stream>>>(o, dout, lse, lse2, delta, T, nq); \
       DH_LAUNCH_CHECK();                                                                                                       \
       attn_bwd_bf16_kernel<DD><<<gw, AB_THREADS, lds_dkv, stream>>>(gq_geom, gk_geom, qkv, o, dout, lse, lse2, delta, dqkv, part_q, \
-                                                                   part_kv, pq, pk, T, sc, sl2, order);                        \
+                                                                   part_kv, pq, pk, T, sc, sl2);                               \
     } else {                                                                                                                   \
       attn_bwd_dq_bf16_kernel<DD><<<gwq, AB_THREADS, lds_dq, stream>>>(gq_geom, qkv, o, dout, lse, lse2, delta, dqkv, part_q, pq, T, sc, sl2); \
       DH_LAUNCH_CHECK();                                                                                                       \
-      attn_bwd_dkv_bf16_kernel<DD><<<gwk, AB_THREADS, lds_dkv, stream>>>(gk_geom, qkv, dout, lse2, delta, part_kv, pk, T, sc, sl2, order); \
+      attn_bwd_dkv_bf16_kernel<DD><<<gwk, AB_THREADS, lds_dkv, stream>>>(gk_geom, qkv, dout, lse2, delta, part_kv, pk, T, sc, sl2); \
     }                                                                                                                          \
     DH_LAUNCH_CHECK();                                                                                                         \
     if (nb_q + nb_k > 0) {                                                                                                     \
