@@ -233,13 +233,14 @@ bool dh_glu_fwd_fits(int T, int F, int H);
 int dh_launch_gemm_swiglu_fwd_bf16(int T, int F, int H, const bf16_t* x, const bf16_t* Wgu, bf16_t* gu, bf16_t* a, hipStream_t stream);
 bool dh_glu_bwd_fits(int T, int F, int H);
 int dh_launch_gemm_swiglu_bwd_bf16(int T, int F, int H, const bf16_t* dy, const bf16_t* Wd, const bf16_t* gu, bf16_t* dgu, hipStream_t stream);
-// Data and weight gradient of a linear layer in one launch (see gemm_bf16.hip); *_pays: whether that is expected to be faster.
-bool dh_gemm_pair_pays(int T, int k, int n);
+// Data and weight gradient of a linear layer in one launch (see gemm_bf16.hip); *_pays: whether that is expected to be faster; beside:
+// while another stream's kernels run.
+bool dh_gemm_pair_pays(int T, int k, int n, bool beside);
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
-                             hipStream_t stream);
-bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n);
+                             bool beside, hipStream_t stream);
+bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
-                                     bf16_t* dX, float* dW, hipStream_t stream);
+                                     bf16_t* dX, float* dW, bool beside, hipStream_t stream);
 // Attention launchers: seq = queries per sequence; kv == nullptr selects plain causal attention over the packed
 // qkv rows, otherwise keys/values come from kv[batch*(q_off+seq), ldkv] and their gradients go to dkv likewise.
 int dh_launch_attn_fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv,

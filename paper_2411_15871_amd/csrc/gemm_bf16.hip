@@ -65,7 +65,7 @@ struct GemmPlan {
   int bm, bn, ranges, range_k, splits, k_per_split;  // K ranges that are summed apart, and the K of one
   int k_chain;                          // the K ranges are summed one after the other in the block (0: not)
   int tail_tiles, tail_splits, tail_k;  // tail launch (0 tiles = none): its tiles, K splits and K per split
-  double ns;                            // estimated time
+  double ns, cu_ns;                     // estimated time; what the launches keep the chip from others
 };
 
 static int num_cus() {  // of the current device
@@ -156,10 +156,11 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
     double ns = (double)((blocks + cus - 1) / cus) * tt.block;
     // A long product that leaves units idle leaves them to the other strand: half of what those would have done counts.
     if (ns > kLong) ns = 0.5 * (ns + tt.block * blocks / cus);
-    ns += kLaunch;
-    if (splits > 1) ns += kSecondLaunch + (double)mn * (4 * splits + (acc ? 8 : 2)) / 5000;  // the partials read at 5 TB/s
+    const double sum = splits > 1 ? kSecondLaunch + (double)mn * (4 * splits + (acc ? 8 : 2)) / 5000 : 0;  // the partials read at 5 TB/s
+    ns += kLaunch + sum;
     if (p.ns != 0 && ns >= p.ns) return;
     p.ns = ns;
+    p.cu_ns = tt.block * blocks / cus + kLaunch / 2 + sum;
     p.cfg = tt.cfg;
     p.bm = c.bm; p.bn = c.bn;
     p.splits = splits;
@@ -179,9 +180,13 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
 
 // The tile shape of a data and a weight gradient that go out as one launch, each with the K ranges it has by itself (the same bits),
 // summed in the block.  False where two launches are expected to be as fast: large products, which fill the chip by themselves.
+// beside: another stream's kernels run at the same time, and use the units that a launch leaves idle: what the launch takes of the chip then
+// counts as much as when it ends.  (Two strands of 3 x 2727 tokens, 584 wide, heads of 64: 64x64 tiles for both gradients of the QKV projection
+// end as soon as two launches of large tiles, and take 1.6 times their unit time: step 561 -> 581 us; of 3010 tokens, 1408 wide
+// with heads of 64 572 -> 583; with this 564 and 528.)
 // The estimate hands the blocks of the product whose blocks take longer to the units first, then the other's to whichever is free.
 struct GemmShape { int M, N, K; };
-static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, GemmPlan& pd, GemmPlan& pw, bool& w_first) {
+static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool beside, GemmPlan& pd, GemmPlan& pw, bool& w_first) {
   const int cus = num_cus(), ng = std::max(1, groups);
   pd = choose_plan(d.M, d.N, d.K, false, (size_t)-1, groups);
   pw = choose_plan(w.M, w.N, w.K, true, (size_t)-1, groups);
@@ -189,7 +194,7 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, Gemm
   // A data gradient cut into many ranges would walk them one after the other, with weights that come from memory: 1344x512x4608
   // 35 us apart, 40 as one launch.  (A weight gradient's operands have just been written: 512x1024x4000 in seven ranges 26 -> 20.)
   if (pd.ranges > 4) return false;
-  const double apart = pd.ns + pw.ns;
+  const double shared = beside ? 0.5 : 0.0, apart = (1 - shared) * (pd.ns + pw.ns) + shared * (pd.cu_ns + pw.cu_ns);
   double best = 0;
   for (const TileCost& c : kTiles) {
     if (c.bm * c.bn == 256 * 256) continue;
@@ -216,7 +221,7 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, Gemm
       const double beside = std::min(t1, std::max(0.0, even - t1));
       end = std::max(end, 2 * beside + (t1 - beside) * (wf ? c.alone : c.alone_cold));
     }
-    const double ns = kLaunch + end;
+    const double ns = (1 - shared) * (kLaunch + end) + shared * (even + kLaunch / 2);
     if (best != 0 && ns >= best) continue;
     best = ns;
     w_first = wf;
@@ -231,7 +236,7 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, Gemm
   // (Nor where the weight gradient's float32 result is most of the work: a data gradient of few long blocks beside blocks that keep
   // the memory busy takes longer than by itself, T = 384, 3680 x 8496: 121 us apart, 158 as one launch.)
   // The second launch's gap is not in the estimate; of long products the forward strand's blocks use the units left idle.
-  return best < apart * (apart > kLong * 1.5 ? 0.95 : 1.03) && 8.0 * w.M * w.N * ng / 5000 < 0.5 * best;
+  return best < apart * (apart > kLong * 1.5 ? 0.95 : beside ? 1.0 : 1.03) && 8.0 * w.M * w.N * ng / 5000 < 0.5 * best;
 }
 
 // Launch indices of the tail launch: from the first index of the last round to the end of the (padded) index range.
@@ -423,37 +428,37 @@ static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w
     default: return launch_pair<8>(d, w, w_first, stream, n_groups);
   }
 }
-bool dh_gemm_pair_pays(int T, int k, int n) {
+bool dh_gemm_pair_pays(int T, int k, int n, bool beside) {
   if (T <= 0 || k % 8 || n % 8) return false;
   GemmPlan pd, pw;
   bool w_first;
-  return choose_pair({T, k, n}, {k, n, T}, 0, pd, pw, w_first);
+  return choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first);
 }
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
-                             hipStream_t stream) {
+                             bool beside, hipStream_t stream) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
   GemmPlan pd, pw;
   bool w_first;
-  (void)choose_pair({T, k, n}, {k, n, T}, 0, pd, pw, w_first);
+  (void)choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first);
   GemmArgs d = gemm_args(T, k, n, dY, W, dX, EPI_STORE_BF16, pd), w = gemm_args(k, n, T, X, dY, dW, EPI_ACC_F32, pw);
   if (gu != nullptr) { d.glu_mode = GLU_BWD; d.glu_f = k; d.glu_in = gu; }
   return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1);
 }
 // The same for the experts' linears (group_rows as in dh_launch_gemm_grouped_bf16; T bounds the rows of all groups).
-bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n) {
+bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside) {
   if (T <= 0 || n_groups > 64 || k % 8 || n % 8) return false;
   GemmPlan pd, pw;
   bool w_first;
   const int avg = std::max(1, T / n_groups);
-  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, pd, pw, w_first);
+  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first);
 }
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
-                                     bf16_t* dX, float* dW, hipStream_t stream) {
+                                     bf16_t* dX, float* dW, bool beside, hipStream_t stream) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "grouped gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
   GemmPlan pd, pw;
   bool w_first;
   const int avg = std::max(1, T / n_groups);
-  (void)choose_pair({avg, k, n}, {k, n, avg}, n_groups, pd, pw, w_first);
+  (void)choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first);
   return launch_pair_cfg(pd.cfg, grouped_args(1, n_groups, group_rows, T, n, k, dY, W, dX, pd),
                          grouped_args(2, n_groups, group_rows, T, k, n, X, dY, dW, pw), w_first, stream, n_groups);
 }

@@ -28,8 +28,9 @@ struct dh_layer {
   // SwiGLU runs in the epilogue of the gate/up projection (forward) / of the down projection's data gradient (backward)
   // where the shapes allow; the activation operator of that direction then launches nothing
   bool fuse_act_fwd, fuse_act_bwd;
-  // the linears (PairedLinear) whose data and weight gradient go out as one launch when the plan has them next to each other
-  bool pair_launch[4];
+  // the linears (PairedLinear) whose data and weight gradient go out as one launch when the plan has them next to each other: by
+  // themselves [0] and beside the other strand [1]
+  bool pair_launch[2][4];
   // backward all-reduces carried by a weight-gradient GEMM's launch: bit 1 = B_AR3 with B_FC1_WGRAD, bit 2 = B_AR4 with
   // B_QKV_WGRAD; in force only while the stand-ins run on a block budget (comm_blocks > 0)
   int fuse_comm;
@@ -256,10 +257,15 @@ static void choose_pairs(dh_layer* L) {
   const dh_layer_config& c = L->c;
   const bool bf = c.dtype == DH_BF16, moe = c.arch == DH_ARCH_MOE;
   const int Fin = c.arch == DH_ARCH_GPT ? c.ffn : 2 * c.ffn;
-  L->pair_launch[PAIR_FC2] = bf && (moe ? dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, c.ffn, c.hidden) : dh_gemm_pair_pays(L->T, c.ffn, c.hidden));
-  L->pair_launch[PAIR_FC1] = bf && (moe ? dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, c.hidden, Fin) : dh_gemm_pair_pays(L->T, c.hidden, Fin));
-  L->pair_launch[PAIR_PROJ] = bf && dh_gemm_pair_pays(L->T, L->n_o, c.hidden);
-  L->pair_launch[PAIR_QKV] = bf && dh_gemm_pair_pays(L->T, c.hidden, L->n_qkv);
+  for (int beside = 0; beside < 2; beside++) {
+    auto dense = [&](int k, int n) { return bf && dh_gemm_pair_pays(L->T, k, n, beside); };
+    auto ffn = [&](int k, int n) { return moe ? bf && dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, k, n, beside) : dense(k, n); };
+    bool* pays = L->pair_launch[beside];
+    pays[PAIR_FC2] = ffn(c.ffn, c.hidden);
+    pays[PAIR_FC1] = ffn(c.hidden, Fin);
+    pays[PAIR_PROJ] = dense(L->n_o, c.hidden);
+    pays[PAIR_QKV] = dense(c.hidden, L->n_qkv);
+  }
 }
 
 extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
@@ -992,7 +998,7 @@ static int run_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipSt
 }
 
 // The linear whose data gradient is `op` and whose weight gradient is `next`, if the two are to share a launch; -1 otherwise.
-static int paired_linear(const dh_layer* L, int op, int next) {
+static int paired_linear(const dh_layer* L, int op, int next, bool beside) {
   static const int llama[4][2] = {{DH_B_FC2_DGRAD, DH_B_FC2_WGRAD}, {DH_B_FC1_DGRAD, DH_B_FC1_WGRAD}, {DH_B_PROJ_DGRAD, DH_B_PROJ_WGRAD}, {DH_B_QKV_DGRAD, DH_B_QKV_WGRAD}};
   static const int cp[4][2] = {{DH_CB_FC2_DGRAD, DH_CB_FC2_WGRAD}, {DH_CB_FC1_DGRAD, DH_CB_FC1_WGRAD}, {DH_CB_PROJ_DGRAD, DH_CB_PROJ_WGRAD}, {DH_CB_QKV_DGRAD, DH_CB_QKV_WGRAD}};
   static const int gpt[4][2] = {{DH_GB_FC2_DGRAD, DH_GB_FC2_WGRAD}, {DH_GB_FC1_DGRAD, DH_GB_FC1_WGRAD}, {DH_GB_PROJ_DGRAD, DH_GB_PROJ_WGRAD}, {DH_GB_QKV_DGRAD, DH_GB_QKV_WGRAD}};
@@ -1001,22 +1007,22 @@ static int paired_linear(const dh_layer* L, int op, int next) {
   for (int i = 0; i < 4; i++) {
     if (ops[i][0] != op || ops[i][1] != next) continue;
     if ((i == PAIR_FC1 && fused_collective(L, 1)) || (i == PAIR_QKV && fused_collective(L, 2))) return -1;  // the weight gradient rides in an all-reduce's launch
-    return L->pair_launch[i] ? i : -1;
+    return L->pair_launch[beside][i] ? i : -1;
   }
   return -1;
 }
-static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, hipStream_t s) {
+static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, bool beside, hipStream_t s) {
   const dh_layer_config& c = L->c;
   const int T = L->T, Tf = L->Tf, H = c.hidden, F = c.ffn;
   const bool gpt = c.arch == DH_ARCH_GPT, moe = c.arch == DH_ARCH_MOE;
   const char* sv = (const char*)b.saved;
   auto dense = [&](int k, int n, const void* dY, const void* W, const void* X, size_t dX, float* dW, const void* gu = nullptr) {
-    const int rc = dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, s);
+    const int rc = dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside, s);
     return rc || !gpt ? rc : gpt_bias_grad(L, which, b, ws, s);
   };
   auto experts = [&](int k, int n, size_t dY, const void* W, size_t X, size_t dX, float* dW) {
     return dh_launch_gemm_grouped_pair_bf16(c.n_local_experts, moe_tables_of(L, b.saved).group_rows, Tf, k, n, (const bf16_t*)(ws + dY), (const bf16_t*)W,
-                                            (const bf16_t*)(sv + X), (bf16_t*)(ws + dX), dW, s);
+                                            (const bf16_t*)(sv + X), (bf16_t*)(ws + dX), dW, beside, s);
   };
   switch (which) {
     case PAIR_FC2:
@@ -1103,9 +1109,9 @@ extern "C" int dh_layer_bwd(dh_layer* L, const dh_bwd_args* b, void* ws, size_t 
   int order[DH_MAX_OPS];
   default_order(L->gb, order);
   for (int k = 0; k < L->gb.n_ops; k++) {
-    const int pair = k + 1 < L->gb.n_ops ? paired_linear(L, order[k], order[k + 1]) : -1;
+    const int pair = k + 1 < L->gb.n_ops ? paired_linear(L, order[k], order[k + 1], false) : -1;
     if (pair >= 0) k++;
-    rc = pair >= 0 ? run_bwd_pair(L, pair, *b, (char*)ws, (hipStream_t)stream) : run_bwd_op(L, order[k], *b, (char*)ws, (hipStream_t)stream);
+    rc = pair >= 0 ? run_bwd_pair(L, pair, *b, (char*)ws, false, (hipStream_t)stream) : run_bwd_op(L, order[k], *b, (char*)ws, (hipStream_t)stream);
     if (rc) return rc;
   }
   return DH_OK;
@@ -1243,10 +1249,10 @@ static int enqueue_si(dh_layer* L, dh_layer* LB, const dh_fwd_args* alpha, const
           continue;
         }
         const int next = bj < p.b_end ? plan->bwd_order[bj] : -1;
-        const int pair = next >= 0 && !(two && plan->bwd_side[next]) ? paired_linear(LB, op, next) : -1;
+        const int pair = next >= 0 && !(two && plan->bwd_side[next]) ? paired_linear(LB, op, next, two) : -1;
         if (pair >= 0) {  // a linear's two gradients, next to each other on this strand
           bj++;
-          if ((rc = wait_for_inputs(LB->gb, pb, next, sb)) || (rc = run_bwd_pair(LB, pair, *beta, ws_b, sb))) return rc;
+          if ((rc = wait_for_inputs(LB->gb, pb, next, sb)) || (rc = run_bwd_pair(LB, pair, *beta, ws_b, two, sb))) return rc;
           continue;
         }
         if (dh_leaves_strand(LB->gb, op, bj < p.b_end ? &plan->bwd_order[bj] : nullptr)) rc = on_comm_stream(L, sb, comm_stream_of(L, LB->gb.is_comm[op], scb), &pb.ev[op], [&](hipStream_t s) { return run_bwd_op(LB, op, *beta, ws_b, s); });
