@@ -409,7 +409,10 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
   if (rc != DH_OK) return rc;
   g.group_part = 2;
   g.M = std::min(max_rows, g.part1_bm - 1);  // a remainder is shorter than a large tile
-  p.cfg = 1;
+  // The remainders' row counts are data; a group's is half a large tile on average.  Few of them leave most units idle with 128x128 tiles, each
+  // walking all of K by itself: two groups, 12800 -> 4096 features, 172 us, with 64x64 tiles 95; 6400 -> 4096 80 -> 36.  (Twice as many blocks, four groups
+  // of 4096 features, are as fast with either: 235 and 238 us for the whole product.)
+  p.cfg = (long long)n_groups * ((g.N + 127) / 128) * 4 <= num_cus() ? 3 : 1;
   return mode == 0 ? launch_layout<false, false>(g, p, stream, n_groups) : launch_layout<false, true>(g, p, stream, n_groups);
 }
 
