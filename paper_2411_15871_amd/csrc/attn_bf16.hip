@@ -1014,28 +1014,35 @@ __global__ __launch_bounds__(AB_THREADS) void attn_bwd_dkv_bf16_kernel(const Att
 // Per-row statistics of the backward pass for the dK/dV blocks: delta[h,t] = sum_c dO[t,h,c] O[t,h,c] and
 // lse2[h,t] = lse[h,t] log2(e).  The sum runs in the order the dQ blocks use for their own copy (two halves of the row,
 // each 8 elements out of every 16, one fused multiply-add per element, halves added last), so both kernels work with
-// the same numbers.  One thread per (token, head).
+// the same numbers.  Two neighbouring lanes per (token, head), one for each half, in blocks of one wave: bound by one round of loads.  (A thread
+// per row in blocks of 256: 528 tokens, 4 heads 6.6 us, now 2.8.)
 template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
-                                                            const float* __restrict__ lse, float* __restrict__ lse2,
-                                                            float* __restrict__ delta, int T, int nq) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(64) void attn_bwd_prep_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                                                           const float* __restrict__ lse, float* __restrict__ lse2,
+                                                           float* __restrict__ delta, int T, int nq) {
+  const size_t i = (size_t)blockIdx.x * 32 + (threadIdx.x >> 1);
   if (i >= (size_t)T * nq) return;
-  const int h = (int)(i % nq);
-  const size_t t = i / nq;
-  const bf16_t* orow = o + (t * nq + h) * D;
-  const bf16_t* drow = dout + (t * nq + h) * D;
-  float half[2] = {0.f, 0.f};
+  const int kg = threadIdx.x & 1, h = (int)(i % nq);
+  const size_t t = i / nq, at = (size_t)h * T + t;
+  const bf16_t* orow = o + (t * nq + h) * D + kg * 8;
+  const bf16_t* drow = dout + (t * nq + h) * D + kg * 8;
+  const float l = lse[at];
+  bf16x8 a[D / 16], b[D / 16];
 #pragma unroll
-  for (int kg = 0; kg < 2; kg++)
+  for (int ks = 0; ks < D / 16; ks++) {
+    a[ks] = *reinterpret_cast<const bf16x8*>(drow + ks * 16);
+    b[ks] = *reinterpret_cast<const bf16x8*>(orow + ks * 16);
+  }
+  float half = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(drow + ks * 16 + kg * 8), b = *reinterpret_cast<const bf16x8*>(orow + ks * 16 + kg * 8);
+  for (int ks = 0; ks < D / 16; ks++)
 #pragma unroll
-      for (int e = 0; e < 8; e++) half[kg] = fmaf((float)a[e], (float)b[e], half[kg]);
-    }
-  delta[(size_t)h * T + t] = half[0] + half[1];
-  lse2[(size_t)h * T + t] = lse[(size_t)h * T + t] * LOG2E;
+    for (int e = 0; e < 8; e++) half = fmaf((float)a[ks][e], (float)b[ks][e], half);
+  const float other = __shfl_xor(half, 1, 64);
+  if (kg == 0) {
+    delta[at] = half + other;
+    lse2[at] = l * LOG2E;
+  }
 }
 
 // dk,dv[token][kv head] = sum over the chunks of the token's key block (ascending) of the float32 partials, where it has several.
@@ -1380,7 +1387,7 @@ int dh_launch_attn_bwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
       ready[IDX] = true;                                                                                                       \
     }                                                                                                                          \
     if (nq == nkv) {                                                                                                           \
-      attn_bwd_prep_kernel<DD><<<(unsigned)(((size_t)T * nq + 255) / 256), 256, 0, stream>>>(o, dout, lse, lse2, delta, T, nq); \
+      attn_bwd_prep_kernel<DD><<<(unsigned)(((size_t)T * nq + 31) / 32), 64, 0, stream>>>(o, dout, lse, lse2, delta, T, nq); \
       DH_LAUNCH_CHECK();                                                                                                       \
       attn_bwd_bf16_kernel<DD><<<gw, AB_THREADS, lds_dkv, stream>>>(gq_geom, gk_geom, qkv, o, dout, lse, lse2, delta, dqkv, part_q, \
                                                                    part_kv, pq, pk, T, sc, sl2);                               \
