@@ -3,6 +3,7 @@
 // All are HBM-bound: every tensor is read or written exactly once with 16-byte (bf16) or
 // 2x16-byte (fp32) accesses per thread; reductions are wave/block reductions in registers.
 #include <mutex>
+#include <type_traits>
 #include "common.h"
 
 #define ROW_THREADS 256
@@ -24,15 +25,19 @@ template <typename T> struct RowSrc<T, true> {
   __device__ __forceinline__ void load(Vec8<T>& v, size_t off) const {
     v.load_stream((const T*)parts.p[0] + off);
     int r = 1;
-    for (; r + 7 <= n; r += 7) {  // seven loads in flight (eight ranks: all of them)
-      Vec8<T> w[7];
+    auto take = [&](auto count) {
+      constexpr int N = decltype(count)::value;
+      Vec8<T> w[N];
 #pragma unroll
-      for (int u = 0; u < 7; u++) w[u].load_stream((const T*)parts.p[r + u] + off);
+      for (int u = 0; u < N; u++) w[u].load_stream((const T*)parts.p[r + u] + off);
 #pragma unroll
-      for (int u = 0; u < 7; u++)
+      for (int u = 0; u < N; u++)
 #pragma unroll
         for (int i = 0; i < 8; i++) v.v[i] += w[u].v[i];
-    }
+      r += N;
+    };
+    while (r + 7 <= n) take(std::integral_constant<int, 7>());  // seven loads in flight (eight ranks: all of them)
+    if (r + 3 <= n) take(std::integral_constant<int, 3>());     // (four ranks)
     for (; r < n; r++) {
       Vec8<T> w;
       w.load_stream((const T*)parts.p[r] + off);
