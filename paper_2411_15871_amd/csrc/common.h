@@ -241,6 +241,9 @@ int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t
 bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream);
+bool dh_gemm_f32_pair_pays(int n_groups, int T, int k, int n);
+int dh_launch_gemm_f32_pair(int n_groups, const int32_t* group_rows, int T, int k, int n, const float* dY, const float* W, const float* X, float* dX,
+                            float* dW, hipStream_t stream);
 // Attention launchers: seq = queries per sequence; kv == nullptr selects plain causal attention over the packed
 // qkv rows, otherwise keys/values come from kv[batch*(q_off+seq), ldkv] and their gradients go to dkv likewise.
 int dh_launch_attn_fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv,

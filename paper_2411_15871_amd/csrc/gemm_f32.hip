@@ -14,6 +14,7 @@
 #define F32_KS 16          // K of one step: four matrix instructions deep
 #define F32_AHEAD 2
 #define F32_MAX_WAVES 16
+#define F32_PAIR_BLOCKS 2048  // blocks of a launch that two products share (see dh_gemm_f32_pair_pays)
 
 // Fragments of one K step of an operand: v[t][e] = element (row, k0 + 4*(lane/16) + e) for the NT 16-row tiles t, where
 // row = 16 t + lane%16 for a K-contiguous operand and NT*(lane%16) + t for a K-major one (two tiles interleave, so
@@ -66,65 +67,76 @@ __device__ __forceinline__ void f32_fetch(F32Frag<NT>& f, const float* __restric
   }
 }
 
+struct F32Args {
+  int M, N, K;
+  const float *A, *B;
+  float* C;
+  int accumulate;
+  const float* bias;
+  const int32_t* group_rows;
+  int group_mode, vec_out, waves;  // waves: how many share K; the others of a block only help to add
+};
+// One tile; blockIdx.z is the group.
 template <int NT, bool TA, bool TB, bool VEC>
-__global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
-                                                                      const float* __restrict__ B, float* __restrict__ C, int accumulate,
-                                                                      const float* __restrict__ bias, const int32_t* __restrict__ group_rows,
-                                                                      int group_mode, int rows_in_x, int vec_out) {
+__device__ __forceinline__ void f32_tile(const F32Args& g, int tile_m, int tile_n, float* part) {  // part: [waves][TILE][LD]
   constexpr int TILE = 16 * NT, LD = TILE + 4;  // square tiles; row pitch of a partial tile
-  extern __shared__ float part[];               // [waves][TILE][LD]
-  const int tile_m = rows_in_x ? blockIdx.x : blockIdx.y, tile_n = rows_in_x ? blockIdx.y : blockIdx.x;
-  if (group_rows != nullptr) {  // grouped: blockIdx.z = group, its rows follow those of the groups before it
+  int M = g.M, K = g.K;
+  const int N = g.N, waves = g.waves;
+  const float *__restrict__ A = g.A, *__restrict__ B = g.B, *__restrict__ bias = g.bias;
+  float* __restrict__ C = g.C;
+  if (g.group_rows != nullptr) {  // grouped: its rows follow those of the groups before it
     int row0 = 0;
-    for (int i = 0; i < (int)blockIdx.z; i++) row0 += group_rows[i];
-    const int rows = group_rows[blockIdx.z];
-    if (group_mode == 2) {  // weight gradient: the group's rows are the K range
+    for (int i = 0; i < (int)blockIdx.z; i++) row0 += g.group_rows[i];
+    const int rows = g.group_rows[blockIdx.z];
+    if (g.group_mode == 2) {  // weight gradient: the group's rows are the K range
       A += (size_t)row0 * M; B += (size_t)row0 * N; C += (size_t)blockIdx.z * M * N; K = rows;
     } else {
       A += (size_t)row0 * K; B += (size_t)blockIdx.z * K * N; C += (size_t)row0 * N; M = rows;
     }
     if (rows == 0 || tile_m * TILE >= M) return;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m0 = tile_m * TILE, n0 = tile_n * TILE;
   const int steps = (K + F32_KS - 1) / F32_KS, per = (steps + waves - 1) / waves;
   const int k_begin = wave * per * F32_KS, k_end = min(K, k_begin + per * F32_KS);
-  f32x4 acc[NT][NT];
+  if (wave < waves) {
+    f32x4 acc[NT][NT];
 #pragma unroll
-  for (int i = 0; i < NT; i++)
+    for (int i = 0; i < NT; i++)
 #pragma unroll
-    for (int j = 0; j < NT; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  F32Frag<NT> a[F32_AHEAD], b[F32_AHEAD];
-  auto fetch = [&](int s, int k) {
-    f32_fetch<NT, TA, VEC>(a[s], A, m0, k, M, K, k_end, lane);
-    f32_fetch<NT, !TB, VEC>(b[s], B, n0, k, N, K, k_end, lane);
-  };
+      for (int j = 0; j < NT; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    F32Frag<NT> a[F32_AHEAD], b[F32_AHEAD];
+    auto fetch = [&](int s, int k) {
+      f32_fetch<NT, TA, VEC>(a[s], A, m0, k, M, K, k_end, lane);
+      f32_fetch<NT, !TB, VEC>(b[s], B, n0, k, N, K, k_end, lane);
+    };
 #pragma unroll
-  for (int s = 0; s < F32_AHEAD; s++) fetch(s, k_begin + s * F32_KS);
-  for (int k = k_begin; k < k_end; k += F32_AHEAD * F32_KS) {
+    for (int s = 0; s < F32_AHEAD; s++) fetch(s, k_begin + s * F32_KS);
+    for (int k = k_begin; k < k_end; k += F32_AHEAD * F32_KS) {
 #pragma unroll
-    for (int s = 0; s < F32_AHEAD; s++) {
+      for (int s = 0; s < F32_AHEAD; s++) {
 #pragma unroll
-      for (int e = 0; e < 4; e++)
+        for (int e = 0; e < 4; e++)
 #pragma unroll
-        for (int i = 0; i < NT; i++)
+          for (int i = 0; i < NT; i++)
 #pragma unroll
-          for (int j = 0; j < NT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s].v[i][e], b[s].v[j][e], acc[i][j], 0, 0, 0);
-      fetch(s, k + (s + F32_AHEAD) * F32_KS);
-    }
-  }
-  // acc[i][j][r]: row index 4*(lane/16) + r of A's tile i, column index lane%16 of B's tile j
-  float* mine = part + wave * (TILE * LD);
-#pragma unroll
-  for (int i = 0; i < NT; i++)
-#pragma unroll
-    for (int j = 0; j < NT; j++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int ri = 4 * (lane >> 4) + r, cj = lane & 15;
-        const int row = TA ? NT * ri + i : 16 * i + ri, col = !TB ? NT * cj + j : 16 * j + cj;
-        mine[row * LD + col] = acc[i][j][r];
+            for (int j = 0; j < NT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s].v[i][e], b[s].v[j][e], acc[i][j], 0, 0, 0);
+        fetch(s, k + (s + F32_AHEAD) * F32_KS);
       }
+    }
+    // acc[i][j][r]: row index 4*(lane/16) + r of A's tile i, column index lane%16 of B's tile j
+    float* mine = part + wave * (TILE * LD);
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+#pragma unroll
+      for (int j = 0; j < NT; j++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int ri = 4 * (lane >> 4) + r, cj = lane & 15;
+          const int row = TA ? NT * ri + i : 16 * i + ri, col = !TB ? NT * cj + j : 16 * j + cj;
+          mine[row * LD + col] = acc[i][j][r];
+        }
+  }
   __syncthreads();
   for (int x = threadIdx.x; x < TILE * TILE / 4; x += blockDim.x) {
     const int row = x / (TILE / 4), c = (x % (TILE / 4)) * 4, gm = m0 + row, gn = n0 + c;
@@ -132,47 +144,75 @@ __global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(int M, int
     f32x4 s = *reinterpret_cast<const f32x4*>(part + row * LD + c);
     for (int w = 1; w < waves; w++) s += *reinterpret_cast<const f32x4*>(part + w * (TILE * LD) + row * LD + c);
     float* dst = C + (size_t)gm * N + gn;
-    if (vec_out) {  // N a multiple of 4, C and bias 16-byte aligned
+    if (g.vec_out) {  // N a multiple of 4, C and bias 16-byte aligned
       if (gn >= N) continue;
       if (bias) s += *reinterpret_cast<const f32x4*>(bias + gn);
-      if (accumulate) s += *reinterpret_cast<const f32x4*>(dst);
+      if (g.accumulate) s += *reinterpret_cast<const f32x4*>(dst);
       *reinterpret_cast<f32x4*>(dst) = s;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; e++)
         if (gn + e < N) {
           const float v = bias ? s[e] + bias[gn + e] : s[e];
-          dst[e] = accumulate ? dst[e] + v : v;
+          dst[e] = g.accumulate ? dst[e] + v : v;
         }
     }
   }
 }
 
+template <int NT, bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_kernel(const F32Args g, int rows_in_x) {
+  extern __shared__ float part[];
+  f32_tile<NT, TA, TB, VEC>(g, rows_in_x ? blockIdx.x : blockIdx.y, rows_in_x ? blockIdx.y : blockIdx.x, part);
+}
+// A linear's data gradient (first blocks_d blocks) and weight gradient in one launch: they read the same dY and are chains of latencies, one behind the
+// other as launches of their own (128 tokens, 256 wide: 5 + 4.6, 8.2 + 5.4, 4.1 + 4.1 and 6 + 4.8 us; the two-strand step 129 -> 112 us).
+template <int NTD, int NTW>
+__global__ __launch_bounds__(64 * F32_MAX_WAVES) void gemm_f32_pair_kernel(const F32Args d, const F32Args w, int blocks_d, int tiles_nd, int tiles_nw) {
+  extern __shared__ float part[];
+  const int bx = blockIdx.x;
+  if (bx < blocks_d) f32_tile<NTD, false, true, true>(d, bx / tiles_nd, bx % tiles_nd, part);
+  else f32_tile<NTW, true, false, true>(w, (bx - blocks_d) / tiles_nw, (bx - blocks_d) % tiles_nw, part);
+}
+
+template <typename Kernel>
+static int f32_allow_lds(Kernel kernel, bool* attr_set, int nt) {
+  const int dev = dh_device_index();
+  if (!attr_set[dev]) {
+    DH_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, F32_MAX_WAVES * 16 * nt * (16 * nt + 4) * (int)sizeof(float)));
+    attr_set[dev] = true;
+  }
+  return DH_OK;
+}
+static F32Args f32_args(int M, int N, int K, int k_typical, const float* A, const float* B, float* C, bool accumulate, const float* bias,
+                        const int32_t* group_rows, int group_mode) {
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  const int waves = std::min(F32_MAX_WAVES, std::max(1, (k_typical + 31) / 32));
+  return {M, N, K, A, B, C, accumulate ? 1 : 0, bias, group_rows, group_mode, N % 4 == 0 && aligned(C) && aligned(bias), waves};
+}
+static bool f32_vec(bool ta, bool tb, const F32Args& g) {
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  return aligned(g.A) && aligned(g.B) && (ta ? g.M : g.K) % 4 == 0 && (tb ? g.K : g.N) % 4 == 0;
+}
+// 16x16 tiles load twice as much per product: they pay only while 32x32 tiles come to fewer blocks than compute units.
+static bool f32_small(int M, int N, int n_groups) { return (long long)((M + 31) / 32) * ((N + 31) / 32) * n_groups < 256; }
+
 template <bool TA, bool TB>
 static int launch_f32(int M, int N, int K, int k_typical, const float* A, const float* B, float* C, bool accumulate, const float* bias,
                       const int32_t* group_rows, int group_mode, int n_groups, hipStream_t stream) {
-  const int waves = std::min(F32_MAX_WAVES, std::max(1, (k_typical + 31) / 32));
-  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  const bool vec = aligned(A) && aligned(B) && (TA ? M : K) % 4 == 0 && (TB ? K : N) % 4 == 0;
-  const int vec_out = N % 4 == 0 && aligned(C) && aligned(bias);
-  // 16x16 tiles load twice as much per product: they pay only while 32x32 tiles come to fewer blocks than compute units.
-  const bool small = (long long)((M + 31) / 32) * ((N + 31) / 32) * n_groups < 256;
-#define GO(NT, V)                                                                                                               \
-  do {                                                                                                                          \
-    constexpr int TILE = 16 * NT, PART = TILE * (TILE + 4) * (int)sizeof(float);                                                \
-    static bool attr_set[DH_MAX_DEVICES] = {};                                                                                  \
-    const int dev = dh_device_index();                                                                                          \
-    if (!attr_set[dev]) {                                                                                                       \
-      DH_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<NT, TA, TB, V>, hipFuncAttributeMaxDynamicSharedMemorySize,       \
-                                 F32_MAX_WAVES * PART));                                                                        \
-      attr_set[dev] = true;                                                                                                     \
-    }                                                                                                                           \
-    const int tm = (M + TILE - 1) / TILE, tn = (N + TILE - 1) / TILE, rows_in_x = tm > 65535; /* y holds no more blocks */       \
-    dim3 grid(rows_in_x ? tm : tn, rows_in_x ? tn : tm, n_groups);                                                              \
-    gemm_f32_kernel<NT, TA, TB, V><<<grid, 64 * waves, waves * PART, stream>>>(M, N, K, A, B, C, accumulate ? 1 : 0, bias,      \
-                                                                               group_rows, group_mode, rows_in_x, vec_out);     \
+  const F32Args g = f32_args(M, N, K, k_typical, A, B, C, accumulate, bias, group_rows, group_mode);
+  const bool vec = f32_vec(TA, TB, g);
+#define GO(NT, V)                                                                                                         \
+  do {                                                                                                                    \
+    constexpr int TILE = 16 * NT, PART = TILE * (TILE + 4) * (int)sizeof(float);                                          \
+    static bool attr_set[DH_MAX_DEVICES] = {};                                                                            \
+    const int rc = f32_allow_lds(gemm_f32_kernel<NT, TA, TB, V>, attr_set, NT);                                           \
+    if (rc) return rc;                                                                                                    \
+    const int tm = (M + TILE - 1) / TILE, tn = (N + TILE - 1) / TILE, rows_in_x = tm > 65535; /* y holds no more blocks */ \
+    dim3 grid(rows_in_x ? tm : tn, rows_in_x ? tn : tm, n_groups);                                                        \
+    gemm_f32_kernel<NT, TA, TB, V><<<grid, 64 * g.waves, g.waves * PART, stream>>>(g, rows_in_x);                         \
   } while (0)
-  if (small) { if (vec) GO(1, true); else GO(1, false); }
+  if (f32_small(M, N, n_groups)) { if (vec) GO(1, true); else GO(1, false); }
   else { if (vec) GO(2, true); else GO(2, false); }
 #undef GO
   DH_LAUNCH_CHECK();
@@ -195,4 +235,46 @@ int dh_launch_gemm_grouped_f32(int mode, int n_groups, const int32_t* group_rows
   if (mode == 0) return launch_f32<false, false>(max_rows, dim_b, dim_a, dim_a, A, B, C, false, nullptr, group_rows, 0, n_groups, stream);
   if (mode == 1) return launch_f32<false, true>(max_rows, dim_b, dim_a, dim_a, A, B, C, false, nullptr, group_rows, 1, n_groups, stream);
   return launch_f32<true, false>(dim_a, dim_b, max_rows, max_rows / n_groups, A, B, C, true, nullptr, group_rows, 2, n_groups, stream);
+}
+
+// dX[T, k] = dY[T, n] * W[k, n]^T and dW[k, n] += X[T, k]^T * dY, as one launch with the bits of the two apart (each keeps its tile and its
+// waves' shares of K).  group_rows != nullptr: per group as in dh_launch_gemm_grouped_f32.  Up to a few rounds of blocks: 22 backward passes and steps of up to
+// 2048 blocks took 0.86-1.01 of their time with launches apart; beyond, the products are a rate and waves that only help to add are in the way.
+static long long f32_blocks(int M, int N, int n_groups) {
+  const int tile = f32_small(M, N, n_groups) ? 16 : 32;
+  return (long long)((M + tile - 1) / tile) * ((N + tile - 1) / tile) * n_groups;
+}
+bool dh_gemm_f32_pair_pays(int n_groups, int T, int k, int n) {
+  return T > 0 && f32_blocks(T, k, n_groups) + f32_blocks(k, n, n_groups) <= F32_PAIR_BLOCKS;
+}
+int dh_launch_gemm_f32_pair(int n_groups, const int32_t* group_rows, int T, int k, int n, const float* dY, const float* W, const float* X, float* dX,
+                            float* dW, hipStream_t stream) {
+  const F32Args d = f32_args(T, k, n, n, dY, W, dX, false, nullptr, group_rows, 1);
+  const F32Args w = f32_args(k, n, T, group_rows ? T / n_groups : T, X, dY, dW, true, nullptr, group_rows, 2);
+  if (T <= 0 || !f32_vec(false, true, d) || !f32_vec(true, false, w) || !dh_gemm_f32_pair_pays(n_groups, T, k, n)) {
+    const int rc = group_rows ? dh_launch_gemm_grouped_f32(1, n_groups, group_rows, T, n, k, dY, W, dX, stream)
+                              : dh_launch_gemm_f32(false, true, T, k, n, dY, W, dX, false, nullptr, stream);
+    if (rc) return rc;
+    return group_rows ? dh_launch_gemm_grouped_f32(2, n_groups, group_rows, T, k, n, X, dY, dW, stream)
+                      : dh_launch_gemm_f32(true, false, k, n, T, X, dY, dW, true, nullptr, stream);
+  }
+  const int waves = std::max(d.waves, w.waves);
+#define GO(NTD, NTW)                                                                                                          \
+  do {                                                                                                                        \
+    constexpr int TD = 16 * NTD, TW = 16 * NTW;                                                                               \
+    static bool attr_set[DH_MAX_DEVICES] = {};                                                                                \
+    const int rc = f32_allow_lds(gemm_f32_pair_kernel<NTD, NTW>, attr_set, NTD > NTW ? NTD : NTW);                            \
+    if (rc) return rc;                                                                                                        \
+    const int lds = std::max(d.waves * TD * (TD + 4), w.waves * TW * (TW + 4)) * (int)sizeof(float);                          \
+    const int nd = (k + TD - 1) / TD, nw = (n + TW - 1) / TW, blocks_d = (T + TD - 1) / TD * nd, blocks_w = (k + TW - 1) / TW * nw; \
+    gemm_f32_pair_kernel<NTD, NTW><<<dim3(blocks_d + blocks_w, 1, n_groups), 64 * waves, lds, stream>>>(d, w, blocks_d, nd, nw); \
+  } while (0)
+  const bool sd = f32_small(T, k, n_groups), sw = f32_small(k, n, n_groups);
+  if (sd && sw) GO(1, 1);
+  else if (sd) GO(1, 2);
+  else if (sw) GO(2, 1);
+  else GO(2, 2);
+#undef GO
+  DH_LAUNCH_CHECK();
+  return DH_OK;
 }

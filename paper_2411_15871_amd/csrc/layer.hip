@@ -258,8 +258,11 @@ static void choose_pairs(dh_layer* L) {
   const bool bf = c.dtype == DH_BF16, moe = c.arch == DH_ARCH_MOE;
   const int Fin = c.arch == DH_ARCH_GPT ? c.ffn : 2 * c.ffn;
   for (int beside = 0; beside < 2; beside++) {
-    auto dense = [&](int k, int n) { return bf && dh_gemm_pair_pays(L->T, k, n, beside); };
-    auto ffn = [&](int k, int n) { return moe ? bf && dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, k, n, beside) : dense(k, n); };
+    auto dense = [&](int k, int n) { return bf ? dh_gemm_pair_pays(L->T, k, n, beside) : dh_gemm_f32_pair_pays(1, L->T, k, n); };
+    auto ffn = [&](int k, int n) {
+      if (!moe) return dense(k, n);
+      return bf ? dh_gemm_grouped_pair_pays(c.n_local_experts, L->Tf, k, n, beside) : dh_gemm_f32_pair_pays(c.n_local_experts, L->Tf, k, n);
+    };
     bool* pays = L->pair_launch[beside];
     pays[PAIR_FC2] = ffn(c.ffn, c.hidden);
     pays[PAIR_FC1] = ffn(c.hidden, Fin);
@@ -1014,13 +1017,17 @@ static int paired_linear(const dh_layer* L, int op, int next, bool beside) {
 static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, bool beside, hipStream_t s) {
   const dh_layer_config& c = L->c;
   const int T = L->T, Tf = L->Tf, H = c.hidden, F = c.ffn;
-  const bool gpt = c.arch == DH_ARCH_GPT, moe = c.arch == DH_ARCH_MOE;
+  const bool gpt = c.arch == DH_ARCH_GPT, moe = c.arch == DH_ARCH_MOE, f32 = c.dtype == DH_F32;
   const char* sv = (const char*)b.saved;
   auto dense = [&](int k, int n, const void* dY, const void* W, const void* X, size_t dX, float* dW, const void* gu = nullptr) {
-    const int rc = dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside, s);
+    const int rc = f32 ? dh_launch_gemm_f32_pair(1, nullptr, T, k, n, (const float*)dY, (const float*)W, (const float*)X, (float*)(ws + dX), dW, s)
+                       : dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside, s);
     return rc || !gpt ? rc : gpt_bias_grad(L, which, b, ws, s);
   };
   auto experts = [&](int k, int n, size_t dY, const void* W, size_t X, size_t dX, float* dW) {
+    if (f32)
+      return dh_launch_gemm_f32_pair(c.n_local_experts, moe_tables_of(L, b.saved).group_rows, Tf, k, n, (const float*)(ws + dY), (const float*)W,
+                                     (const float*)(sv + X), (float*)(ws + dX), dW, s);
     return dh_launch_gemm_grouped_pair_bf16(c.n_local_experts, moe_tables_of(L, b.saved).group_rows, Tf, k, n, (const bf16_t*)(ws + dY), (const bf16_t*)W,
                                             (const bf16_t*)(sv + X), (bf16_t*)(ws + dX), dW, beside, s);
   };
