@@ -2,6 +2,7 @@
 // bias-dropout-add operator fused in, dropout p = 0), RoPE, SwiGLU, residual add.
 // All are HBM-bound: every tensor is read or written exactly once with 16-byte (bf16) or
 // 2x16-byte (fp32) accesses per thread; reductions are wave/block reductions in registers.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include "common.h"
@@ -230,54 +231,68 @@ __global__ __launch_bounds__(COLSUM_THREADS) void colsum_finish_kernel(const flo
 // ratio = base^(-2/d); the angle is reduced to [-pi, pi] in double, and only sine and cosine of the reduced
 // angle are taken in float (absolute error ~1e-7).
 // ADJACENT: pair i is elements (2i, 2i+1): the thread's 8 pairs are 16 consecutive elements.
-template <typename T, bool ADJACENT>
-__global__ void rope_kernel(T* __restrict__ t, int rows, int seq, int pos0, int n_heads, int d, int row_stride, double log2_base,
-                            double ratio, int inverse) {
-  int half = d / 2;
-  int chunks = half / 8;
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t total = (size_t)rows * n_heads * chunks;
-  if (idx >= total) return;
-  int c = (int)(idx % chunks);
-  int head = (int)((idx / chunks) % n_heads);
-  size_t row = idx / ((size_t)chunks * n_heads);
-  int pos = pos0 + (int)(row % seq);
-  T* pa = t + row * row_stride + (size_t)head * d + (ADJACENT ? c * 16 : c * 8);
-  T* pb = pa + (ADJACENT ? 8 : half);
-  Vec8<T> a, b, oa, ob;
-  a.load(pa);
-  b.load(pb);
-  if (ADJACENT) {  // de-interleave: a = first elements of the 8 pairs, b = second elements
-    Vec8<T> lo = a, hi = b;
+// HEADS: heads a thread rotates, with one set of angles.  Bound by forming angles, sines and cosines with one head a thread, by memory with four
+// (4096 rows of 40 heads of 128 21.0 -> 13.4 us, 6.3 TB/s; 8192 of 9 11.2 -> 7.3, 4000 of 32 of 64 10.3 -> 6.5, 4096 of 5 5.1 -> 4.5), by one thread's chain where
+// there are few (256 of 5 3.65 us, four heads a thread 3.85): four from 2^17 threads of one head on.
+template <typename T, bool ADJACENT, int HEADS>
+__global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ t, size_t row0, unsigned threads, int seq, int pos0, int n_heads, int d, int row_stride,
+                                                   double log2_base, double ratio, int inverse) {
+  const int half = d / 2;
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x, chunks = half / 8, groups = (n_heads + HEADS - 1) / HEADS;
+  if (idx >= threads) return;
+  const int c = idx % chunks, head0 = idx / chunks % groups * HEADS;
+  const size_t row = row0 + idx / (chunks * groups);
+  const int pos = pos0 + (int)(row % seq);
+  T* pa = t + row * row_stride + (size_t)head0 * d + (ADJACENT ? c * 16 : c * 8);
+  Raw8<T> ra[HEADS], rb[HEADS];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      a.v[i] = lo.v[2 * i]; b.v[i] = lo.v[2 * i + 1];
-      a.v[4 + i] = hi.v[2 * i]; b.v[4 + i] = hi.v[2 * i + 1];
+  for (int h = 0; h < HEADS; h++)
+    if (head0 + h < n_heads) {
+      ra[h].load(pa + h * d);
+      rb[h].load(pa + h * d + (ADJACENT ? 8 : half));
     }
-  }
+  float sn[8], co[8];
   double theta = exp2(-2.0 * (double)(c * 8) / (double)d * log2_base);
 #pragma unroll
   for (int i = 0; i < 8; i++) {
     double ang = (double)pos * theta;
     ang -= 6.283185307179586476925 * rint(ang * 0.15915494309189533577);
     theta *= ratio;
-    float sn, co;
-    sincosf((float)ang, &sn, &co);
-    float s = inverse ? -sn : sn;
-    oa.v[i] = a.v[i] * co - b.v[i] * s;
-    ob.v[i] = a.v[i] * s + b.v[i] * co;
+    sincosf((float)ang, &sn[i], &co[i]);
+    if (inverse) sn[i] = -sn[i];
   }
-  if (ADJACENT) {
-    Vec8<T> lo, hi;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      lo.v[2 * i] = oa.v[i]; lo.v[2 * i + 1] = ob.v[i];
-      hi.v[2 * i] = oa.v[4 + i]; hi.v[2 * i + 1] = ob.v[4 + i];
+  for (int h = 0; h < HEADS; h++) {
+    if (head0 + h >= n_heads) break;
+    Vec8<T> a, b, oa, ob;
+    a.from(ra[h]);
+    b.from(rb[h]);
+    if (ADJACENT) {  // de-interleave: a = first elements of the 8 pairs, b = second elements
+      Vec8<T> lo = a, hi = b;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        a.v[i] = lo.v[2 * i]; b.v[i] = lo.v[2 * i + 1];
+        a.v[4 + i] = hi.v[2 * i]; b.v[4 + i] = hi.v[2 * i + 1];
+      }
     }
-    oa = lo; ob = hi;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const float s = sn[i];
+      oa.v[i] = fmaf(a.v[i], co[i], -__fmul_rn(b.v[i], s));  // the same roundings whatever HEADS is
+      ob.v[i] = fmaf(b.v[i], co[i], __fmul_rn(a.v[i], s));
+    }
+    if (ADJACENT) {
+      Vec8<T> lo, hi;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        lo.v[2 * i] = oa.v[i]; lo.v[2 * i + 1] = ob.v[i];
+        hi.v[2 * i] = oa.v[4 + i]; hi.v[2 * i + 1] = ob.v[4 + i];
+      }
+      oa = lo; ob = hi;
+    }
+    oa.store(pa + h * d);
+    ob.store(pa + h * d + (ADJACENT ? 8 : half));
   }
-  oa.store(pa);
-  ob.store(pb);
 }
 
 // ------------------------------------------------------------------------------------ SwiGLU
@@ -455,14 +470,21 @@ extern "C" int dh_rope_pairs(int dtype, int pairing, int T, int seq, int pos0, i
             head_dim, row_stride);
   if (T == 0) return DH_OK;
   if (!t) DH_FAIL(DH_ERR_INVALID_ARG, "rope: null pointer");
-  size_t total = (size_t)T * n_heads * (head_dim / 16);
-  dim3 g((unsigned)((total + 255) / 256)), b(256);
   const double l2b = log2((double)base), ratio = exp2(-2.0 / (double)head_dim * l2b);
-#define GO(TT, ADJ) rope_kernel<TT, ADJ><<<g, b, 0, (hipStream_t)stream>>>((TT*)t, T, seq, pos0, n_heads, head_dim, row_stride, l2b, ratio, inverse)
-  if (dtype == DH_BF16) { if (pairing == DH_ROPE_ADJACENT) GO(bf16_t, true); else GO(bf16_t, false); }
-  else { if (pairing == DH_ROPE_ADJACENT) GO(float, true); else GO(float, false); }
+  const bool four = (size_t)T * n_heads * (head_dim / 16) >= (size_t)1 << 17;
+  const size_t per_row = (size_t)(four ? (n_heads + 3) / 4 : n_heads) * (head_dim / 16), most = std::max<size_t>(1, ((size_t)1 << 31) / per_row);
+  for (size_t row0 = 0; row0 < (size_t)T; row0 += most) {  // (a launch's threads are counted in 32 bits)
+    const unsigned threads = (unsigned)(std::min(most, (size_t)T - row0) * per_row);
+#define GO(TT, ADJ, N)                                                                                                                       \
+  rope_kernel<TT, ADJ, N><<<(threads + 255) / 256, 256, 0, (hipStream_t)stream>>>((TT*)t, row0, threads, seq, pos0, n_heads, head_dim, row_stride, \
+                                                                                 l2b, ratio, inverse)
+#define GO2(TT, ADJ) do { if (four) GO(TT, ADJ, 4); else GO(TT, ADJ, 1); } while (0)
+    if (dtype == DH_BF16) { if (pairing == DH_ROPE_ADJACENT) GO2(bf16_t, true); else GO2(bf16_t, false); }
+    else { if (pairing == DH_ROPE_ADJACENT) GO2(float, true); else GO2(float, false); }
+#undef GO2
 #undef GO
-  DH_LAUNCH_CHECK();
+    DH_LAUNCH_CHECK();
+  }
   return DH_OK;
 }
 
