@@ -195,6 +195,10 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool
   // 35 us apart, 40 as one launch.  (A weight gradient's operands have just been written: 512x1024x4000 in seven ranges 26 -> 20.)
   if (pd.ranges > 4) return false;
   const double shared = beside ? 0.5 : 0.0, apart = (1 - shared) * (pd.ns + pw.ns) + shared * (pd.cu_ns + pw.cu_ns);
+  // Small tiles fetch their operands often, and blocks of two products at a time find less of them in the L2s, which hold 32 MiB together: beyond
+  // that they take a quarter longer than estimated (7616 tokens, 304 x 2104, 64x64: 55 us against 48 apart; four sequential and two-strand steps
+  // 2-3 % faster with this, 26 others the same; from 18 MB on instead, three of them 1-4 % slower).
+  const double operands = 2.0 * ng * ((double)d.M * (d.N + d.K) + (double)d.K * d.N);
   double best = 0;
   for (const TileCost& c : kTiles) {
     if (c.bm * c.bn == 256 * 256) continue;
@@ -221,7 +225,7 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool
       const double beside = std::min(t1, std::max(0.0, even - t1));
       end = std::max(end, 2 * beside + (t1 - beside) * (wf ? c.alone : c.alone_cold));
     }
-    const double ns = (1 - shared) * (kLaunch + end) + shared * (even + kLaunch / 2);
+    const double ns = (c.bm * c.bn < 128 * 128 && operands > 30e6 ? 1.25 : 1.0) * ((1 - shared) * (kLaunch + end) + shared * (even + kLaunch / 2));
     if (best != 0 && ns >= best) continue;
     best = ns;
     w_first = wf;
