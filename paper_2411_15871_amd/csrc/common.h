@@ -237,7 +237,7 @@ int dh_launch_gemm_swiglu_bwd_bf16(int T, int F, int H, const bf16_t* dy, const 
 // while another stream's kernels run.
 bool dh_gemm_pair_pays(int T, int k, int n, bool beside);
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
-                             bool beside, hipStream_t stream);
+                             bool beside, void* ws, size_t ws_bytes, hipStream_t stream);
 bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream);

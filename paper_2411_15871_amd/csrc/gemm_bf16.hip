@@ -179,21 +179,23 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
 }
 
 // The tile shape of a data and a weight gradient that go out as one launch, each with the K ranges it has by itself (the same bits),
-// summed in the block.  False where two launches are expected to be as fast: large products, which fill the chip by themselves.
+// summed in the block.  PAIR_APART where two launches are expected to be as fast (large products, which fill the chip by themselves): pd and pw
+// are valid then, too.  PAIR_NONE: there is no launch that holds both, pd and pw are the plans of the products by themselves.
 // beside: another stream's kernels run at the same time, and use the units that a launch leaves idle: what the launch takes of the chip then
 // counts as much as when it ends.  (Two strands of 3 x 2727 tokens, 584 wide, heads of 64: 64x64 tiles for both gradients of the QKV projection
 // end as soon as two launches of large tiles, and take 1.6 times their unit time: step 561 -> 581 us; of 3010 tokens, 1408 wide
 // with heads of 64 572 -> 583; with this 564 and 528.)
 // The estimate hands the blocks of the product whose blocks take longer to the units first, then the other's to whichever is free.
 struct GemmShape { int M, N, K; };
-static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool beside, GemmPlan& pd, GemmPlan& pw, bool& w_first) {
+enum PairChoice { PAIR_NONE, PAIR_APART, PAIR_TOGETHER };
+static PairChoice choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool beside, GemmPlan& pd, GemmPlan& pw, bool& w_first) {
   const int cus = num_cus(), ng = std::max(1, groups);
   pd = choose_plan(d.M, d.N, d.K, false, (size_t)-1, groups);
   pw = choose_plan(w.M, w.N, w.K, true, (size_t)-1, groups);
-  if (pd.tail_tiles > 0 || pw.tail_tiles > 0) return false;  // more than a round of the largest tiles, and K ranges of its own
+  if (pd.tail_tiles > 0 || pw.tail_tiles > 0) return PAIR_NONE;  // more than a round of the largest tiles, and K ranges of its own
   // A data gradient cut into many ranges would walk them one after the other, with weights that come from memory: 1344x512x4608
   // 35 us apart, 40 as one launch.  (A weight gradient's operands have just been written: 512x1024x4000 in seven ranges 26 -> 20.)
-  if (pd.ranges > 4) return false;
+  if (pd.ranges > 4) return PAIR_NONE;
   const double shared = beside ? 0.5 : 0.0, apart = (1 - shared) * (pd.ns + pw.ns) + shared * (pd.cu_ns + pw.cu_ns);
   // Small tiles fetch their operands often, and blocks of two products at a time find less of them in the L2s, which hold 32 MiB together: beyond
   // that they take a quarter longer than estimated (7616 tokens, 304 x 2104, 64x64: 55 us against 48 apart; four sequential and two-strand steps
@@ -240,7 +242,7 @@ static bool choose_pair(const GemmShape& d, const GemmShape& w, int groups, bool
   // (Nor where the weight gradient's float32 result is most of the work: a data gradient of few long blocks beside blocks that keep
   // the memory busy takes longer than by itself, T = 384, 3680 x 8496: 121 us apart, 158 as one launch.)
   // The second launch's gap is not in the estimate; of long products the forward strand's blocks use the units left idle.
-  return best < apart * (apart > kLong * 1.5 ? 0.95 : beside ? 1.0 : 1.03) && 8.0 * w.M * w.N * ng / 5000 < 0.5 * best;
+  return best < apart * (apart > kLong * 1.5 ? 0.95 : beside ? 1.0 : 1.03) && 8.0 * w.M * w.N * ng / 5000 < 0.5 * best ? PAIR_TOGETHER : PAIR_APART;
 }
 
 // Launch indices of the tail launch: from the first index of the last round to the end of the (padded) index range.
@@ -422,7 +424,7 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
 
 // The two gradient products of a linear layer whose dY is [T, n], weight [k, n] and input [T, k]: dX[T, k] = dY * W^T and
 // dW[k, n] += X^T * dY, as one launch with the bits of the two apart.  gu != nullptr: dX goes through SwiGLU's backward as in
-// dh_launch_gemm_swiglu_bwd_bf16 (dX is then d(gate | up)[T, 2k]).
+// dh_launch_gemm_swiglu_bwd_bf16 (dX is then d(gate | up)[T, 2k]).  Products that no one launch holds go out apart, with ws as in dh_launch_gemm_bf16.
 static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups) {
   switch (cfg) {
     case 1: return launch_pair<1>(d, w, w_first, stream, n_groups);
@@ -439,14 +441,18 @@ bool dh_gemm_pair_pays(int T, int k, int n, bool beside) {
   if (T <= 0 || k % 8 || n % 8) return false;
   GemmPlan pd, pw;
   bool w_first;
-  return choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first);
+  return choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first) == PAIR_TOGETHER;
 }
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
-                             bool beside, hipStream_t stream) {
+                             bool beside, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
   GemmPlan pd, pw;
   bool w_first;
-  (void)choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first);
+  if (choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first) == PAIR_NONE) {  // e.g. dh_gemm_pair_pays was asked with another device current
+    const int rc = gu != nullptr ? dh_launch_gemm_swiglu_bwd_bf16(T, k, n, dY, W, gu, dX, stream)
+                                 : dh_launch_gemm_bf16(false, true, T, k, n, dY, W, dX, false, nullptr, ws, ws_bytes, stream);
+    return rc ? rc : dh_launch_gemm_bf16(true, false, k, n, T, X, dY, dW, true, nullptr, ws, ws_bytes, stream);
+  }
   GemmArgs d = gemm_args(T, k, n, dY, W, dX, EPI_STORE_BF16, pd), w = gemm_args(k, n, T, X, dY, dW, EPI_ACC_F32, pw);
   if (gu != nullptr) { d.glu_mode = GLU_BWD; d.glu_f = k; d.glu_in = gu; }
   return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1);
@@ -457,7 +463,7 @@ bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside) {
   GemmPlan pd, pw;
   bool w_first;
   const int avg = std::max(1, T / n_groups);
-  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first);
+  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first) == PAIR_TOGETHER;
 }
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream) {
@@ -465,7 +471,10 @@ int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, in
   GemmPlan pd, pw;
   bool w_first;
   const int avg = std::max(1, T / n_groups);
-  (void)choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first);
+  if (choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first) == PAIR_NONE) {
+    const int rc = dh_launch_gemm_grouped_bf16(1, n_groups, group_rows, T, n, k, dY, W, dX, stream);
+    return rc ? rc : dh_launch_gemm_grouped_bf16(2, n_groups, group_rows, T, k, n, X, dY, dW, stream);
+  }
   return launch_pair_cfg(pd.cfg, grouped_args(1, n_groups, group_rows, T, n, k, dY, W, dX, pd),
                          grouped_args(2, n_groups, group_rows, T, k, n, X, dY, dW, pw), w_first, stream, n_groups);
 }

@@ -1021,7 +1021,8 @@ static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, 
   const char* sv = (const char*)b.saved;
   auto dense = [&](int k, int n, const void* dY, const void* W, const void* X, size_t dX, float* dW, const void* gu = nullptr) {
     const int rc = f32 ? dh_launch_gemm_f32_pair(1, nullptr, T, k, n, (const float*)dY, (const float*)W, (const float*)X, (float*)(ws + dX), dW, s)
-                       : dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside, s);
+                       : dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside,
+                                                 ws + L->b_gemm, L->b_gemm_bytes, s);
     return rc || !gpt ? rc : gpt_bias_grad(L, which, b, ws, s);
   };
   auto experts = [&](int k, int n, size_t dY, const void* W, size_t X, size_t dX, float* dW) {
