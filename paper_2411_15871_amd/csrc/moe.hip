@@ -32,17 +32,20 @@ __global__ void moe_route_kernel(int T, int E, const float* __restrict__ logits,
 }
 
 // dlogits[t,e] = p_k (dp_k - sum_j p_j dp_j) for the two kept experts, 0 elsewhere.  A thread per element (one per token, storing E
-// elements apart from its neighbours': 1500 tokens of 16 experts 3.9 us, now 2.6).
+// elements apart from its neighbours': 1500 tokens of 16 experts 3.9 us, now 2.6), up to the grid of ROUTE_BWD_BLOCKS: T * E may exceed the 2^32 - 1
+// threads a launch can have (2^24 tokens of 256 experts).
+#define ROUTE_BWD_BLOCKS (1u << 20)
 __global__ void moe_route_bwd_kernel(int T, int E, const float* __restrict__ dprob, const int32_t* __restrict__ idx,
                                      const float* __restrict__ prob, float* __restrict__ dlogits) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t t = i / E;
-  const int e = (int)(i - t * E);
-  if (t >= (size_t)T) return;
-  const float p0 = prob[2 * t], p1 = prob[2 * t + 1], g0 = dprob[2 * t], g1 = dprob[2 * t + 1];
-  const int i0 = idx[2 * t], i1 = idx[2 * t + 1];
-  const float s = p0 * g0 + p1 * g1;
-  dlogits[i] = e == i1 ? p1 * (g1 - s) : e == i0 ? p0 * (g0 - s) : 0.f;
+  const size_t n = (size_t)T * E, stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const size_t t = i / E;
+    const int e = (int)(i - t * E);
+    const float p0 = prob[2 * t], p1 = prob[2 * t + 1], g0 = dprob[2 * t], g1 = dprob[2 * t + 1];
+    const int i0 = idx[2 * t], i1 = idx[2 * t + 1];
+    const float s = p0 * g0 + p1 * g1;
+    dlogits[i] = e == i1 ? p1 * (g1 - s) : e == i0 ? p0 * (g0 - s) : 0.f;
+  }
 }
 
 // ------------------------------------------------------------------------------------ permutation plan (M2, M3)
@@ -220,7 +223,7 @@ extern "C" int dh_moe_route_bwd(int T, int E, const float* dprob, const int32_t*
   if (T < 0 || E < 2 || E > 256) DH_FAIL(DH_ERR_SHAPE, "moe_route_bwd: T=%d E=%d (E must be 2..256)", T, E);
   if (T == 0) return DH_OK;
   if (!dprob || !idx || !prob || !dlogits) DH_FAIL(DH_ERR_INVALID_ARG, "moe_route_bwd: null pointer");
-  moe_route_bwd_kernel<<<(unsigned)(((size_t)T * E + 255) / 256), 256, 0, (hipStream_t)stream>>>(T, E, dprob, idx, prob, dlogits);
+  moe_route_bwd_kernel<<<(unsigned)std::min<size_t>(((size_t)T * E + 255) / 256, ROUTE_BWD_BLOCKS), 256, 0, (hipStream_t)stream>>>(T, E, dprob, idx, prob, dlogits);
   DH_LAUNCH_CHECK();
   return DH_OK;
 }
