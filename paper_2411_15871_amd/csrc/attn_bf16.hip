@@ -827,9 +827,8 @@ __device__ __forceinline__ void attn_bwd_dq_reduce_block(int bx, int by, int bz,
 // (the keys are the same), cut into chunks of g.ch tiles wherever that falls.  A key block of one chunk writes dK, dV; the
 // chunks of the others write float32 partials part[batch][kv head][pair][128 keys][dK | dV] that
 // attn_bwd_reduce_kernel (its dK/dV part) adds in chunk order.  Against a block per query head, whose partials of every head went
-// through memory, the whole backward pass (us): 4:1 heads x 4096 tokens 111 -> 102, 4096 queries over 12288 keys 382 -> 328, 32:8 heads x 4096
-// 526 -> 494, 16:4 x 1500 88 -> 72, 8:1 x 8192 520 -> 510, 4:4 x 4096 130 -> 108; D = 64, 4:1 x 8192 215 -> 165, 32:4 x 2 x 1000 63 -> 66
-// (a head group's tile bookkeeping beside tiles half as long).
+// through memory, the whole backward pass (us, chunk lengths as they were): 4:1 heads x 4096 tokens 103 -> 93, 4096 queries over 12288 keys 371 -> 315,
+// 32:8 x 4096 508 -> 471, 16:4 x 1500 86 -> 81, 8:1 x 8192 499 -> 493; D = 64, 4:1 x 8192 210 -> 164, 16:4 x 3010 135 -> 115, 16:2 x 5000 234 -> 229.
 template <int D>
 __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom& g, const bf16_t* __restrict__ qkv,
                                                    const bf16_t* __restrict__ dout, const float* __restrict__ lse2,
@@ -933,12 +932,17 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
 #pragma unroll
     for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ds + 8 * x + 4 * kg);
     if (qb < jw + 32 || qb + AB_KT > seq) {  // diagonal tile, or rows past the end of the sequence
+      // One comparison a row, four rows at a time: two a row, all ahead of the selects, held 64 scalar registers at D = 64, and the
+      // loop's own scalars (bases, strides, the head and tile to fetch next) were fetched from vector lanes in every tile (91 spilled: 32:4 heads x 1200
+      // tokens, the whole backward pass, 65 us; now none, 56.  2 x 1000 69 -> 65, 8:1 x 4096 104 -> 97).
+      const int first = qb + 4 * kg;
+      const uint32_t rows = (uint32_t)max(seq - jk, 0);
 #pragma unroll
       for (int mt = 0; mt < 2; mt++)
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-          const int qi = qb + mt * 32 + 8 * (r >> 2) + 4 * kg + (r & 3);
-          if (qi < jk || qi >= seq) st[mt][r] = 0.f;
+          st[mt][r] = (uint32_t)(first + mt * 32 + 8 * (r >> 2) + (r & 3) - jk) < rows ? st[mt][r] : 0.f;
+          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
     }
     // dV^T += dO^T P; once a quarter of P (8 registers of a tile) is packed for its products, it is turned
@@ -1109,9 +1113,10 @@ static int attn_num_cus() {  // of the current device
 // first; what a chunk length takes is simulated and the best one taken.  The hardware hands blocks to the 8 dies in turn and, on a die, to its 4
 // shader engines in turn, none before the one ahead of it: a block waits for a unit of its engine though others are
 // free.  (That order fits what chunk lengths measure: dK/dV of 8 heads x 8192 tokens on one key/value head, 136 / 140 / 144 tiles a chunk
-// 535 / 504 / 509 us for the whole backward pass, where the first free unit would make 136 the best.)  The constants are measured on MI355X (microseconds at D = 128): a block's tile with two
-// blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its unit, 2.0; a block beyond its tiles 3, with a partial
-// dK/dV result to store 9; partial results are read back at 4-5 MB per microsecond, by a launch of its own that takes 4-12.
+// 535 / 504 / 509 us for the whole backward pass, where the first free unit would make 136 the best.)  The constants are measured on MI355X
+// (microseconds at D = 128): a block's tile with two blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its
+// unit, 2.0; a block beyond its tiles 3, with a partial dK/dV result to store 9; partial results are read back at 4-5 MB per microsecond, by a launch
+// of its own that takes 4-12.
 // Where every query head has a key/value head of its own, dQ and dK/dV units fill one launch, alternating, and are cut alike.
 enum { PICK_FWD, PICK_DQ, PICK_DKV, PICK_BOTH };
 struct PickKey {
