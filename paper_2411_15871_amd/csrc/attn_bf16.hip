@@ -1114,7 +1114,7 @@ static int attn_num_cus() {  // of the current device
 // shader engines in turn, none before the one ahead of it: a block waits for a unit of its engine though others are
 // free.  (That order fits what chunk lengths measure: dK/dV of 8 heads x 8192 tokens on one key/value head, 136 / 140 / 144 tiles a chunk
 // 535 / 504 / 509 us for the whole backward pass, where the first free unit would make 136 the best.)  The constants are measured on MI355X
-// (microseconds at D = 128): a block's tile with two blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its
+// (microseconds at D = 128; dQ at D = 64 below): a block's tile with two blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its
 // unit, 2.0; a block beyond its tiles 3, with a partial dK/dV result to store 9; partial results are read back at 4-5 MB per microsecond, by a launch
 // of its own that takes 4-12.
 // Where every query head has a key/value head of its own, dQ and dK/dV units fill one launch, alternating, and are cut alike.
@@ -1140,11 +1140,69 @@ static std::vector<int> dkv_units(int seq, int q_off, int grp, int ch) {
 struct LaunchModel {
   int resident;       // blocks a unit holds
   double tile, alone, ovh, us_per_byte, merge;
+  bool tail;          // a block whose neighbour on the unit is through goes on faster
 };
 static LaunchModel launch_model(int kind, int d) {
   const double w = d / 128.0;
-  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 1 / 5.0e6, 4.0};
-  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 1 / 4.0e6, 12.0};
+  // D = 64: fitted with the tail to ten shapes, 600 to 7000 tokens on 8 to 32 heads; the length taken is 0.3 % behind the best one on average.  Without it (and
+  // with the constants of D = 128) whole rows, whose longest blocks end by themselves, looked longer than they are: 16:2 heads x 5000 tokens
+  // dQ in chunks of 68 tiles 120 us, whole 102.
+  if (kind == PICK_DQ && d == 64) return {2, 1.1, 0.65, 3.0, 1 / 3.0e6, 4.0, true};
+  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 1 / 5.0e6, 4.0, false};
+  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 1 / 4.0e6, 12.0, false};
+}
+// simulate_launch for blocks that share a unit two by two, each as fast as the unit's other block lets it be.
+static double simulate_tail(const LaunchModel& m, const std::vector<int>& units, int heads) {
+  struct Unit { double at, left[2]; int n, version; };  // work left of its n blocks at time `at`, in us of a block alone
+  struct Event {
+    double end;
+    int engine, unit, version;
+    bool operator<(const Event& o) const { return end > o.end; }
+  };
+  const int per = std::max(1, attn_num_cus() / 32);
+  std::vector<Unit> unit(32 * per, Unit{0.0, {0.0, 0.0}, 0, 0});
+  std::priority_queue<Event> ends;
+  const long long all = (long long)units.size() * heads;
+  long long next[8];  // of the blocks of a die
+  for (int die = 0; die < 8; die++) next[die] = die;
+  auto rate = [&](const Unit& u) { return u.n > 1 ? m.alone : 1.0; };
+  auto advance = [&](Unit& u, double now) {
+    for (int i = 0; i < u.n; i++) u.left[i] -= rate(u) * (now - u.at);
+    u.at = now;
+  };
+  auto expect = [&](int engine, int c) {
+    Unit& u = unit[engine * per + c];
+    u.version++;
+    if (u.n > 0) ends.push({u.at + (u.n > 1 ? std::min(u.left[0], u.left[1]) : u.left[0]) / rate(u), engine, c, u.version});
+  };
+  auto place = [&](int die, double now) {  // the die's next blocks, in order, until one finds its engine full
+    for (; next[die] < all; next[die] += 8) {
+      const int engine = die * 4 + (int)((next[die] >> 3) & 3);
+      int c = 0;
+      for (int i = 1; i < per; i++) if (unit[engine * per + i].n < unit[engine * per + c].n) c = i;
+      Unit& u = unit[engine * per + c];
+      if (u.n >= 2) return;
+      advance(u, now);
+      u.left[u.n++] = units[next[die] / heads] * m.tile * m.alone + m.ovh;
+      expect(engine, c);
+    }
+  };
+  for (int die = 0; die < 8; die++) place(die, 0.0);
+  double now = 0.0;
+  while (!ends.empty()) {
+    const Event e = ends.top();
+    ends.pop();
+    Unit& u = unit[e.engine * per + e.unit];
+    if (e.version != u.version) continue;
+    now = e.end;
+    advance(u, now);
+    int n = 0;
+    for (int i = 0; i < u.n; i++) if (u.left[i] > 1e-6) u.left[n++] = u.left[i];
+    u.n = n;
+    expect(e.engine, e.unit);
+    place(e.engine / 4, now);
+  }
+  return now;
 }
 // units: tiles of the units of one head, in launch order.
 static double simulate_launch(const LaunchModel& m, const std::vector<int>& units, int heads) {
@@ -1200,11 +1258,11 @@ static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int gr
       units = q_units;
     }
     if ((long long)units.size() * heads > 16 * slots && ch < AB_WHOLE) return;  // so many rounds need no chunks as short
-    const double t = simulate_launch(m, units, heads) + (bytes > 0 ? bytes * heads * 128 * sizeof(float) * m.us_per_byte + m.merge : 0.0);
+    const double t = (m.tail ? simulate_tail(m, units, heads) : simulate_launch(m, units, heads)) + (bytes > 0 ? bytes * heads * 128 * sizeof(float) * m.us_per_byte + m.merge : 0.0);
     if (t < best_t) { best_t = t; best = ch; }
   };
-  consider(AB_WHOLE);
   if ((long long)nblk * heads < 8 * slots && nblk <= 1024) {
+    consider(AB_WHOLE);
     const int least = kind == PICK_DKV ? 1 : 2;  // dQ: even, so that every wave sees a chunk's first tile
     for (int c = 4; c < max_tiles; c += std::max(least, c / 32 * least)) consider(c);
   }
