@@ -272,19 +272,27 @@ typedef struct {
   double rate_bwd[DH_MAX_OPS][DH_MAX_OPS];
   double p_pair[DH_MAX_OPS][DH_MAX_OPS];    /* P_ij of one instance of each, seconds, from the measured rates */
   double oef[DH_MAX_OPS][DH_MAX_OPS];       /* Eq. 1 */
+  /* Backward operators that strand beta issues as one launch where they follow one another in a segment pair and the second is not
+   * beside the strand (a linear's data and weight gradient): joint[j] = 1 + the operator that goes out with operator j when it comes
+   * right after it, 0 = none.  Where set, the two together take t_joint[j] alone and progress beside forward operator i at these rates. */
+  int joint[DH_MAX_OPS];
+  double t_joint[DH_MAX_OPS];
+  double rate_fwd_joint[DH_MAX_OPS][DH_MAX_OPS];
+  double rate_bwd_joint[DH_MAX_OPS][DH_MAX_OPS];
 } dh_overlap_table;
 
 /* Eq. 1: (t_i + t_j - p_ij) / min(t_i, t_j).  Host only; returns the value. */
 double dh_oef(double t_i, double t_j, double p_ij);
 
 /* Co-run time of a forward segment with a backward segment under the two-queue fluid model
- * (each strand runs its operators in order; a pair of active operators progresses at the table's
- * rates; a lone operator at rate 1).  seg_f/seg_b: host arrays of operator ids.  Host only;
+ * (each strand runs its operators in order, those of table.joint as one; a pair of active operators progresses at the
+ * table's rates; a lone operator at rate 1).  seg_f/seg_b: host arrays of operator ids.  Host only;
  * returns seconds, or a negative dh_status cast to double on bad arguments. */
 double dh_segment_cost(const dh_overlap_table* t, const int* seg_f, int n_f, const int* seg_b, int n_b);
 
 /* Measures the table on the current device: every operator alone and every forward/backward pair
- * co-started on two streams (collective stand-ins on comm_stream).  The strands' buffers must
+ * co-started on two streams (collective stand-ins on comm_stream), and the same of the operators that dh_si_step
+ * issues as one launch.  The strands' buffers must
  * already hold a completed forward (alpha, beta) and backward (beta) so every operator has valid
  * inputs.  The operators run over and over in place: the gradient buffers are added to, and alpha's
  * saved slot, alpha's out and beta's dx are overwritten (RoPE turns alpha's saved qkv again on every
@@ -353,7 +361,7 @@ typedef struct {
  * two strands, the communication stream(s) and the cross-node stream are lanes that run their operators in issue
  * order; a stand-in on a lane of its own starts behind what its strand has issued and holds up only the operators
  * that consume its result (dh_op_graph.in_strand says which stand-ins stay in their strand's lane instead); bwd_side
- * operators run in alpha's lane -- and integrated as a fluid: every active operator
+ * operators run in alpha's lane; two operators of table.joint that follow one another are one -- and integrated as a fluid: every active operator
  * advances at the product of its profiled pairwise rates against the other active operators (operators of one
  * direction through like_other, rate 1 where that is 0).  barrier_cost is added per segment pair.  This is P of Eq. 2
  * for three and more participants (a stand-in beside two compute kernels), which the two-queue dh_segment_cost cannot

@@ -69,8 +69,32 @@ def pair_dp(p_f, p_b, p_fb):
     return T[nf][nb], steps[::-1]
 
 
-def segment_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b):
+def join(seg_b, t_b, rate_f, rate_b, joint):
+    """Backward operators that follow one another and go out as one launch become one operator of its own time and rates.
+    joint: {op: (operator that goes out with it, time, rates of the forward operators, its rates beside them)}.  Returns the
+    sequence and the table with the joint operators added behind the others."""
+    t_b, rate_f, rate_b = list(t_b), [list(r) for r in rate_f], [list(r) for r in rate_b]
+    seq, k = [], 0
+    while k < len(seg_b):
+        op = seg_b[k]
+        if op in joint and k + 1 < len(seg_b) and seg_b[k + 1] == joint[op][0]:
+            _, t, rf, rb = joint[op]
+            seq.append(len(t_b))
+            t_b.append(t)
+            for i in range(len(rate_f)):
+                rate_f[i].append(rf[i])
+                rate_b[i].append(rb[i])
+            k += 2
+        else:
+            seq.append(op)
+            k += 1
+    return seq, t_b, rate_f, rate_b
+
+
+def segment_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, joint=None):
     """Fluid co-run time of forward operators seg_f (ids, in order) with backward operators seg_b."""
+    if joint:
+        seg_b, t_b, rate_f, rate_b = join(seg_b, t_b, rate_f, rate_b, joint)
     fi = bi = 0
     rem_f = t_f[seg_f[0]] if seg_f else 0.0
     rem_b = t_b[seg_b[0]] if seg_b else 0.0
@@ -158,7 +182,7 @@ def rates_from_corun(t_a, t_b, end_a, end_b):
 
 
 def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm_f=None, comm_b=None, lanes=(0, 0, 0),
-              side=(), like_f=None, like_b=None, stay_f=None, stay_b=None):
+              side=(), like_f=None, like_b=None, stay_f=None, stay_b=None, joint=None):
     """Fluid co-run time of one segment pair on the executor's streams.
     comm_x[op]: 0 compute, 1 collective stand-in, 2 cross-node transfer.  lanes = (comm_alpha, comm_beta, cross):
     comm_alpha 0/1 = alpha's collectives in alpha's stream / on the communication stream; comm_beta 0/1/2 = in beta's
@@ -166,10 +190,26 @@ def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm
     the cross-node stream.  side: backward operators that run beside their strand (in alpha's stream).
     like_x[op]: id of the like operator in the other direction (or absent).
     stay_x[op]: collectives kept in their strand's stream: 2 always, 1 where the strand's next operator of the pair needs
-    the result or none follows (absent or 0: never)."""
+    the result or none follows (absent or 0: never).
+    joint: see join(); the second operator of a launch is then not beside the strand, and a joint launch is like whatever its first
+    operator is like, else like what its second is."""
     comm_f, comm_b = comm_f or {}, comm_b or {}
     like_f, like_b = like_f or {}, like_b or {}
     stay_f, stay_b = stay_f or {}, stay_b or {}
+    joint = {op: v for op, v in (joint or {}).items() if op not in side and v[0] not in side}
+    members = {}   # of the joint operators in the sequence
+    if joint:
+        seg, t_b, rate_f, rate_b = join(seg_b, t_b, rate_f, rate_b, joint)
+        like_b = dict(like_b)
+        k = 0
+        for op in seg:
+            members[op] = tuple(seg_b[k: k + 2]) if op != seg_b[k] else (op,)
+            k += len(members[op])
+            for m in members[op]:
+                if op not in like_b and m in like_b:
+                    like_b[op] = like_b[m]
+        seg_b = seg
+    inputs_of = lambda op: members.get(op, (op,))
     A, B, COMM, COMM_B, CROSS = "alpha", "beta", "comm", "comm_beta", "cross"
 
     def stream_of(direction, kind):
@@ -218,11 +258,12 @@ def lane_cost(seg_f, seg_b, t_f, t_b, rate_f, rate_b, deps_f=(), deps_b=(), comm
                 submit("f", op, A, ())
         if bi < len(seg_b):
             op = seg_b[bi]; bi += 1
-            strand_waits_for_inputs("b", op, deps_b, B)
+            for m in inputs_of(op):
+                strand_waits_for_inputs("b", m, deps_b, B)
             if op in side:
                 submit("b", op, A, set(queue[B][-1:]) | waits[B])   # behind beta's issued work and what beta waits for
                 continue
-            st = B if stays(stay_b, deps_b, op, seg_b[bi:]) else stream_of("b", comm_b.get(op, 0))
+            st = B if stays(stay_b, deps_b, op, [inputs_of(o)[0] for o in seg_b[bi:]]) else stream_of("b", comm_b.get(op, 0))
             if st != B:
                 pending["b"][op] = submit("b", op, st, queue[B][-1:])
             else:

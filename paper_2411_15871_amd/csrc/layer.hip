@@ -1386,10 +1386,12 @@ extern "C" void dh_si_graph_destroy(dh_si_graph* g) {
 // ------------------------------------------------------------------------------------ profiler
 struct TimedOp {
   int dir, op;
+  int pair;  // PairedLinear whose launch op's is, or -1
 };
 
 static int launch_op(dh_layer* L, const TimedOp& o, const dh_fwd_args& a, const dh_bwd_args& b, char* ws_f, char* ws_b,
                      hipStream_t s) {
+  if (o.pair >= 0) return run_bwd_pair(L, o.pair, b, ws_b, true, s);
   return o.dir == 0 ? run_fwd_op(L, o.op, a, ws_f, s) : run_bwd_op(L, o.op, b, ws_b, s);
 }
 
@@ -1478,12 +1480,21 @@ extern "C" int dh_profile_pairs(dh_layer* L, const dh_fwd_args* alpha, const dh_
     if (cs) return cs;
     return dir == 0 ? sa : sb;
   };
+  // everything that is timed: single operators, then the backward ones that enqueue_si issues as one launch (as it does beside another strand)
+  std::vector<TimedOp> ops_f, ops_b;
+  int joint[DH_MAX_OPS] = {};  // goes into the table once its times and rates are there
+  for (int i = 0; i < NF; i++) ops_f.push_back({0, i, -1});
+  for (int j = 0; j < NB; j++) ops_b.push_back({1, j, -1});
+  for (int j = 0; j < NB; j++)
+    for (int next = 0; next < NB; next++) {
+      const int pair = paired_linear(L, j, next, true);
+      if (pair >= 0) { ops_b.push_back({1, j, pair}); joint[j] = next + 1; }
+    }
+  auto t_of = [&](const TimedOp& o) -> double& { return o.dir == 0 ? out->t_fwd[o.op] : o.pair >= 0 ? out->t_joint[o.op] : out->t_bwd[o.op]; };
   // solo times
-  for (int dir = 0; dir < 2; dir++) {
-    const int n = dir == 0 ? NF : NB;
-    for (int op = 0; op < n; op++) {
-      hipStream_t s = stream_of(dir, op);
-      TimedOp t{dir, op};
+  for (const auto* ops : {&ops_f, &ops_b})
+    for (const TimedOp& t : *ops) {
+      hipStream_t s = stream_of(t.dir, t.op);
       if ((rc = launch_op(L, t, *alpha, *beta, ws_f, ws_b, s))) { cleanup(); return rc; }  // warm-up
       // two timed groups of reps launches, the shorter one counts: a hiccup of the machine (a clock ramp, a first touch)
       // lengthens one group, not both, and every pair measurement below is sized from these times
@@ -1501,18 +1512,17 @@ extern "C" int dh_profile_pairs(dh_layer* L, const dh_fwd_args* alpha, const dh_
       }
       // an operator that launches nothing (a Send/Recv stand-in with no peer, an activation that runs in its
       // neighbour's epilogue) measures ~0: floor it, so that the repeat counts, rates and Eq. 1 below stay finite
-      (dir == 0 ? out->t_fwd : out->t_bwd)[op] = std::max(best, 1e-7);
+      t_of(t) = std::max(best, 1e-7);
     }
-  }
   // pairs: both operators repeated so that the two streams stay busy for about the same window
-  for (int i = 0; i < NF; i++)
-    for (int j = 0; j < NB; j++) {
-      const double ta = out->t_fwd[i], tb = out->t_bwd[j];
+  for (const TimedOp& A : ops_f)
+    for (const TimedOp& B : ops_b) {
+      const int i = A.op, j = B.op;
+      const double ta = t_of(A), tb = t_of(B);
       const double window = std::max(ta, tb) * reps;
       const int ra = (int)std::min(64.0 * reps, std::max(1.0, std::round(window / ta)));
       const int rb = (int)std::min(64.0 * reps, std::max(1.0, std::round(window / tb)));
       hipStream_t s1 = stream_of(0, i), s2 = stream_of(1, j);
-      TimedOp A{0, i}, B{1, j};
       double end_a, end_b;
       if (s1 == s2) {  // both on the one communication stream: they serialise
         end_a = ta * ra;
@@ -1543,12 +1553,14 @@ extern "C" int dh_profile_pairs(dh_layer* L, const dh_fwd_args* alpha, const dh_
       else { qa = (wa - (end_a - t1)) / t1; qb = wb / t1; }
       qa = std::min(1.0, std::max(0.02, qa));
       qb = std::min(1.0, std::max(0.02, qb));
-      out->rate_fwd[i][j] = qa;
-      out->rate_bwd[i][j] = qb;
+      (B.pair >= 0 ? out->rate_fwd_joint : out->rate_fwd)[i][j] = qa;
+      (B.pair >= 0 ? out->rate_bwd_joint : out->rate_bwd)[i][j] = qb;
+      if (B.pair >= 0) continue;
       const int sf[1] = {i}, sbk[1] = {j};
       out->p_pair[i][j] = dh_segment_cost(out, sf, 1, sbk, 1);
       out->oef[i][j] = dh_oef(ta, tb, out->p_pair[i][j]);
     }
+  memcpy(out->joint, joint, sizeof(joint));
   cleanup();
   return DH_OK;
 }

@@ -10,15 +10,21 @@
 
 extern "C" double dh_oef(double t_i, double t_j, double p_ij) { return (t_i + t_j - p_ij) / std::min(t_i, t_j); }
 
+// Whether the backward operators sb[k] and sb[k+1] go out as one launch (dh_overlap_table.joint).
+static bool joint_at(const dh_overlap_table& t, const int* sb, int nb, int k) { return k + 1 < nb && t.joint[sb[k]] == sb[k + 1] + 1; }
+
 // Two-queue fluid model.  While forward operator a and backward operator b are both running they
 // advance at the profiled rates; when one finishes the next operator of its strand starts at once;
 // when one strand runs dry the other proceeds undisturbed.
 static double segment_cost(const dh_overlap_table& t, const int* sf, int nf, const int* sb, int nb) {
   int fi = 0, bi = 0;
   double now = 0.0;
-  double left_f = nf > 0 ? t.t_fwd[sf[0]] : 0.0, left_b = nb > 0 ? t.t_bwd[sb[0]] : 0.0;
+  auto work_b = [&](int k) { return k >= nb ? 0.0 : joint_at(t, sb, nb, k) ? t.t_joint[sb[k]] : t.t_bwd[sb[k]]; };
+  auto next_b = [&](int k) { return joint_at(t, sb, nb, k) ? k + 2 : k + 1; };
+  double left_f = nf > 0 ? t.t_fwd[sf[0]] : 0.0, left_b = work_b(0);
   while (fi < nf && bi < nb) {
-    const double rf = t.rate_fwd[sf[fi]][sb[bi]], rb = t.rate_bwd[sf[fi]][sb[bi]];
+    const bool joint = joint_at(t, sb, nb, bi);
+    const double rf = (joint ? t.rate_fwd_joint : t.rate_fwd)[sf[fi]][sb[bi]], rb = (joint ? t.rate_bwd_joint : t.rate_bwd)[sf[fi]][sb[bi]];
     const double need_f = left_f / rf, need_b = left_b / rb;
     const double dt = std::min(need_f, need_b);
     now += dt;
@@ -26,13 +32,22 @@ static double segment_cost(const dh_overlap_table& t, const int* sf, int nf, con
     left_b -= rb * dt;
     const bool f_done = need_f <= need_b, b_done = need_b <= need_f;
     if (f_done) { ++fi; left_f = fi < nf ? t.t_fwd[sf[fi]] : 0.0; }
-    if (b_done) { ++bi; left_b = bi < nb ? t.t_bwd[sb[bi]] : 0.0; }
+    if (b_done) { bi = next_b(bi); left_b = work_b(bi); }
   }
   if (fi < nf) { now += left_f; for (int k = fi + 1; k < nf; k++) now += t.t_fwd[sf[k]]; }
-  if (bi < nb) { now += left_b; for (int k = bi + 1; k < nb; k++) now += t.t_bwd[sb[k]]; }
+  if (bi < nb) { now += left_b; for (int k = next_b(bi); k < nb; k = next_b(k)) now += work_b(k); }
   return now;
 }
 
+// joint entries name a backward operator of the table, and have a time and rates.
+static bool joint_ok(const dh_overlap_table& t) {
+  for (int j = 0; j < t.n_bwd; j++) {
+    if (t.joint[j] == 0) continue;
+    if (t.joint[j] < 0 || t.joint[j] > t.n_bwd || t.joint[j] == j + 1 || !(t.t_joint[j] >= 0.0)) return false;
+    for (int i = 0; i < t.n_fwd; i++) if (!(t.rate_fwd_joint[i][j] > 0.0) || !(t.rate_bwd_joint[i][j] > 0.0)) return false;
+  }
+  return true;
+}
 static int check_table_ids(const dh_overlap_table* t, const int* sf, int nf, const int* sb, int nb) {
   if (!t || nf < 0 || nb < 0 || (nf > 0 && !sf) || (nb > 0 && !sb)) return DH_ERR_INVALID_ARG;
   if (t->n_fwd < 0 || t->n_fwd > DH_MAX_OPS || t->n_bwd < 0 || t->n_bwd > DH_MAX_OPS) return DH_ERR_INVALID_ARG;
@@ -41,7 +56,7 @@ static int check_table_ids(const dh_overlap_table* t, const int* sf, int nf, con
   for (int i = 0; i < nf; i++)
     for (int j = 0; j < nb; j++)
       if (!(t->rate_fwd[sf[i]][sb[j]] > 0.0) || !(t->rate_bwd[sf[i]][sb[j]] > 0.0)) return DH_ERR_INVALID_ARG;
-  return DH_OK;
+  return joint_ok(*t) ? DH_OK : DH_ERR_INVALID_ARG;
 }
 
 extern "C" double dh_segment_cost(const dh_overlap_table* t, const int* seg_f, int n_f, const int* seg_b, int n_b) {
@@ -205,6 +220,7 @@ extern "C" int dh_plan_search(const dh_op_graph* fwd, const dh_op_graph* bwd, co
   for (int i = 0; i < fwd->n_ops; i++)
     for (int j = 0; j < bwd->n_ops; j++)
       if (!(table->rate_fwd[i][j] > 0.0) || !(table->rate_bwd[i][j] > 0.0)) DH_FAIL(DH_ERR_INVALID_ARG, "plan_search: non-positive rate at (%d,%d)", i, j);
+  if (!joint_ok(*table)) DH_FAIL(DH_ERR_INVALID_ARG, "plan_search: joint operators out of range or without rates");
   if (max_orders <= 0) max_orders = 20000;  // every order of the layers' graphs (5760 for the Llama backward graph); dh_plan_count_orders tells
   std::vector<std::vector<int>> of, ob;
   long long tot_f = 0, tot_b = 0;
@@ -236,7 +252,8 @@ extern "C" int dh_plan_search(const dh_op_graph* fwd, const dh_op_graph* bwd, co
 // stream.  A stand-in issued on another lane than its strand's starts when everything its strand has issued so far
 // is done, and the strand waits for it only before an operator that consumes its result (operator graph) -- so weight
 // gradients overlap their own strand's collective (Sec. 4.2: the movable, "self-overlapping" operators), and an
-// operator flagged bwd_side runs on alpha's lane once beta's operators before it are done; which stand-ins stay in their
+// operator flagged bwd_side runs on alpha's lane once beta's operators before it are done; a data and a weight gradient that
+// the executor issues as one launch (dh_overlap_table.joint) are one node; which stand-ins stay in their
 // strand's lane is the executor's own rule (dh_leaves_strand).  The model replays exactly that issue logic as a dependency graph over lanes (a lane runs its operators in issue order) and integrates it as a
 // fluid: an active operator advances at the product of the pairwise rates of the table against every other active
 // operator.  Pairs of one direction are not in the table (the profiler co-runs forward with backward operators); they
@@ -246,6 +263,7 @@ namespace {
 enum { LANE_A = 0, LANE_B = 1, LANE_COMM = 2, LANE_COMM_B = 3, LANE_CROSS = 4, N_LANES = 5 };
 struct Node {
   int dir, op, lane;
+  int joint;  // the operator that goes out with op, or -1
   double work;
   int ndep;
   int dep[4 + DH_MAX_OPS];  // nodes that must have finished (besides the lane's previous node)
@@ -267,13 +285,15 @@ struct LaneSim {
   // rate of x while y is active
   double pair_rate(const Node& x, const Node& y) const {
     int xd = x.dir, xo = x.op, yd = y.dir, yo = y.op;
+    bool joint = x.joint >= 0 || y.joint >= 0;  // the backward one of the two, below
     if (xd == yd) {  // same direction: stand in the like operator of the other direction for one of them
       const dh_op_graph& g = xd == 0 ? gf : gb;
-      if (g.like_other[yo] > 0) { yd = 1 - yd; yo = g.like_other[yo] - 1; }
-      else if (g.like_other[xo] > 0) { xd = 1 - xd; xo = g.like_other[xo] - 1; }
+      auto like = [&](const Node& n) { return g.like_other[n.op] > 0 || n.joint < 0 ? g.like_other[n.op] : g.like_other[n.joint]; };
+      if (like(y) > 0) { yd = 1 - yd; yo = like(y) - 1; joint = x.joint >= 0; }
+      else if (like(x) > 0) { xd = 1 - xd; xo = like(x) - 1; joint = y.joint >= 0; }
       else return 1.0;
     }
-    return xd == 0 ? t.rate_fwd[xo][yo] : t.rate_bwd[yo][xo];
+    return xd == 0 ? (joint ? t.rate_fwd_joint : t.rate_fwd)[xo][yo] : (joint ? t.rate_bwd_joint : t.rate_bwd)[yo][xo];
   }
   // Builds the nodes of one segment pair the way dh_si_step issues it (alternating forward and backward operators).
   void build(const int* fo, int nf, const int* bo, int nb, const int* side) {
@@ -283,10 +303,10 @@ struct LaneSim {
     for (int i = 0; i < DH_MAX_OPS; i++) pend_f[i] = pend_b[i] = -1;
     std::vector<int> carry[N_LANES];  // extra dependencies of the next node issued on a lane (stream waits)
     auto last_of = [&](int lane) { return lane_nodes[lane].empty() ? -1 : lane_nodes[lane].back(); };
-    auto add = [&](int dir, int op, int lane, int extra_dep) {
+    auto add = [&](int dir, int op, int lane, int extra_dep, int joint = -1) {
       Node n;
-      n.dir = dir; n.op = op; n.lane = lane; n.ndep = 0;
-      n.work = dir == 0 ? t.t_fwd[op] : t.t_bwd[op];
+      n.dir = dir; n.op = op; n.lane = lane; n.joint = joint; n.ndep = 0;
+      n.work = dir == 0 ? t.t_fwd[op] : joint >= 0 ? t.t_joint[op] : t.t_bwd[op];
       for (int d : carry[lane]) n.dep[n.ndep++] = d;
       carry[lane].clear();
       if (extra_dep >= 0) n.dep[n.ndep++] = extra_dep;
@@ -315,6 +335,12 @@ struct LaneSim {
           std::vector<int> deps = carry[LANE_B];
           const int n = add(1, op, LANE_A, last_of(LANE_B));
           for (int d : deps) nodes[n].dep[nodes[n].ndep++] = d;
+          continue;
+        }
+        if (joint_at(t, bo, nb, bj - 1) && !(side && side[bo[bj]])) {
+          const int next = bo[bj++];
+          wait_inputs(gb, pend_b, next, LANE_B);
+          add(1, op, LANE_B, -1, next);
           continue;
         }
         const int lane = dh_leaves_strand(gb, op, bj < nb ? &bo[bj] : nullptr) ? comm_lane(1, gb.is_comm[op]) : LANE_B;
@@ -376,7 +402,7 @@ int check_table_for(const dh_op_graph* fwd, const dh_op_graph* bwd, const dh_ove
       if (!(table->rate_fwd[i][j] > 0.0) || !(table->rate_bwd[i][j] > 0.0)) return DH_ERR_INVALID_ARG;
   for (int i = 0; i < fwd->n_ops; i++) if (fwd->like_other[i] < 0 || fwd->like_other[i] > bwd->n_ops) return DH_ERR_INVALID_ARG;
   for (int j = 0; j < bwd->n_ops; j++) if (bwd->like_other[j] < 0 || bwd->like_other[j] > fwd->n_ops) return DH_ERR_INVALID_ARG;
-  return DH_OK;
+  return joint_ok(*table) ? DH_OK : DH_ERR_INVALID_ARG;
 }
 
 // Barrier placement with the lane model as P: the same recurrence as place_barriers.

@@ -90,7 +90,8 @@ class dh_overlap_table(C.Structure):
     _fields_ = [("n_fwd", C.c_int), ("n_bwd", C.c_int), ("t_fwd", C.c_double * DH_MAX_OPS),
                 ("t_bwd", C.c_double * DH_MAX_OPS), ("rate_fwd", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS),
                 ("rate_bwd", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS), ("p_pair", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS),
-                ("oef", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS)]
+                ("oef", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS), ("joint", C.c_int * DH_MAX_OPS), ("t_joint", C.c_double * DH_MAX_OPS),
+                ("rate_fwd_joint", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS), ("rate_bwd_joint", (C.c_double * DH_MAX_OPS) * DH_MAX_OPS)]
 
 
 class dh_seg_pair(C.Structure):
@@ -317,8 +318,13 @@ def dh_oef(t_i, t_j, p_ij):
     return lib.dh_oef(t_i, t_j, p_ij)
 
 
-def make_table(t_fwd, t_bwd, rate_fwd, rate_bwd):
+def make_table(t_fwd, t_bwd, rate_fwd, rate_bwd, joint=None):
+    """joint: {op: (operator that goes out with it, time, rates of the forward operators, its rates beside them)} (see dh_overlap_table)."""
     t = dh_overlap_table()
+    for op, (other, time, rf, rb) in (joint or {}).items():
+        t.joint[op], t.t_joint[op] = other + 1, time
+        for i in range(len(t_fwd)):
+            t.rate_fwd_joint[i][op], t.rate_bwd_joint[i][op] = rf[i], rb[i]
     t.n_fwd, t.n_bwd = len(t_fwd), len(t_bwd)
     for i, v in enumerate(t_fwd):
         t.t_fwd[i] = v

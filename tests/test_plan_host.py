@@ -364,3 +364,72 @@ def test_lane_search_on_every_architecture_graph(name):
                 assert mk <= dh.dh_plan_cost(gf, gb, tab, free, ln, bc) * (1 + 1e-9)
     finally:
         dh.dh_layer_destroy(L)
+
+
+# ------------------------------------------------------------------ two backward operators in one launch
+def rand_joint(nf, op, other, t_b):
+    """Operator `other` goes out with `op` where it comes right after it (dh_overlap_table.joint)."""
+    return {op: (other, random.uniform(0.6, 1.0) * (t_b[op] + t_b[other]), [random.uniform(0.2, 1.0) for _ in range(nf)],
+                 [random.uniform(0.2, 1.0) for _ in range(nf)])}
+
+
+def test_joint_operators_match_the_oracle():
+    """Segment cost, plan cost under every placement and both searches, with operators that the executor issues as one launch: at a
+    segment's end and across its border, beside the strand (then apart), behind a collective whose result the second one needs."""
+    for trial in range(40):
+        nf, nb, deps_f, deps_b, t_f, t_b, rf, rb, gf, gb, okw = rand_case()
+        joint = {**rand_joint(nf, 0, 4, t_b), **rand_joint(nf, 2, 5, t_b)}
+        if trial & 1:
+            joint.update(rand_joint(nf, 3, 5, t_b))   # 5 goes out with either
+        tab = dh.make_table(t_f, t_b, rf, rb, joint)
+        for _ in range(4):
+            sf, sb = [random.randrange(nf) for _ in range(random.randrange(5))], random.sample(range(nb), random.randrange(nb + 1))
+            ref = P.segment_cost(sf, sb, t_f, t_b, rf, rb, joint)
+            assert abs(dh.dh_segment_cost(tab, sf, sb) - ref) <= 1e-12 * max(1.0, ref)
+        fo, bo = rand_order(nf, deps_f), random.choice([[0, 4, 1, 2, 5, 3], [0, 4, 1, 2, 3, 5], rand_order(nb, deps_b)])
+        cut_f, cut_b = random.randrange(nf + 1), random.randrange(nb + 1)
+        pairs = [q for q in [(0, cut_f, 0, cut_b), (cut_f, nf, cut_b, nb)] if q[0] != q[1] or q[2] != q[3]]
+        side = tuple(op for op in (4, 5) if random.random() < 0.3)
+        stay_b = {1: random.randrange(3)}
+        gs = dh.make_graph(nb, deps_b, comm={1: 1}, side_ok=(4, 5), like=okw["like_b"], in_strand=stay_b)
+        plan = dh.make_plan(fo, bo, pairs, side)
+        for lanes in [(0, 0, 0), (1, 1, 0), (1, 2, 0), (0, 2, 0)]:
+            got = dh.dh_plan_cost(gf, gs, tab, plan, dh.lanes(*lanes), 0.01)
+            ref = P.plan_cost_lanes(pairs, fo, bo, t_f, t_b, rf, rb, 0.01, lanes=lanes, side=side, stay_b=stay_b, joint=joint, **okw)
+            assert abs(got - ref) <= 1e-11 * max(1.0, ref), (lanes, fo, bo, pairs, side, joint)
+        if trial < 2:
+            plan, mk, _ = dh.dh_plan_search_lanes(gf, gb, tab, dh.lanes(1, 2, 0), 0.02, 0)
+            best = min(P.search_cuts_lanes(of, ob, t_f, t_b, rf, rb, 0.02, lanes=(1, 2, 0), side=sd, joint=joint, **okw)[0]
+                       for of in P.topo_orders(nf, deps_f) for ob in P.topo_orders(nb, deps_b) for sd in [(), (4,), (5,), (4, 5)])
+            assert mk >= best - 1e-11
+            assert abs(dh.dh_plan_cost(gf, gb, tab, plan, dh.lanes(1, 2, 0), 0.02) - mk) <= 1e-11 * max(1.0, mk)
+
+
+def test_joint_entries_are_checked():
+    nf, nb, deps_f, deps_b, t_f, t_b, rf, rb, gf, gb, _ = rand_case()
+    good = rand_joint(nf, 0, 4, t_b)[0]
+    for bad in ({0: (0,) + good[1:]}, {0: (nb,) + good[1:]}, {0: (-3,) + good[1:]}, {0: (4, -1.0) + good[2:]}, {0: good[:2] + ([0.0] * nf, good[3])}):
+        tab = dh.make_table(t_f, t_b, rf, rb, bad)
+        plan = dh.make_plan(list(range(nf)), list(range(nb)), [(0, nf, 0, nb)])
+        for call in (lambda: dh.dh_segment_cost(tab, [0], [0, 4]), lambda: dh.dh_plan_cost(gf, gb, tab, plan, dh.lanes(0, 0, 0)),
+                     lambda: dh.dh_plan_search(gf, gb, tab, 0.0, 4), lambda: dh.dh_plan_search_lanes(gf, gb, tab, dh.lanes(0, 0, 0), 0.0, 4)):
+            with pytest.raises(dh.DhelixError):
+                call()
+
+
+def test_searches_keep_together_what_is_cheaper_together():
+    """A weight gradient that runs undisturbed beside a late forward operator, and slowly beside the early ones, moves there; where it costs next to
+    nothing in its data gradient's launch, it stays behind that."""
+    nf, nb, deps_f, deps_b, _, _, _, _, gf, gb, _ = rand_case()
+    t_f, t_b = [1.0] * nf, [2.0, 0.1, 1.0, 1.0, 2.0, 0.1]
+    rf, rb = [[1.0] * nb for _ in range(nf)], [[1.0] * nb for _ in range(nf)]
+    for i in range(nf):
+        rb[i][4] = rf[i][4] = 0.5 if i < nf - 1 else 1.0
+    joint = {0: (4, 2.1, [1.0] * nf, [1.0] * nf)}
+    for search in (lambda t: dh.dh_plan_search(gf, gb, t, 0.0, 0)[0], lambda t: dh.dh_plan_search_lanes(gf, gb, t, dh.lanes(0, 0, 0), 0.0, 0)[0]):
+        apart, together = search(dh.make_table(t_f, t_b, rf, rb)), search(dh.make_table(t_f, t_b, rf, rb, joint))
+        fo, bo, pairs = dh.plan_to_py(apart)
+        assert bo.index(4) > 1
+        fo, bo, pairs = dh.plan_to_py(together)
+        assert bo.index(4) == bo.index(0) + 1 and not together.bwd_side[4]
+        assert any(c <= bo.index(0) and bo.index(4) < d for _, _, c, d in pairs)  # in one segment pair: one launch
