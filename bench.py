@@ -393,6 +393,8 @@ def main():
         for placement, (lanes, c, cb) in placements.items():
             plan, predicted, info = dh.dh_plan_search_lanes(gf, gb, table, lanes, args.barrier_cost, 0)
             rows.append(["searched", placement, predicted, None, plan, info])
+            fixed, predicted, info = dh.dh_plan_search_lanes(gf, gb, table, lanes, args.barrier_cost, 1)
+            rows.append(["searched, default orders", placement, predicted, None, fixed, info])
             for name, q in (("default orders, one pair", free_plan), ("sequential", seq_plan)):
                 rows.append([name, placement, dh.dh_plan_cost(gf, gb, table, q, lanes, args.barrier_cost), None, q, None])
         t_search = time.perf_counter() - t0
@@ -401,12 +403,12 @@ def main():
             (label, t_search, info.orders_fwd_tried, info.orders_bwd_tried, "truncated" if info.truncated else "all of them", info.refined))
         for r in rows:
             r[3] = measure(r[4], r[1])
-        # Every plan that runs comes from dh_plan_search_lanes, one per placement of the stand-ins; which of the three
-        # placements to use is a property of the machine (how its queues and caches take a third and fourth stream) that
-        # the pairwise table does not hold, so that one choice is made by measurement.  The other rows are measured too,
-        # so that the table shows what the model is worth.
-        searched = [r for r in rows if r[0] == "searched"]
-        best = min(searched, key=lambda r: r[3])
+        # The search proposes a plan per placement of the stand-ins, over all operator orders and over the default ones alone.  Which
+        # of them runs is decided by measurement: how a machine's queues and caches take a third and fourth stream is not in
+        # the pairwise table, and plans that the model holds within 1 % of each other have measured 5 % apart (the GPT shard:
+        # 2381 us searched over all orders, 2272 in the default ones, predicted 2132 and 2196), so the default orders, free-running, are a
+        # candidate as well.  The sequential rows are there to show what the model is worth.
+        best = min((r for r in rows if r[0] != "sequential"), key=lambda r: r[3])
         lines = ["predicted (lane model) vs measured step time, workload %s, stand-ins on %s blocks" % (args.workload, comm_blocks or "payload-sized"),
                  "%-28s %-36s %12s %12s %8s" % ("plan", "stand-ins on", "predicted us", "measured us", "ratio")]
         for name, placement, pred, meas, _, _ in rows:
@@ -420,7 +422,7 @@ def main():
         plan, placement = best[4], best[1]
         lanes, c, cb = placements[placement]
         segs, side = describe(plan)
-        log("[%s] chosen plan (stand-ins on %s), beside the strand %s:" % (label, placement, side), segs)
+        log("[%s] chosen plan (%s; stand-ins on %s), beside the strand %s:" % (label, best[0], placement, side), segs)
         dh.dh_layer_set_beta_comm_stream(run.layer, cb)
         step = lambda q=plan: run.si_step(alpha, beta, q, sa, sb, c)
         ts_si = event_times(step, steps, warmup)
@@ -433,7 +435,7 @@ def main():
         dh.dh_layer_set_comm_blocks(run.layer, comm_blocks)
         t_si, t_seq, t_si_nc, t_seq_nc = median(ts_si), median(ts_seq), median(ts_si_nc), median(ts_seq_nc)
         visible = max(0.0, t_si - t_si_nc)
-        rec = {"comm_blocks": comm_blocks, "standins_on": placement, "plan_pairs": len(segs), "beside_strand": side,
+        rec = {"comm_blocks": comm_blocks, "plan": best[0], "standins_on": placement, "plan_pairs": len(segs), "beside_strand": side,
                "ms_si": t_si * 1e3, "ms_sequential": t_seq * 1e3, "ms_si_no_comm": t_si_nc * 1e3, "ms_sequential_no_comm": t_seq_nc * 1e3,
                "ms_standins_solo": t_comm * 1e3, "speedup_vs_sequential": t_seq / t_si,
                "comm_visible_ms": visible * 1e3, "comm_hidden_frac": (1.0 - visible / t_comm) if t_comm > 0 else None,
@@ -562,7 +564,7 @@ def main():
         "dtype": "bf16" if cfg["bf16"] else "f32", "data": "synthetic",
         "config": {"workload": args.workload, "arch": cfg["arch"], "tokens_per_strand": run.T, "comm_blocks": args.comm_blocks,
                    "cp": [cfg["cp_rank"], cfg["cp_ranks"]] if cfg["arch"] == "llama_cp" else None, "plan_pairs": len(segs),
-                   "plan": "dh_plan_search_lanes (lane model, all operator orders), beside the strand: %s" % ("+".join(side) or "none"),
+                   "plan": "%s (lane model), beside the strand: %s" % (rec["plan"], "+".join(side) or "none"),
                    "execution": "eager (one launch per operator)", "standins_on": rec["standins_on"]},
         "pct_bf16_peak": 100.0 * value / BF16_MFMA_PEAK_TFLOPS,
         "tflops_full_attention_convention": H.model_flops(cfg, full_attention=True) / t_si / 1e12,
