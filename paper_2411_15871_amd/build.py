@@ -2,6 +2,7 @@
 
     python -m paper_2411_15871_amd.build [--force]
 """
+import glob
 import os
 import subprocess
 import sys
@@ -24,7 +25,7 @@ EXTRA_FLAGS = {"attn_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor
 
 
 def _deps_mtime():
-    hdrs = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "gemm_bf16.h"), os.path.join(HERE, "..", "include", "dhelix.h")]
+    hdrs = glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(HERE, "..", "include", "dhelix.h")]
     return max(os.path.getmtime(h) for h in hdrs)
 
 
