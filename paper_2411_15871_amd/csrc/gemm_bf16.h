@@ -57,7 +57,7 @@ struct GemmArgs {
   const bf16_t* bias;          // optional [N], added before the bf16 store
   const int32_t* group_rows;   // grouped GEMM: device array of row counts (blockIdx.z = group), else nullptr
   int group_mode;              // 0/1: groups split M (A and C rows), B per group; 2: groups split K, C per group
-  // Modes 0/1 are issued as two launches: part 1 with the large tile, part 2 with the 128x128 tile.  When the groups'
+  // Modes 0/1 are issued as two launches: part 1 with the large tile, part 2 with 128x128 or 64x64 tiles.  When the groups'
   // large tiles would leave the last round of tiles over the compute units nearly empty (the row counts are data), part 1
   // keeps only each group's whole large-tile rows and part 2 takes the remainders; otherwise part 1 does everything.
   int group_part, n_groups, part1_bm, part1_bn, cus;
@@ -78,7 +78,7 @@ struct GemmArgs {
   // follow.  0 = none.
   int ar_blocks;
   int n_split;  // > 1: K splits of a launch whose index range covers splits x tiles, split after split (0: split = blockIdx.y)
-  int k_chain;  // K range a block sums on its own before it joins the total (a multiple of 32; 0: the whole split)
+  int k_chain;  // K range a block sums on its own before it joins the total (a multiple of G_BK, see g_check_chain; 0: the whole split)
 };
 // The stand-in's operands travel as a kernel argument of their own: GemmArgs is edited by the grouped path and lives in
 // registers, the partial pointers are indexed at run time and stay in the argument segment.
@@ -787,13 +787,18 @@ static int allow_lds(const void* kernel, bool* attr_set, int bytes) {
   }
   return DH_OK;
 }
+// A block counts its K ranges in stages: of a range that is no whole number of them it would make another one, of less than a stage none that ends.
+static int g_check_chain(const GemmArgs& g) {
+  if (g.k_chain < 0 || g.k_chain % G_BK) DH_FAIL(DH_ERR_INVALID_ARG, "gemm: K ranges of %d are no whole stages of %d", g.k_chain, G_BK);
+  return DH_OK;
+}
 // Launches `kernel` (tiles of BM x BN, LDS_BYTES of dynamic LDS) over the launch indices [tile_first, tile_first + n_tiles)
 // (n_tiles < 0: all of them).
 template <int BM, int BN, int LDS_BYTES, typename Kernel>
 static int launch_tiles(Kernel kernel, bool* attr_set, GemmArgs g, int splits, hipStream_t stream, int n_groups, int tile_first, int n_tiles,
                         const GemmAr* ar) {
-  const int rc = allow_lds((const void*)kernel, attr_set, LDS_BYTES);
-  if (rc) return rc;
+  int rc = g_check_chain(g);
+  if (rc || (rc = allow_lds((const void*)kernel, attr_set, LDS_BYTES))) return rc;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + BN - 1) / BN;
   g.n_split = n_tiles < 0 ? splits : 0;
@@ -845,8 +850,8 @@ template <int BM, int BN, int S, int OCC>
 static int launch_pair_tile(GemmArgs d, GemmArgs w, bool w_first, hipStream_t stream, int n_groups) {
   static bool attr_set[DH_MAX_DEVICES] = {};
   constexpr int ld = g_lds_bytes<BM, BN, S, false, true, false>(), lw = g_lds_bytes<BM, BN, S, true, false, true>(), lds = ld > lw ? ld : lw;
-  const int rc = allow_lds((const void*)gemm_bf16_pair_kernel<BM, BN, S, OCC>, attr_set, lds);
-  if (rc) return rc;
+  int rc;
+  if ((rc = g_check_chain(d)) || (rc = g_check_chain(w)) || (rc = allow_lds((const void*)gemm_bf16_pair_kernel<BM, BN, S, OCC>, attr_set, lds))) return rc;
   int blocks[2];
   GemmArgs* g[2] = {&d, &w};
   for (int i = 0; i < 2; i++) {

@@ -434,7 +434,8 @@ static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w
     case 5: return launch_pair<5>(d, w, w_first, stream, n_groups);
     case 6: return launch_pair<6>(d, w, w_first, stream, n_groups);
     case 7: return launch_pair<7>(d, w, w_first, stream, n_groups);
-    default: return launch_pair<8>(d, w, w_first, stream, n_groups);
+    case 8: return launch_pair<8>(d, w, w_first, stream, n_groups);
+    default: DH_FAIL(DH_ERR_INVALID_ARG, "gemm pair: no kernel with tile shape %d", cfg);
   }
 }
 bool dh_gemm_pair_pays(int T, int k, int n, bool beside) {
