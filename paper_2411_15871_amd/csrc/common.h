@@ -236,6 +236,8 @@ int dh_launch_gemm_swiglu_bwd_bf16(int T, int F, int H, const bf16_t* dy, const 
 // Data and weight gradient of a linear layer in one launch (see gemm_bf16.hip); *_pays: whether that is expected to be faster; beside:
 // while another stream's kernels run.
 bool dh_gemm_pair_pays(int T, int k, int n, bool beside);
+// The tile shape (GemmPlan.cfg) such a launch takes, 0 where it does not pay; n_groups 0: not grouped.
+int dh_gemm_pair_shape(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
                              bool beside, void* ws, size_t ws_bytes, hipStream_t stream);
 bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside);

@@ -438,12 +438,14 @@ static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w
     default: DH_FAIL(DH_ERR_INVALID_ARG, "gemm pair: no kernel with tile shape %d", cfg);
   }
 }
-bool dh_gemm_pair_pays(int T, int k, int n, bool beside) {
-  if (T <= 0 || k % 8 || n % 8) return false;
+int dh_gemm_pair_shape(int n_groups, int T, int k, int n, bool beside) {
+  if (T <= 0 || n_groups > 64 || k % 8 || n % 8) return 0;
   GemmPlan pd, pw;
   bool w_first;
-  return choose_pair({T, k, n}, {k, n, T}, 0, beside, pd, pw, w_first) == PAIR_TOGETHER;
+  const int rows = n_groups > 0 ? std::max(1, T / n_groups) : T;
+  return choose_pair({rows, k, n}, {k, n, rows}, n_groups, beside, pd, pw, w_first) == PAIR_TOGETHER ? pd.cfg : 0;
 }
+bool dh_gemm_pair_pays(int T, int k, int n, bool beside) { return dh_gemm_pair_shape(0, T, k, n, beside) != 0; }
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
                              bool beside, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
@@ -459,13 +461,7 @@ int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t
   return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1);
 }
 // The same for the experts' linears (group_rows as in dh_launch_gemm_grouped_bf16; T bounds the rows of all groups).
-bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside) {
-  if (T <= 0 || n_groups > 64 || k % 8 || n % 8) return false;
-  GemmPlan pd, pw;
-  bool w_first;
-  const int avg = std::max(1, T / n_groups);
-  return choose_pair({avg, k, n}, {k, n, avg}, n_groups, beside, pd, pw, w_first) == PAIR_TOGETHER;
-}
+bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside) { return dh_gemm_pair_shape(n_groups, T, k, n, beside) != 0; }
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "grouped gemm pair (bf16): T=%d k=%d n=%d", T, k, n);

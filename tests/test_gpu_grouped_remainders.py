@@ -28,3 +28,25 @@ def test_grouped_remainders(rows, n):
             err = (got[r0: r0 + r].float() - ref).norm(dim=1) / ref.norm(dim=1)
             assert float(err.max()) <= 4e-3  # per row: a rounding of 2^-9 an element
         r0 += r
+
+
+# A remainder's rows have the bits they have as part of a group that ends with a whole large tile: neither the launch nor its tile shape
+# (64x64 where remainders are few, else 128x128) shows in them.
+@pytest.mark.parametrize("rows", [[2049, 2048], [2113, 1983], [1025, 1279, 1024, 1024]])
+def test_remainder_rows_have_the_bits_of_whole_tiles(rows):
+    from paper_2411_15871_amd import dhelix as dh
+    print("case", rows, flush=True)
+    n, k, G = 4096, 4096, len(rows)
+    whole = [-(-r // 256) * 256 for r in rows]
+    g = torch.Generator(device="cuda").manual_seed(sum(rows))
+    bf = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    xs, W = [bf(w, k) for w in whole], bf(G, k, n)
+    outs = []
+    for counts in (rows, whole):
+        x, tot = torch.cat([v[:r] for v, r in zip(xs, counts)]).contiguous(), sum(counts)
+        c = torch.full((tot, n), 7.0, dtype=torch.bfloat16, device="cuda")
+        dh.dh_gemm_grouped(dh.DH_BF16, 0, G, torch.tensor(counts, dtype=torch.int32, device="cuda"), tot, k, n, x, W, c)
+        outs.append(torch.split(c, counts))
+    torch.cuda.synchronize()
+    for few, all_, r in zip(*outs, rows):
+        assert torch.equal(few, all_[:r])
