@@ -388,7 +388,8 @@ extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   L->b_attn = take(cur, L->b_attn_bytes);
   L->b_norm_bytes = gpt ? dh_layernorm_bwd_ws_bytes(L->Ts, c.hidden) : dh_rmsnorm_bwd_ws_bytes(L->Ts, c.hidden);
   L->b_norm = take(cur, L->b_norm_bytes);
-  L->b_colsum_bytes = gpt ? dh_colsum_ws_bytes(L->T, (int)std::max(std::max(H, F), (size_t)L->n_qkv)) : 0;
+  // The linears of the sequence shard have fewer rows, but more partial ones where only the whole sequence is long enough to take 32 rows a block.
+  L->b_colsum_bytes = gpt ? std::max(dh_colsum_ws_bytes(L->T, (int)std::max(F, (size_t)L->n_qkv)), dh_colsum_ws_bytes(L->Ts, (int)H)) : 0;
   L->b_colsum = take(cur, L->b_colsum_bytes);
   L->b_dyp = take(cur, moe ? Tf * H * es : 0);
   L->b_dprob = take(cur, moe ? 2 * T * 4 : 0);
