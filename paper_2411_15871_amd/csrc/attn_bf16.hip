@@ -149,7 +149,9 @@ __device__ __forceinline__ int nth_rest(int idx, int n, Rest rest) {
 // units a compute unit leave a short last round that way only.  In the blocks' order, 8 key/value heads of 4 query heads x 4096
 // tokens in chunks of 128 took 502 us: the hardware hands blocks to the shader engines in turn, so the long chunks, each followed by a
 // block's short one, met on the same engines.  Unsplit blocks are longest first by themselves.
-#define AB_WHOLE (1 << 20)  // tiles per chunk of a launch that splits no block
+// Tiles per chunk of a launch that splits no block: more than any block has (a key block has its group's heads x tokens / 64 of them, 2^20 with 64 heads
+// and 2^20 tokens).
+#define AB_WHOLE (1 << 30)
 __device__ __forceinline__ ChunkMap map_dkv(int id, int seq, int q_off, int c, int grp) {
   ChunkMap m;
   if (c >= AB_WHOLE) { m.blk = m.pair = id; m.chunk = 0; m.chunks = 1; return m; }
@@ -1316,7 +1318,7 @@ static int pick_chunk(int kind, int seq, int q_off, int heads, int d, int grp) {
 // Tiles per chunk of the forward kernel; 0 = blocks are not split.
 static int fwd_chunk_tiles(int batch, int seq, int q_off, int nq, int d) {
   const int ch = pick_chunk(PICK_FWD, seq, q_off, nq * batch, d, 1);
-  return ch >= (1 << 20) ? 0 : ch;
+  return ch >= AB_WHOLE ? 0 : ch;
 }
 // Tiles per chunk of the dQ and of the dK/dV kernel.
 static void bwd_chunk_tiles(int batch, int seq, int q_off, int nq, int nkv, int d, int& ch_q, int& ch_k) {

@@ -1,4 +1,4 @@
-"""Chunk lengths of the attention backward pass at D = 64, seen in the workspace it asks for.  No GPU needed (the rule then counts on 256 compute units,
+"""Chunk lengths of the attention backward pass, seen in the workspace it asks for.  No GPU needed (the rule then counts on 256 compute units,
 an MI355X's)."""
 import pytest
 
@@ -13,3 +13,12 @@ def test_whole_rows_have_no_dq_partials(batch, seq, nq, nkv, dkv_tiles):
     tiles = [nq // nkv * ((seq - i + 63) // 64) for i in range(0, seq, 128)]  # of a key block: its group's heads, one after the other
     partials = batch * nkv * sum(-(-t // dkv_tiles) for t in tiles) * 128 * 2 * d * 4
     assert dh.dh_attn_bwd_workspace_bytes(dh.DH_BF16, batch, seq, nq, nkv, d) == stats + partials
+
+
+# Over more than 1024 key blocks no block is cut, however many tiles its head group has (more than 2^20 here): were a length left that such blocks exceed, the
+# launch would count their chunks, and the kernel, which takes every unit for a whole block, would walk blocks behind the last one.
+@pytest.mark.parametrize("seq,nq,d", [(1100000, 64, 64), (1100000, 64, 128), (4300000, 16, 64)])
+def test_blocks_of_very_long_head_groups_stay_whole(seq, nq, d):
+    stats = -(-nq * seq * 4 // 256) * 256
+    assert nq * (-(-seq // 64)) > 1 << 20
+    assert dh.dh_attn_bwd_workspace_bytes(dh.DH_BF16, 1, seq, nq, 1, d) == stats
