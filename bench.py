@@ -175,7 +175,10 @@ def write_pair_table(path, args, table, fnames, bnames, t_f, t_b):
     with open(path, "w") as f:
         f.write("operator-pair table, workload %s, %d repetitions per measurement\n" % (args.workload, args.profile_reps))
         f.write("solo us, forward : " + "  ".join("%s %.1f" % (fnames[i], t_f[i] * 1e6) for i in range(nf)) + "\n")
-        f.write("solo us, backward: " + "  ".join("%s %.1f" % (bnames[j], t_b[j] * 1e6) for j in range(nb)) + "\n\n")
+        f.write("solo us, backward: " + "  ".join("%s %.1f" % (bnames[j], t_b[j] * 1e6) for j in range(nb)) + "\n")
+        joint = [j for j in range(nb) if table.joint[j]]
+        f.write("two operators of strand beta as one launch: " +
+                ("  ".join("%s+%s %.1f" % (bnames[j], bnames[table.joint[j] - 1], table.t_joint[j] * 1e6) for j in joint) or "none") + "\n\n")
         f.write("cell: rate kept while co-running forward%/backward%, then OEF (Eq. 1); rows: forward operator of strand alpha, "
                 "columns: backward operator of strand beta\n")
         f.write("%-8s" % "" + "".join("%-14s" % n[2:] for n in bnames[:nb]) + "\n")
