@@ -1116,32 +1116,35 @@ static int attn_num_cus() {  // of the current device
 // shader engines in turn, none before the one ahead of it: a block waits for a unit of its engine though others are
 // free.  (That order fits what chunk lengths measure: dK/dV of 8 heads x 8192 tokens on one key/value head, 136 / 140 / 144 tiles a chunk
 // 535 / 504 / 509 us for the whole backward pass, where the first free unit would make 136 the best.)  The constants are measured on MI355X
-// (microseconds at D = 128; dQ at D = 64 below): a block's tile with two blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its
-// unit, 2.0; a block beyond its tiles 3, with a partial dK/dV result to store 9; partial results are read back at 4-5 MB per microsecond, by a launch
-// of its own that takes 4-12.
-// Where every query head has a key/value head of its own, dQ and dK/dV units fill one launch, alternating, and are cut alike.
+// (microseconds at D = 128; D = 64 below): a block's tile with two blocks on its unit 2.2 for dQ (0.55 of that with one), dK/dV, alone on its
+// unit, 2.0; a block beyond its tiles 3 (dQ), 7 (dK/dV; 9 where they share a launch), with a partial dK/dV result 2 more; partial results are written and
+// read back at 2-5 MB per microsecond, by a launch of its own that takes 4-12 and that dK/dV's share with dQ's.
+// Where every query head has a key/value head of its own, dQ and dK/dV units fill one launch, alternating, and are cut alike, up to the
+// longest of either kind: behind a key buffer the query blocks' rows are far longer than the key blocks' columns (4 heads x 189 queries over 7997 keys: 125
+// and 3 tiles), and lengths up to the columns' alone left them whole (176 us, cut into 14 tiles 36).
 enum { PICK_FWD, PICK_DQ, PICK_DKV, PICK_BOTH };
 struct PickKey {
-  int kind, seq, q_off, nq_all, d, grp, cus;
+  int kind, seq, q_off, nq_all, d, grp, merged, cus;
   bool operator<(const PickKey& o) const {
-    return std::tie(kind, seq, q_off, nq_all, d, grp, cus) < std::tie(o.kind, o.seq, o.q_off, o.nq_all, o.d, o.grp, o.cus);
+    return std::tie(kind, seq, q_off, nq_all, d, grp, merged, cus) < std::tie(o.kind, o.seq, o.q_off, o.nq_all, o.d, o.grp, o.merged, o.cus);
   }
 };
+struct LaunchUnit { int tiles; bool part; };  // part: it stores a partial result
 // Tiles of the units of a dK/dV launch, in launch order (see map_dkv).
-static std::vector<int> dkv_units(int seq, int q_off, int grp, int ch) {
-  std::vector<int> tiles, rest;
+static std::vector<LaunchUnit> dkv_units(int seq, int q_off, int grp, int ch) {
+  std::vector<LaunchUnit> units, rest;
   for (int i = 0; i < (seq + 127) / 128; i++) {
     const int t = grp * dkv_tiles(i, seq, q_off);
-    tiles.insert(tiles.end(), t / ch, ch);
-    if (t % ch) rest.push_back(t % ch);
+    units.insert(units.end(), t / ch, {ch, t > ch});
+    if (t % ch) rest.push_back({t % ch, t > ch});
   }
-  std::sort(rest.begin(), rest.end(), std::greater<int>());
-  tiles.insert(tiles.end(), rest.begin(), rest.end());
-  return tiles;
+  std::stable_sort(rest.begin(), rest.end(), [](const LaunchUnit& a, const LaunchUnit& b) { return a.tiles > b.tiles; });
+  units.insert(units.end(), rest.begin(), rest.end());
+  return units;
 }
 struct LaunchModel {
   int resident;       // blocks a unit holds
-  double tile, alone, ovh, us_per_byte, merge;
+  double tile, alone, ovh, part, us_per_byte, merge;  // part: what a partial result adds to a block
   bool tail;          // a block whose neighbour on the unit is through goes on faster
 };
 static LaunchModel launch_model(int kind, int d) {
@@ -1149,12 +1152,18 @@ static LaunchModel launch_model(int kind, int d) {
   // D = 64: fitted with the tail to ten shapes, 600 to 7000 tokens on 8 to 32 heads; the length taken is 0.3 % behind the best one on average.  Without it (and
   // with the constants of D = 128) whole rows, whose longest blocks end by themselves, looked longer than they are: 16:2 heads x 5000 tokens
   // dQ in chunks of 68 tiles 120 us, whole 102.
-  if (kind == PICK_DQ && d == 64) return {2, 1.1, 0.65, 3.0, 1 / 3.0e6, 4.0, true};
-  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 1 / 5.0e6, 4.0, false};
-  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 1 / 4.0e6, 12.0, false};
+  if (kind == PICK_DQ && d == 64) return {2, 1.1, 0.65, 3.0, 0.0, 1 / 3.0e6, 4.0, true};
+  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 0.0, 1 / 5.0e6, 4.0, false};
+  // dK/dV of grouped heads: fitted to 60 shapes, 100 to 7000 queries of up to 64 heads, keys before them or not: the length taken is 0.9 % behind the best one on
+  // average, 3.7 with one set of constants for this and the shared launch.  Those priced a cut so high that the few blocks of short sequences walked their
+  // whole head group one tile after the other (whole pass, 4:2 heads x 224 tokens 32.6 us, in chunks of two tiles 26; D = 64, 32:8 x 145 27 and 20; a block
+  // per query head 29 and 22).
+  if (kind == PICK_DKV && d == 64) return {2, 1.6, 0.92, 2.2, 1.0, 1 / 1.5e6, 5.0, false};
+  if (kind == PICK_DKV) return {1, 2.0, 1.0, 7.0, 2.0, 1 / 2.0e6, 4.0, false};
+  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 0.0, 1 / 4.0e6, 12.0, false};
 }
 // simulate_launch for blocks that share a unit two by two, each as fast as the unit's other block lets it be.
-static double simulate_tail(const LaunchModel& m, const std::vector<int>& units, int heads) {
+static double simulate_tail(const LaunchModel& m, const std::vector<LaunchUnit>& units, int heads) {
   struct Unit { double at, left[2]; int n, version; };  // work left of its n blocks at time `at`, in us of a block alone
   struct Event {
     double end;
@@ -1185,7 +1194,7 @@ static double simulate_tail(const LaunchModel& m, const std::vector<int>& units,
       Unit& u = unit[engine * per + c];
       if (u.n >= 2) return;
       advance(u, now);
-      u.left[u.n++] = units[next[die] / heads] * m.tile * m.alone + m.ovh;
+      u.left[u.n++] = units[next[die] / heads].tiles * m.tile * m.alone + m.ovh;
       expect(engine, c);
     }
   };
@@ -1206,8 +1215,8 @@ static double simulate_tail(const LaunchModel& m, const std::vector<int>& units,
   }
   return now;
 }
-// units: tiles of the units of one head, in launch order.
-static double simulate_launch(const LaunchModel& m, const std::vector<int>& units, int heads) {
+// units: those of one head, in launch order.
+static double simulate_launch(const LaunchModel& m, const std::vector<LaunchUnit>& units, int heads) {
   typedef std::priority_queue<double, std::vector<double>, std::greater<double>> Queue;
   const int cus = attn_num_cus();
   Queue unit[8][4];
@@ -1217,27 +1226,33 @@ static double simulate_launch(const LaunchModel& m, const std::vector<int>& unit
   const double tile = m.tile * (all <= cus ? m.alone : 1.0);
   double makespan = 0.0;
   long long k = 0;
-  for (int t : units)
+  for (const LaunchUnit& u : units)
     for (int h = 0; h < heads; h++, k++) {
       Queue& q = unit[k & 7][(k >> 3) & 3];
       double& start = ahead[k & 7];
       start = std::max(start, q.top());
       q.pop();
-      const double end = start + t * tile + m.ovh;
+      const double end = start + u.tiles * tile + m.ovh + (u.part ? m.part : 0.0);
       q.push(end);
       makespan = std::max(makespan, end);
     }
   return makespan;
 }
-// heads: heads * batch of the launch (query heads; key/value heads for dK/dV); grp: query heads of a key/value head.
-static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int grp) {
-  const LaunchModel m = launch_model(kind, d);
-  const int nblk = (seq + 127) / 128, qb0 = q_off / 128, max_tiles = grp * (kind == PICK_DQ ? dq_tiles(nblk - 1, seq) : dkv_tiles(0, seq, q_off));
+// heads: heads * batch of the launch (query heads; key/value heads for dK/dV); grp: query heads of a key/value head; merged: partial results are
+// added by a launch that is there anyway.
+static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int grp, bool merged) {
+  LaunchModel m = launch_model(kind, d);
+  if (merged) m.merge = 0.0;
+  const int nblk = (seq + 127) / 128, qb0 = q_off / 128, most_q = dq_tiles(nblk - 1, seq), most_k = grp * dkv_tiles(0, seq, q_off);
+  const int max_tiles = kind == PICK_DQ ? most_q : kind == PICK_DKV ? most_k : std::max(most_q, most_k);
   const long long slots = (long long)attn_num_cus() * m.resident;
+  const long long all_blocks = (long long)nblk * heads, before_q = (long long)qb0 * heads;  // before_q: short key blocks ahead of the queries
   int best = AB_WHOLE;
   double best_t = 1e300;
   auto consider = [&](int ch) {
-    std::vector<int> units, q_units;
+    const long long count = (kind >= PICK_DKV ? total_pairs_dkv(seq, q_off, ch, grp) : 0) + (kind != PICK_DKV ? total_pairs_dq(seq, q_off, ch) : 0);
+    if (count * heads > 16 * slots + (kind == PICK_BOTH ? before_q : 0) && ch < AB_WHOLE) return;  // so many rounds need no chunks as short
+    std::vector<LaunchUnit> units, q_units;
     double bytes = 0;  // of partial results, per head
     if (kind >= PICK_DKV) {
       units = dkv_units(seq, q_off, grp, ch);
@@ -1246,11 +1261,11 @@ static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int gr
     if (kind != PICK_DKV)
       for (int i = nblk - 1; i >= qb0; i--) {
         const int tiles = dq_tiles(i, seq), n = chunks_of(tiles, ch);
-        for (int c = 0; c < n; c++) q_units.push_back(std::min(ch, tiles - c * ch));
+        for (int c = 0; c < n; c++) q_units.push_back({std::min(ch, tiles - c * ch), n > 1});
         bytes += n > 1 ? n * (double)d : 0;
       }
     if (kind == PICK_BOTH) {  // as attn_bwd_bf16_kernel takes them
-      std::vector<int> all;
+      std::vector<LaunchUnit> all;
       for (size_t k = 0; k < std::max(units.size(), q_units.size()); k++) {
         if (k < units.size()) all.push_back(units[k]);
         if (k < q_units.size()) all.push_back(q_units[k]);
@@ -1259,18 +1274,16 @@ static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int gr
     } else if (kind != PICK_DKV) {
       units = q_units;
     }
-    if ((long long)units.size() * heads > 16 * slots && ch < AB_WHOLE) return;  // so many rounds need no chunks as short
     const double t = (m.tail ? simulate_tail(m, units, heads) : simulate_launch(m, units, heads)) + (bytes > 0 ? bytes * heads * 128 * sizeof(float) * m.us_per_byte + m.merge : 0.0);
     if (t < best_t) { best_t = t; best = ch; }
   };
-  if ((long long)nblk * heads < 8 * slots && nblk <= 1024) {
+  if (all_blocks - (kind == PICK_BOTH ? before_q : 0) < 8 * slots && all_blocks < 32 * slots && nblk <= 1024) {
     consider(AB_WHOLE);
     const int least = kind == PICK_DKV ? 1 : 2;  // dQ: even, so that every wave sees a chunk's first tile
-    for (int c = 4; c < max_tiles; c += std::max(least, c / 32 * least)) consider(c);
+    for (int c = 2 * least; c < max_tiles; c += std::max(least, c / 32 * least)) consider(c);
   }
   return best;
 }
-
 
 // Chunk length of a forward launch: a few lengths and a plain list schedule (1.45 us a tile at D = 128, 3 a block, partial results there
 // and back at 2 MB per microsecond and 12 for their launch); where splitting pays, then the shortest length whose blocks are all resident
@@ -1304,14 +1317,14 @@ static int pick_fwd_chunk(int seq, int q_off, int heads, int d) {
   return best;
 }
 
-static int pick_chunk(int kind, int seq, int q_off, int heads, int d, int grp) {
+static int pick_chunk(int kind, int seq, int q_off, int heads, int d, int grp, bool merged = false) {
   static std::mutex mu;
   static std::map<PickKey, int> cache;
-  const PickKey key{kind, seq, q_off, heads, d, grp, attn_num_cus()};
+  const PickKey key{kind, seq, q_off, heads, d, grp, merged ? 1 : 0, attn_num_cus()};
   std::lock_guard<std::mutex> lock(mu);
   auto it = cache.find(key);
   if (it == cache.end())
-    it = cache.emplace(key, kind == PICK_FWD ? pick_fwd_chunk(seq, q_off, heads, d) : pick_bwd_chunk(kind, seq, q_off, heads, d, grp)).first;
+    it = cache.emplace(key, kind == PICK_FWD ? pick_fwd_chunk(seq, q_off, heads, d) : pick_bwd_chunk(kind, seq, q_off, heads, d, grp, merged)).first;
   return it->second;
 }
 
@@ -1324,9 +1337,10 @@ static int fwd_chunk_tiles(int batch, int seq, int q_off, int nq, int d) {
 static void bwd_chunk_tiles(int batch, int seq, int q_off, int nq, int nkv, int d, int& ch_q, int& ch_k) {
   if (nq == nkv) {
     ch_q = ch_k = pick_chunk(PICK_BOTH, seq, q_off, nq * batch, d, 1);
+    if (ch_k >= dkv_tiles(0, seq, q_off)) ch_k = AB_WHOLE;  // no key block is cut: none need look for its chunk (4 heads x 189 over 7997 keys 40 -> 36 us)
   } else {
     ch_q = pick_chunk(PICK_DQ, seq, q_off, nq * batch, d, 1);
-    ch_k = pick_chunk(PICK_DKV, seq, q_off, nkv * batch, d, nq / nkv);
+    ch_k = pick_chunk(PICK_DKV, seq, q_off, nkv * batch, d, nq / nkv, total_pairs_dq(seq, q_off, ch_q) > (seq + 127) / 128 - q_off / 128);
   }
 }
 

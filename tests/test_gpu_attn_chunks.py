@@ -28,10 +28,12 @@ def reference(q, k, v, do, q_off):
 
 
 # one block of one tile, blocks of a single chunk (no partial results), many chunks a block, a ragged last tile in every head, groups of 2 to
-# 16 heads, several sequences, queries behind a key buffer, more than 64 blocks (two to a lane of the unit search), both head widths
+# 16 heads, several sequences, queries behind a key buffer, more than 64 blocks (two to a lane of the unit search), both head widths; chunks of two
+# tiles; equal heads behind a key buffer: rows cut and columns whole, both cut
 @pytest.mark.parametrize("batch,seq,q_off,nq,nkv,d", [(1, 40, 0, 2, 1, 128), (2, 130, 0, 8, 2, 128), (1, 300, 0, 16, 1, 128), (3, 257, 0, 4, 1, 64),
                                                       (1, 1500, 0, 16, 4, 128), (2, 1000, 0, 32, 4, 64), (1, 700, 1152, 4, 1, 128), (2, 333, 256, 6, 3, 64),
-                                                      (1, 8300, 0, 2, 1, 64), (1, 2000, 0, 3, 3, 128)])
+                                                      (1, 8300, 0, 2, 1, 64), (1, 2000, 0, 3, 3, 128), (1, 224, 0, 4, 2, 128), (1, 145, 0, 32, 8, 64),
+                                                      (1, 189, 7808, 4, 4, 128), (4, 187, 2048, 1, 1, 64), (1, 1231, 3840, 2, 2, 128)])
 def test_grouped_attention_backward(dh, batch, seq, q_off, nq, nkv, d):
     print("case", batch, seq, q_off, nq, nkv, d, flush=True)
     gen = torch.Generator(device="cuda").manual_seed(seq + nq)
