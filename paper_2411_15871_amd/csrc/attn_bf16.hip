@@ -1148,19 +1148,21 @@ struct LaunchModel {
   bool tail;          // a block whose neighbour on the unit is through goes on faster
 };
 static LaunchModel launch_model(int kind, int d) {
-  const double w = d / 128.0;
   // D = 64: fitted with the tail to ten shapes, 600 to 7000 tokens on 8 to 32 heads; the length taken is 0.3 % behind the best one on average.  Without it (and
   // with the constants of D = 128) whole rows, whose longest blocks end by themselves, looked longer than they are: 16:2 heads x 5000 tokens
   // dQ in chunks of 68 tiles 120 us, whole 102.
   if (kind == PICK_DQ && d == 64) return {2, 1.1, 0.65, 3.0, 0.0, 1 / 3.0e6, 4.0, true};
-  if (kind == PICK_DQ) return {2, 2.2 * w, 0.55, 3.0, 0.0, 1 / 5.0e6, 4.0, false};
+  if (kind == PICK_DQ) return {2, 2.2, 0.55, 3.0, 0.0, 1 / 5.0e6, 4.0, false};
   // dK/dV of grouped heads: fitted to 60 shapes, 100 to 7000 queries of up to 64 heads, keys before them or not: the length taken is 0.9 % behind the best one on
   // average, 3.7 with one set of constants for this and the shared launch.  Those priced a cut so high that the few blocks of short sequences walked their
   // whole head group one tile after the other (whole pass, 4:2 heads x 224 tokens 32.6 us, in chunks of two tiles 26; D = 64, 32:8 x 145 27 and 20; a block
   // per query head 29 and 22).
   if (kind == PICK_DKV && d == 64) return {2, 1.6, 0.92, 2.2, 1.0, 1 / 1.5e6, 5.0, false};
   if (kind == PICK_DKV) return {1, 2.0, 1.0, 7.0, 2.0, 1 / 2.0e6, 4.0, false};
-  return {d == 64 ? 2 : 1, (d == 64 ? 3.2 : 2.0) * w, d == 64 ? 0.625 : 1.0, 9.0 * w, 0.0, 1 / 4.0e6, 12.0, false};
+  // The shared launch at D = 64: fitted to 48 shapes, 0.9 % behind the best length on average (2.9 with overheads scaled from D = 128, which cut
+  // rows that are faster whole: 8 heads x 2 x 1660 tokens 50 us, whole 45).
+  if (d == 64) return {2, 1.73, 0.76, 8.0, 0.25, 1 / 1.1e6, 5.6, false};
+  return {1, 2.0, 1.0, 9.0, 0.0, 1 / 4.0e6, 12.0, false};
 }
 // simulate_launch for blocks that share a unit two by two, each as fast as the unit's other block lets it be.
 static double simulate_tail(const LaunchModel& m, const std::vector<LaunchUnit>& units, int heads) {
