@@ -94,9 +94,10 @@ static const TileCost kTiles[] = {{0, 0, 256, 256, 1270, 800, 1337, 3000, 0, 0},
                                   {3, 3, 64, 64, 235, 1100, 225, 150, 0.9, 1.1}};
 static const double kLaunch = 2000, kSecondLaunch = 4000, kLong = 100e3;  // ns: a launch's ramp; a dependent second launch, ramp and gap
 struct TileTime { int cfg; double block; bool two; };  // ns a block takes of its unit; whether two share one
-// blocks: of the whole launch; stages, store bytes an element, ranges: of one product's tiles.
-static TileTime tile_time(const TileCost& c, long long blocks, int stages, double store_bytes, int chained_ranges) {
-  const bool many = blocks > num_cus();
+// blocks: of the whole launch; stages, store bytes an element, ranges: of one product's tiles.  (cus is passed in: asking the runtime for the current
+// device costs some 40 ns each time, and a plan has seven shapes.)
+static TileTime tile_time(const TileCost& c, int cus, long long blocks, int stages, double store_bytes, int chained_ranges) {
+  const bool many = blocks > cus;
   double store = (double)c.bm * c.bn * store_bytes / 20;  // a unit's share of the memory's rate, 20 bytes a ns
   if (c.cfg_many == 1 && many) store *= 0.6;               // one block stores while the other multiplies
   return {many ? c.cfg_many : c.cfg_one, stages * (double)(many ? c.many : c.one) + (many ? c.fill_many : c.fill_one) + store + chained_ranges * 200.0,
@@ -152,7 +153,7 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
   auto consider = [&](const TileCost& c, int splits, bool chained) {
     const long long blocks = tiles(c.bm, c.bn) * splits * std::max(1, groups);
     const int stages = splits > 1 ? per : nkt;
-    const TileTime tt = tile_time(c, blocks, stages, splits > 1 ? 4 : acc ? 8 : 2, chained ? ranges : 0);
+    const TileTime tt = tile_time(c, cus, blocks, stages, splits > 1 ? 4 : acc ? 8 : 2, chained ? ranges : 0);
     double ns = (double)((blocks + cus - 1) / cus) * tt.block;
     // A long product that leaves units idle leaves them to the other strand: half of what those would have done counts.
     if (ns > kLong) ns = 0.5 * (ns + tt.block * blocks / cus);
@@ -206,8 +207,8 @@ static PairChoice choose_pair(const GemmShape& d, const GemmShape& w, int groups
     if (c.bm * c.bn == 256 * 256) continue;
     auto blocks_of = [&](const GemmShape& g) { return (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * ng; };
     const long long nd = blocks_of(d), nw = blocks_of(w);
-    const TileTime td = tile_time(c, nd + nw, (d.K + 63) / 64, 2, pd.ranges > 1 ? pd.ranges : 0);
-    const TileTime tw = tile_time(c, nd + nw, (w.K + 63) / 64, 8, pw.ranges > 1 ? pw.ranges : 0);
+    const TileTime td = tile_time(c, cus, nd + nw, (d.K + 63) / 64, 2, pd.ranges > 1 ? pd.ranges : 0);
+    const TileTime tw = tile_time(c, cus, nd + nw, (w.K + 63) / 64, 8, pw.ranges > 1 ? pw.ranges : 0);
     const bool wf = tw.block > td.block;
     const long long n1 = wf ? nw : nd, n2 = wf ? nd : nw, q = n1 / cus, r = n1 % cus;
     const double t1 = wf ? tw.block : td.block, t2 = wf ? td.block : tw.block;
