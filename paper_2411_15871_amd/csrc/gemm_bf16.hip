@@ -121,8 +121,9 @@ static TileTime tile_time(const TileCost& c, int cus, long long blocks, int stag
 // sooner.
 //
 // groups > 0: a grouped launch, `groups` products of this (average) size.  Its K is never cut (a group's extents are known on
-// the device alone), so there are no ranges, and every tile shape is considered over the tiles of all groups.
-static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int groups = 0) {
+// the device alone), so there are no ranges, and every tile shape is considered over the tiles of all groups.  b_kmajor: B's columns are
+// contiguous and no part of a sum over rows (mode 0 of grouped launches, where it matters).
+static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int groups = 0, bool b_kmajor = false) {
   const int cus = num_cus();
   auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const int nkt = std::max(1, (K + 63) / 64);  // ranges are made in units of 64, a stage
@@ -150,7 +151,7 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
     }
   }
   const size_t mn = (size_t)M * N;
-  auto consider = [&](const TileCost& c, int splits, bool chained) {
+  auto consider = [&](const TileCost& c, int splits, bool chained, double at_most = 1.0) {  // at_most: of the best other's time
     const long long blocks = tiles(c.bm, c.bn) * splits * std::max(1, groups);
     const int stages = splits > 1 ? per : nkt;
     const TileTime tt = tile_time(c, cus, blocks, stages, splits > 1 ? 4 : acc ? 8 : 2, chained ? ranges : 0);
@@ -159,7 +160,7 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
     if (ns > kLong) ns = 0.5 * (ns + tt.block * blocks / cus);
     const double sum = splits > 1 ? kSecondLaunch + (double)mn * (4 * splits + (acc ? 8 : 2)) / 5000 : 0;  // the partials read at 5 TB/s
     ns += kLaunch + sum;
-    if (p.ns != 0 && ns >= p.ns) return;
+    if (p.ns != 0 && ns >= at_most * p.ns) return;
     p.ns = ns;
     p.cu_ns = tt.block * blocks / cus + kLaunch / 2 + sum;
     p.cfg = tt.cfg;
@@ -169,9 +170,16 @@ static GemmPlan choose_plan(int M, int N, int K, bool acc, size_t ws_bytes, int 
     p.k_chain = chained ? per * 64 : 0;
   };
   for (const TileCost& c : kTiles) {
-    // Grouped launches: the square shapes and 256x128; 64x64 only where 128x128 tiles would be fewer than 96 (4 x (1000 x 512 x 6000):
-    // the same time within the estimate's error, four times the traffic).
-    if (groups > 0 && ((c.bm != c.bn && c.bm != 256) || (c.bm == 64 && tiles(128, 128) * groups >= 96))) continue;
+    // Grouped launches: the square shapes and 256x128.  64x64 where 128x128 tiles would be fewer than 96; beyond, only where they are expected to take less
+    // than 0.79 of the time (4 x (1000 x 512 x 6000): the same time within the estimate's error, four times the traffic): weight gradients (76 shapes:
+    // 0.77 of the time of 128x128 tiles, 0.94 at worst), and data gradients of more than a round of them (51 shapes, 0.92 on average, 0.54 to 1.44; within a
+    // round the weights' rate counts, which the estimate does not see: 6, 0.81 to 1.13).  Not with weights as they are stored (B K-major, 128 bytes of a row a stage): eight
+    // shapes 0.99 on average, 0.72 to 1.25.
+    if (groups > 0 && c.bm != c.bn && c.bm != 256) continue;
+    if (groups > 0 && c.bm == 64 && tiles(128, 128) * groups >= 96) {
+      if (acc || (!b_kmajor && tiles(64, 64) * groups > cus)) consider(c, 1, false, 0.79);
+      continue;
+    }
     if (ranges == 1) consider(c, 1, false);
     else if (ws_bytes / (mn * sizeof(float)) >= (size_t)ranges) consider(c, ranges, false);
     if (ranges > 1 && c.bm * c.bn < 256 * 256) consider(c, 1, true);
@@ -388,7 +396,7 @@ int dh_launch_gemm_swiglu_bwd_bf16(int T, int F, int H, const bf16_t* dy, const 
 // (float32).  No split-K: every group is one launch slice of the same grid.
 static GemmPlan grouped_plan(int mode, int n_groups, int max_rows, int dim_a, int dim_b) {  // for groups of about equal size
   const int avg = std::max(1, max_rows / n_groups);
-  return mode == 2 ? choose_plan(dim_a, dim_b, avg, true, 0, n_groups) : choose_plan(avg, dim_b, dim_a, false, 0, n_groups);
+  return mode == 2 ? choose_plan(dim_a, dim_b, avg, true, 0, n_groups) : choose_plan(avg, dim_b, dim_a, false, 0, n_groups, mode == 0);
 }
 void dh_gemm_grouped_bf16_tile(int mode, int n_groups, int max_rows, int dim_a, int dim_b, int* rows, int* cols) {
   const GemmPlan p = grouped_plan(mode, n_groups, max_rows, dim_a, dim_b);

@@ -78,6 +78,14 @@ def test_context_parallel_layer_configuration_is_checked():
     dh.dh_layer_destroy(plain)
 
 
+# Short weight gradients, whose 128x128 tiles would be one part-filled round (mode 2: 776 x 576 over 782 rows a group 16.1 us, with 64x64 tiles 12.4), and data
+# gradients of many groups with few rows (mode 1: 6 rows each, 1696 -> 4576 features, 68 and 51).  With weights as they are stored 64x64 tiles are no faster.
+@pytest.mark.parametrize("mode,groups,rows,a,b,tile", [(2, 4, 3127, 776, 576, 64), (2, 2, 1355, 192, 3296, 64), (2, 16, 2233, 280, 320, 64), (1, 16, 101, 1696, 4576, 64),
+                                                       (1, 16, 146, 288, 1144, 64), (0, 16, 101, 1696, 4576, 128), (2, 2, 1160, 2072, 2368, 128)])
+def test_grouped_gemm_takes_small_tiles_where_large_ones_are_half_empty(mode, groups, rows, a, b, tile):
+    assert dh.dh_gemm_grouped_tile(mode, groups, rows, a, b) == (tile, tile)
+
+
 @pytest.mark.parametrize("groups,rows,a,b", [(4, 512, 2048, 1408), (4, 1024, 1024, 2048), (8, 512, 2048, 2048), (4, 2048, 4096, 1600), (1, 8000, 1024, 3000),
                                              (4, 1000, 6000, 512), (2, 2500, 768, 768), (2, 1500, 2048, 3200)])
 def test_grouped_gemm_tiles_fill_the_chip_once(groups, rows, a, b):
