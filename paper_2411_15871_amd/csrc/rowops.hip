@@ -233,7 +233,8 @@ __global__ __launch_bounds__(COLSUM_THREADS) void colsum_finish_kernel(const flo
 // ADJACENT: pair i is elements (2i, 2i+1): the thread's 8 pairs are 16 consecutive elements.
 // HEADS: heads a thread rotates, with one set of angles.  Bound by forming angles, sines and cosines with one head a thread, by memory with four
 // (4096 rows of 40 heads of 128 21.0 -> 13.4 us, 6.3 TB/s; 8192 of 9 11.2 -> 7.3, 4000 of 32 of 64 10.3 -> 6.5, 4096 of 5 5.1 -> 4.5), by one thread's chain where
-// there are few (256 of 5 3.65 us, four heads a thread 3.85): four from 2^17 threads of one head on.
+// there are few (256 of 5 3.65 us, four heads a thread 3.85): four from 2^17 threads of one head on.  Adjacent pairs in float32 stay with one: a lane's 64
+// consecutive bytes of each of four heads come in more pieces than the angles are worth (4764 rows of 30 heads of 128 31 us, 35.5 with four; 12 shapes 5-13 % slower).
 template <typename T, bool ADJACENT, int HEADS>
 __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ t, size_t row0, unsigned threads, int seq, int pos0, int n_heads, int d, int row_stride,
                                                    double log2_base, double ratio, int inverse) {
@@ -471,7 +472,7 @@ extern "C" int dh_rope_pairs(int dtype, int pairing, int T, int seq, int pos0, i
   if (T == 0) return DH_OK;
   if (!t) DH_FAIL(DH_ERR_INVALID_ARG, "rope: null pointer");
   const double l2b = log2((double)base), ratio = exp2(-2.0 / (double)head_dim * l2b);
-  const bool four = (size_t)T * n_heads * (head_dim / 16) >= (size_t)1 << 17;
+  const bool four = (size_t)T * n_heads * (head_dim / 16) >= (size_t)1 << 17 && !(dtype == DH_F32 && pairing == DH_ROPE_ADJACENT);
   const size_t per_row = (size_t)(four ? (n_heads + 3) / 4 : n_heads) * (head_dim / 16), most = std::max<size_t>(1, ((size_t)1 << 31) / per_row);
   for (size_t row0 = 0; row0 < (size_t)T; row0 += most) {  // (a launch's threads are counted in 32 bits)
     const unsigned threads = (unsigned)(std::min(most, (size_t)T - row0) * per_row);
@@ -480,7 +481,7 @@ extern "C" int dh_rope_pairs(int dtype, int pairing, int T, int seq, int pos0, i
                                                                                  l2b, ratio, inverse)
 #define GO2(TT, ADJ) do { if (four) GO(TT, ADJ, 4); else GO(TT, ADJ, 1); } while (0)
     if (dtype == DH_BF16) { if (pairing == DH_ROPE_ADJACENT) GO2(bf16_t, true); else GO2(bf16_t, false); }
-    else { if (pairing == DH_ROPE_ADJACENT) GO2(float, true); else GO2(float, false); }
+    else { if (pairing == DH_ROPE_ADJACENT) GO(float, true, 1); else GO2(float, false); }
 #undef GO2
 #undef GO
     DH_LAUNCH_CHECK();
