@@ -195,6 +195,17 @@ __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[2]) {
 __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[4]) {
   asm volatile("s_nop 15\n\ts_nop 15" : "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3]));
 }
+// The same three for a loop whose every instruction has its place (attn_bwd_dkv_pinned): volatile, so that they stay in the order written, and without wait
+// states of their own.  A fragment the vector ALU has written is ready a matrix instruction later, a result two of them later.
+__device__ __forceinline__ void mfma_first(f32x16& acc, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
+}
+__device__ __forceinline__ void mfma_next(f32x16& acc, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
+}
+__device__ __forceinline__ void mfma_grad(f32x16& acc, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
 // The AGPR placement (AGPR = true) pays where one wave has a SIMD's register file to itself and ordinary registers are short
 // (D = 128, one block per compute unit).  With D = 64 everything fits the ordinary registers, and where two waves share the
 // file (the dQ kernel at D = 128) they are one budget of 256: there the compiler would only shuttle an AGPR-constrained value
@@ -243,6 +254,14 @@ template <int D>
 __device__ __forceinline__ void tile_dma(const char* base, const uint32_t (&v)[ATile<D>::IPW], uint32_t lds_tile, int wave) {
 #pragma unroll
   for (int j = 0; j < ATile<D>::IPW; j++) dma16_base(base, v[j], lds_tile + (wave * ATile<D>::IPW + j) * 1024);
+}
+
+// The same with transfer j's KiB as a constant that the hardware adds to both addresses (see dma.h): v[j] is that much less.
+template <int D>
+__device__ __forceinline__ void tile_dma_at(const char* base, const uint32_t (&v)[ATile<D>::IPW], uint32_t lds_tile, int wave) {
+  const uint32_t m = dma_lds(lds_tile + wave * ATile<D>::IPW * 1024);
+#pragma unroll
+  for (int j = 0; j < ATile<D>::IPW; j++) dma16_at(m, base, v[j], j * 1024);
 }
 
 // Byte offsets inside a tile of the two kinds of fragment reads, precomputed per lane.
@@ -871,6 +890,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   uint32_t vq[TL::IPW], vo[TL::IPW];
   tile_voff<D>(vq, ld, wave, lane, AB_KT);
   tile_voff<D>(vo, ldo, wave, lane, AB_KT);
+#pragma unroll
+  for (int j = 0; j < TL::IPW; j++) { vq[j] -= j * 1024; vo[j] -= j * 1024; }  // for tile_dma_at: transfer j moves rows from 512 j / D on, of at least 2 D bytes
   const uint32_t ldsQ = lds_address(smem), ldsO = ldsQ + AB_RING * TL::BYTES;
   // The block's tiles: nt query tiles q0 + 64*t of each head of the group, counted through; this chunk walks [f0, f1).
   const int nt = dkv_tiles(cm.blk, seq, g.q_off), f0 = cm.chunk * g.ch, f1 = min(g.grp * nt, f0 + g.ch);
@@ -888,8 +909,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     const char* qp = qbase + ti * qstride + gi * (D * sizeof(bf16_t));
     const char* op = obase + ti * ostride + gi * (D * sizeof(bf16_t));
     if (valid >= AB_KT) {
-      tile_dma<D>(qp, vq, ldsQ + slot * TL::BYTES, wave);
-      tile_dma<D>(op, vo, ldsO + slot * TL::BYTES, wave);
+      tile_dma_at<D>(qp, vq, ldsQ + slot * TL::BYTES, wave);
+      tile_dma_at<D>(op, vo, ldsO + slot * TL::BYTES, wave);
     } else {
       uint32_t vc[TL::IPW];
       tile_voff<D>(vc, ld, wave, lane, valid);
@@ -900,66 +921,250 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     dma4_base(srow + (size_t)gi * T + ti * AB_KT, (uint32_t)(min(lane, valid - 1) * sizeof(float)), ldsS + slot * AB_KT * sizeof(float));
     if (++ti == nt) { ti = 0; gi++; }
   };
-  issue(0);
-  if (f0 + 1 < f1) issue(1);
-  int slot = 0;
-  for (int f = f0; f < f1; f++, slot = slot == AB_RING - 1 ? 0 : slot + 1) {
-    if (f + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
-    __syncthreads();
-    if (f + 2 < f1) issue(slot == 0 ? AB_RING - 1 : slot - 1);
-    const int qb = q0 + tc * AB_KT;
-    if (++tc == nt) tc = 0;
-    if (qb + AB_KT - 1 < jw) continue;  // every query of the tile precedes every key of this wave
-    TilePtrs<D> Qp, Op;
-    Qp.set(sm + slot * TL::BYTES, fa);
-    Op.set(sm + (AB_RING + slot) * TL::BYTES, fa);
-    const float* ls = lse_s + slot * AB_KT;
-    const float* ds = del_s + slot * AB_KT;
-    f32x4 lv[8];  // rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
+  if constexpr (D == 128) {
+    // One wave has a SIMD to itself: beside its matrix instructions runs only what stands between them.  A 32x32x16 one keeps the matrix cores 32 cycles, a
+    // tile's 64 of them 2048; a tile's other instructions (32 exponentials, 100 more of the vector ALU, 112 LDS reads, 9 transfers, 70 scalar ones) fill about
+    // as many issue cycles and fit in their shadows if every slot gets its share.  Left to the compiler, half of dP's products ended up
+    // behind all exponentials, and a tile took 4500 cycles.  So the matrix instructions are volatile, each is followed by its share, and all of it is pinned; fragments are
+    // requested six products ahead (transposed ones eight); the next tile is published beside this one's dK products and its first fragments are read
+    // there, so that no tile begins with a wait.  Measured alone (us, before and after): 32:8 heads x 4096 tokens 315 -> 283, 8:1 x 8192 306 -> 260, 4:1
+    // x 4096 queries over 12288 keys 207 -> 178, 4:1 x 4096 53 -> 45, in the shared launch 2 x 2048 x 8 heads 85 -> 75.  In cycles it is 20 % (667 -> 532
+    // thousand, matrix cores busy 40 -> 50 %): the clock falls from 2.1 to 1.9 GHz, the power limit takes the rest.
+    static_assert(AB_KT == 64 && AB_RING == 3, "slots below");
+    constexpr int KS = D / 16, OFF1 = AB_RING * TL::BYTES;
+    const lds_char* dir[KS];
+    const lds_char* t0[D / 32];
+    const lds_char* t1[D / 32];
+    const lds_char* stp = sm + 2 * AB_RING * TL::BYTES + 4 * kg * sizeof(float);  // statistics of the lane's rows
 #pragma unroll
-    for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ls + 8 * x + 4 * kg);
+    for (int ks = 0; ks < KS; ks++) dir[ks] = sm + fa.kdir[ks];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++) { t0[dt] = sm + fa.tr0[dt]; t1[dt] = sm + fa.tr1[dt]; }
+    bf16x8 fr[4][2];         // score fragments of four k-steps
+    bf16x8 tr[3][D / 32];    // transposed fragments of three groups of 16 rows: dO's groups are 0-3, Q's 4-7
+    bf16x8 pf[2];            // packed P (groups 0-3), then dS (4-7)
+    f32x4 lv[8];             // log sums of rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
     f32x16 st[2], dp[2];
-    // P from S beside the dP products
-    score_tiles2<D, AB_RING * TL::BYTES, 3>(st, Qp, kf, dp, vf, [&](int j) {
-      constexpr int N = 8 / (D / 16);
+    auto frag = [&](int step, int mt) {  // k-step `step` of the tile's S products, from KS on of its dP products
+      fr[step & 3][mt] = lds_frag(dir[step & (KS - 1)], (step < KS ? 0 : OFF1) + mt * 32 * TL::LD * 2);
+    };
+    auto trfrag = [&](int group, int dt) { tr[group % 3][dt] = lds_frag_tr(t0[dt], t1[dt], (group < 4 ? OFF1 : 0) + (group & 3) * 16 * TL::LD * 2); };
+    auto pack2 = [&](int group, int e) {  // elements 2e, 2e+1 of the group's fragment
+      const f32x16& t = st[(group & 3) >> 1];
+      pf[group & 1][2 * e] = (bf16_t)t[8 * (group & 1) + 2 * e];
+      pf[group & 1][2 * e + 1] = (bf16_t)t[8 * (group & 1) + 2 * e + 1];
+    };
+    auto pack_share = [&](int group, int i) {  // beside the i-th product of the group before: none beside the last, a product later than the vector ALU writes
+      if (i == 0) { pack2(group, 0); pack2(group, 1); }
+      else if (i < 3) pack2(group, i + 1);
+    };
+#define AB_PIN() __builtin_amdgcn_sched_barrier(0)
+    // dP comes out as delta - dP: the accumulators start from the rows' delta and V enters negated (dS and dK negated likewise, until dK is stored): a subtraction
+    // an element less.  Against float64 dK is as far off as with the subtraction behind the sum (2.405 and 2.406e-3 to 1.766 and 1.766e-3).
 #pragma unroll
-      for (int i = 0; i < N; i++) {
-        const int x = j * N + i, mt = x >> 2, q4 = x & 3;
-#pragma unroll
-        for (int e = 0; e < 4; e++) st[mt][4 * q4 + e] = fast_exp2(fmaf(st[mt][4 * q4 + e], scale_log2, -lv[x][e]));
-      }
-    });
-    TrFrags<D> fr;
-    tr_fetch<D>(fr, Op, 0);
-#pragma unroll
-    for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ds + 8 * x + 4 * kg);
-    if (qb < jw + 32 || qb + AB_KT > seq) {  // diagonal tile, or rows past the end of the sequence
-      // One comparison a row, four rows at a time: two a row, all ahead of the selects, held 64 scalar registers at D = 64, and the
-      // loop's own scalars (bases, strides, the head and tile to fetch next) were fetched from vector lanes in every tile (91 spilled: 32:4 heads x 1200
-      // tokens, the whole backward pass, 65 us; now none, 56.  2 x 1000 69 -> 65, 8:1 x 4096 104 -> 97).
-      const int first = qb + 4 * kg;
-      const uint32_t rows = (uint32_t)max(seq - jk, 0);
-#pragma unroll
-      for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          st[mt][r] = (uint32_t)(first + mt * 32 + 8 * (r >> 2) + (r & 3) - jk) < rows ? st[mt][r] : 0.f;
-          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int ks = 0; ks < KS; ks++) {
+      typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+      vf[ks] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[ks]) ^ 0x80008000u);
+      asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
     }
-    // dV^T += dO^T P; once a quarter of P (8 registers of a tile) is packed for its products, it is turned
-    // into dS = P (dP - delta) in place while those products run; then dK^T += Q^T dS.
-    acc_tile_tr<D, true, AGPR>(dvt, fr, Op, st, Qp, [&](int g) {
+    issue(0);
+    if (f0 + 1 < f1) issue(1);
+    if (f0 + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
+    __syncthreads();
 #pragma unroll
-      for (int r = 8 * (g & 1); r < 8 * (g & 1) + 8; r++) st[g >> 1][r] *= dp[g >> 1][r] - lv[4 * (g >> 1) + (r >> 2)][r & 3];
-    });
-    acc_tile_tr<D, false, AGPR>(dkt, fr, Qp, st, Qp, [](int) {});
+    for (int step = 0; step < 3; step++) { frag(step, 0); frag(step, 1); }
+    const uint32_t ldsQw = ldsQ + wave * (TL::IPW * 1024), tile_bytes = TL::BYTES;
+    const int ragged_ti = (seq - q0) % AB_KT != 0 ? nt - 1 : nt;  // the tile of each head that is not whole
+    int slot = 0;
+    const char *qp, *op, *sp;  // of the tile to transfer next
+    auto sources = [&]() {
+      qp = qbase + ti * qstride + gi * (D * sizeof(bf16_t));
+      op = obase + ti * ostride + gi * (D * sizeof(bf16_t));
+      sp = reinterpret_cast<const char*>(srow + (size_t)gi * T + ti * AB_KT);
+    };
+    sources();
+    for (int f = f0; f < f1; f++) {
+      const int next = slot == AB_RING - 1 ? 0 : slot + 1, free_slot = slot == 0 ? AB_RING - 1 : slot - 1;
+      const int step_tile = (next - slot) * TL::BYTES, step_stat = (next - slot) * AB_KT * (int)sizeof(float);
+      asm volatile("s_barrier" ::: "memory");  // every wave is done with tile f-1: its slot is filled next
+      const int qb = q0 + tc * AB_KT;
+      if (++tc == nt) tc = 0;
+      const bool more = f + 2 < f1, idle = qb + AB_KT - 1 < jw;  // idle: every query of the tile precedes every key of this wave
+      const bool beside = more && !idle && ti != ragged_ti;
+      if (more && !beside) { issue(free_slot); sources(); }
+      auto publish = [&]() {  // tile f+1, whose transfers are followed by tile f+2's
+        if (more) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * TL::IPW + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      };
+      auto shift_dir = [&]() {
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) dir[ks] += step_tile;
+      };
+      auto shift_tr = [&]() {
+#pragma unroll
+        for (int dt = 0; dt < D / 32; dt++) { t0[dt] += step_tile; t1[dt] += step_tile; }
+      };
+      slot = next;
+      if (idle) {
+        publish();
+        shift_dir();
+        shift_tr();
+        stp += step_stat;
+#pragma unroll
+        for (int step = 0; step < 3; step++) { frag(step, 0); frag(step, 1); }
+        continue;
+      }
+      auto scores = [&](auto transfers) {
+        constexpr bool TRANSFERS = decltype(transfers)::value;
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          if (i < 2) mfma_first(st[i & 1], fr[(i >> 1) & 3][i & 1], kf[i >> 1]);
+          else mfma_next(st[i & 1], fr[(i >> 1) & 3][i & 1], kf[i >> 1]);
+          frag((i >> 1) + 3, i & 1);
+          if (i < 8) {
+            const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stp + AB_RING * AB_KT * sizeof(float) + i * 32);
+#pragma unroll
+            for (int e = 0; e < 4; e++) dp[i >> 2][4 * (i & 3) + e] = v[e];
+          } else {
+            lv[i - 8] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stp + (i - 8) * 32);
+          }
+          if (TRANSFERS) {
+            if (i == 2) m = dma_lds(ldsQw + free_slot * tile_bytes);
+            if (i == 6) m = dma_lds(ldsQw + free_slot * tile_bytes + AB_RING * tile_bytes);
+            if (i >= 2 && i < 6) dma16_at(m, qp, vq[i - 2], (i - 2) * 1024);
+            if (i >= 6 && i < 10) dma16_at(m, op, vo[i - 6], (i - 6) * 1024);
+            if (i == 10) dma4_base(sp, lane * sizeof(float), ldsS + free_slot * AB_KT * sizeof(float));
+            if (i == 12) {
+              qp += qstride;
+              op += ostride;
+              sp += AB_KT * sizeof(float);
+            }
+          }
+          AB_PIN();
+        }
+      };
+      if (beside) {
+        scores(std::true_type{});
+        if (++ti == nt) { ti = 0; gi++; sources(); }
+      } else {
+        scores(std::false_type{});
+      }
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        const int ks = i >> 1, mt = i & 1;
+        mfma_next(dp[mt], fr[(ks + KS) & 3][mt], vf[ks]);
+        if (ks + 3 < KS) frag(ks + KS + 3, mt);
+        if (i >= 8) trfrag((i - 8) >> 2, i & 3);
+        if (i >= 2) {  // P from S, 32 values over 14 slots
+#pragma unroll
+          for (int x = (i - 2) * 32 / 14; x < (i - 1) * 32 / 14; x++) st[x >> 4][x & 15] = fast_exp2(fmaf(st[x >> 4][x & 15], scale_log2, -lv[x >> 2][x & 3]));
+        }
+        AB_PIN();
+      }
+      if (qb < jw + 32 || qb + AB_KT > seq) {  // diagonal tile, or rows past the end of the sequence
+        const int first = qb + 4 * kg;
+        const uint32_t rows = (uint32_t)max(seq - jk, 0);
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) {
+            st[mt][r] = (uint32_t)(first + mt * 32 + 8 * (r >> 2) + (r & 3) - jk) < rows ? st[mt][r] : 0.f;
+            if ((r & 3) == 3) AB_PIN();
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; e++) pack2(0, e);
+      // dV^T += dO^T P; a group of P, once packed, becomes -dS = P (delta - dP) in place
+      asm volatile("s_nop 1" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        const int g = i >> 2, dt = i & 3;
+        mfma_grad(dvt[dt], tr[g % 3][dt], pf[g & 1]);
+        trfrag(g + 2, dt);
+#pragma unroll
+        for (int x = 8 * g + 2 * dt; x < 8 * g + 2 * dt + 2; x++) st[x >> 4][x & 15] *= dp[x >> 4][x & 15];
+        pack_share(g + 1, dt);
+        if (i == 8) shift_dir();
+        AB_PIN();
+      }
+      // -dK^T += Q^T (-dS)
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        const int g = 4 + (i >> 2), dt = i & 3;
+        mfma_grad(dkt[dt], tr[g % 3][dt], pf[g & 1]);
+        if (g < 6) trfrag(g + 2, dt);
+        if (g < 7) pack_share(g + 1, dt);
+        if (i == 8) publish();
+        if (i == 9) shift_tr();
+        if (i >= 10) frag((i - 10) >> 1, i & 1);
+        AB_PIN();
+      }
+      stp += step_stat;
+    }
+  } else {
+    issue(0);
+    if (f0 + 1 < f1) issue(1);
+    int slot = 0;
+    for (int f = f0; f < f1; f++, slot = slot == AB_RING - 1 ? 0 : slot + 1) {
+      if (f + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
+      __syncthreads();
+      if (f + 2 < f1) issue(slot == 0 ? AB_RING - 1 : slot - 1);
+      const int qb = q0 + tc * AB_KT;
+      if (++tc == nt) tc = 0;
+      if (qb + AB_KT - 1 < jw) continue;  // every query of the tile precedes every key of this wave
+      TilePtrs<D> Qp, Op;
+      Qp.set(sm + slot * TL::BYTES, fa);
+      Op.set(sm + (AB_RING + slot) * TL::BYTES, fa);
+      const float* ls = lse_s + slot * AB_KT;
+      const float* ds = del_s + slot * AB_KT;
+      f32x4 lv[8];  // rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
+  #pragma unroll
+      for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ls + 8 * x + 4 * kg);
+      f32x16 st[2], dp[2];
+      // P from S beside the dP products
+      score_tiles2<D, AB_RING * TL::BYTES, 3>(st, Qp, kf, dp, vf, [&](int j) {
+        constexpr int N = 8 / (D / 16);
+  #pragma unroll
+        for (int i = 0; i < N; i++) {
+          const int x = j * N + i, mt = x >> 2, q4 = x & 3;
+  #pragma unroll
+          for (int e = 0; e < 4; e++) st[mt][4 * q4 + e] = fast_exp2(fmaf(st[mt][4 * q4 + e], scale_log2, -lv[x][e]));
+        }
+      });
+      TrFrags<D> fr;
+      tr_fetch<D>(fr, Op, 0);
+  #pragma unroll
+      for (int x = 0; x < 8; x++) lv[x] = *reinterpret_cast<const f32x4*>(ds + 8 * x + 4 * kg);
+      if (qb < jw + 32 || qb + AB_KT > seq) {  // diagonal tile, or rows past the end of the sequence
+        // One comparison a row, four rows at a time: two a row, all ahead of the selects, held 64 scalar registers at D = 64, and the
+        // loop's own scalars (bases, strides, the head and tile to fetch next) were fetched from vector lanes in every tile (91 spilled: 32:4 heads x 1200
+        // tokens, the whole backward pass, 65 us; now none, 56.  2 x 1000 69 -> 65, 8:1 x 4096 104 -> 97).
+        const int first = qb + 4 * kg;
+        const uint32_t rows = (uint32_t)max(seq - jk, 0);
+  #pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+  #pragma unroll
+          for (int r = 0; r < 16; r++) {
+            st[mt][r] = (uint32_t)(first + mt * 32 + 8 * (r >> 2) + (r & 3) - jk) < rows ? st[mt][r] : 0.f;
+            if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+      }
+      // dV^T += dO^T P; once a quarter of P (8 registers of a tile) is packed for its products, it is turned
+      // into dS = P (dP - delta) in place while those products run; then dK^T += Q^T dS.
+      acc_tile_tr<D, true, AGPR>(dvt, fr, Op, st, Qp, [&](int g) {
+  #pragma unroll
+        for (int r = 8 * (g & 1); r < 8 * (g & 1) + 8; r++) st[g >> 1][r] *= dp[g >> 1][r] - lv[4 * (g >> 1) + (r >> 2)][r & 3];
+      });
+      acc_tile_tr<D, false, AGPR>(dkt, fr, Qp, st, Qp, [](int) {});
+    }
   }
   acc_settle<AGPR>(dkt);
   acc_settle<AGPR>(dvt);
   __syncthreads();  // every wave is done with the Q/dO rings: their LDS serves the output turn (dK, then dV)
+  const float kscale = D == 128 ? -scale : scale;
   auto dk_quad = [&](int dt, int q4) {
-    return f32x4{dkt[dt][4 * q4] * scale, dkt[dt][4 * q4 + 1] * scale, dkt[dt][4 * q4 + 2] * scale, dkt[dt][4 * q4 + 3] * scale};
+    return f32x4{dkt[dt][4 * q4] * kscale, dkt[dt][4 * q4 + 1] * kscale, dkt[dt][4 * q4 + 2] * kscale, dkt[dt][4 * q4 + 3] * kscale};
   };
   auto dv_quad = [&](int dt, int q4) { return f32x4{dvt[dt][4 * q4], dvt[dt][4 * q4 + 1], dvt[dt][4 * q4 + 2], dvt[dt][4 * q4 + 3]}; };
   if (cm.chunks > 1) {
