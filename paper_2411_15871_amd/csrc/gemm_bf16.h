@@ -473,15 +473,59 @@ __device__ __forceinline__ bool g_begin(GemmArgs& g, int bx, GemmTile& w) {
 // with float32 accumulation 889 -> 785; 4096x3584x4096 100 -> 86 us; 4096x4096x1792 53 -> 46 us.  With 32x32x16
 // instructions in the same schedule: 766 us at 8192^3.
 // The large-tile kernel: four waves, one per SIMD, each owning a 128x128 part of C (256 accumulator registers in AGPRs).
-// K is consumed 64 at a time from two LDS stages (A and B, 32 KiB each).  A K tile is worked off in four quadrants
-// (a0 b0, a0 b1, a1 b1, a1 b0: halves of 64 rows / columns); the fragments of the half that comes next are read while
-// the current quadrant's products are issued, so a stage has been read completely after the second quadrant.  One barrier
-// there (it also publishes the next stage), and the transfers of tile t+2 follow into the stage just emptied.  Matrix
-// instructions, LDS reads and transfers are interleaved two products at a time and pinned in that order.
-#define GW_STAGE 65536u
+// K is consumed 64 at a time.  A K tile is worked off in four quadrants (a0 b0, a0 b1, a1 b1, a1 b0: halves of 64 rows / columns of a wave's
+// part); the fragments of the half that comes next are read while the current quadrant's products are issued.  So the first halves of A and B are read
+// in the third and fourth quadrant of the tile before and the second halves in the first two, and the LDS is a ring of four slots of 32 KiB, each the same half of both
+// operands: after each second quadrant a barrier publishes the next slot and frees the one just read, whose refill follows.  A transfer has one and a half
+// tiles (about 2 us) until it is needed; as a ring of two whole tiles it had half a tile to one, less than the memory's latency while another
+// strand's kernels load it, and in launches of several rounds, whose blocks run out of step and miss the L2 more often.  Measured against that ring (us): Llama-70B
+// shard's gate/up products 712 -> 669 (forward), 659 -> 622 (data gradient), 780 -> 733 (weight gradient), its interleaved step 6100 -> 5797; 8192^3 alone 1530
+// TFLOP/s either way.  A fifth slot (all of the LDS): the step 1 % slower.  Matrix instructions, LDS reads and transfers are
+// interleaved two products at a time and pinned in that order.
+#define GW_SLOT 32768u
+#define GW_RING 4
+
+// Half h of a 256-wide operand tile: the 64 rows (columns) h*64 .. h*64+63 of either wave row (wave column).  Tile index of the half's u-th.
+__device__ __forceinline__ int gw_row(int h, int u) { return (u >> 6) * 128 + h * 64 + (u & 63); }
+// Offsets of a wave's transfers of both halves, four each; as g_offsets.
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_offsets(uint32_t (&voff)[8], int r0, int R, int K, int wave, int lane, int half_jump = 0) {
+#pragma unroll
+  for (int x = 0; x < 8; x++) {
+    int u, k;
+    g_chunk<128, KMAJOR>(wave, x & 3, lane, u, k);
+    const int r = gw_row(x >> 2, u);
+    if (KMAJOR) {
+      const int col = half_jump != 0 ? r + (r >= 128 ? half_jump : 0) : min(r0 + r, R - 8) - r0;
+      voff[x] = (uint32_t)(((size_t)k * R + col) * sizeof(bf16_t));
+    } else {
+      voff[x] = (uint32_t)(((size_t)(min(r0 + r, R - 1) - r0) * K + k) * sizeof(bf16_t));
+    }
+    voff[x] += 2 * G_BIAS - (x & 3) * 1024;  // see g_bias_transfers
+  }
+}
+// Half h of a stage that reaches beyond k_end; as g_issue_ragged.
+template <bool KMAJOR>
+__device__ __forceinline__ void gw_issue_ragged(uint32_t lds_wave, const bf16_t* __restrict__ base, int h, int r0, int k0, int R, int K, int k_end, int wave,
+                                                int lane, int half_jump = 0) {
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    int u, k;
+    g_chunk<128, KMAJOR>(wave, j, lane, u, k);
+    int r = gw_row(h, u);
+    r += r0 + (r >= 128 ? half_jump : 0);
+    k += k0;
+    const bf16_t* src = (r < R && k < k_end) ? base + (KMAJOR ? (size_t)k * R + r : (size_t)r * K + k) : reinterpret_cast<const bf16_t*>(dh_zero_chunk);
+    dma16(src, lds_wave + j * 1024);
+  }
+}
 
 template <bool TA, bool TB, bool F32OUT>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmArgs g, const GemmAr ar) {
+  // Weight gradients claim 500 registers: with the 484 they need, blocks of up to 24 registers fit beside them (a Send/Recv stand-in's 8), and the launch waits
+  // for the tiles that share their unit: 224 tiles beside such an exchange 119 us, sharing 136; the context-parallel 8B step 1360 and 1376.
+  if (TA) asm volatile("" ::: "v240");
   if (g_standin_block(g, ar)) return;
   GemmTile w;
   if (!g_begin<256, 256>(g, (int)blockIdx.x - g.ar_blocks, w)) return;
@@ -493,30 +537,33 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmArgs g, cons
   const int nb0 = glu_fwd ? w.tn * 128 : w.n0, n = w.n, n_full = w.n_full;
 
   uint32_t voa[8], vob[8];
-  g_offsets<256, TA>(voa, w.m0, g.M, g.K, wave, lane);
-  g_offsets<256, !TB>(vob, nb0, g.N, g.K, wave, lane, jump);
+  gw_offsets<TA>(voa, w.m0, g.M, g.K, wave, lane);
+  gw_offsets<!TB>(vob, nb0, g.N, g.K, wave, lane, jump);
   const size_t sa = (TA ? (size_t)G_BK * g.M : (size_t)G_BK) * sizeof(bf16_t);
   const size_t sb = (TB ? (size_t)G_BK : (size_t)G_BK * g.N) * sizeof(bf16_t);
   // next tile to transfer
-  const char* ap = g_uniform(reinterpret_cast<const char*>(g.A + (TA ? (size_t)w.k_begin * g.M + w.m0 : (size_t)w.m0 * g.K + w.k_begin)));
-  const char* bp = g_uniform(reinterpret_cast<const char*>(g.B + (TB ? (size_t)nb0 * g.K + w.k_begin : (size_t)w.k_begin * g.N + nb0)));
-  const uint32_t ldsA = lds_address(smem_raw) + wave * 8192u, ldsB = ldsA + 32768u;
-  g_bias_transfers(ap, voa);
-  g_bias_transfers(bp, vob);
-  auto issue = [&](int t) {
-    const uint32_t so = (t & 1) * GW_STAGE;
+  const char* ap = g_uniform(reinterpret_cast<const char*>(g.A + (TA ? (size_t)w.k_begin * g.M + w.m0 : (size_t)w.m0 * g.K + w.k_begin))) - G_BIAS;
+  const char* bp = g_uniform(reinterpret_cast<const char*>(g.B + (TB ? (size_t)nb0 * g.K + w.k_begin : (size_t)w.k_begin * g.N + nb0))) - G_BIAS;
+  const uint32_t lds0 = lds_address(smem_raw) + wave * 4096u;
+  // Half h of tile t: A's half in the first 16 KiB of its slot, B's in the second.
+  auto issue = [&](int t, int h) {
+    const uint32_t slot = lds0 + ((t & 1) * 2 + h) * GW_SLOT;
     if (t < n_full) {
-      g_transfers_of_stage(ldsA + so, ap, voa);
-      g_transfers_of_stage(ldsB + so, bp, vob);
+      const uint32_t ma = dma_lds(slot + G_BIAS);
+#pragma unroll
+      for (int j = 0; j < 4; j++) dma16_at(ma, ap, voa[h * 4 + j], j * 1024 - G_BIAS);
+      const uint32_t mb = dma_lds(slot + 16384u + G_BIAS);
+#pragma unroll
+      for (int j = 0; j < 4; j++) dma16_at(mb, bp, vob[h * 4 + j], j * 1024 - G_BIAS);
     } else {
-      g_issue_ragged<256, TA>(ldsA + so, g.A, w.m0, w.k_begin + t * G_BK, g.M, g.K, w.k_end, wave, lane);
-      g_issue_ragged<256, !TB>(ldsB + so, g.B, nb0, w.k_begin + t * G_BK, g.N, g.K, w.k_end, wave, lane, jump);
+      gw_issue_ragged<TA>(slot, g.A, h, w.m0, w.k_begin + t * G_BK, g.M, g.K, w.k_end, wave, lane);
+      gw_issue_ragged<!TB>(slot + 16384u, g.B, h, nb0, w.k_begin + t * G_BK, g.N, g.K, w.k_end, wave, lane, jump);
     }
   };
-  if (n > 0) issue(0);
+  if (n > 0) { issue(0, 0); issue(0, 1); }
   ap += sa;
   bp += sb;
-  if (n > 1) issue(1);
+  if (n > 1) { issue(1, 0); issue(1, 1); }
   ap += sa;
   bp += sb;
 
@@ -528,12 +575,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmArgs g, cons
   g_settle(acc);
   const lds_char* pa[4];
   const lds_char* pb[4];
-  g_pointers<TA>(pa, (const lds_char*)smem_raw, (wave >> 1) * 8, lane);
-  g_pointers<!TB>(pb, (const lds_char*)smem_raw + 32768, (wave & 1) * 8, lane);
+  g_pointers<TA>(pa, (const lds_char*)smem_raw, (wave >> 1) * 4, lane);
+  g_pointers<!TB>(pb, (const lds_char*)smem_raw + 16384, (wave & 1) * 4, lane);
 
   bf16x8 fa0[8], fa1[8], fbx[8], fby[8];  // halves of 64 rows / columns: [k-step of 32][16-row tile]
-  auto rd_a = [&](int half, int e) { return g_frag<TA>(pa, e >> 2, half * 4 + (e & 3)); };
-  auto rd_b = [&](int half, int e) { return g_frag<!TB>(pb, e >> 2, half * 4 + (e & 3)); };
+  auto rd_a = [&](int half, int e) { return g_frag<TA>(pa, e >> 2, e & 3, half * (int)GW_SLOT); };
+  auto rd_b = [&](int half, int e) { return g_frag<!TB>(pb, e >> 2, e & 3, half * (int)GW_SLOT); };
   auto shift = [&](const lds_char* (&p)[4], int d) {
 #pragma unroll
     for (int x = 0; x < 4; x++) p[x] += d;
@@ -551,37 +598,54 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmArgs g, cons
       G_PIN();
     }
   };
+  // Everything up to this half has landed and every wave is through with the half before it: at most LATER transfers, those of
+  // halves further on, are still under way.
+#define GW_PUBLISH(LATER) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LATER) : "memory")
   if (n > 0) {
-    if (n > 1) G_VMCNT(16); else G_VMCNT(0);
+    if (n > 1) G_VMCNT(24); else G_VMCNT(8);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 8; e++) { fa0[e] = rd_a(0, e); fbx[e] = rd_b(0, e); }
+    if (n > 1) GW_PUBLISH(16); else GW_PUBLISH(0);
   }
   int t = 0;
-  // Works off tile t in stage S.  b0 holds the fragments of its first B half, b1 receives those of the second and then
+  // Works off tile t, of parity S.  f0 holds the fragments of its first B half, f1 receives those of the second and then
   // the next tile's first half.  STEADY: tile t+2 is a full tile, its transfers go out between the products.
   auto step = [&](auto stage, auto steady, bf16x8 (&f0)[8], bf16x8 (&f1)[8]) {
     constexpr int S = decltype(stage)::value;
     constexpr bool STEADY = decltype(steady)::value;
-    constexpr int to_next = S == 0 ? (int)GW_STAGE : -(int)GW_STAGE;
-    quad(fa0, f0, 0, 0, [&](int i) { if ((i & 1) == 0) f1[i >> 1] = rd_b(1, i >> 1); });
+    constexpr int to_next = S == 0 ? (int)(2 * GW_SLOT) : -(int)(2 * GW_SLOT);
+    const bool later = t + 2 < n;
+    uint32_t m = 0;
+    auto transfer = [&](int i, int h) {  // the i-th transfer of half h of tile t+2
+      if (i == 0) m = dma_lds(lds0 + (S * 2 + h) * GW_SLOT + G_BIAS);
+      if (i == 4) m = dma_lds(lds0 + (S * 2 + h) * GW_SLOT + 16384u + G_BIAS);
+      if (i < 4) dma16_at(m, ap, voa[h * 4 + i], i * 1024 - G_BIAS);
+      else dma16_at(m, bp, vob[h * 4 + i - 4], (i - 4) * 1024 - G_BIAS);
+    };
+    if (!STEADY && later) issue(t + 2, 0);
+    quad(fa0, f0, 0, 0, [&](int i) {
+      if ((i & 1) == 0) f1[i >> 1] = rd_b(1, i >> 1);
+      else if (STEADY) transfer(i >> 1, 0);
+    });
     quad(fa0, f1, 0, 1, [&](int i) {
       if (i < 8) fa1[i] = rd_a(1, i);
-      if (i == 13) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (i == 13) {
+        if (STEADY || later) GW_PUBLISH(16); else GW_PUBLISH(8);
+      }
     });
     shift(pa, to_next);
     shift(pb, to_next);
-    if (!STEADY && t + 2 < n) issue(t + 2);
-    uint32_t m = 0;
+    if (!STEADY && later) issue(t + 2, 1);
     quad(fa1, f1, 1, 1, [&](int i) {
-      if (STEADY && i == 0) m = dma_lds(ldsA + S * GW_STAGE + G_BIAS);
       if ((i & 1) == 0) fa0[i >> 1] = rd_a(0, i >> 1);
-      else if (STEADY) dma16_at(m, ap, voa[i >> 1], (i >> 1) * 1024 - G_BIAS);
+      else if (STEADY) transfer(i >> 1, 1);
     });
     quad(fa1, f0, 1, 0, [&](int i) {
-      if (STEADY && i == 0) m = dma_lds(ldsB + S * GW_STAGE + G_BIAS);
-      if ((i & 1) == 0) f1[i >> 1] = rd_b(0, i >> 1);
-      else if (STEADY) dma16_at(m, bp, vob[i >> 1], (i >> 1) * 1024 - G_BIAS);
+      if (i < 8) f1[i] = rd_b(0, i);
+      if (i == 13) {
+        if (STEADY || later) GW_PUBLISH(16); else GW_PUBLISH(0);
+      }
     });
     ap += sa;
     bp += sb;
@@ -816,7 +880,7 @@ template <bool TA, bool TB, bool F32OUT>
 static int launch_wide(const GemmArgs& g, int splits, hipStream_t stream, int n_groups = 1, int tile_first = 0, int n_tiles = -1,
                        const GemmAr* ar = nullptr) {
   static bool attr_set[DH_MAX_DEVICES] = {};
-  return launch_tiles<256, 256, 2 * GW_STAGE>(gemm_bf16_wide_kernel<TA, TB, F32OUT>, attr_set, g, splits, stream, n_groups, tile_first, n_tiles, ar);
+  return launch_tiles<256, 256, GW_RING * GW_SLOT>(gemm_bf16_wide_kernel<TA, TB, F32OUT>, attr_set, g, splits, stream, n_groups, tile_first, n_tiles, ar);
 }
 template <int BM, int BN, int S, bool TA, bool TB, bool F32OUT>
 constexpr int g_lds_bytes() {  // the ring, or the epilogue's turn of the tile where that takes more
