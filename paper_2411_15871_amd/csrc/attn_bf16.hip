@@ -959,6 +959,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       else if (i < 3) pack2(group, i + 1);
     };
 #define AB_PIN() __builtin_amdgcn_sched_barrier(0)
+    issue(0);
+    if (f0 + 1 < f1) issue(1);
     // dP comes out as delta - dP: the accumulators start from the rows' delta and V enters negated (dS and dK negated likewise, until dK is stored): a subtraction
     // an element less.  Against float64 dK is as far off as with the subtraction behind the sum (2.405 and 2.406e-3 to 1.766 and 1.766e-3).
 #pragma unroll
@@ -967,12 +969,6 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       vf[ks] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[ks]) ^ 0x80008000u);
       asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
     }
-    issue(0);
-    if (f0 + 1 < f1) issue(1);
-    if (f0 + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
-    __syncthreads();
-#pragma unroll
-    for (int step = 0; step < 3; step++) { frag(step, 0); frag(step, 1); }
     const uint32_t ldsQw = ldsQ + wave * (TL::IPW * 1024), tile_bytes = TL::BYTES;
     const int ragged_ti = (seq - q0) % AB_KT != 0 ? nt - 1 : nt;  // the tile of each head that is not whole
     int slot = 0;
@@ -983,6 +979,10 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       sp = reinterpret_cast<const char*>(srow + (size_t)gi * T + ti * AB_KT);
     };
     sources();
+    if (f0 + 1 < f1) dma_wait<2 * TL::IPW + 1>(); else dma_wait<0>();
+    __syncthreads();
+#pragma unroll
+    for (int step = 0; step < 3; step++) { frag(step, 0); frag(step, 1); }
     for (int f = f0; f < f1; f++) {
       const int next = slot == AB_RING - 1 ? 0 : slot + 1, free_slot = slot == 0 ? AB_RING - 1 : slot - 1;
       const int step_tile = (next - slot) * TL::BYTES, step_stat = (next - slot) * AB_KT * (int)sizeof(float);
