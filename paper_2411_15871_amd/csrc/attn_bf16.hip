@@ -15,8 +15,8 @@
 // matching A operand (V^T, K^T, dO^T, Q^T: "k" is the token index, the slow dimension in memory)
 // comes from LDS through the transposing load ds_read_b64_tr_b16.
 //
-// 64-token tiles stream global -> LDS directly (see dma.h) through a ring of three slots (two in the
-// forward kernel, so that two of its blocks fit a compute unit): the transfer of tile t+2 (t+1) is issued
+// 64-token tiles stream global -> LDS directly (see dma.h) through a ring of three slots (two or three in the
+// forward kernels, so that two of their blocks fit a compute unit): the transfer of tile t+2 (t+1) is issued
 // right after the barrier that publishes tile t.  A tile is stored
 // [token][D] unpadded; the 16-byte chunk c of row r sits at chunk position c ^ swz(r), which makes
 // the 16-byte fragment reads (16 consecutive rows, one chunk) and the transposing reads (4
@@ -225,6 +225,11 @@ template <bool AGPR, int N> __device__ __forceinline__ void acc_settle(f32x16 (&
   if constexpr (AGPR) mfma_acc_settle(a);
 }
 
+
+// Wait states after which the vector ALU may read score tiles.
+__device__ __forceinline__ void mfma_settle(f32x16 (&a)[2]) {
+  asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a[0]), "+v"(a[1]));
+}
 
 template <int D>
 struct ATile {
@@ -445,10 +450,12 @@ static int fwd_units(int seq, int q_off, int ch) {
   return n;
 }
 
-// grid (units * nq * batch); wave w owns query rows i0 + 32w .. +31.  The K and V tiles go through two LDS
-// slots each (64 KiB per block at D = 128), so that two blocks fit a compute unit: the matrix work of
-// one block's waves then overlaps the softmax arithmetic of the other's.
+// Wave w of a block owns query rows i0 + 32w .. +31.  Tile slots: the loop in phases two for K and two for V, so that two blocks share a unit at either head width;
+// the pipelined one of D = 128 (attn_fwd_pinned) reads K a tile ahead of V, so a V tile stays a tile longer.
 #define AF_RING 2
+#define AF_K_RING 2
+#define AF_V_RING 3
+#define AF_BIAS 4096  // see tile_voff_biased
 
 // A wave's 32 rows x D columns in the transposed accumulator layout (lane l32 = row, kg = lane / 32; quad (dt, q4) of
 // a lane is columns dt*32 + 8*q4 + 4*kg .. +3) leave through a wave-private LDS region so that a lane stores 16 bytes
@@ -498,6 +505,340 @@ __device__ __forceinline__ void wave_rows_out_bf16(bf16_t* reg, int lane, Quad q
   }
 }
 #define AF_TAU 8.0f  // log2 of the headroom a row's probabilities may take over its reference maximum
+#define AB_PIN() __builtin_amdgcn_sched_barrier(0)
+
+// Both halves of the wave: lane l and lane l ^ 32 get f of the two values.
+template <class F>
+__device__ __forceinline__ float across_halves(float v, F f) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return f(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+
+// Offsets for dma16_at with transfer j's KiB as its constant, which the hardware adds to the LDS and to the memory address; the base is AF_BIAS bytes
+// before the tile, so that no offset is negative, whatever the clamped row.
+template <int D>
+__device__ __forceinline__ void tile_voff_biased(uint32_t (&v)[ATile<D>::IPW], int ld, int wave, int lane, int rows_valid) {
+  asm volatile("" : "+v"(lane));  // computed here: shared with the other tiles' offsets it would hold registers through the main loop
+  tile_voff<D>(v, ld, wave, lane, rows_valid);
+#pragma unroll
+  for (int j = 0; j < ATile<D>::IPW; j++) v[j] += AF_BIAS - j * 1024;
+}
+
+// The D = 128 tile loop: key tiles [t0, t1) of one unit (q: the wave's rows); a wave stops at its last tile with a visible key, at most one short of t1.
+// ot: unnormalised output, m: reference maximum (log2), l: sum of the probabilities.
+//
+// With the phases one after the other (scores, softmax, P V) a tile took 2190 cycles, about its 1024 of matrix instructions and its 1400 of
+// vector ALU added up, although two blocks shared the unit.  Here iteration t forms the scores of tile t+1 beside the exponentials of
+// tile t, and the maximum of tile t+1 beside the P V products of tile t; every matrix instruction is volatile and followed by its share of the
+// rest, and all of it is pinned.  A barrier an iteration, in its P V half, publishes K(t+2) and V(t+1) and retires K(t+1) and V(t-1), whose slots the
+// next iteration fills (tiles behind the unit's end are its last one again, so that every iteration has 8 transfers).
+// The same sums in the same order as the loop in phases: the same bits.
+//
+// Measured alone (us, in phases -> here): 32:8 heads x 4096 tokens 165 -> 153, 8:1 x 8192 185 -> 163, 4:1 x 4096 queries over 12288 keys 129 -> 115,
+// 2 x 2048 x 8 heads 44.4 -> 38.7, 16:4 x 1500 33.8 -> 29.9.  In cycles it is 17 % (290 -> 240 thousand at 32:8 heads, matrix cores busy 46 -> 56 %): the
+// clock falls from 1.75 to 1.65 GHz, the power limit takes the rest.  Without the LDS reads (results meaningless) the same loop takes 200 thousand cycles and 108 us, so these
+// are its largest single cost; two heads of a group a block, which halves them but needs a unit's registers for one block, 149 us there and 135 over 12288 keys,
+// 23 instead of 15.7 for 3 x 683 tokens: a block's start and end (6 us, 40 KiB of code to fetch) have nothing beside them.  One block a unit with rings of three and four
+// slots: 175.
+__device__ __forceinline__ void attn_fwd_pinned(char* smem, const char* kbase, const char* vbase, size_t tstride, int ldkv, int seq, int t0, int t1, int iw,
+                                                float scale_log2, const bf16_t* q, f32x16 (&ot)[4], float& m, float& l) {
+  constexpr int D = 128, KS = D / 16;
+  using TL = ATile<D>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, kg = lane >> 5;
+  const int tile_end = min(t1, (iw + 31) / AB_KT + 1), iq = iw + l32;
+  const int ragged = seq % AB_KT != 0 ? seq / AB_KT : -1;  // the sequence's last tile if it is not whole
+  const lds_char* sm = (const lds_char*)smem;
+  const uint32_t ldsKw = lds_address(smem) + wave * (TL::IPW * 1024), ldsVw = ldsKw + AF_K_RING * TL::BYTES;
+  auto first_fetch = [&](const char* base, int t, uint32_t lds) {
+    t = min(t, t1 - 1);
+    uint32_t v[TL::IPW];
+    tile_voff_biased<D>(v, ldkv, wave, lane, min(seq - t * AB_KT, AB_KT));
+    const uint32_t m0 = dma_lds(lds);
+#pragma unroll
+    for (int j = 0; j < TL::IPW; j++) dma16_at(m0, base + t * tstride - AF_BIAS, v[j], j * 1024);
+  };
+  first_fetch(kbase, t0, ldsKw);
+  bf16x8 qf[KS];
+  load_row_frags<D>(qf, q, iq < seq, kg);
+  first_fetch(vbase, t0, ldsVw);
+  first_fetch(kbase, t0 + 1, ldsKw + TL::BYTES);
+  int kt = min(t0 + 2, t1 - 1), vt = min(t0 + 1, t1 - 1);  // tiles to transfer next
+  const char* kp = kbase + kt * tstride - AF_BIAS;
+  const char* vp = vbase + vt * tstride - AF_BIAS;
+  uint32_t vk[TL::IPW], vv[TL::IPW];
+  tile_voff_biased<D>(vk, ldkv, wave, lane, min(seq - kt * AB_KT, AB_KT));
+  tile_voff_biased<D>(vv, ldkv, wave, lane, min(seq - vt * AB_KT, AB_KT));
+
+  const lds_char* dir[KS];
+  const lds_char* tr0[D / 32];
+  const lds_char* tr1[D / 32];
+  {
+    FragAddr<D> fa;
+    fa.init(lane);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) dir[ks] = sm + fa.kdir[ks];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; dt++) {
+      tr0[dt] = sm + AF_K_RING * TL::BYTES + fa.tr0[dt];
+      tr1[dt] = sm + AF_K_RING * TL::BYTES + fa.tr1[dt];
+    }
+  }
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++) mfma_acc_zero(ot[dt]);
+  pin_frags(qf);
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) asm volatile("" : "+a"(qf[ks]));
+  typedef f32x16 Scores[2];
+  bf16x8 fr[4][2];       // K fragments of four k-steps: asked for three steps ahead
+  bf16x8 tr[4][D / 32];  // V fragments of the tile's four groups of 16 keys: two groups ahead
+  bf16x8 pf[4];          // the groups' packed probabilities
+  Scores sa, sb;         // scores, then probabilities, of even and odd iterations
+  auto frag = [&](int step, int mt) { fr[step & 3][mt] = lds_frag(dir[step], mt * 32 * TL::LD * 2); };
+  auto trfrag = [&](int g, int dt) { tr[g][dt] = lds_frag_tr(tr0[dt], tr1[dt], g * 16 * TL::LD * 2); };
+  auto first_frags = [&]() {
+#pragma unroll
+    for (int step = 0; step < 3; step++) { frag(step, 0); frag(step, 1); }
+  };
+  auto score = [&](Scores& s, int i) {
+    if (i < 2) mfma_first(s[i & 1], fr[0][i & 1], qf[0]);
+    else mfma_next(s[i & 1], fr[(i >> 1) & 3][i & 1], qf[i >> 1]);
+    if ((i >> 1) + 3 < KS) frag((i >> 1) + 3, i & 1);
+  };
+  float mx, rs;
+  auto prob = [&](Scores& s, int x) {
+    float p = fast_exp2(fmaf(s[x >> 4][x & 15], scale_log2, -m));
+    rs += p;
+    asm volatile("" : "+v"(p), "+v"(rs));  // here, not behind the mask's branch
+    s[x >> 4][x & 15] = p;
+  };
+  auto pack = [&](const Scores& s, int x) {  // elements 2x, 2x+1
+    pf[x >> 2][2 * (x & 3)] = (bf16_t)s[x >> 3][2 * (x & 7)];
+    pf[x >> 2][2 * (x & 3) + 1] = (bf16_t)s[x >> 3][2 * (x & 7) + 1];
+  };
+  auto max2 = [&](const Scores& s, int x) {
+    const float v = fmaxf(s[x >> 3][2 * (x & 7)], s[x >> 3][2 * (x & 7) + 1]);
+    mx = x == 0 ? v : fmaxf(mx, v);
+  };
+  auto larger = [](float a, float b) { return fmaxf(a, b); };
+  auto sum = [](float a, float b) { return a + b; };
+  auto mask = [&](Scores& s, int t) {  // the tile crosses the diagonal for this wave: no key above the row
+    if (t * AB_KT + AB_KT - 1 <= iw) return;
+    mfma_settle(s);
+#pragma unroll
+    for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        s[mt][r] = t * AB_KT + mt * 32 + 8 * (r >> 2) + 4 * kg + (r & 3) > iq ? -INFINITY : s[mt][r];
+        if ((r & 3) == 3) AB_PIN();
+      }
+  };
+  int k_slot = 1, v_slot = 0;  // K: the tile whose scores come next, V: the tile whose products come next
+
+  dma_wait<2 * TL::IPW>();
+  __syncthreads();  // K(t0)
+  first_frags();
+#pragma unroll
+  for (int i = 0; i < 16; i++) { score(sa, i); AB_PIN(); }
+  mfma_settle(sa);
+  mask(sa, t0);
+#pragma unroll
+  for (int x = 0; x < 16; x++) max2(sa, x);
+  mx = across_halves(mx, larger);
+  m = fmaxf(-INFINITY, mx * scale_log2);  // finite: the unit's first key is visible to every row
+  l = 0.f;
+  dma_wait<0>();
+  __syncthreads();  // V(t0), K(t0+1)
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) dir[ks] += TL::BYTES;
+  first_frags();
+
+  // The reference maximum m of a row moves only when some row of the wave outgrows its reference by more than
+  // 2^AF_TAU (then every row takes its true maximum and the accumulators are rescaled); otherwise the tile's
+  // probabilities are formed against the old reference and may reach 2^AF_TAU, which float32 sums and the bf16 P
+  // fragments hold without loss of relative precision.  The result depends on m only through rounding: the
+  // normalisation by l at the end and lse = m + log2 l use the same reference.  After the first few tiles of a row the
+  // rescaling (one multiply per accumulator element per tile) almost never runs.
+  auto reference = [&]() {
+    const float mnew = mx * scale_log2;
+    if (__any(mnew > m + AF_TAU)) {
+      mfma_acc_settle(ot);
+      const float mn = fmaxf(m, mnew);
+      const float alpha = fast_exp2(m - mn);
+      l *= alpha;
+      m = mn;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) ot[dt][r] *= alpha;
+    }
+  };
+  // P V of the tile behind tr0: 16 slots, in each `beside(slot)` and its share of the last group's probabilities and of the packing
+  auto products = [&](Scores& s, auto beside) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      mfma_grad(ot[i & 3], tr[i >> 2][i & 3], pf[i >> 2]);
+      if (i < 8) trfrag((i >> 2) + 2, i & 3);
+      if (i < 4) pack(s, 8 + i);
+      if (i < 8) prob(s, 24 + i);
+      else if (i < 10) { pack(s, 2 * i - 4); pack(s, 2 * i - 3); }
+      beside(i);
+      AB_PIN();
+    }
+  };
+  auto step = [&](Scores& s, Scores& next, int t) {
+    uint32_t m0 = 0;
+    rs = 0.f;
+    const int k_next = k_slot ^ 1, v_next = v_slot == AF_V_RING - 1 ? 0 : v_slot + 1;  // these held K(t) and V(t-2)
+    // scores of tile t+1 beside three quarters of tile t's probabilities
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      score(next, i);
+      if (i == 0) m0 = dma_lds(ldsKw + k_next * TL::BYTES);
+      if (i == 4) m0 = dma_lds(ldsVw + v_next * TL::BYTES);
+      if (i < 4) dma16_at(m0, kp, vk[i], i * 1024);
+      else if (i < 8) dma16_at(m0, vp, vv[i - 4], (i - 4) * 1024);
+      else trfrag((i - 8) >> 2, i & 3);
+#pragma unroll
+      for (int x = i * 24 / 16; x < (i + 1) * 24 / 16; x++) prob(s, x);
+      if (i >= 6 && i < 10) pack(s, i - 6);
+      if (i >= 11 && i < 15) pack(s, i - 7);
+      if (i == 15) asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));
+      AB_PIN();
+    }
+    mask(next, t + 1);
+    // products of tile t beside its last probabilities and the maximum of tile t+1's scores
+    products(s, [&](int i) {
+      if (i >= 3 && i < 11) { max2(next, 2 * (i - 3)); max2(next, 2 * (i - 3) + 1); }
+      if (i >= 4 && i < 8) {
+        dir[2 * (i - 4)] += (k_next - k_slot) * TL::BYTES;
+        dir[2 * (i - 4) + 1] += (k_next - k_slot) * TL::BYTES;
+      }
+      if (i == 9) l += across_halves(rs, sum);
+      if (i == 11) {
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        mx = across_halves(mx, larger);
+      }
+      if (i >= 12 && i < 15) { frag(i - 12, 0); frag(i - 12, 1); }
+      if (i >= 12) {
+        tr0[i & 3] += (v_next - v_slot) * TL::BYTES;
+        tr1[i & 3] += (v_next - v_slot) * TL::BYTES;
+      }
+    });
+    k_slot = k_next;
+    v_slot = v_next;
+    if (kt < t1 - 1) {
+      kp += tstride;
+      if (++kt == ragged) tile_voff_biased<D>(vk, ldkv, wave, lane, seq - kt * AB_KT);
+    }
+    if (vt < t1 - 1) {
+      vp += tstride;
+      if (++vt == ragged) tile_voff_biased<D>(vv, ldkv, wave, lane, seq - vt * AB_KT);
+    }
+    reference();
+  };
+  int t = t0;
+  for (; t + 2 < tile_end; t += 2) {
+    step(sa, sb, t);
+    step(sb, sa, t + 1);
+  }
+  if (t + 1 < tile_end) {
+    step(sa, sb, t);
+    sa[0] = sb[0];
+    sa[1] = sb[1];
+  }
+  // the wave's last tile
+  if (tile_end < t1) {  // other waves go on: this wave's share of their last V tile
+    const uint32_t m0 = dma_lds(ldsVw + (v_slot == AF_V_RING - 1 ? 0 : v_slot + 1) * TL::BYTES);
+#pragma unroll
+    for (int j = 0; j < TL::IPW; j++) dma16_at(m0, vp, vv[j], j * 1024);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+#pragma unroll
+  for (int i = 0; i < 8; i++) trfrag(i >> 2, i & 3);
+  rs = 0.f;
+#pragma unroll
+  for (int x = 0; x < 24; x++) prob(sa, x);
+#pragma unroll
+  for (int x = 0; x < 8; x++) pack(sa, x);
+  AB_PIN();
+  asm volatile("s_nop 3" ::: "memory");
+  products(sa, [](int) {});
+  l += across_halves(rs, sum);
+  mfma_acc_settle(ot);
+  dma_wait<0>();  // the rings' memory is used again
+}
+
+// Positions of a unit's rows, common to the kernels below.
+struct FwdUnit { int blk, chunk, nchunks, pair; };
+__device__ __forceinline__ FwdUnit fwd_unit(int launch, int seq, int qb0, int ch, int units) {
+  FwdUnit f = {0, 0, 1, 0};
+  if (ch == 0) {
+    f.pair = units - 1 - launch;
+    f.blk = qb0 + f.pair;
+  } else {  // heaviest block first; `pair` numbers the (block, chunk) units in natural order
+    const int last = (seq + 127) / 128 - 1;
+    const UnitOf u = find_unit(launch, last - qb0 + 1, [&](int v) { return fwd_chunks(last - v, seq, ch); });
+    f.blk = last - u.v;
+    f.nchunks = fwd_chunks(f.blk, seq, ch);
+    f.chunk = u.rem;
+    f.pair = units - u.before - f.nchunks + u.rem;
+  }
+  return f;
+}
+// A wave's 32 rows leave: the unit's partial result, or the final rows and lse.  unit: index of the partial result.
+template <int D>
+__device__ __forceinline__ void fwd_rows_out(char* smem, const FwdUnit& u, size_t unit, int seq, int iw, int lane, int wave, const f32x16 (&ot)[D / 32], float m,
+                                             float l, bf16_t* orow, size_t ldo, float* lse_row, float* part_o, float* part_ml) {
+  const int l32 = lane & 31, iq = iw + l32, r0 = wave * 32;
+  if (u.nchunks > 1) {  // partial result of this chunk
+    wave_rows_out_f32<D>(
+        reinterpret_cast<float*>(smem) + wave * (32 * D), lane,
+        [&](int dt, int q4) { return f32x4{ot[dt][4 * q4], ot[dt][4 * q4 + 1], ot[dt][4 * q4 + 2], ot[dt][4 * q4 + 3]}; },
+        [&](int r) { return iw + r < seq ? part_o + (unit * 128 + r0 + r) * D : nullptr; });
+    if (iq < seq && lane < 32) {
+      part_ml[(unit * 128 + r0 + l32) * 2] = m;
+      part_ml[(unit * 128 + r0 + l32) * 2 + 1] = l;
+    }
+    return;
+  }
+  const float inv = 1.0f / l;
+  wave_rows_out_bf16<D>(
+      reinterpret_cast<bf16_t*>(smem) + wave * (32 * D), lane,
+      [&](int dt, int q4) {
+        return f32x4{ot[dt][4 * q4] * inv, ot[dt][4 * q4 + 1] * inv, ot[dt][4 * q4 + 2] * inv, ot[dt][4 * q4 + 3] * inv};
+      },
+      [&](int r) { return iw + r < seq ? orow + (size_t)r * ldo : nullptr; });
+  if (iq < seq && lane < 32) lse_row[l32] = (m + log2f(l)) * 0.6931471805599453f;
+}
+
+// grid (units * nq * batch), D = 128
+__global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_pinned_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+                                                                             float* __restrict__ lse, int T, float scale_log2, int ch, int units,
+                                                                             float* __restrict__ part_o, float* __restrict__ part_ml) {
+  constexpr int D = 128;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];  // K ring, then V ring
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int seq = g.seq, nq = g.nq, nkv = g.nkv, ldkv = g.ldkv, ld = (nq + 2 * nkv) * D;
+  const int hb = blockIdx.x % g.nq_all, h = hb % nq, b = hb / nq, hk = h / (nq / nkv);
+  const FwdUnit u = fwd_unit(blockIdx.x / g.nq_all, seq, g.q_off / 128, ch, units);
+  const int i0 = u.blk * 128, iw = i0 + wave * 32;  // positions in the sequence
+  const size_t ktok0 = (size_t)b * seq;
+  const long long qtok0 = (long long)b * (seq - g.q_off) - g.q_off;  // local token of position p = qtok0 + p
+  const char* kbase = reinterpret_cast<const char*>(g.kv + ktok0 * ldkv + (size_t)hk * D);
+  const char* vbase = reinterpret_cast<const char*>(g.kv + ktok0 * ldkv + (size_t)(nkv + hk) * D);
+  const int tiles_all = (min(seq, i0 + 128) + AB_KT - 1) / AB_KT;  // keys needed by this block: [0, 64*tiles_all)
+  const int t0 = u.chunk * ch, t1 = ch == 0 ? tiles_all : min(tiles_all, t0 + ch);  // this unit: tiles [t0, t1)
+  f32x16 ot[D / 32];
+  float m, l;
+  attn_fwd_pinned(smem, kbase, vbase, (size_t)AB_KT * ldkv * sizeof(bf16_t), ldkv, seq, t0, t1, iw, scale_log2,
+                  qkv + (size_t)(qtok0 + min(iw + (lane & 31), seq - 1)) * ld + (size_t)h * D, ot, m, l);
+  __syncthreads();  // every wave is done with the K/V rings: their LDS serves the output turn
+  fwd_rows_out<D>(smem, u, ((size_t)b * nq + h) * units + u.pair, seq, iw, lane, wave, ot, m, l, o + (size_t)(qtok0 + iw) * nq * D + (size_t)h * D,
+                  (size_t)nq * D, lse + (size_t)h * T + qtok0 + iw, part_o, part_ml);
+}
+
+// The loop in phases: D = 64, and units too short for a pipeline.  grid (units * nq * batch)
 template <int D>
 __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const AttnGeom g, const bf16_t* __restrict__ qkv,
                                                                    bf16_t* __restrict__ o, float* __restrict__ lse, int T,
@@ -508,23 +849,12 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
   const lds_char* sm = (const lds_char*)smem;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, kg = lane >> 5;
-  const int seq = g.seq, nq = g.nq, nkv = g.nkv, qb0 = g.q_off / 128, ldkv = g.ldkv;
-  const int hb = blockIdx.x % g.nq_all, launch = blockIdx.x / g.nq_all;
+  const int seq = g.seq, nq = g.nq, nkv = g.nkv, ldkv = g.ldkv;
+  const int hb = blockIdx.x % g.nq_all;
   const int h = hb % nq, b = hb / nq, hk = h / (nq / nkv);
   const int ld = (nq + 2 * nkv) * D;
-  int blk, chunk = 0, nchunks = 1, pair;
-  if (ch == 0) {
-    pair = units - 1 - launch;
-    blk = qb0 + pair;
-  } else {  // heaviest block first; `pair` numbers the (block, chunk) units in natural order
-    const int last = (seq + 127) / 128 - 1;
-    const UnitOf u = find_unit(launch, last - qb0 + 1, [&](int v) { return fwd_chunks(last - v, seq, ch); });
-    blk = last - u.v;
-    nchunks = fwd_chunks(blk, seq, ch);
-    chunk = u.rem;
-    pair = units - u.before - nchunks + u.rem;
-  }
-  const int i0 = blk * 128, iw = i0 + wave * 32, iq = iw + l32;  // positions in the sequence
+  const FwdUnit u = fwd_unit(blockIdx.x / g.nq_all, seq, g.q_off / 128, ch, units);
+  const int i0 = u.blk * 128, iw = i0 + wave * 32, iq = iw + l32;  // positions in the sequence
   const size_t ktok0 = (size_t)b * seq;
   const long long qtok0 = (long long)b * (seq - g.q_off) - g.q_off;  // local token of position p = qtok0 + p
   const char* kbase = reinterpret_cast<const char*>(g.kv + ktok0 * ldkv + (size_t)hk * D);
@@ -534,19 +864,19 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
   bf16x8 qf[D / 16];
   load_row_frags<D>(qf, qkv + (size_t)(qtok0 + min(iq, seq - 1)) * ld + (size_t)h * D, iq < seq, kg);
   f32x16 ot[D / 32];
-#pragma unroll
-  for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-    for (int r = 0; r < 16; r++) ot[dt][r] = 0.f;
   float m = -INFINITY, l = 0.f;
-
+  const int tiles_all = (min(seq, i0 + 128) + AB_KT - 1) / AB_KT;  // keys needed by this block: [0, 64*tiles_all)
+  const int t_begin = u.chunk * ch, ntiles = ch == 0 ? tiles_all : min(tiles_all, t_begin + ch);  // this unit: [t_begin, ntiles)
+  pin_frags(qf);
   FragAddr<D> fa;
   fa.init(lane);
   uint32_t voff[TL::IPW];
   tile_voff<D>(voff, ldkv, wave, lane, AB_KT);
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) ot[dt][r] = 0.f;
   const uint32_t ldsK = lds_address(smem), ldsV = ldsK + AF_RING * TL::BYTES;
-  const int tiles_all = (min(seq, i0 + 128) + AB_KT - 1) / AB_KT;  // keys needed by this block: [0, 64*tiles_all)
-  const int t_begin = chunk * ch, ntiles = ch == 0 ? tiles_all : min(tiles_all, t_begin + ch);  // this unit: [t_begin, ntiles)
   auto issue = [&](int t) {
     const int slot = (t - t_begin) % AF_RING, valid = seq - t * AB_KT;
     if (valid >= AB_KT) {
@@ -559,7 +889,6 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
       tile_dma<D>(vbase + t * tstride, vc, ldsV + slot * TL::BYTES, wave);
     }
   };
-  pin_frags(qf);
   issue(t_begin);
   int slot = 0;
   for (int t = t_begin; t < ntiles; t++, slot ^= 1) {
@@ -584,12 +913,7 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
 #pragma unroll
     for (int r = 1; r < 16; r++) mx = fmaxf(mx, fmaxf(st[0][r], st[1][r]));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    // The reference maximum m of a row moves only when some row of the wave outgrows its reference by more than
-    // 2^AF_TAU (then every row takes its true maximum and the accumulators are rescaled); otherwise the tile's
-    // probabilities are formed against the old reference and may reach 2^AF_TAU, which float32 sums and the bf16 P
-    // fragments hold without loss of relative precision.  The result depends on m only through rounding: the
-    // normalisation by l at the end and lse = m + log2 l use the same reference.  After the first few tiles of a row the
-    // rescaling (one multiply per accumulator element per tile) almost never runs.
+    // The reference maximum moves as in attn_fwd_pinned.
     const float mnew = mx * scale_log2;  // finite from the unit's first tile on: its first key is visible to every row
     float rs = 0.f;
     if (__any(mnew > m + AF_TAU)) {
@@ -623,26 +947,8 @@ __global__ __launch_bounds__(AB_THREADS, 2) void attn_fwd_bf16_kernel(const Attn
       }
   }
   __syncthreads();  // every wave is done with the K/V rings: their LDS serves the output turn
-  if (nchunks > 1) {  // partial result of this chunk
-    const size_t unit = ((size_t)b * nq + h) * units + pair;
-    wave_rows_out_f32<D>(
-        reinterpret_cast<float*>(smem) + wave * (32 * D), lane,
-        [&](int dt, int q4) { return f32x4{ot[dt][4 * q4], ot[dt][4 * q4 + 1], ot[dt][4 * q4 + 2], ot[dt][4 * q4 + 3]}; },
-        [&](int r) { return iw + r < seq ? part_o + (unit * 128 + (iw + r - i0)) * D : nullptr; });
-    if (iq < seq && kg == 0) {
-      part_ml[(unit * 128 + (iq - i0)) * 2] = m;
-      part_ml[(unit * 128 + (iq - i0)) * 2 + 1] = l;
-    }
-    return;
-  }
-  const float inv = 1.0f / l;
-  wave_rows_out_bf16<D>(
-      reinterpret_cast<bf16_t*>(smem) + wave * (32 * D), lane,
-      [&](int dt, int q4) {
-        return f32x4{ot[dt][4 * q4] * inv, ot[dt][4 * q4 + 1] * inv, ot[dt][4 * q4 + 2] * inv, ot[dt][4 * q4 + 3] * inv};
-      },
-      [&](int r) { return iw + r < seq ? o + (size_t)(qtok0 + iw + r) * nq * D + (size_t)h * D : nullptr; });
-  if (iq < seq && kg == 0) lse[(size_t)h * T + qtok0 + iq] = (m + log2f(l)) * 0.6931471805599453f;
+  fwd_rows_out<D>(smem, u, ((size_t)b * nq + h) * units + u.pair, seq, iw, lane, wave, ot, m, l, o + (size_t)(qtok0 + iw) * nq * D + (size_t)h * D,
+                  (size_t)nq * D, lse + (size_t)h * T + qtok0 + iw, part_o, part_ml);
 }
 
 // Merges the chunks of the query blocks that were split: with M = max_c m_c, o = sum_c 2^(m_c-M) o_c / L,
@@ -958,7 +1264,6 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       if (i == 0) { pack2(group, 0); pack2(group, 1); }
       else if (i < 3) pack2(group, i + 1);
     };
-#define AB_PIN() __builtin_amdgcn_sched_barrier(0)
     issue(0);
     if (f0 + 1 < f1) issue(1);
     // dP comes out as delta - dP: the accumulators start from the rows' delta and V enters negated (dS and dK negated likewise, until dK is stored): a subtraction
@@ -1570,6 +1875,10 @@ size_t dh_attn_fwd_bf16_ws_bytes(int batch, int seq_q, int q_off, int nq, int nk
   return (size_t)batch * nq * fwd_units(seq, q_off, ch) * 128 * ((size_t)d + 2) * sizeof(float);
 }
 
+// Whether the pipelined kernel takes a launch: units of few tiles spend longer in its start (the first tile's scores stand alone, twice the code is
+// fetched) than its loop gains.  us, in phases and pipelined: 4:1 heads x 300 tokens (5 tiles) 9.3 and 9.7, 32:8 x 343 (6) 11.8 and 11.9,
+// 8:2 x 1280 (chunks of 8) 23.1 and 23.6, 3 x 488 on 4:2 (8) 13.8 and 13.4, 4:1 x 4096 (chunks of 10) 39.0 and 38.0, 3 x 683 (11) 17.0 and 15.7.
+static bool fwd_pinned(int d, int seq, int ch) { return d == 128 && (ch > 0 ? ch : fwd_tiles((seq + 127) / 128 - 1, seq)) >= 10; }
 int dh_launch_attn_fwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const bf16_t* qkv, const bf16_t* kv, int ldkv, int q_off,
                             bf16_t* o, float* lse, void* ws, size_t ws_bytes, hipStream_t stream) {
   int rc;
@@ -1585,22 +1894,26 @@ int dh_launch_attn_fwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const 
   const int units = ch > 0 ? fwd_units(seq, q_off, ch) : nblk;
   float* part_o = (float*)ws;
   float* part_ml = ch > 0 ? part_o + (size_t)batch * nq * units * 128 * d : nullptr;
-  dim3 grid((unsigned)units * nq * batch), cgrid(nblk * 8, nq, batch);
+  dim3 cgrid(nblk * 8, nq, batch);
   const float sl2 = (float)(1.4426950408889634 / sqrt((double)d));
-  const size_t lds = 2 * AF_RING * (size_t)AB_KT * d * 2;
-  static bool ready_dev[DH_MAX_DEVICES][2] = {};
+  static bool ready_dev[DH_MAX_DEVICES][3] = {};
   bool* ready = ready_dev[dh_device_index()];
-  if (d == 128) {
-    if (!ready[0]) { if ((rc = set_lds(attn_fwd_bf16_kernel<128>, lds))) return rc; ready[0] = true; }
-    attn_fwd_bf16_kernel<128><<<grid, AB_THREADS, lds, stream>>>(g, qkv, o, lse, T, sl2, ch, units, part_o, part_ml);
+  auto launch = [&](auto kernel, bool& set, int slots) -> int {
+    const size_t lds = (size_t)slots * AB_KT * d * sizeof(bf16_t);
+    if (!set) {
+      if (int e = set_lds(kernel, lds)) return e;
+      set = true;
+    }
+    kernel<<<(unsigned)units * nq * batch, AB_THREADS, lds, stream>>>(g, qkv, o, lse, T, sl2, ch, units, part_o, part_ml);
     DH_LAUNCH_CHECK();
-    if (ch > 0) attn_fwd_combine_kernel<128><<<cgrid, 256, 0, stream>>>(seq, q_off, nq, ch, units, part_o, part_ml, o, lse, T);
-  } else {
-    if (!ready[1]) { if ((rc = set_lds(attn_fwd_bf16_kernel<64>, lds))) return rc; ready[1] = true; }
-    attn_fwd_bf16_kernel<64><<<grid, AB_THREADS, lds, stream>>>(g, qkv, o, lse, T, sl2, ch, units, part_o, part_ml);
-    DH_LAUNCH_CHECK();
-    if (ch > 0) attn_fwd_combine_kernel<64><<<cgrid, 256, 0, stream>>>(seq, q_off, nq, ch, units, part_o, part_ml, o, lse, T);
-  }
+    return DH_OK;
+  };
+  if (fwd_pinned(d, seq, ch)) rc = launch(attn_fwd_pinned_bf16_kernel, ready[0], AF_K_RING + AF_V_RING);
+  else if (d == 128) rc = launch(attn_fwd_bf16_kernel<128>, ready[1], 2 * AF_RING);
+  else rc = launch(attn_fwd_bf16_kernel<64>, ready[2], 2 * AF_RING);
+  if (rc || ch == 0) return rc;
+  if (d == 128) attn_fwd_combine_kernel<128><<<cgrid, 256, 0, stream>>>(seq, q_off, nq, ch, units, part_o, part_ml, o, lse, T);
+  else attn_fwd_combine_kernel<64><<<cgrid, 256, 0, stream>>>(seq, q_off, nq, ch, units, part_o, part_ml, o, lse, T);
   DH_LAUNCH_CHECK();
   return DH_OK;
 }
