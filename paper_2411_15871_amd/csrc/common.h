@@ -240,6 +240,11 @@ bool dh_gemm_pair_pays(int T, int k, int n, bool beside);
 int dh_gemm_pair_shape(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
                              bool beside, void* ws, size_t ws_bytes, hipStream_t stream);
+// The same with a column sum for the launch to carry (nullptr: none); *carried is set if it does, otherwise the sum is still to be made.
+struct BiasGrad { const bf16_t* x; int rows, n; float* dst; };  // dst[n] += column sums of x[rows, n]
+bool dh_colsum_direct(int T, int N);  // whether dh_colsum makes these sums in one launch
+int dh_launch_gemm_pair_bias_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
+                                  bool beside, void* ws, size_t ws_bytes, hipStream_t stream, const BiasGrad* bias, bool* carried);
 bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside);
 int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X,
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream);

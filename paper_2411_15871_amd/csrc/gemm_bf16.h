@@ -831,12 +831,54 @@ __global__ __launch_bounds__(256, OCC) void gemm_bf16_tile_kernel(GemmArgs g, co
   g_tile<BM, BN, S, TA, TB, F32OUT>(g, (int)blockIdx.x - g.ar_blocks, smem_raw);
 }
 
+// A column sum (a bias gradient) that a pair's launch carries: blocks from `first` on, 32 columns each.
+struct GemmColsum {
+  BiasGrad of;
+  int first;
+};
+// The sums of colsum_direct_kernel in its order, the same bits, by 256 threads in four turns: 256 row lanes add every 256th row, then the
+// sixteen lanes of each of sixteen groups, then the groups.
+__device__ __forceinline__ void g_colsum(const BiasGrad& c, int blk, float* smem) {
+  const int cl = threadIdx.x & 3, col = blk * 32 + cl * 8, colc = min(col, c.n - 8);
+#pragma unroll
+  for (int p = 0; p < 4; p++) {
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int r = p * 64 + (threadIdx.x >> 2); r < c.rows; r += 256 * 8) {
+      bf16x8 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) v[u] = *reinterpret_cast<const bf16x8*>(c.x + (size_t)min(r + 256 * u, c.rows - 1) * c.n + colc);
+#pragma unroll
+      for (int u = 0; u < 8; u++)
+#pragma unroll
+        for (int i = 0; i < 8; i++) s[i] = r + 256 * u < c.rows ? s[i] + (float)v[u][i] : s[i];
+    }
+#pragma unroll
+    for (int d = 4; d < 64; d <<= 1)
+#pragma unroll
+      for (int i = 0; i < 8; i++) s[i] += __shfl_xor(s[i], d, 64);
+    if ((threadIdx.x & 63) < 4)
+#pragma unroll
+      for (int i = 0; i < 8; i++) smem[(p * 4 + (threadIdx.x >> 6)) * 32 + cl * 8 + i] = s[i];
+  }
+  __syncthreads();
+  if (threadIdx.x < 32 && blk * 32 + (int)threadIdx.x < c.n) {
+    float t = smem[threadIdx.x];
+#pragma unroll
+    for (int k = 1; k < 16; k++) t += smem[k * 32 + threadIdx.x];
+    c.dst[blk * 32 + threadIdx.x] += t;
+  }
+}
+
 // A data gradient (A [M,K], B [N,K], bf16 result) and a weight gradient (A [K,M], B [K,N], added to float32) in one launch: the two
 // GEMMs of a linear layer's backward pass read the same dY and do not depend on each other.  The first n_first blocks are
 // the tiles of the one whose blocks take longer.
 template <int BM, int BN, int S, int OCC>
-__global__ __launch_bounds__(256, OCC) void gemm_bf16_pair_kernel(GemmArgs d, GemmArgs w, int n_first, int w_first) {
+__global__ __launch_bounds__(256, OCC) void gemm_bf16_pair_kernel(GemmArgs d, GemmArgs w, int n_first, int w_first, const GemmColsum cs) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  if ((int)blockIdx.x >= cs.first) {
+    g_colsum(cs.of, (int)blockIdx.x - cs.first, reinterpret_cast<float*>(smem_raw));
+    return;
+  }
   const bool second = (int)blockIdx.x >= n_first;
   const int bx = second ? (int)blockIdx.x - n_first : (int)blockIdx.x;
   if (second != (w_first != 0)) g_tile<BM, BN, S, true, false, true>(w, bx, smem_raw);
@@ -911,7 +953,7 @@ int launch_out(const GemmArgs& g, int cfg, int splits, hipStream_t stream, int n
 }
 
 template <int BM, int BN, int S, int OCC>
-static int launch_pair_tile(GemmArgs d, GemmArgs w, bool w_first, hipStream_t stream, int n_groups) {
+static int launch_pair_tile(GemmArgs d, GemmArgs w, bool w_first, hipStream_t stream, int n_groups, const BiasGrad* bias, bool* carried) {
   static bool attr_set[DH_MAX_DEVICES] = {};
   constexpr int ld = g_lds_bytes<BM, BN, S, false, true, false>(), lw = g_lds_bytes<BM, BN, S, true, false, true>(), lds = ld > lw ? ld : lw;
   int rc;
@@ -924,19 +966,28 @@ static int launch_pair_tile(GemmArgs d, GemmArgs w, bool w_first, hipStream_t st
     g[i]->tiles_per_xcd = (g[i]->tiles_m * g[i]->tiles_n + 7) / 8;
     blocks[i] = g[i]->tiles_per_xcd * 8;
   }
-  gemm_bf16_pair_kernel<BM, BN, S, OCC><<<dim3(blocks[0] + blocks[1], 1, n_groups), 256, lds, stream>>>(d, w, blocks[w_first ? 1 : 0], w_first ? 1 : 0);
+  // A column sum of one launch rides along where units are free for its blocks: of the backward chain of a small layer it is a launch of 4 us less per linear
+  // (4 heads x 2 x 264 tokens, 520 wide: the step 141 -> 126).  Behind tiles that fill the units it would be a round of its own.
+  GemmColsum cs = {{nullptr, 0, 0, nullptr}, blocks[0] + blocks[1]};
+  int extra = 0;
+  if (bias != nullptr && dh_colsum_direct(bias->rows, bias->n) && cs.first + (bias->n + 31) / 32 <= OCC * d.cus) {
+    cs.of = *bias;
+    extra = (bias->n + 31) / 32;
+    *carried = true;
+  }
+  gemm_bf16_pair_kernel<BM, BN, S, OCC><<<dim3(cs.first + extra, 1, n_groups), 256, lds, stream>>>(d, w, blocks[w_first ? 1 : 0], w_first ? 1 : 0, cs);
   DH_LAUNCH_CHECK();
   return DH_OK;
 }
 // Launches the pair with tile shape `cfg`.  Three sources hold the shapes, so that they compile side by side.
 template <int CFG>
-int launch_pair(const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups) {
-  if constexpr (CFG == 2) return launch_pair_tile<256, 128, 3, 1>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 3) return launch_pair_tile<64, 64, 4, 2>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 4) return launch_pair_tile<128, 128, 4, 1>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 5) return launch_pair_tile<192, 128, 4, 1>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 6) return launch_pair_tile<96, 128, 4, 1>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 7) return launch_pair_tile<96, 128, 2, 2>(d, w, w_first, stream, n_groups);
-  else if constexpr (CFG == 8) return launch_pair_tile<64, 128, 3, 2>(d, w, w_first, stream, n_groups);
-  else return launch_pair_tile<128, 128, 2, 2>(d, w, w_first, stream, n_groups);
+int launch_pair(const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups, const BiasGrad* bias, bool* carried) {
+  if constexpr (CFG == 2) return launch_pair_tile<256, 128, 3, 1>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 3) return launch_pair_tile<64, 64, 4, 2>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 4) return launch_pair_tile<128, 128, 4, 1>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 5) return launch_pair_tile<192, 128, 4, 1>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 6) return launch_pair_tile<96, 128, 4, 1>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 7) return launch_pair_tile<96, 128, 2, 2>(d, w, w_first, stream, n_groups, bias, carried);
+  else if constexpr (CFG == 8) return launch_pair_tile<64, 128, 3, 2>(d, w, w_first, stream, n_groups, bias, carried);
+  else return launch_pair_tile<128, 128, 2, 2>(d, w, w_first, stream, n_groups, bias, carried);
 }

@@ -5,14 +5,14 @@ extern template int launch_out<false, true, false>(const GemmArgs&, int, int, hi
 extern template int launch_out<false, true, true>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
 extern template int launch_out<true, false, false>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
 extern template int launch_out<true, false, true>(const GemmArgs&, int, int, hipStream_t, int, int, int, const GemmAr*);
-extern template int launch_pair<1>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<2>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<3>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<4>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<5>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<6>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<7>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
-extern template int launch_pair<8>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int);
+extern template int launch_pair<1>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<2>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<3>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<4>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<5>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<6>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<7>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
+extern template int launch_pair<8>(const GemmArgs&, const GemmArgs&, bool, hipStream_t, int, const BiasGrad*, bool*);
 
 // Adds the split-K partials in split order; writes bf16 or accumulates into float32.
 __global__ void splitk_reduce_kernel(const float* __restrict__ part, int splits, size_t mn, void* __restrict__ C, int epi,
@@ -434,16 +434,17 @@ int dh_launch_gemm_grouped_bf16(int mode, int n_groups, const int32_t* group_row
 // The two gradient products of a linear layer whose dY is [T, n], weight [k, n] and input [T, k]: dX[T, k] = dY * W^T and
 // dW[k, n] += X^T * dY, as one launch with the bits of the two apart.  gu != nullptr: dX goes through SwiGLU's backward as in
 // dh_launch_gemm_swiglu_bwd_bf16 (dX is then d(gate | up)[T, 2k]).  Products that no one launch holds go out apart, with ws as in dh_launch_gemm_bf16.
-static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups) {
+static int launch_pair_cfg(int cfg, const GemmArgs& d, const GemmArgs& w, bool w_first, hipStream_t stream, int n_groups, const BiasGrad* bias = nullptr,
+                           bool* carried = nullptr) {
   switch (cfg) {
-    case 1: return launch_pair<1>(d, w, w_first, stream, n_groups);
-    case 2: return launch_pair<2>(d, w, w_first, stream, n_groups);
-    case 3: return launch_pair<3>(d, w, w_first, stream, n_groups);
-    case 4: return launch_pair<4>(d, w, w_first, stream, n_groups);
-    case 5: return launch_pair<5>(d, w, w_first, stream, n_groups);
-    case 6: return launch_pair<6>(d, w, w_first, stream, n_groups);
-    case 7: return launch_pair<7>(d, w, w_first, stream, n_groups);
-    case 8: return launch_pair<8>(d, w, w_first, stream, n_groups);
+    case 1: return launch_pair<1>(d, w, w_first, stream, n_groups, bias, carried);
+    case 2: return launch_pair<2>(d, w, w_first, stream, n_groups, bias, carried);
+    case 3: return launch_pair<3>(d, w, w_first, stream, n_groups, bias, carried);
+    case 4: return launch_pair<4>(d, w, w_first, stream, n_groups, bias, carried);
+    case 5: return launch_pair<5>(d, w, w_first, stream, n_groups, bias, carried);
+    case 6: return launch_pair<6>(d, w, w_first, stream, n_groups, bias, carried);
+    case 7: return launch_pair<7>(d, w, w_first, stream, n_groups, bias, carried);
+    case 8: return launch_pair<8>(d, w, w_first, stream, n_groups, bias, carried);
     default: DH_FAIL(DH_ERR_INVALID_ARG, "gemm pair: no kernel with tile shape %d", cfg);
   }
 }
@@ -457,6 +458,10 @@ int dh_gemm_pair_shape(int n_groups, int T, int k, int n, bool beside) {
 bool dh_gemm_pair_pays(int T, int k, int n, bool beside) { return dh_gemm_pair_shape(0, T, k, n, beside) != 0; }
 int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
                              bool beside, void* ws, size_t ws_bytes, hipStream_t stream) {
+  return dh_launch_gemm_pair_bias_bf16(T, k, n, dY, W, X, dX, dW, gu, beside, ws, ws_bytes, stream, nullptr, nullptr);
+}
+int dh_launch_gemm_pair_bias_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t* W, const bf16_t* X, bf16_t* dX, float* dW, const bf16_t* gu,
+                                  bool beside, void* ws, size_t ws_bytes, hipStream_t stream, const BiasGrad* bias, bool* carried) {
   if (T <= 0 || k <= 0 || n <= 0 || k % 8 || n % 8) DH_FAIL(DH_ERR_SHAPE, "gemm pair (bf16): T=%d k=%d n=%d", T, k, n);
   GemmPlan pd, pw;
   bool w_first;
@@ -467,7 +472,8 @@ int dh_launch_gemm_pair_bf16(int T, int k, int n, const bf16_t* dY, const bf16_t
   }
   GemmArgs d = gemm_args(T, k, n, dY, W, dX, EPI_STORE_BF16, pd), w = gemm_args(k, n, T, X, dY, dW, EPI_ACC_F32, pw);
   if (gu != nullptr) { d.glu_mode = GLU_BWD; d.glu_f = k; d.glu_in = gu; }
-  return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1);
+  d.cus = num_cus();
+  return launch_pair_cfg(pd.cfg, d, w, w_first, stream, 1, bias, carried);
 }
 // The same for the experts' linears (group_rows as in dh_launch_gemm_grouped_bf16; T bounds the rows of all groups).
 bool dh_gemm_grouped_pair_pays(int n_groups, int T, int k, int n, bool beside) { return dh_gemm_pair_shape(n_groups, T, k, n, beside) != 0; }

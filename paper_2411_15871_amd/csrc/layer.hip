@@ -805,16 +805,19 @@ static int gpt_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hipSt
 }
 
 // Bias gradients of the GPT layer's linears: part of their weight-gradient operators.
-static int gpt_bias_grad(dh_layer* L, int which, const dh_bwd_args& b, char* ws, hipStream_t s) {
-  const dh_layer_config& c = L->c;
-  const int T = L->T, Ts = L->Ts, H = c.hidden, F = c.ffn, dt = c.dtype;
-  void* cws = ws + L->b_colsum;
+struct BiasOf { const void* dy; int rows, n; float* db; };
+static BiasOf gpt_bias_of(const dh_layer* L, int which, const dh_bwd_args& b, char* ws) {
+  const int T = L->T, Ts = L->Ts, H = L->c.hidden;
   switch (which) {
-    case PAIR_FC2: return dh_colsum(dt, Ts, H, b.dout, L->g.dbfc2, cws, L->b_colsum_bytes, s);
-    case PAIR_FC1: return dh_colsum(dt, T, F, ws + L->b_dgu, L->g.dbfc1, cws, L->b_colsum_bytes, s);
-    case PAIR_PROJ: return dh_colsum(dt, Ts, H, ws + L->b_dx2, L->g.dbo, cws, L->b_colsum_bytes, s);
-    default: return dh_colsum(dt, T, L->n_qkv, ws + L->b_dqkv, L->g.dbqkv, cws, L->b_colsum_bytes, s);
+    case PAIR_FC2: return {b.dout, Ts, H, L->g.dbfc2};
+    case PAIR_FC1: return {ws + L->b_dgu, T, L->c.ffn, L->g.dbfc1};
+    case PAIR_PROJ: return {ws + L->b_dx2, Ts, H, L->g.dbo};
+    default: return {ws + L->b_dqkv, T, L->n_qkv, L->g.dbqkv};
   }
+}
+static int gpt_bias_grad(dh_layer* L, int which, const dh_bwd_args& b, char* ws, hipStream_t s) {
+  const BiasOf o = gpt_bias_of(L, which, b, ws);
+  return dh_colsum(L->c.dtype, o.rows, o.n, o.dy, o.db, ws + L->b_colsum, L->b_colsum_bytes, s);
 }
 static int gpt_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hipStream_t s) {
   const dh_layer_config& c = L->c;
@@ -1021,10 +1024,16 @@ static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, 
   const bool gpt = c.arch == DH_ARCH_GPT, moe = c.arch == DH_ARCH_MOE, f32 = c.dtype == DH_F32;
   const char* sv = (const char*)b.saved;
   auto dense = [&](int k, int n, const void* dY, const void* W, const void* X, size_t dX, float* dW, const void* gu = nullptr) {
+    bool carried = !gpt;
+    BiasGrad bias;
+    if (gpt) {
+      const BiasOf o = gpt_bias_of(L, which, b, ws);
+      bias = {(const bf16_t*)o.dy, o.rows, o.n, o.db};
+    }
     const int rc = f32 ? dh_launch_gemm_f32_pair(1, nullptr, T, k, n, (const float*)dY, (const float*)W, (const float*)X, (float*)(ws + dX), dW, s)
-                       : dh_launch_gemm_pair_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside,
-                                                 ws + L->b_gemm, L->b_gemm_bytes, s);
-    return rc || !gpt ? rc : gpt_bias_grad(L, which, b, ws, s);
+                       : dh_launch_gemm_pair_bias_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside,
+                                                      ws + L->b_gemm, L->b_gemm_bytes, s, gpt ? &bias : nullptr, &carried);
+    return rc || carried ? rc : gpt_bias_grad(L, which, b, ws, s);
   };
   auto experts = [&](int k, int n, size_t dY, const void* W, size_t X, size_t dX, float* dW) {
     if (f32)

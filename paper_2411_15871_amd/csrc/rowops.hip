@@ -747,11 +747,11 @@ __global__ void bias_residual_add_kernel(const T* __restrict__ a, const RowSrc<T
   x.store(out + idx * 8);
 }
 
-// dst[col] += sum over the rows of x, in one launch: a block owns 32 columns (4 lanes of 8), its 256 row lanes each add every 256th row,
+// dst[col] += sum over the rows of x, in one launch (or as blocks of a pair of products, g_colsum): a block owns 32 columns (4 lanes of 8), its 256 row lanes each add every 256th row,
 // 8 in flight, then the lanes of a wave and the waves are added, in an order fixed by the shapes alone.
 // For inputs whose two launches below (partial rows, then their sum) are mostly launches: 264 rows of 2048 columns 5.0 -> 3.9 us, 1024 of 2048 5.4 -> 4.1,
 // 2048 of 768 6.4 -> 4.2; 2048 of 4096 as long, 2048 of 8192 10.9 -> 12.7, 4096 of 768 6.5 -> 9.2: few blocks, each with 64 bytes of a row.
-static bool colsum_direct(int T, int N) { return T <= 2048 && (long long)T * N <= 8 << 20; }
+bool dh_colsum_direct(int T, int N) { return T <= 2048 && (long long)T * N <= 8 << 20; }
 template <typename T>
 __global__ __launch_bounds__(1024) void colsum_direct_kernel(const T* __restrict__ x, int rows, int N, float* __restrict__ dst) {
   __shared__ float part[16][32];
@@ -1009,7 +1009,7 @@ extern "C" int dh_colsum(int dtype, int T, int N, const void* x, float* out, voi
   if (!x || !out) DH_FAIL(DH_ERR_INVALID_ARG, "colsum: null pointer");
   if (!ws || ws_bytes < dh_colsum_ws_bytes(T, N)) DH_FAIL(DH_ERR_WORKSPACE_TOO_SMALL, "colsum: workspace %zu < %zu bytes", ws_bytes, dh_colsum_ws_bytes(T, N));
   hipStream_t s = (hipStream_t)stream;
-  if (colsum_direct(T, N)) {
+  if (dh_colsum_direct(T, N)) {
     if (dtype == DH_BF16) colsum_direct_kernel<bf16_t><<<(N + 31) / 32, 1024, 0, s>>>((const bf16_t*)x, T, N, out);
     else colsum_direct_kernel<float><<<(N + 31) / 32, 1024, 0, s>>>((const float*)x, T, N, out);
     DH_LAUNCH_CHECK();
