@@ -221,33 +221,40 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_fwd_f32_kernel(int 
   if (wave == 0 && g == 0 && iq < seq) lse[(size_t)h * T + tok] = M + logf(L);
 }
 
-// dQ; also stores delta[h, t] = sum_c dout[t,h,c] * o[t,h,c] for the dK/dV kernel that follows.  grid as the forward kernel.
+struct A32Bwd {
+  int seq, nq, nkv, d, ldkv, q_off, lddkv, T;
+  const float *qkv, *kv, *o, *dout, *lse;
+  float *delta, *dqkv, *dkv;
+};
+// sum_c dout[c] * o[c] of the row the lane's fragments hold a part of
 template <int DT>
-__global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(int seq, int nq, int nkv, int d, const float* __restrict__ qkv,
-                                                                         const float* __restrict__ kv, int ldkv, int q_off,
-                                                                         const float* __restrict__ o, const float* __restrict__ dout,
-                                                                         const float* __restrict__ lse, float* __restrict__ delta,
-                                                                         float* __restrict__ dqkv, int T) {
+__device__ __forceinline__ float row_delta(const RowFrag<DT>& dof, const float* o, bool valid, int g, int d) {
+  RowFrag<DT> of;
+  of.load(o, valid, g, d);
+  float dl = 0.f;
+#pragma unroll
+  for (int c = 0; c < DT; c++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) dl = fmaf(dof.v[c][e], of.v[c][e], dl);
+  return group_sum(dl);
+}
+
+// dQ of query tile `tile_q` of head h, sequence b; also stores delta[h, t] = sum_c dout[t,h,c] * o[t,h,c].
+template <int DT>
+__device__ __forceinline__ void attn_bwd_dq_f32(const A32Bwd& a, int tile_q, int h, int b, float* os) {
   constexpr int A32_WAVES = a32_waves<DT>();
-  extern __shared__ float os[];
+  const int seq = a.seq, nq = a.nq, nkv = a.nkv, d = a.d, ldkv = a.ldkv, q_off = a.q_off, T = a.T;
+  const float *__restrict__ qkv = a.qkv, *__restrict__ kv = a.kv, *__restrict__ o = a.o, *__restrict__ dout = a.dout, *__restrict__ lse = a.lse;
+  float *__restrict__ delta = a.delta, *__restrict__ dqkv = a.dqkv;
   constexpr int LD = DT * 16 + 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
-  const int h = blockIdx.y, b = blockIdx.z, hk = h / (nq / nkv), i0 = (gridDim.x - 1 - blockIdx.x) * 16, iq = i0 + l16;
+  const int hk = h / (nq / nkv), i0 = tile_q * 16, iq = i0 + l16;
   const int ld = (nq + 2 * nkv) * d;
   const float scale = 1.0f / sqrtf((float)d);
   const size_t tok = (size_t)b * seq + min(iq, seq - 1);
   RowFrag<DT> q, dof;
   dof.load(dout + tok * nq * d + (size_t)h * d, iq < seq, g, d);
-  float dl = 0.f;
-  {
-    RowFrag<DT> of;
-    of.load(o + tok * nq * d + (size_t)h * d, iq < seq, g, d);
-#pragma unroll
-    for (int c = 0; c < DT; c++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) dl = fmaf(dof.v[c][e], of.v[c][e], dl);
-    dl = group_sum(dl);
-  }
+  const float dl = row_delta<DT>(dof, o + tok * nq * d + (size_t)h * d, iq < seq, g, d);
   if (wave == 0 && g == 0 && iq < seq) delta[(size_t)h * T + tok] = dl;
   q.load(qkv + tok * ld + (size_t)h * d, iq < seq, g, d);
 #pragma unroll
@@ -301,18 +308,17 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(i
   }
 }
 
-// dK, dV.  grid (16-key tiles per sequence, nkv, sequences); a tile's work is every (query head of the group, query tile) pair.
-template <int DT>
-__global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(int seq, int nq, int nkv, int d, const float* __restrict__ qkv,
-                                                                          const float* __restrict__ kv, int ldkv, int q_off,
-                                                                          const float* __restrict__ dout, const float* __restrict__ lse,
-                                                                          const float* __restrict__ delta, float* __restrict__ dkv,
-                                                                          int lddkv, int T) {
+// dK, dV of key tile `tile_k` of key/value head hk, sequence b: every (query head of the group, query tile) pair.  OWN_DELTA: delta is formed here as the dQ tiles do,
+// which may not have stored it yet.
+template <int DT, bool OWN_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv_f32(const A32Bwd& a, int tile_k, int hk, int b, float* os) {  // os: [16 keys][dK | dV], row pitch 2*DT*16 + 4
   constexpr int A32_WAVES = a32_waves<DT>();
-  extern __shared__ float os[];  // [16 keys][dK | dV], row pitch 2*DT*16 + 4
+  const int seq = a.seq, nq = a.nq, nkv = a.nkv, d = a.d, ldkv = a.ldkv, q_off = a.q_off, T = a.T, lddkv = a.lddkv;
+  const float *__restrict__ qkv = a.qkv, *__restrict__ kv = a.kv, *__restrict__ dout = a.dout, *__restrict__ lse = a.lse, *__restrict__ delta = a.delta;
+  float* __restrict__ dkv = a.dkv;
   constexpr int LD = 2 * DT * 16 + 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
-  const int hk = blockIdx.y, b = blockIdx.z, grp = nq / nkv, S = q_off + seq, j0 = blockIdx.x * 16, jk = j0 + l16;
+  const int grp = nq / nkv, S = q_off + seq, j0 = tile_k * 16, jk = j0 + l16;
   const int ld = (nq + 2 * nkv) * d;
   const float scale = 1.0f / sqrtf((float)d);
   const float* krow = kv + ((size_t)b * S + min(jk, S - 1)) * ldkv + (size_t)hk * d;
@@ -337,6 +343,8 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
     ColFrag<DT> qc, oc;
     oc.start(ob, (size_t)nq * d, i0, seq - 1, l16, g, d);
     qc.start(qb, ld, i0, seq - 1, l16, g, d);
+    float own = 0.f;
+    if constexpr (OWN_DELTA) own = row_delta<DT>(dof, a.o + row * nq * d + (size_t)h * d, true, g, d);
     const f32x4 s = dot_tile<DT>(q, k);  // rows = queries, column = key
     const f32x4 dp = dot_tile<DT>(dof, v);
     f32x4 p, ds;
@@ -347,7 +355,8 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
       const size_t st = (size_t)h * T + tok0 + min(i, seq - 1);
       const bool counts = !partial || (i < seq && q_off + i >= jk);
       p[e] = counts ? expf(s[e] - lse[st]) : 0.f;
-      ds[e] = counts ? p[e] * (dp[e] - delta[st]) : 0.f;
+      const float dl = OWN_DELTA ? __shfl(own, 4 * g + e, 64) : delta[st];  // lane l16 holds row i0 + l16's
+      ds[e] = counts ? p[e] * (dp[e] - dl) : 0.f;
       seen |= counts ? 1 << e : 0;
     }
     oc.accumulate_seen(dv, p, partial, seen);
@@ -378,6 +387,26 @@ __global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(
   }
 }
 
+// The two as launches of their own, grids (16-query tiles, longest rows first, nq, sequences) and (16-key tiles, nkv, sequences) ...
+template <int DT>
+__global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dq_f32_kernel(const A32Bwd a) {
+  extern __shared__ float os[];
+  attn_bwd_dq_f32<DT>(a, gridDim.x - 1 - blockIdx.x, blockIdx.y, blockIdx.z, os);
+}
+template <int DT>
+__global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_dkv_f32_kernel(const A32Bwd a) {
+  extern __shared__ float os[];
+  attn_bwd_dkv_f32<DT, false>(a, blockIdx.x, blockIdx.y, blockIdx.z, os);
+}
+// ... and as one, grid (key tiles * nkv + query tiles * nq, 1, sequences).
+template <int DT>
+__global__ __launch_bounds__(64 * a32_waves<DT>()) void attn_bwd_f32_kernel(const A32Bwd a, int tiles_k, int tiles_q) {
+  extern __shared__ float os[];
+  const int x = blockIdx.x, n_k = tiles_k * a.nkv;
+  if (x < n_k) attn_bwd_dkv_f32<DT, true>(a, x % tiles_k, x / tiles_k, blockIdx.z, os);
+  else attn_bwd_dq_f32<DT>(a, tiles_q - 1 - (x - n_k) % tiles_q, (x - n_k) / tiles_q, blockIdx.z, os);
+}
+
 static int check_f32(int d) {
   if (d > 256 || d % 4) DH_FAIL(DH_ERR_SHAPE, "attention (fp32): head_dim %d must be a multiple of 4, at most 256", d);
   return DH_OK;
@@ -385,6 +414,7 @@ static int check_f32(int d) {
 
 // Sequences of one launch: the third dimension of a grid holds 65535 blocks.
 #define A32_MAX_BATCH 65535
+#define A32_ONE_LAUNCH 2048  // blocks of a backward pass in one launch (see bwd_f32)
 
 template <int DT>
 static int fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv, int q_off, float* o, float* lse,
@@ -419,11 +449,23 @@ static int bwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv,
   for (int b0 = 0; b0 < batch; b0 += A32_MAX_BATCH) {
     const size_t t0 = (size_t)b0 * seq, k0 = (size_t)b0 * (q_off + seq);
     const int nb = std::min(batch - b0, A32_MAX_BATCH);
-    attn_bwd_dq_f32_kernel<DT><<<dim3((seq + 15) / 16, nq, nb), 64 * a32_waves<DT>(), 16 * (DT * 16 + 4) * sizeof(float), stream>>>(
-        seq, nq, nkv, d, qkv + t0 * ld, kv + k0 * ldkv, ldkv, q_off, o + t0 * nq * d, dout + t0 * nq * d, lse + t0, delta + t0, dqkv + t0 * ld, T);
+    const A32Bwd a = {seq, nq, nkv, d, ldkv, q_off, lddkv, T, qkv + t0 * ld, kv + k0 * ldkv, o + t0 * nq * d, dout + t0 * nq * d, lse + t0,
+                      delta + t0, dqkv + t0 * ld, dkv + k0 * lddkv};
+    const int tiles_q = (seq + 15) / 16, tiles_k = (q_off + seq + 15) / 16;
+    const size_t lds_q = 16 * (DT * 16 + 4) * sizeof(float), lds_k = 16 * (2 * DT * 16 + 4) * sizeof(float);
+    // A few rounds of blocks are chains of latencies, and one launch makes the two kinds' chains run side by side (us, two launches and one: 4 heads x 128 of 64
+    // 19.2 and 10.2, 8:1 x 128 of 128 99.7 and 87, 8 x 1000 of 64 132 and 110, 16 x 1024 of 64, 2048 blocks, 244 and 226; the same bits).  Further rounds fill the units by
+    // themselves, and the sums for delta that every key tile makes again are work there.
+    if constexpr (DT <= 8) {
+      if (((long long)tiles_q * nq + (long long)tiles_k * nkv) * nb <= A32_ONE_LAUNCH) {
+        attn_bwd_f32_kernel<DT><<<dim3(tiles_q * nq + tiles_k * nkv, 1, nb), 64 * a32_waves<DT>(), lds_k, stream>>>(a, tiles_k, tiles_q);
+        DH_LAUNCH_CHECK();
+        continue;
+      }
+    }
+    attn_bwd_dq_f32_kernel<DT><<<dim3(tiles_q, nq, nb), 64 * a32_waves<DT>(), lds_q, stream>>>(a);
     DH_LAUNCH_CHECK();
-    attn_bwd_dkv_f32_kernel<DT><<<dim3((q_off + seq + 15) / 16, nkv, nb), 64 * a32_waves<DT>(), 16 * (2 * DT * 16 + 4) * sizeof(float), stream>>>(
-        seq, nq, nkv, d, qkv + t0 * ld, kv + k0 * ldkv, ldkv, q_off, dout + t0 * nq * d, lse + t0, delta + t0, dkv + k0 * lddkv, lddkv, T);
+    attn_bwd_dkv_f32_kernel<DT><<<dim3(tiles_k, nkv, nb), 64 * a32_waves<DT>(), lds_k, stream>>>(a);
     DH_LAUNCH_CHECK();
   }
   return DH_OK;
