@@ -250,7 +250,9 @@ int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, in
                                      bf16_t* dX, float* dW, bool beside, hipStream_t stream);
 bool dh_gemm_f32_pair_pays(int n_groups, int T, int k, int n);
 int dh_launch_gemm_f32_pair(int n_groups, const int32_t* group_rows, int T, int k, int n, const float* dY, const float* W, const float* X, float* dX,
-                            float* dW, hipStream_t stream);
+                            float* dW, hipStream_t stream, const float* gu = nullptr);
+int dh_launch_gemm_f32_swiglu_fwd(int T, int F, int H, const float* x, const float* Wgu, float* gu, float* a, hipStream_t stream);
+int dh_launch_gemm_f32_swiglu_bwd(int T, int F, int H, const float* dy, const float* Wd, const float* gu, float* dgu, hipStream_t stream);
 // Attention launchers: seq = queries per sequence; kv == nullptr selects plain causal attention over the packed
 // qkv rows, otherwise keys/values come from kv[batch*(q_off+seq), ldkv] and their gradients go to dkv likewise.
 int dh_launch_attn_fwd_f32(int batch, int seq, int nq, int nkv, int d, const float* qkv, const float* kv, int ldkv,

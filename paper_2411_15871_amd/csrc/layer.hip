@@ -271,6 +271,14 @@ static void choose_pairs(dh_layer* L) {
   }
 }
 
+// Which activations the neighbouring products take along (mask: 1 forward, 2 backward): in float32 always, a launch less on a chain of short ones.
+static void set_fused_activation(dh_layer* L, int mask) {
+  const dh_layer_config& c = L->c;
+  const bool glu_layer = c.arch == DH_ARCH_LLAMA || c.arch == DH_ARCH_LLAMA_CP, f32 = c.dtype == DH_F32;
+  L->fuse_act_fwd = (mask & 1) && glu_layer && (f32 || dh_glu_fwd_fits(L->T, c.ffn, c.hidden));
+  L->fuse_act_bwd = (mask & 2) && glu_layer && (f32 || dh_glu_bwd_fits(L->T, c.ffn, c.hidden));
+}
+
 extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   if (!cfg || !out) DH_FAIL(DH_ERR_INVALID_ARG, "layer_create: null pointer");
   const dh_layer_config& c = *cfg;
@@ -315,10 +323,8 @@ extern "C" int dh_layer_create(const dh_layer_config* cfg, dh_layer** out) {
   L->T = c.batch * c.seq;
   L->Ts = c.arch == DH_ARCH_GPT ? L->T / c.n_ranks : L->T;
   L->Tf = c.arch == DH_ARCH_MOE ? 2 * L->T : L->T;
-  const bool glu_layer = c.dtype == DH_BF16 && (c.arch == DH_ARCH_LLAMA || c.arch == DH_ARCH_LLAMA_CP);
   L->fuse_comm = 0;
-  L->fuse_act_fwd = glu_layer && dh_glu_fwd_fits(L->T, c.ffn, c.hidden);
-  L->fuse_act_bwd = glu_layer && dh_glu_bwd_fits(L->T, c.ffn, c.hidden);
+  set_fused_activation(L, 3);
   L->n_qkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   L->n_o = c.n_q_heads * c.head_dim;
   choose_pairs(L);
@@ -468,11 +474,8 @@ extern "C" int dh_layer_set_fused_collective(dh_layer* L, int mask) {
 
 extern "C" int dh_layer_set_fused_activation(dh_layer* L, int enable) {
   if (!L) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_fused_activation: null layer");
-  const dh_layer_config& c = L->c;
-  const bool glu_layer = c.dtype == DH_BF16 && (c.arch == DH_ARCH_LLAMA || c.arch == DH_ARCH_LLAMA_CP);
   if (enable < 0 || enable > 3) DH_FAIL(DH_ERR_INVALID_ARG, "layer_set_fused_activation: mask %d outside 0..3", enable);
-  L->fuse_act_fwd = (enable & 1) && glu_layer && dh_glu_fwd_fits(L->T, c.ffn, c.hidden);
-  L->fuse_act_bwd = (enable & 2) && glu_layer && dh_glu_bwd_fits(L->T, c.ffn, c.hidden);
+  set_fused_activation(L, enable);
   return (L->fuse_act_fwd ? 1 : 0) | (L->fuse_act_bwd ? 2 : 0);
 }
 
@@ -595,6 +598,8 @@ static int llama_fwd_op(dh_layer* L, int op, const dh_fwd_args& a, char* ws, hip
       if (reduction_with_consumer(L)) return DH_OK;  // done by F_AR1's launch
       return dh_rmsnorm_fwd(dt, T, H, a.x, ws + L->f_red, L->w.g2, c.eps, sv + L->s_x2, sv + L->s_h2, (float*)(sv + L->s_rstd2), s);
     case DH_F_FC1:
+      if (L->fuse_act_fwd && dt == DH_F32)
+        return dh_launch_gemm_f32_swiglu_fwd(T, F, H, (const float*)(sv + L->s_h2), (const float*)L->w.Wgu, (float*)(sv + L->s_gu), (float*)(sv + L->s_a), s);
       if (L->fuse_act_fwd)
         return dh_launch_gemm_swiglu_fwd_bf16(T, F, H, (const bf16_t*)(sv + L->s_h2), (const bf16_t*)L->w.Wgu, (bf16_t*)(sv + L->s_gu),
                                               (bf16_t*)(sv + L->s_a), s);
@@ -625,6 +630,8 @@ static int llama_bwd_op(dh_layer* L, int op, const dh_bwd_args& b, char* ws, hip
   const size_t gwb = side_ws ? L->f_gemm_bytes : L->b_gemm_bytes, n = (size_t)T * H;
   switch (op) {
     case DH_B_FC2_DGRAD:
+      if (L->fuse_act_bwd && dt == DH_F32)
+        return dh_launch_gemm_f32_swiglu_bwd(T, F, H, (const float*)b.dout, (const float*)L->w.Wd, (const float*)(sv + L->s_gu), (float*)(ws + L->b_dgu), s);
       if (L->fuse_act_bwd)
         return dh_launch_gemm_swiglu_bwd_bf16(T, F, H, (const bf16_t*)b.dout, (const bf16_t*)L->w.Wd, (const bf16_t*)(sv + L->s_gu),
                                               (bf16_t*)(ws + L->b_dgu), s);
@@ -1030,7 +1037,8 @@ static int run_bwd_pair(dh_layer* L, int which, const dh_bwd_args& b, char* ws, 
       const BiasOf o = gpt_bias_of(L, which, b, ws);
       bias = {(const bf16_t*)o.dy, o.rows, o.n, o.db};
     }
-    const int rc = f32 ? dh_launch_gemm_f32_pair(1, nullptr, T, k, n, (const float*)dY, (const float*)W, (const float*)X, (float*)(ws + dX), dW, s)
+    const int rc = f32 ? dh_launch_gemm_f32_pair(1, nullptr, T, k, n, (const float*)dY, (const float*)W, (const float*)X, (float*)(ws + dX), dW, s,
+                                                 (const float*)gu)
                        : dh_launch_gemm_pair_bias_bf16(T, k, n, (const bf16_t*)dY, (const bf16_t*)W, (const bf16_t*)X, (bf16_t*)(ws + dX), dW, (const bf16_t*)gu, beside,
                                                       ws + L->b_gemm, L->b_gemm_bytes, s, gpt ? &bias : nullptr, &carried);
     return rc || carried ? rc : gpt_bias_grad(L, which, b, ws, s);
