@@ -875,11 +875,11 @@ __device__ __forceinline__ void g_colsum(const BiasGrad& c, int blk, float* smem
 template <int BM, int BN, int S, int OCC>
 __global__ __launch_bounds__(256, OCC) void gemm_bf16_pair_kernel(GemmArgs d, GemmArgs w, int n_first, int w_first, const GemmColsum cs) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
-  if ((int)blockIdx.x >= cs.first) {
+  const bool second = (int)blockIdx.x >= n_first;
+  if (__builtin_expect(second && (int)blockIdx.x >= cs.first, 0)) {
     g_colsum(cs.of, (int)blockIdx.x - cs.first, reinterpret_cast<float*>(smem_raw));
     return;
   }
-  const bool second = (int)blockIdx.x >= n_first;
   const int bx = second ? (int)blockIdx.x - n_first : (int)blockIdx.x;
   if (second != (w_first != 0)) g_tile<BM, BN, S, true, false, true>(w, bx, smem_raw);
   else g_tile<BM, BN, S, false, true, false>(d, bx, smem_raw);
