@@ -1229,13 +1229,14 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   };
   if constexpr (D == 128) {
     // One wave has a SIMD to itself: beside its matrix instructions runs only what stands between them.  A 32x32x16 one keeps the matrix cores 32 cycles, a
-    // tile's 64 of them 2048; a tile's other instructions (32 exponentials, 100 more of the vector ALU, 112 LDS reads, 9 transfers, 70 scalar ones) fill about
+    // tile's 64 of them 2048; a tile's other instructions (32 exponentials, 130 more of the vector ALU, 112 LDS reads, 9 transfers, 70 scalar ones) fill about
     // as many issue cycles and fit in their shadows if every slot gets its share.  Left to the compiler, half of dP's products ended up
     // behind all exponentials, and a tile took 4500 cycles.  So the matrix instructions are volatile, each is followed by its share, and all of it is pinned; fragments are
     // requested six products ahead (transposed ones eight); the next tile is published beside this one's dK products and its first fragments are read
-    // there, so that no tile begins with a wait.  Measured alone (us, before and after): 32:8 heads x 4096 tokens 315 -> 283, 8:1 x 8192 306 -> 260, 4:1
-    // x 4096 queries over 12288 keys 207 -> 178, 4:1 x 4096 53 -> 45, in the shared launch 2 x 2048 x 8 heads 85 -> 75.  In cycles it is 20 % (667 -> 532
-    // thousand, matrix cores busy 40 -> 50 %): the clock falls from 2.1 to 1.9 GHz, the power limit takes the rest.
+    // there, so that no tile begins with a wait.  The same bits as in phases.  The whole backward pass (us, before and after): 32:8 heads x 4096 tokens 492 -> 465, 8:1 x
+    // 8192 497 -> 473, 4:1 x 4096 queries over 12288 keys 330 -> 305, 2 x 2048 x 8 heads 81.4 -> 72.5, 4:1 x 4096 92 -> 88; sequences of one tile pay for the longer
+    // start (four of 64 tokens 9.8 -> 10.3).  (Accumulators that start from the rows' delta save the 32 subtractions, 0.6 % of these, and
+    // round at delta's scale on the way: a score gradient that cancels loses the small terms.)
     static_assert(AB_KT == 64 && AB_RING == 3, "slots below");
     constexpr int KS = D / 16, OFF1 = AB_RING * TL::BYTES;
     const lds_char* dir[KS];
@@ -1249,8 +1250,9 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     bf16x8 fr[4][2];         // score fragments of four k-steps
     bf16x8 tr[3][D / 32];    // transposed fragments of three groups of 16 rows: dO's groups are 0-3, Q's 4-7
     bf16x8 pf[2];            // packed P (groups 0-3), then dS (4-7)
-    f32x4 lv[8];             // log sums of rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
+    f32x4 lv[8], dl[8];      // log sums and delta of rows 32*mt + 8*q4 + 4*kg + e of the tile at [4*mt + q4]
     f32x16 st[2], dp[2];
+    auto row_stat = [&](int ring, int x) { return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stp + ring + x * 32); };
     auto frag = [&](int step, int mt) {  // k-step `step` of the tile's S products, from KS on of its dP products
       fr[step & 3][mt] = lds_frag(dir[step & (KS - 1)], (step < KS ? 0 : OFF1) + mt * 32 * TL::LD * 2);
     };
@@ -1266,14 +1268,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
     };
     issue(0);
     if (f0 + 1 < f1) issue(1);
-    // dP comes out as delta - dP: the accumulators start from the rows' delta and V enters negated (dS and dK negated likewise, until dK is stored): a subtraction
-    // an element less.  Against float64 dK is as far off as with the subtraction behind the sum (2.405 and 2.406e-3 to 1.766 and 1.766e-3).
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-      vf[ks] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[ks]) ^ 0x80008000u);
-      asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
-    }
+    for (int ks = 0; ks < KS; ks++) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
     const uint32_t ldsQw = ldsQ + wave * (TL::IPW * 1024), tile_bytes = TL::BYTES;
     const int ragged_ti = (seq - q0) % AB_KT != 0 ? nt - 1 : nt;  // the tile of each head that is not whole
     int slot = 0;
@@ -1327,13 +1323,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
           if (i < 2) mfma_first(st[i & 1], fr[(i >> 1) & 3][i & 1], kf[i >> 1]);
           else mfma_next(st[i & 1], fr[(i >> 1) & 3][i & 1], kf[i >> 1]);
           frag((i >> 1) + 3, i & 1);
-          if (i < 8) {
-            const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stp + AB_RING * AB_KT * sizeof(float) + i * 32);
-#pragma unroll
-            for (int e = 0; e < 4; e++) dp[i >> 2][4 * (i & 3) + e] = v[e];
-          } else {
-            lv[i - 8] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(stp + (i - 8) * 32);
-          }
+          if (i < 8) dl[i] = row_stat(AB_RING * AB_KT * sizeof(float), i);
+          else lv[i - 8] = row_stat(0, i - 8);
           if (TRANSFERS) {
             if (i == 2) m = dma_lds(ldsQw + free_slot * tile_bytes);
             if (i == 6) m = dma_lds(ldsQw + free_slot * tile_bytes + AB_RING * tile_bytes);
@@ -1358,7 +1349,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
 #pragma unroll
       for (int i = 0; i < 16; i++) {
         const int ks = i >> 1, mt = i & 1;
-        mfma_next(dp[mt], fr[(ks + KS) & 3][mt], vf[ks]);
+        if (ks == 0) mfma_first(dp[mt], fr[KS & 3][mt], vf[0]);
+        else mfma_next(dp[mt], fr[(ks + KS) & 3][mt], vf[ks]);
         if (ks + 3 < KS) frag(ks + KS + 3, mt);
         if (i >= 8) trfrag((i - 8) >> 2, i & 3);
         if (i >= 2) {  // P from S, 32 values over 14 slots
@@ -1380,7 +1372,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       }
 #pragma unroll
       for (int e = 0; e < 4; e++) pack2(0, e);
-      // dV^T += dO^T P; a group of P, once packed, becomes -dS = P (delta - dP) in place
+      // dV^T += dO^T P; a group of P, once packed, becomes dS = P (dP - delta) in place
       asm volatile("s_nop 1" ::: "memory");
 #pragma unroll
       for (int i = 0; i < 16; i++) {
@@ -1388,12 +1380,12 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
         mfma_grad(dvt[dt], tr[g % 3][dt], pf[g & 1]);
         trfrag(g + 2, dt);
 #pragma unroll
-        for (int x = 8 * g + 2 * dt; x < 8 * g + 2 * dt + 2; x++) st[x >> 4][x & 15] *= dp[x >> 4][x & 15];
+        for (int x = 8 * g + 2 * dt; x < 8 * g + 2 * dt + 2; x++) st[x >> 4][x & 15] *= dp[x >> 4][x & 15] - dl[x >> 2][x & 3];
         pack_share(g + 1, dt);
         if (i == 8) shift_dir();
         AB_PIN();
       }
-      // -dK^T += Q^T (-dS)
+      // dK^T += Q^T dS
 #pragma unroll
       for (int i = 0; i < 16; i++) {
         const int g = 4 + (i >> 2), dt = i & 3;
@@ -1467,9 +1459,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
   acc_settle<AGPR>(dkt);
   acc_settle<AGPR>(dvt);
   __syncthreads();  // every wave is done with the Q/dO rings: their LDS serves the output turn (dK, then dV)
-  const float kscale = D == 128 ? -scale : scale;
   auto dk_quad = [&](int dt, int q4) {
-    return f32x4{dkt[dt][4 * q4] * kscale, dkt[dt][4 * q4 + 1] * kscale, dkt[dt][4 * q4 + 2] * kscale, dkt[dt][4 * q4 + 3] * kscale};
+    return f32x4{dkt[dt][4 * q4] * scale, dkt[dt][4 * q4 + 1] * scale, dkt[dt][4 * q4 + 2] * scale, dkt[dt][4 * q4 + 3] * scale};
   };
   auto dv_quad = [&](int dt, int q4) { return f32x4{dvt[dt][4 * q4], dvt[dt][4 * q4 + 1], dvt[dt][4 * q4 + 2], dvt[dt][4 * q4 + 3]}; };
   if (cm.chunks > 1) {

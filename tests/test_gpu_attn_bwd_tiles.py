@@ -1,4 +1,4 @@
-"""bf16 attention backward, D = 128: the dK/dV loop publishes a tile ahead and starts dP from the rows' delta.  Units of one to five tiles (the ring has
+"""bf16 attention backward, D = 128: the dK/dV loop publishes a tile ahead.  Units of one to five tiles (the ring has
 three slots), whole and ragged last tiles, waves that see nothing of a head's first tile, heads that follow one another inside a unit."""
 import pytest
 import torch
