@@ -195,8 +195,8 @@ __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[2]) {
 __device__ __forceinline__ void mfma_acc_settle(f32x16 (&a)[4]) {
   asm volatile("s_nop 15\n\ts_nop 15" : "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3]));
 }
-// The same three for a loop whose every instruction has its place (attn_bwd_dkv_pinned): volatile, so that they stay in the order written, and without wait
-// states of their own.  A fragment the vector ALU has written is ready a matrix instruction later, a result two of them later.
+// The same three for loops whose every instruction has its place (attn_fwd_pinned, attn_bwd_dkv_block at D = 128): volatile, so that they stay in the order
+// written, and without wait states of their own.  A fragment the vector ALU has written is ready a matrix instruction later, a result two of them later.
 __device__ __forceinline__ void mfma_first(f32x16& acc, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
 }
@@ -206,6 +206,9 @@ __device__ __forceinline__ void mfma_next(f32x16& acc, bf16x8 a, bf16x8 b) {
 __device__ __forceinline__ void mfma_grad(f32x16& acc, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+// Wait states between the vector ALU's packing of a fragment and mfma_grad, which has none of its own and hides the hazard from the compiler.  The
+// fragment is an operand, so that the packing cannot be scheduled behind them.
+__device__ __forceinline__ void frag_settle(bf16x8& f) { asm volatile("s_nop 3" : "+v"(f)); }
 // The AGPR placement (AGPR = true) pays where one wave has a SIMD's register file to itself and ordinary registers are short
 // (D = 128, one block per compute unit).  With D = 64 everything fits the ordinary registers, and where two waves share the
 // file (the dQ kernel at D = 128) they are one budget of 256: there the compiler would only shuttle an AGPR-constrained value
@@ -703,7 +706,7 @@ __device__ __forceinline__ void attn_fwd_pinned(char* smem, const char* kbase, c
       for (int x = i * 24 / 16; x < (i + 1) * 24 / 16; x++) prob(s, x);
       if (i >= 6 && i < 10) pack(s, i - 6);
       if (i >= 11 && i < 15) pack(s, i - 7);
-      if (i == 15) asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));
+      if (i == 15) asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));  // packed by now: the first products, behind this matrix instruction, read them
       AB_PIN();
     }
     mask(next, t + 1);
@@ -762,7 +765,8 @@ __device__ __forceinline__ void attn_fwd_pinned(char* smem, const char* kbase, c
 #pragma unroll
   for (int x = 0; x < 8; x++) pack(sa, x);
   AB_PIN();
-  asm volatile("s_nop 3" ::: "memory");
+  frag_settle(pf[1]);
+  frag_settle(pf[0]);
   products(sa, [](int) {});
   l += across_halves(rs, sum);
   mfma_acc_settle(ot);
@@ -1372,8 +1376,8 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const int bid, const AttnGeom
       }
 #pragma unroll
       for (int e = 0; e < 4; e++) pack2(0, e);
+      frag_settle(pf[0]);
       // dV^T += dO^T P; a group of P, once packed, becomes dS = P (dP - delta) in place
-      asm volatile("s_nop 1" ::: "memory");
 #pragma unroll
       for (int i = 0; i < 16; i++) {
         const int g = i >> 2, dt = i & 3;
