@@ -251,6 +251,7 @@ int dh_launch_gemm_grouped_pair_bf16(int n_groups, const int32_t* group_rows, in
 bool dh_gemm_f32_pair_pays(int n_groups, int T, int k, int n);
 int dh_launch_gemm_f32_pair(int n_groups, const int32_t* group_rows, int T, int k, int n, const float* dY, const float* W, const float* X, float* dX,
                             float* dW, hipStream_t stream, const float* gu = nullptr);
+bool dh_glu_f32_fwd_fits(int T, int F, int H);
 int dh_launch_gemm_f32_swiglu_fwd(int T, int F, int H, const float* x, const float* Wgu, float* gu, float* a, hipStream_t stream);
 int dh_launch_gemm_f32_swiglu_bwd(int T, int F, int H, const float* dy, const float* Wd, const float* gu, float* dgu, hipStream_t stream);
 // Attention launchers: seq = queries per sequence; kv == nullptr selects plain causal attention over the packed

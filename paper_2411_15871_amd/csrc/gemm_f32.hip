@@ -289,16 +289,23 @@ int dh_launch_gemm_f32(bool ta, bool tb, int M, int N, int K, const float* A, co
   return launch_f32<true, true>(M, N, K, K, A, B, C, accumulate, bias, nullptr, 0, 1, stream);
 }
 
+static int f32_glu_tile(int T, int F) { return f32_small(T, 2 * F, 1) ? 16 : 32; }
+static long long f32_glu_blocks(int T, int F) {
+  const int tile = f32_glu_tile(T, F);
+  return (long long)((T + tile - 1) / tile) * ((F + tile - 1) / tile);
+}
+// Whether the gate/up projection takes SwiGLU along in its launch.  Up to two blocks a unit the product waits for latencies and the second launch is the gain (us,
+// apart and as one: 128 tokens, 256 -> 2 x 688, 9.1 with the gap between launches and 6.3; 333, 512 -> 2 x 1368, 25.7 and 23.4; 512, 1024 -> 2 x 1024, 36.5 and
+// 33.3); beyond, twice the waves and memory a block are in each other's way (1024, 256 -> 2 x 688, 704 blocks, 17.8 and 20.1), and the two stay
+// operators that a plan places.
+bool dh_glu_f32_fwd_fits(int T, int F, int H) { return F % 4 == 0 && H % 4 == 0 && f32_glu_blocks(T, F) <= 512; }
 // gu [T, 2F] = x * Wgu and a = silu(gate) * up; dgu [T, 2F] = SwiGLU's backward of dy * Wd^T.  The bits of the product and the row-wise operator.
 int dh_launch_gemm_f32_swiglu_fwd(int T, int F, int H, const float* x, const float* Wgu, float* gu, float* a, hipStream_t stream) {
   if (T == 0) return DH_OK;
   const F32Args g = f32_args(T, 2 * F, H, H, x, Wgu, gu, false, nullptr, nullptr, 0, a);  // a: for its alignment
-  const int tile = f32_small(T, 2 * F, 1) ? 16 : 32, tn = (F + tile - 1) / tile;
-  const long long blocks = (long long)((T + tile - 1) / tile) * tn;
-  // Up to two blocks a unit the product waits for latencies and the second launch is the gain (us, apart and as one: 128 tokens, 256 -> 2 x 688, 9.1 with the gap
-  // between launches and 6.3; 333, 512 -> 2 x 1368, 25.7 and 23.4; 512, 1024 -> 2 x 1024, 36.5 and 33.3); beyond, twice the waves and memory a block are in each
-  // other's way (1024, 256 -> 2 x 688, 704 blocks, 17.8 and 20.1).
-  if (!f32_vec(false, false, g) || !g.vec_out || F % 4 != 0 || blocks > 512) {
+  const int tile = f32_glu_tile(T, F), tn = (F + tile - 1) / tile;
+  const long long blocks = f32_glu_blocks(T, F);
+  if (!f32_vec(false, false, g) || !g.vec_out || !dh_glu_f32_fwd_fits(T, F, H)) {  // operands that are not aligned
     const int rc = dh_launch_gemm_f32(false, false, T, 2 * F, H, x, Wgu, gu, false, nullptr, stream);
     return rc ? rc : dh_swiglu_fwd(DH_F32, T, F, gu, a, stream);
   }

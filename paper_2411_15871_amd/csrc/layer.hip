@@ -271,11 +271,12 @@ static void choose_pairs(dh_layer* L) {
   }
 }
 
-// Which activations the neighbouring products take along (mask: 1 forward, 2 backward): in float32 always, a launch less on a chain of short ones.
+// Which activations the neighbouring products take along (mask: 1 forward, 2 backward): where one launch holds both.  (The float32 data gradient's tiles do at
+// any size.)
 static void set_fused_activation(dh_layer* L, int mask) {
   const dh_layer_config& c = L->c;
   const bool glu_layer = c.arch == DH_ARCH_LLAMA || c.arch == DH_ARCH_LLAMA_CP, f32 = c.dtype == DH_F32;
-  L->fuse_act_fwd = (mask & 1) && glu_layer && (f32 || dh_glu_fwd_fits(L->T, c.ffn, c.hidden));
+  L->fuse_act_fwd = (mask & 1) && glu_layer && (f32 ? dh_glu_f32_fwd_fits(L->T, c.ffn, c.hidden) : dh_glu_fwd_fits(L->T, c.ffn, c.hidden));
   L->fuse_act_bwd = (mask & 2) && glu_layer && (f32 || dh_glu_bwd_fits(L->T, c.ffn, c.hidden));
 }
 

@@ -1,6 +1,6 @@
 """Float32: SwiGLU in the epilogues of the gate/up projection and of the down projection's data gradient, against the separate operators: the same bits.  Widths
-that end inside a tile, K of one wave to all sixteen, one product's waves side by side or in turn, more blocks than one launch takes; the data
-gradient alone and paired with the weight gradient."""
+that end inside a tile, K of one wave to all sixteen, one product's waves side by side or in turn, more blocks than one launch takes (the forward
+activation stays apart then); the data gradient alone and paired with the weight gradient."""
 import pytest
 import torch
 
@@ -19,7 +19,7 @@ def test_same_bits_as_separate(T, hidden, ffn, arch):
     try:
         got = {}
         for mask in (3, 0):
-            assert dh.dh_layer_set_fused_activation(run.layer, mask) == mask
+            assert dh.dh_layer_set_fused_activation(run.layer, mask) == (mask if T * ffn <= 512 * 32 * 32 else mask & 2)
             s = run.strand(0)
             run.zero_grads()
             run.fwd(s)
