@@ -16,8 +16,9 @@
 // comes from LDS through the transposing load ds_read_b64_tr_b16.
 //
 // 64-token tiles stream global -> LDS directly (see dma.h) through a ring of three slots (two or three in the
-// forward kernels, so that two of their blocks fit a compute unit): the transfer of tile t+2 (t+1) is issued
-// right after the barrier that publishes tile t.  A tile is stored
+// forward kernels, so that two of their blocks fit a compute unit): in the loops in phases the transfer of tile t+2 (t+1) is issued
+// right after the barrier that publishes tile t; in the pinned ones (attn_fwd_pinned, attn_bwd_dkv_block at D = 128) the transfers stand between score
+// products, tile t+2's beside tile t's (forward: K of t+2 and V of t+1).  A tile is stored
 // [token][D] unpadded; the 16-byte chunk c of row r sits at chunk position c ^ swz(r), which makes
 // the 16-byte fragment reads (16 consecutive rows, one chunk) and the transposing reads (4
 // consecutive rows x 64 bytes) both bank-conflict free for 256-byte rows (D = 128).
@@ -538,8 +539,8 @@ __device__ __forceinline__ void tile_voff_biased(uint32_t (&v)[ATile<D>::IPW], i
 // next iteration fills (tiles behind the unit's end are its last one again, so that every iteration has 8 transfers).
 // The same sums in the same order as the loop in phases: the same bits.
 //
-// Measured alone (us, in phases -> here): 32:8 heads x 4096 tokens 165 -> 153, 8:1 x 8192 185 -> 163, 4:1 x 4096 queries over 12288 keys 129 -> 115,
-// 2 x 2048 x 8 heads 44.4 -> 38.7, 16:4 x 1500 33.8 -> 29.9.  In cycles it is 17 % (290 -> 240 thousand at 32:8 heads, matrix cores busy 46 -> 56 %): the
+// Measured alone, both in turn in a loop of launches (us, in phases -> here): 32:8 heads x 4096 tokens 152 -> 141, 8:1 x 8192 175 -> 157, 4:1 x 4096 queries over
+// 12288 keys 119 -> 108, 2 x 2048 x 8 heads 43.9 -> 36.7, 16:4 x 1500 32.4 -> 27.8.  In cycles it is 17 % (290 -> 240 thousand at 32:8 heads, matrix cores busy 46 -> 56 %): the
 // clock falls from 1.75 to 1.65 GHz, the power limit takes the rest.  Without the LDS reads (results meaningless) the same loop takes 200 thousand cycles and 108 us, so these
 // are its largest single cost; two heads of a group a block, which halves them but needs a unit's registers for one block, 149 us there and 135 over 12288 keys,
 // 23 instead of 15.7 for 3 x 683 tokens: a block's start and end (6 us, 40 KiB of code to fetch) have nothing beside them.  One block a unit with rings of three and four
@@ -1792,12 +1793,13 @@ static int pick_bwd_chunk(int kind, int seq, int q_off, int heads, int d, int gr
   return best;
 }
 
-// Chunk length of a forward launch: a few lengths and a plain list schedule (1.45 us a tile at D = 128, 3 a block, partial results there
+// Chunk length of a forward launch: a few lengths and a plain list schedule (1.45 us a tile at D = 128, the loop in phases, 3 a block, partial results there
 // and back at 2 MB per microsecond and 12 for their launch); where splitting pays, then the shortest length whose blocks are all resident
 // at once, two a unit (4 heads x 4096 tokens, 16 -> 10 tiles 48 -> 42 us; one block more than fits costs a second round).
 // The model above finds shorter launches (3 x 1365 tokens, 4 heads, 29 -> 24 us; 4 heads x 8192 at D = 64 89 -> 61 us), but other lengths
 // add a row's partial results over other ranges of keys, and then gradients that are all rounding come out as other noise (the router's,
-// exactly zero where a token's two experts hold the same weights): the lengths stay.
+// exactly zero where a token's two experts hold the same weights): the lengths stay, also where they are the 8 tiles that the loop in phases takes
+// (fwd_pinned).
 static int pick_fwd_chunk(int seq, int q_off, int heads, int d) {
   const int nblk = (seq + 127) / 128, qb0 = q_off / 128, slots = attn_num_cus();
   auto units_of = [&](int ch) { return (long long)total_pairs_dq(seq, q_off, ch); };  // the tiles dQ walks
@@ -1872,7 +1874,7 @@ size_t dh_attn_fwd_bf16_ws_bytes(int batch, int seq_q, int q_off, int nq, int nk
 
 // Whether the pipelined kernel takes a launch: units of few tiles spend longer in its start (the first tile's scores stand alone, twice the code is
 // fetched) than its loop gains.  us, in phases and pipelined: 4:1 heads x 300 tokens (5 tiles) 9.3 and 9.7, 32:8 x 343 (6) 11.8 and 11.9,
-// 8:2 x 1280 (chunks of 8) 23.1 and 23.6, 3 x 488 on 4:2 (8) 13.8 and 13.4, 4:1 x 4096 (chunks of 10) 39.0 and 38.0, 3 x 683 (11) 17.0 and 15.7.
+// 8:2 x 1280 (chunks of 8) 23.1 and 23.6, 3 x 488 on 4:2 (8) 13.8 and 13.4, 4:1 x 4096 (chunks of 10) 36.6 and 35.6, 3968 35.3 and 34.4, 3 x 683 (11) 16.5 and 15.2.
 static bool fwd_pinned(int d, int seq, int ch) { return d == 128 && (ch > 0 ? ch : fwd_tiles((seq + 127) / 128 - 1, seq)) >= 10; }
 int dh_launch_attn_fwd_bf16(int batch, int seq_q, int nq, int nkv, int d, const bf16_t* qkv, const bf16_t* kv, int ldkv, int q_off,
                             bf16_t* o, float* lse, void* ws, size_t ws_bytes, hipStream_t stream) {

@@ -106,9 +106,13 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_fwd_kernel(const T* __res
 __host__ __device__ static inline int norm_bwd_rpb(int rows) { return rows >= 4096 ? 8 : rows >= 1024 ? 4 : rows >= 512 ? 2 : 1; }
 // Short rows leave threads of a block idle (1024 columns are 128 threads' work), and its rows are a chain of loads and sums one after the other: G
 // groups of threads take every G-th row each, side by side.  Columns, and the order of a row's sum, are those of one group.
-// us with the column sums behind it, one group and G, bf16: RMSNorm, 8192 x 256 12.2 -> 8.8 (four), 4000 x 512 9.8 -> 8.6, 2048 x 1024 8.9 -> 8.0 (two); LayerNorm
-// 15.4 -> 10.7, 12.2 -> 10.2, 11.3 -> 10.1.  Two groups of longer inputs already move as much as memory gives and only hold more rows' loads: LayerNorm, 4000 x
-// 1024 14.5 -> 15.2, float32 RMSNorm 16.0 -> 17.0 (bf16 12.0 -> 11.9, where it sums partials 260 -> 257 a backward pass of two).  Below 1024 rows a block has one or two.
+// us of the bare operator with the column sums behind it, one group and four, bf16: RMSNorm, 2048 x 512 8.3 -> 6.9, 8192 x 512 14.1 -> 12.6, LayerNorm 10.3 -> 7.4, 17.3 ->
+// 14.3 (float32 8.8 -> 8.4 and 15.7 -> 16.4, 10.5 -> 9.6 and 17.9 -> 17.4).  One and two: RMSNorm, 1024 x 1024 7.8 -> 7.1, 2048 x 1024 9.6 -> 9.5, LayerNorm 9.7 -> 8.2, 11.9 ->
+// 11.3, 2048 x 640 8.6 -> 7.8 and 10.6 -> 9.5.  Two groups are drawn by what they gain inside a layer, where the norm reads the ranks' partial buffers one after the other or what
+// a product has just written: backward passes of small layers, bf16, 1024 to 8192 rows of 640 to 1024, 1.00 to 1.07 times as fast on one, two and eight ranks (4000 x
+// 1024 1.00, 1.02, 1.01; 8192 x 1024 1.01, 1.04, 1.00), float32 up to 2048 rows 1.00 to 1.04, 4000 rows 0.99.  The bare operator in a loop gains less and loses beyond
+// 4 MB a tensor (RMSNorm, bf16 4000 x 1024 12.8 -> 13.6, float32 2048 x 1024 10.6 -> 11.8).  The count does not ask where the gradient comes from: a reduction with its norm has the
+// bits of the two apart.  LayerNorm beyond 2048 rows keeps one group (bare, 4000 x 1024 15.1 -> 16.3; in layers 1.00 to 1.05).  Below 1024 rows a block has one or two.
 template <typename T>
 static int norm_bwd_groups(int rows, int H, bool layernorm) {
   if (rows < 1024 || H > 1024) return 1;
