@@ -543,8 +543,9 @@ __device__ __forceinline__ void tile_voff_biased(uint32_t (&v)[ATile<D>::IPW], i
 // The same sums in the same order as the loop in phases: the same bits.
 //
 // Measured alone, both in turn in a loop of launches (us, in phases -> here): 32:8 heads x 4096 tokens 152 -> 141, 8:1 x 8192 175 -> 157, 4:1 x 4096 queries over
-// 12288 keys 119 -> 108, 2 x 2048 x 8 heads 43.9 -> 36.7, 16:4 x 1500 32.4 -> 27.8.  In cycles it is 17 % (290 -> 240 thousand at 32:8 heads, matrix cores busy 46 -> 56 %): the
-// clock falls from 1.75 to 1.65 GHz, the power limit takes the rest.  Without the LDS reads (results meaningless) the same loop takes 200 thousand cycles and 108 us, so these
+// 12288 keys 119 -> 108, 2 x 2048 x 8 heads 43.9 -> 36.7, 16:4 x 1500 32.4 -> 27.8; as one kernel after the other of a layer 32:8 x 4096 160 -> 145, 2 x 2048 x 8
+// heads 48 -> 45, 4:1 x 4096 31.4 -> 30.0.  In cycles it is 17 % (290 -> 240 thousand at 32:8 heads; matrix cores busy 41 -> 48 % by counters that also count some 10 us around a
+// dispatch): the clock falls from 1.75 to 1.65 GHz, the power limit takes the rest.  Without the LDS reads (results meaningless) the same loop takes 200 thousand cycles and 108 us, so these
 // are its largest single cost; two heads of a group a block, which halves them but needs a unit's registers for one block, 149 us there and 135 over 12288 keys,
 // 23 instead of 15.7 for 3 x 683 tokens: a block's start and end (6 us, 40 KiB of code to fetch) have nothing beside them.  One block a unit with rings of three and four
 // slots: 175.
